@@ -112,6 +112,7 @@ def prepare(case, seed):
     if c["option"] == "proj":
         w = (torch.randn(D, D, generator=g, device="cuda") / D ** 0.5).to(dt)
         kw["w_proj_packed"] = sb.salad_proj_pack(w, H, d)
+        s["w_proj"] = w
     else:
         kw["head_scale"] = torch.rand(H, generator=g, device="cuda")
     if c["option"] == "pruned":
@@ -171,3 +172,64 @@ def tolerance(case):
     if case["dtype"] == "f32":
         return {"rel": 4e-6}
     return {"rel": 1e-2}
+
+
+def exact(case, seed):
+    """The layer in 64 bits with plain torch, head by head and a run of query blocks at a time; None where that takes too long."""
+    c = case
+    B, H, d, T, Hh, W = (c[k] for k in ("B", "H", "d", "T", "Hh", "W"))
+    N, D = T * Hh * W, H * d
+    if work(c)["flops"] > 4e12:
+        return None
+    s = prepare(c, seed)
+    kw, f64 = s["kw"], torch.float64
+    gate = torch.sigmoid(kw["x_t"].to(f64) @ kw["w_gate"].to(f64)).mean(1)
+    dropped = gate < kw.get("drop_threshold", 0.0)
+    positions = torch.arange(N, device="cuda")
+    orders = [positions, (positions % T) * (Hh * W) + positions // T]     # stored row of each position of a head's own order
+    sparse, linear = (torch.empty(B, N, H, d, dtype=f64, device="cuda") for _ in range(2))
+    for b in range(B):
+        for h in range(H):
+            order = orders[s["kinds"][h]]
+            q, k, v = (s[t][b, h].to(f64)[order] for t in "qkv")
+            o = torch.empty_like(q)
+            if c["option"] == "topk":
+                step = c["key_block"]
+                means = torch.stack([k[i:i + step].mean(0) for i in range(0, N, step)])
+                top = (q @ means.T).topk(min(c["topk"], len(means)), 1).indices
+                for i in range(0, N, 2048):
+                    keep = torch.zeros(len(q[i:i + 2048]), len(means), dtype=torch.bool, device="cuda").scatter_(1, top[i:i + 2048], True)
+                    w = (q[i:i + 2048] @ k.T / math.sqrt(d)).masked_fill_(~keep.repeat_interleave(step, 1)[:, :N], -math.inf)
+                    o[i:i + 2048] = torch.softmax(w, 1) @ v
+            else:
+                nb, kept = _kept(c)
+                first = [min(max(i - kept // 2, 0), nb - kept) for i in range(nb)]
+                for i in range(0, nb, 8):                                  # 8 query blocks share one stretch of keys
+                    j = min(i + 8, nb)
+                    lo, hi = first[i] * BLOCK, min((first[j - 1] + kept) * BLOCK, N)
+                    rows = slice(i * BLOCK, min(j * BLOCK, N))
+                    start = torch.tensor(first[i:j], device="cuda").repeat_interleave(BLOCK)[: rows.stop - rows.start, None] * BLOCK
+                    key = torch.arange(lo, hi, device="cuda")[None]
+                    w = (q[rows] @ k[lo:hi].T / math.sqrt(d)).masked_fill_((key < start) | (key >= start + kept * BLOCK), -math.inf)
+                    o[rows] = torch.softmax(w, 1) @ v[lo:hi]
+            sparse[b, order, h] = o
+            if not dropped[b]:
+                pq, pk = q.clamp(min=0), k.clamp(min=0)
+                den = pq @ pk.sum(0) + kw["eps"]
+                if c["option"] == "rope":
+                    cos, sin = (kw[t].to(f64)[order] for t in ("rope_cos", "rope_sin"))
+                    pq, pk = (torch.stack((x[:, ::2] * cos - x[:, 1::2] * sin, x[:, ::2] * sin + x[:, 1::2] * cos), 2).flatten(1) for x in (pq, pk))
+                linear[b, order, h] = (pq @ (pk.T @ v)) / den[:, None]
+    out = torch.empty(B, H, N, d, dtype=f64, device="cuda")
+    for b in range(B):
+        got = sparse[b]
+        if not dropped[b]:
+            if c["option"] == "proj":
+                got = got + kw["lam"] * gate[b] * (linear[b].reshape(N, D) @ s["w_proj"].to(f64)).reshape(N, H, d)
+            else:
+                got = got + kw["lam"] * gate[b] * kw["head_scale"].to(f64)[:, None] * linear[b]
+        out[b] = got.transpose(0, 1)
+    res = {"out": out, "s": gate}
+    if c["option"] == "pruned":
+        res["dropped"] = dropped.to(torch.int32)
+    return res
