@@ -259,55 +259,71 @@ hipError_t launch_rope_pack(const float *rope_cos, const float *rope_sin, size_t
 }
 
 // ------------------------------------------------------------------------------------------------
-// fp32 state for small shapes.  A workgroup owns 64 consecutive elements of [Hs | Z] of one head (for d = 64: one
-// row a of Hs, so relu(K[n][a]) is one broadcast load and V[n][c] a coalesced one) and splits the tokens over 16
-// thread groups (token n goes to group n mod 16); every thread adds its tokens in ascending order with 8 loads in
-// flight, the 16 sums are added in group order through LDS: the same result whatever the launch looks like.
+// fp32 state for small shapes, on v_mfma_f32_16x16x4_f32 (fp32 operands and accumulation).  A workgroup owns one 16 x 16
+// tile of Hs of one head, so that even one head fills 16 (d = 64) or 64 (d = 128) workgroups, and deals the tokens to its 16
+// waves in groups of 4 (group j to wave j mod 16): row i of the A operand is channel a0 + i of a token's relu(K), column i
+// of B channel c0 + i of its V, the 4 tokens are the contraction.  8 groups of loads are in flight per wave.  The 16
+// accumulators are added in wave order through LDS: the same result whatever the launch looks like.  The workgroups of
+// the first column also add up Z.
+// Bound by the latency of the loads: B = 1, H = 4, N = 2080, d = 64: 8.2 us against 18.5 us with one thread per element
+// and token group; H = 2, N = 1024: 5.3 against 7.2 us.
 // ------------------------------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(1024) void state_f32_kernel(const float *__restrict__ k, const float *__restrict__ v,
                                                          int N, int D, float *__restrict__ Hs, float *__restrict__ Z,
                                                          const int32_t *__restrict__ drop, int H)
 {
-    __shared__ float part[16][64];
+    __shared__ float part[16][256], zpart[16][16];
     const int bh = blockIdx.y;
     if (drop && drop[bh / H]) return;                  // pruned sample (Sec. 4.3)
-    const int le = threadIdx.x & 63, g = threadIdx.x >> 6;
-    const int e = blockIdx.x * 64 + le;
-    const bool live = e < D * D + D;
-    const bool is_z = e >= D * D;
-    const int a = is_z ? e - D * D : e / D, c = is_z ? 0 : e - a * D;
-    const float *kb = k + (size_t)bh * N * D + (live ? a : 0);
-    const float *vb = v + (size_t)bh * N * D + c;
-    float s = 0.f;
-    if (live) {
-        int n = g;
-        for (; n + 7 * 16 < N; n += 8 * 16) {
-            float kk[8], vv[8];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
+    const int nt = D / 16, a0 = (blockIdx.x / nt) * 16, c0 = (blockIdx.x % nt) * 16;
+    const float *kb = k + (size_t)bh * N * D + a0 + i;
+    const float *vb = v + (size_t)bh * N * D + c0 + i;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float z = 0.f;
+    for (int n0 = w * 4; n0 < N; n0 += 8 * 64) {
+        float kk[8], vv[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                kk[u] = kb[(size_t)(n + 16 * u) * D];
-                vv[u] = is_z ? 1.f : vb[(size_t)(n + 16 * u) * D];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s = fmaf(fmaxf(kk[u], 0.f), vv[u], s);
+        for (int u = 0; u < 8; ++u) {                  // tokens past the end: any existing row, weight 0
+            const int n = n0 + u * 64 + g;
+            const size_t off = (size_t)(n < N ? n : N - 1) * D;
+            kk[u] = kb[off];
+            vv[u] = vb[off];
         }
-        for (; n < N; n += 16) s = fmaf(fmaxf(kb[(size_t)n * D], 0.f), is_z ? 1.f : vb[(size_t)n * D], s);
-    }
-    part[g][le] = s;
-    __syncthreads();
-    if (g == 0 && live) {
-        float t = part[0][le];
 #pragma unroll
-        for (int i = 1; i < 16; ++i) t += part[i][le];
-        if (is_z) Z[(size_t)bh * D + a] = t;
-        else Hs[(size_t)bh * D * D + e] = t;
+        for (int u = 0; u < 8; ++u) {
+            const bool live = n0 + u * 64 + g < N;
+            kk[u] = live ? fmaxf(kk[u], 0.f) : 0.f;
+            z += kk[u];
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kk[u], live ? vv[u] : 0.f, acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[w][(4 * g + r) * 16 + i] = acc[r];   // register r of lane (i, g): row 4 g + r, column i
+    z += __shfl_xor(z, 16);
+    z += __shfl_xor(z, 32);
+    if (g == 0) zpart[w][i] = z;
+    __syncthreads();
+    const int e = threadIdx.x;
+    if (e < 256) {
+        float t = part[0][e];
+#pragma unroll
+        for (int x = 1; x < 16; ++x) t += part[x][e];
+        Hs[(size_t)bh * D * D + (size_t)(a0 + e / 16) * D + c0 + e % 16] = t;
+    } else if (e < 272 && c0 == 0) {
+        float t = zpart[0][e - 256];
+#pragma unroll
+        for (int x = 1; x < 16; ++x) t += zpart[x][e - 256];
+        Z[(size_t)bh * D + a0 + e - 256] = t;
     }
 }
 
 hipError_t launch_state_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z,
                             const int32_t *drop, int H, hipStream_t st)
 {
-    dim3 grid((D * D + D + 63) / 64, BH), block(1024);
+    dim3 grid((D / 16) * (D / 16), BH), block(1024);
     launch_kernel(state_f32_kernel, grid, block, 0, st, k, v, N, D, Hs, Z, drop, H);
     return take_launch_status();
 }

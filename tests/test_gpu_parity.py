@@ -186,6 +186,23 @@ def test_fp32_path_ragged_d128(oracle):
     compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), tol_abs=1e-4, tol_rel=1e-5, label="f32-d128")
 
 
+@pytest.mark.parametrize("B,H,d,grid,kept", [
+    (1, 1, 64, (1, 1, 1), [1]),              # one token: 15 of a tile's 16 queries and 31 of a unit's 32 keys do not exist
+    (1, 2, 64, (3, 1, 5), [1, 1]),           # 15 tokens, temporal head
+    (2, 3, 64, (1, 1, 17), [1, 1, 1]),       # second tile of 1 query
+    (1, 2, 128, (5, 13, 1), [2, 1]),         # 65 tokens: a block of one key, its second half empty
+    (1, 2, 64, (4, 5, 8), [3, 2]),           # 160 tokens, 32-token tail: units of a row do not divide by the 4 waves
+    (1, 2, 128, (7, 9, 11), [5, 11]),        # 693 tokens: every block kept by the second head
+])
+def test_fp32_tile_edges(oracle, B, H, d, grid, kept):
+    """fp32 kernels at the edges of their 16-query tiles, 32-key units and 4-token groups."""
+    w = wl.small(f"f32-{d}-{grid[0] * grid[1] * grid[2]}", B, H, d, *grid, "f32", 0.5, seed=300 + d + grid[2])
+    inp = wl.make_inputs(w)
+    kinds = wl.head_kinds(w)
+    res = run_layer(w, inp, upload(w, inp), kept, kinds)
+    compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), tol_abs=1e-4, tol_rel=1e-5, label=w.name)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_sixty_four_heads(oracle, d):
     """The largest head count the boundary takes (64: the head-order mask is a 64-bit word, the last head temporal),
