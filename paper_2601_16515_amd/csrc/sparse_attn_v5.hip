@@ -1,20 +1,23 @@
 // Block-sparse softmax attention (Eq. (2)) with the fused linear apply / scale / sum epilogue,
-// d = 128 (and d = 64 on half-size tiles).  Large tile, deep LDS prefetch, ping-pong wave groups.
+// d = 128 (and d = 64 on half-size tiles).  Large tile, deep LDS prefetch, softmax woven into the matrix stream.
 //
 //   * One workgroup = 8 waves = 256 query positions = 4 CSR rows of one (batch, head); one workgroup
-//     per CU (LDS: 4 K + 5 V tiles of 16 KB plus the block list; registers at d = 64, where the tiles are 8 KB).
+//     per CU (LDS: 5 K + 4 V tiles of 16 KB plus the block list; registers at d = 64, where the tiles are 8 KB).
 //   * The ascending union of the 4 rows' kept-block lists is built once per workgroup in LDS (bitmap +
 //     ballot compaction), each entry carrying a 4-bit "kept by query block i" mask.  The main loop
 //     reads one entry per iteration from LDS; no global or scalar load sits on its critical path.
-//   * K and V tiles go straight from global memory into a ring of LDS slots PD blocks ahead of their
-//     use, PD = 3 (global_load_lds_dwordx4, bank swizzle applied on the global side).  The wait before the
-//     per-block barrier is counted (s_waitcnt vmcnt(n)), so PD - 1 blocks of loads stay in flight and
+//   * K and V tiles go straight from global memory into two rings of LDS slots, K four and V two blocks ahead
+//     (global_load_lds_dwordx4, bank swizzle applied on the global side).  The wait before the
+//     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
-//   * Ping-pong: waves 0-3 (group 0) and 4-7 (group 1) share the 4 SIMDs pairwise.  Per KV block a wave
-//     has a matrix part (O += V^T P of the previous block, S = K Q^T of the current one: 32 MFMAs) and a
-//     vector part (softmax of S, then the address arithmetic and issue of the next prefetch).  Group 0
-//     runs matrix then vector, group 1 vector then matrix, so that one wave of a SIMD feeds the matrix
-//     pipe while the other uses the vector ALU.  One barrier per KV block (it also protects the ring).
+//   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
+//     fma / exp / pack / sum of a third half sit between its MFMAs, a few vector instructions after each: alone, this mix
+//     runs at 41 cycles per MFMA with two waves per SIMD (33 without the sums: v_dot2c_f32_bf16 takes 16 cycles of the matrix
+//     pipe).  A block's K and V loads are issued between its two halves.  One barrier per KV block (it also protects
+//     the rings).  Before, the waves of a SIMD took turns, one multiplying while the other did its softmax, which left the
+//     softmax partly exposed.  B = 1, N = 32760, layer call: 24 heads of 64 at 90 % 917 -> 863 us; 12 heads of 128 dense
+//     5921 -> 5842 us, at 90 % 702 -> 699 us: at d = 128 the cycles fall by 5 % and the clock, which the power limit
+//     sets (1.95 -> 1.89 GHz on the dense call), takes most of it back.
 //   * V^T operands come from ds_read_b64_tr_b16, K rows are read through the kappa permutation so
 //     that P never moves between lanes.  LDS operand reads are spread evenly between the MFMAs through a
 //     small ring of fragment registers.
@@ -183,8 +186,6 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
     return take_launch_status();
 }
 
-// PD: prefetch distance in KV blocks.  K(b) is read in iteration b only, V(b) also in iteration b+1: the K ring
-// has PD + 1 slots, the V ring PD + 2.
 // MODE 0: block rows (CSR) through the per-tile union lists.
 // MODE 1: token-level Top-K mask (App. A.1.2).  The tile lists are per (sample, head, tile); an entry is
 //   block | key-block index << 16 | wave mask << 24 (bit 24 + w: some query of wave w keeps the block); each lane
@@ -199,7 +200,7 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 // D = 64 (MODE 0 without ROPE only): the same kernel on half-size tiles.  A row is 8 chunks of 16 bytes instead of 16,
 // so one pass of the 512 threads fetches a whole 64-row tile, the swizzles below take the row pair instead of the row
 // (rows 128 bytes apart alternate between the two halves of the banks), and every fragment count halves.
-template <int D, int PD, bool DBG, int MODE = 0, bool ROPE = false>
+template <int D, bool DBG, int MODE = 0, bool ROPE = false>
 __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
 {
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     constexpr int CH = D / 8;                    // 16-byte chunks per row
     constexpr int RPP = 512 / CH, NPASS = 64 / RPP;   // rows per pass of the 512 threads over a tile, passes per tile
     constexpr int TILE = 64 * D;                 // elements
-    constexpr int NK = PD + 1, NV = PD + 2;
+    constexpr int NK = 5, NV = 4;                // K and V tiles in LDS
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     u16 *Kb = reinterpret_cast<u16 *>(smem);                       // NK tiles
     u16 *Vb = Kb + NK * TILE;                                       // NV tiles
@@ -236,7 +237,6 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, hh = lane >> 5;
-    const int group = wave >> 2;
     const u16 *qb = reinterpret_cast<const u16 *>(a.q) + (size_t)bh * N * D;
     const u16 *kb = reinterpret_cast<const u16 *>(a.k) + (size_t)bh * N * D;
     const u16 *vb = reinterpret_cast<const u16 *>(a.v) + (size_t)bh * N * D;
@@ -298,17 +298,27 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     const unsigned wave_u = (unsigned)__builtin_amdgcn_readfirstlane(wave);
     const unsigned k_lds0 = lds_addr_of(Kb) + wave_u * 1024u;
     const unsigned v_lds0 = lds_addr_of(Vb) + wave_u * 1024u;
-    auto fetch = [&](int blk, int kslot, int vslot) INL {
-        const unsigned kl = k_lds0 + (unsigned)kslot * (unsigned)(TILE * 2);
-        const unsigned vl = v_lds0 + (unsigned)vslot * (unsigned)(TILE * 2);
+    // byte offset of this thread's row i of a block: without a branch (a spatial head is location 0, stride 1)
+    const unsigned magic_u = kind ? magic : 0u, stride_b = (unsigned)((kind ? HW : 1) * D * 2), back_b = (unsigned)(D * 2) - (unsigned)T * stride_b;
+    auto row_bytes = [&](int blk, int i) INL -> unsigned {
+        int p = blk * 64 + i * RPP + lr;
+        p = p < N ? p : N - 1;
+        return (unsigned)p * stride_b + __umulhi((unsigned)p, magic_u) * back_b;     // (p - loc T) stride + loc, in rows of 2 D bytes
+    };
+    struct Rows { unsigned b[NPASS]; };
+    auto rows_of = [&](int blk) INL -> Rows {
+        Rows r;
 #pragma unroll
-        for (int i = 0; i < NPASS; ++i) {
-            int p = blk * 64 + i * RPP + lr;
-            p = p < N ? p : N - 1;
-            const unsigned row_b = (unsigned)row_of_position5(kind, p, T, HW, magic) * (unsigned)(D * 2);
-            lds_dma16_base(kb, row_b + kchunk_b, kl + i * 8192u);
-            lds_dma16_base(vb, row_b + vchunk_b, vl + i * 8192u);
-        }
+        for (int i = 0; i < NPASS; ++i) r.b[i] = row_bytes(blk, i);
+        return r;
+    };
+    auto fetch_k = [&](const Rows &r, int slot) INL {
+#pragma unroll
+        for (int i = 0; i < NPASS; ++i) lds_dma16_base(kb, r.b[i] + kchunk_b, k_lds0 + (unsigned)slot * (unsigned)(TILE * 2) + i * 8192u);
+    };
+    auto fetch_v = [&](const Rows &r, int slot) INL {
+#pragma unroll
+        for (int i = 0; i < NPASS; ++i) lds_dma16_base(vb, r.b[i] + vchunk_b, v_lds0 + (unsigned)slot * (unsigned)(TILE * 2) + i * 8192u);
     };
     // list entries travel in a vector register (lane l holds entry 64 c + l of the current 64-entry
     // chunk c) and are picked with v_readlane: no LDS round trip per iteration
@@ -338,115 +348,82 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     f32x16 s[2];
     Frag5 pf[4];
 
-    // Matrix phase = 32 MFMAs per wave: 16 for O^T += V^T P^T (A = V^T fragment: two transposing 8-byte reads),
-    // then 16 for S^T = K Q^T (A = K fragment: one 16-byte read; the NS products of the block's first 32 keys, then
-    // those of the other 32, so that the softmax finds its first logits finished).  Operand fragments move through a ring of
-    // RING register quads: MFMA i takes ring[i % RING] and the read of fragment i + RING is issued right after
-    // it, so LDS requests are spread evenly over the phase (the LDS has to deliver 1 KB per MFMA per wave,
-    // about three quarters of what it can sustain, and bursts of reads stall the matrix pipe) and at most
-    // 2 RING <= 15 of them are in flight.  The first RING fragments are requested in the preceding vector
-    // phase, once the V tile they come from is known to have landed.
-    constexpr int RING = 7;
+    // The unit of work is half a block (32 keys).  A part = the S products of one half (NS MFMAs, A = K rows) and the O^T
+    // products of one half (2 NDT MFMAs, A = V^T, two transposing 8-byte reads), with the softmax of a third half woven
+    // between them.  Operand fragments move through a ring of RING register quads: step i takes ring[i % RING] and the read
+    // of fragment i + RING is issued right after it; the last steps of a block read the next block's first K fragments.
+    constexpr int RING = 4;                       // 8: 5957 against 5842 us on the dense call
     Frag5 ring[RING];
-    constexpr int NPV = 4 * NDT, NSTEP = NPV + 2 * NS;     // PV steps (4 key groups x NDT), all steps of a block
-    auto read_frag = [&](int i, const u16 *Vt, const u16 *Kt, Frag5 &f) INL {
-        if (i < NPV) {
-            const u16 *vp = Vt + (i / NDT) * 16 * D + voff[i % NDT];
+    constexpr int NPS = NS + 2 * NDT;             // steps of a part
+    static_assert((2 * NPS) % RING == 0, "a block's fragments go round the ring a whole number of times");
+    auto read_frag = [&](int i, const u16 *Vt, const u16 *Kt, const u16 *Kn) INL {     // i counts a block's 2 NPS fragments
+        Frag5 &f = ring[i % RING];
+        const int pt = i / NPS, t = i % NPS;
+        if (t < NS) {
+            const u16 *base = pt < 2 ? Kt : Kn;
+            f.v = *reinterpret_cast<const bf16x8 *>(base + (pt & 1) * 32 * D + koff[t]);
+        } else {
+            const u16 *vp = Vt + ((pt & 1) * 2 + (t - NS) / NDT) * 16 * D + voff[(t - NS) % NDT];
             f.h[0] = TR_READ(vp);
             f.h[1] = TR_READ(vp + 4 * D);
+        }
+    };
+    auto mfma_S = [&](int pt, int t, const Frag5 &f) INL {
+        if (t == 0) {
+            f32x16 z;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[r] = 0.f;
+            s[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[0].v, z, 0, 0, 0);
         } else {
-            const int t = i - NPV;
-            f.v = *reinterpret_cast<const bf16x8 *>(Kt + (t / NS) * 32 * D + koff[t % NS]);
+            s[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[t].v, s[pt], 0, 0, 0);
         }
     };
-    auto mfma_step = [&](int i, const Frag5 &f) INL {
-        if (i < NPV) {
-            o[i % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, pf[i / NDT].v, o[i % NDT], 0, 0, 0);
-        } else {
-            const int t = i - NPV, kt = t / NS, st = t % NS;   // the first 32 keys' logits are complete NS MFMAs before the phase ends
-            if (st == 0) {
-                f32x16 z;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) z[r] = 0.f;
-                s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[st].v, z, 0, 0, 0);
-            } else {
-                s[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[st].v, s[kt], 0, 0, 0);
-            }
-        }
+    auto mfma_PV = [&](int pt, int t, const Frag5 &f) INL {
+        o[t % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, pf[pt * 2 + t / NDT].v, o[t % NDT], 0, 0, 0);
     };
-    auto preload_V = [&](const u16 *Vt) INL {      // fragments 0 .. RING-1 (all of them V^T fragments)
-#pragma unroll
-        for (int i = 0; i < RING; ++i) read_frag(i, Vt, nullptr, ring[i]);
+    // TOPK: a lane whose query did not select the entry's key block gets P = 0 (scale 0, reference +inf) and takes no part
+    // in the reference updates
+    auto selected = [&](uint32_t e) INL -> bool {
+        if (!TOPK) return true;
+        const int J = (int)((e >> 16) & 63u);
+        return (((J & 32) ? qm_hi : qm_lo) >> (J & 31)) & 1u;
     };
-    // steps FIRST .. LAST-1 of the sequence; ring[(FIRST + k) % RING], k < RING, already requested
-    auto run_steps = [&](const u16 *Vt, const u16 *Kt, int first, int last) INL {
-#pragma unroll
-        for (int i = first; i < last; ++i) {
-            mfma_step(i, ring[i % RING]);
-            if (i + RING < last) read_frag(i + RING, Vt, Kt, ring[i % RING]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    auto stage_PV_S = [&](const u16 *Vt, const u16 *Kt) INL { run_steps(Vt, Kt, 0, NSTEP); };
-    auto stage_PV = [&](const u16 *Vt) INL { run_steps(Vt, nullptr, 0, NPV); };
-    auto stage_S = [&](const u16 *Kt) INL {          // rare (first block of a row, blocks another row's mask drops)
-#pragma unroll
-        for (int i = 0; i < RING; ++i) read_frag(NPV + i, nullptr, Kt, ring[(NPV + i) % RING]);
-        run_steps(nullptr, Kt, NPV, NSTEP);
-    };
-    auto stage_softmax = [&](uint32_t e) INL {
+    auto mask_tail = [&](int hf, uint32_t e) INL {           // keys past the sequence end (last block only)
         const int blk = (int)(e & BLKMASK);
-        // TOPK: a lane whose query did not select this key block gets P = 0 (scale 0, reference +inf) and takes
-        // no part in the reference updates
-        bool sel = true;
-        if (TOPK) {
-            const int J = (int)((e >> 16) & 63u);
-            sel = (((J & 32) ? qm_hi : qm_lo) >> (J & 31)) & 1u;
-        }
-        const float cs = (TOPK && !sel) ? 0.f : c2;
-        const float ms = (TOPK && !sel) ? INFINITY : m_run;
         if (blk * 64 + 64 > N) {
-            const int kbase = blk * 64 + hh * 8;
+            const int kbase = blk * 64 + hf * 32 + hh * 8;
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (kbase + kt * 32 + 16 * (r >> 3) + (r & 7) >= N) s[kt][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
+            for (int r = 0; r < 16; ++r)
+                if (kbase + 16 * (r >> 3) + (r & 7) >= N) s[hf][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
         }
-        // P = 2^(S c2 - m) rounded to bf16; returns the lane's sum of the rounded values (what the PV product sees)
-        auto exp_pack = [&]() INL -> float {
-            float ps0 = 0.f, ps1 = 0.f;
+    };
+    // P = 2^(S c2 - m) rounded to bf16, pair q of half hf; returns the packed pair
+    auto pair_exp = [&](float t0, float t1) INL -> uint32_t { return pack2e(__builtin_amdgcn_exp2f(t0), __builtin_amdgcn_exp2f(t1)); };
+    auto exp_pack = [&](int hf, bool sel) INL -> float {
+        const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
+        float ps0 = 0.f, ps1 = 0.f;
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int r = 0; r < 16; r += 2) {
-                    const float mref = TOPK ? (sel ? m_run : ms) : m_run;
-                    const uint32_t w = pack2e(__builtin_amdgcn_exp2f(fmaf(s[kt][r], cs, -mref)),
-                                              __builtin_amdgcn_exp2f(fmaf(s[kt][r + 1], cs, -mref)));
-                    pf[kt * 2 + (r >> 3)].w[(r & 7) >> 1] = w;
-                    if (r & 2) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
-                }
-            // the dot instructions come from inline assembly, so the compiler does not know that another
-            // vector instruction must not read their result in the next four issue slots
-            asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));
-            return ps0 + ps1;
-        };
-        // The reference only has to keep 2^S in range, so the block maximum is not computed unless the
-        // sums say that some logit rose more than 13 binades above the reference (or no reference exists
-        // yet): then the reference moves to the true maximum and the block is redone.
-        float psum = 0.f;
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t w = pair_exp(fmaf(s[hf][2 * q], cs, -mref), fmaf(s[hf][2 * q + 1], cs, -mref));
+            pf[hf * 2 + (q >> 2)].w[q & 3] = w;
+            if (q & 1) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
+        }
+        // the dot instructions come from inline assembly, so the compiler does not know that another
+        // vector instruction must not read their result in the next four issue slots
+        asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));
+        return ps0 + ps1;
+    };
+    // The reference only has to keep 2^S in range, so the maximum is not computed unless the sums say that some logit rose
+    // more than 13 binades above the reference (or no reference exists yet): then the reference moves to the true maximum
+    // and the half is redone.  Every earlier half is in O and l by then.
+    auto settle = [&](int hf, bool sel, float psum) INL {
         bool redo = sel && !have_ref;
-        if (!redo) {
-            psum = exp_pack();
-            redo = __any(!(psum <= 8192.f)) && sel;
-        }
+        redo = redo || (__any(!(psum <= 8192.f)) && sel);
         if (redo) {
-            float mx = s[0][0];
+            float mx = s[hf][0];
 #pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
-            mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run);   // block maximum minus reference
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[hf][r]);
+            mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run);   // maximum minus reference
             const float shift = have_ref ? fmaxf(mx, 0.f) : mx;                // new reference minus old reference
             if (have_ref) {
                 const float alpha = __builtin_amdgcn_exp2f(-shift);
@@ -458,9 +435,72 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             }
             m_run += shift;
             have_ref = true;
-            psum = exp_pack();
+            psum = exp_pack(hf, sel);
         }
         l_run += psum;
+    };
+    // one part: S of half pt of the current block, O of half pt of the previous block, softmax of the other half in flight
+    // (pt 0: the previous block's second half, pt 1: the current block's first half; entry e)
+    auto part = [&](int pt, uint32_t e, const u16 *Vt, const u16 *Kt, const u16 *Kn) INL {
+        const int hf = 1 - pt;
+        mask_tail(hf, e);
+        const bool sel = selected(e);
+        const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
+        constexpr int FS = NPS - 3;
+        float t[16], ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < NPS; ++i) {
+            const int g = pt * NPS + i;
+            if (i < NS) mfma_S(pt, i, ring[g % RING]); else mfma_PV(pt, i - NS, ring[g % RING]);
+            read_frag(g + RING, Vt, Kt, Kn);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int at = q * FS / 8;          // step at which pair q's logits are scaled; its exponentials, packing and sum follow one step apart
+                if (i == at) {
+                    t[2 * q] = fmaf(s[hf][2 * q], cs, -mref);
+                    t[2 * q + 1] = fmaf(s[hf][2 * q + 1], cs, -mref);
+                }
+                if (i == at + 1) {
+                    t[2 * q] = __builtin_amdgcn_exp2f(t[2 * q]);
+                    t[2 * q + 1] = __builtin_amdgcn_exp2f(t[2 * q + 1]);
+                }
+                if (i == at + 2) pf[hf * 2 + (q >> 2)].w[q & 3] = pack2e(t[2 * q], t[2 * q + 1]);
+                if (i == at + 3) {
+                    const uint32_t w = pf[hf * 2 + (q >> 2)].w[q & 3];
+                    if (q & 1) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));     // see exp_pack
+        settle(hf, sel, ps0 + ps1);
+    };
+    // the same work unwoven, for blocks that not both of two successive list entries give this wave (first and last entry,
+    // entries that another query block of the tile keeps)
+    auto finish_prev = [&](uint32_t e, const u16 *Vt) INL {
+        mask_tail(1, e);
+        const bool sel = selected(e);
+#pragma unroll
+        for (int t = 0; t < 4 * NDT; ++t) {
+            if (t == 2 * NDT) settle(1, sel, exp_pack(1, sel));     // after the first half's products: the reference may move here
+            Frag5 f;
+            const u16 *vp = Vt + (t / NDT) * 16 * D + voff[t % NDT];
+            f.h[0] = TR_READ(vp);
+            f.h[1] = TR_READ(vp + 4 * D);
+            mfma_PV(t / (2 * NDT), t % (2 * NDT), f);
+        }
+    };
+    auto start_cur = [&](uint32_t e, const u16 *Kt) INL {
+#pragma unroll
+        for (int t = 0; t < 2 * NS; ++t) {
+            Frag5 f;
+            f.v = *reinterpret_cast<const bf16x8 *>(Kt + (t / NS) * 32 * D + koff[t % NS]);
+            mfma_S(t / NS, t % NS, f);
+        }
+        mask_tail(0, e);
+        const bool sel = selected(e);
+        settle(0, sel, exp_pack(0, sel));
     };
 
     const bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[bh / a.H]);   // pruned sample (Sec. 4.3): out = O_s
@@ -482,72 +522,78 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         }
     };
 
-    // ---- main loop over the union list.  Iteration j: S(j) and softmax(j), PV(j-1); fetch block j+PD.
-    // Block b lives in slot b % NK of the K ring and b % NV of the V ring.
-    // The fetch of block j+PD is issued from each group's vector phase, where its address arithmetic
-    // runs under the other group's MFMAs; the slots it goes to were last read in iteration j-1.
+    // ---- main loop over the union list.  Iteration j: S(j) and the softmax of its first half, the softmax of the second
+    // half of block j-1 and its O products; fetch K of block j+4 and V of block j+2.  Block b lives in slot b % NK of the
+    // K ring and b % NV of the V ring: K(b) is read at the end of iteration b-1 and in b, V(b) in b+1.  The barrier of
+    // iteration j says that everything fetched up to iteration j-3 has landed (K(j+1) and V(j-1) among it), so two
+    // iterations' loads stay in flight, and that iteration j-1 no longer reads the slots that j fetches into.
     int v_last = 0;                         // V-ring slot of the last block: the only tile still read after the loop
     if (n > 0) {
+        constexpr int AK = NK - 1, AV = NV - 2;     // how far ahead K and V are fetched
+        static_assert(AK == 4 && AV == 2, "the waits below count the loads of two iterations");
+        Rows rk[AK - AV + 1];                        // row offsets of blocks j+2 .. j+4, for the V fetches to come
+        {
+            Rows r0 = rows_of((int)(entry(0) & BLKMASK)), r1 = rows_of((int)(entry(min(1, n - 1)) & BLKMASK));
+            rk[0] = rows_of((int)(entry(min(2, n - 1)) & BLKMASK));
+            rk[1] = rows_of((int)(entry(min(3, n - 1)) & BLKMASK));
+            fetch_k(r0, 0);
+            if (n > 1) fetch_k(r1, 1);
+            if (n > 2) fetch_k(rk[0], 2);
+            fetch_v(r0, 0);
+            if (n > 3) fetch_k(rk[1], 3);
+            if (n > 1) fetch_v(r1, 1);
+        }
+        uint32_t e_prev = 0u, eq[AK];                // entries j-1; j .. j+3
 #pragma unroll
-        for (int b = 0; b < PD; ++b)
-            if (b < n) fetch((int)(entry(b) & BLKMASK), b, b);
-        uint32_t e_prev = 0u;
-        uint32_t eq[PD];                          // eq[i] = entry j + i
-#pragma unroll
-        for (int b = 0; b < PD; ++b) eq[b] = b < n ? entry(b) : 0u;
+        for (int b = 0; b < AK; ++b) eq[b] = entry(min(b, n - 1));
         int kslot = 0, vslot = 0;                 // j % NK, j % NV
         for (int j = 0; j < n; ++j) {
-            // all fetches up to block j must have landed; newer ones may stay in flight
-            {
-                int newer = n - 1 - j;
-                if (newer > PD - 1) newer = PD - 1;
-                constexpr int LPB = 2 * NPASS;          // loads per lane and block (K and V, NPASS each)
-                if (newer >= 3) WAIT_VM(3 * LPB);
-                else if (newer == 2) WAIT_VM(2 * LPB);
-                else if (newer == 1) WAIT_VM(LPB);
-                else WAIT_VM(0);
-            }
+            if (j + AK <= n) WAIT_VM(4 * NPASS); else WAIT_VM(0);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
-            const int jf = j + PD;
+            const int jf = j + AK;
             uint32_t e_f = 0u;
             if (jf < n) {
                 if ((jf & 63) == 0) ev = blist[jf + lane];
                 e_f = entry(jf);
             }
-            const bool do_fetch = jf < n;
-            int kslot_f = kslot + PD; if (kslot_f >= NK) kslot_f -= NK;
-            int vslot_f = vslot + PD; if (vslot_f >= NV) vslot_f -= NV;
+            int kslot_f = kslot + AK; if (kslot_f >= NK) kslot_f -= NK;
+            int kslot_n = kslot + 1; if (kslot_n >= NK) kslot_n -= NK;
+            int vslot_f = vslot + AV; if (vslot_f >= NV) vslot_f -= NV;
             int vslot_prev = vslot - 1; if (vslot_prev < 0) vslot_prev += NV;
             const uint32_t e_cur = eq[0];
             const bool kS = (e_cur & mybit) != 0, kP = (j >= 1) && (e_prev & mybit);
-            const u16 *Kt = Kb + kslot * TILE;
+            const u16 *Kt = Kb + kslot * TILE, *Kn = Kb + kslot_n * TILE;
             const u16 *Vt = Vb + vslot_prev * TILE;
-            const u16 *Vc = Vb + vslot * TILE;         // V tile of block j (already landed with K(j))
-            if (group == 0) {
-                if (kP && kS) stage_PV_S(Vt, Kt);
-                else { if (kP) stage_PV(Vt); if (kS) stage_S(Kt); }
-                asm volatile("" ::: "memory");
-                if (kS) preload_V(Vc);                  // for PV(j) in the next iteration; lands under the softmax
-                if (kS) stage_softmax(e_cur);
-                if (do_fetch) fetch((int)(e_f & BLKMASK), kslot_f, vslot_f);
+            auto dma = [&]() INL {
+                if (jf < n) {
+                    rk[2] = rows_of((int)(e_f & BLKMASK));
+                    fetch_k(rk[2], kslot_f);
+                }
+                if (j + AV < n) fetch_v(rk[0], vslot_f);
+            };
+            if (kP && kS) {
+                part(0, e_prev, Vt, Kt, Kn);
+                dma();
+                part(1, e_cur, Vt, Kt, Kn);
             } else {
-                if (kP) preload_V(Vt);                  // for PV(j-1) right after the barrier; lands under the softmax
-                if (kP) stage_softmax(e_prev);
-                if (do_fetch) fetch((int)(e_f & BLKMASK), kslot_f, vslot_f);
-                asm volatile("" ::: "memory");
-                if (kP && kS) stage_PV_S(Vt, Kt);
-                else { if (kP) stage_PV(Vt); if (kS) stage_S(Kt); }
+                dma();
+                if (kP) finish_prev(e_prev, Vt);
+                if (kS) start_cur(e_cur, Kt);
+#pragma unroll
+                for (int i = 0; i < RING; ++i) read_frag(2 * NPS + i, Vt, Kt, Kn);
             }
+            rk[0] = rk[1];
+            rk[1] = rk[2];
             e_prev = e_cur;
 #pragma unroll
-            for (int b = 0; b + 1 < PD; ++b) eq[b] = eq[b + 1];
-            eq[PD - 1] = e_f;
-            ++kslot; if (kslot >= NK) kslot = 0;
+            for (int b = 0; b + 1 < AK; ++b) eq[b] = eq[b + 1];
+            eq[AK - 1] = e_f;
+            kslot = kslot_n;
             ++vslot; if (vslot >= NV) vslot = 0;
         }
-        // tail: the PV product of the last block (group 1 still owes its softmax).  The K ring is idle
-        // from here on, so the epilogue's state fragments are fetched into it under these MFMAs.
+        // tail: the last block's second half and its O products.  The K ring is idle from here on, so the epilogue's
+        // state fragments are fetched into it under these MFMAs.
         WAIT_VM(0);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
@@ -556,10 +602,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         {
             int vslot_prev = vslot - 1; if (vslot_prev < 0) vslot_prev += NV;
             v_last = vslot_prev;
-            const u16 *Vt = Vb + vslot_prev * TILE;
-            const bool kP = (e_prev & mybit) != 0;
-            if (group == 1 && kP) { preload_V(Vt); stage_softmax(e_prev); }
-            if (kP) stage_PV(Vt);
+            if ((e_prev & mybit) != 0) finish_prev(e_prev, Vb + vslot_prev * TILE);
         }
     }
 
@@ -617,13 +660,14 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     }
     if (!DBG) {
         // bf16 results leave through LDS so that every global store is a run of full 256-byte rows: accumulator
-        // layout (lane = query l32; 4 consecutive columns per (dt, g4, hh)) -> a wave-private 8 KB of the V ring
-        // (the four slots that do not hold the last block: nobody reads them any more), 16-byte chunk c of row r at
+        // layout (lane = query l32; 4 consecutive columns per (dt, g4, hh)) -> a wave-private half of a free tile
+        // (K slots 2..4, behind the state, and the V slot after the last block's: nobody reads them any more), 16-byte chunk c of row r at
         // r * 256 + ((c ^ (r & 15)) << 4) -> row layout (4 rows x 16 chunks per instruction).
-        int vs = v_last + 1 + (wave >> 1);
+        int vs = v_last + 1;
         if (vs >= NV) vs -= NV;
+        u16 *free_tile = wave < 6 ? Kb + (2 + (wave >> 1)) * TILE : Vb + vs * TILE;
         constexpr int ROWB = D * 2;          // bytes of a row
-        unsigned char *stg = reinterpret_cast<unsigned char *>(Vb + vs * TILE) + (wave & 1) * (32 * ROWB);
+        unsigned char *stg = reinterpret_cast<unsigned char *>(free_tile) + (wave & 1) * (32 * ROWB);
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -683,18 +727,17 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     }
 }
 
-template <int PD, bool DBG, int MODE = 0, bool ROPE = false, int D = 128>
+template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128>
 static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
 {
     const int ntiles = (a.nb + 3) / 4;
     const int total = MODE == 2 ? a.g_max_tiles : a.B * a.H * ntiles;
     const int per_xcd = (total + 7) / 8;
     const int list_cap = (a.nb + 63) & ~63;
-    const size_t lds = (size_t)(2 * PD + 3) * 64 * D * 2 + (size_t)list_cap * 4;
-    static_assert(PD + 1 >= 2, "the epilogue stages the state fragments (two tiles' worth) in the K ring");
+    const size_t lds = (size_t)9 * 64 * D * 2 + (size_t)list_cap * 4;
     constexpr int kMaxDyn = 160 * 1024 - 2048;   // the static part is rounded up to its 1 KB alignment
     if (lds > (size_t)kMaxDyn) return hipErrorInvalidValue;
-    auto kern = sparse_attn_v5_kernel<D, PD, DBG, MODE, ROPE>;
+    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE>;
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), kMaxDyn, attr_done); e != hipSuccess) return e;
     launch_kernel(kern, dim3(per_xcd * 8), dim3(512), lds, st, a, ntiles, total, per_xcd, list_cap);
@@ -706,12 +749,12 @@ hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st)
     const bool dbg = a.o_sparse_dbg || a.o_linear_dbg;
     if (a.D == 64) {
         if (a.g_desc || a.topk_mask || a.rope_tab) return hipErrorInvalidValue;
-        return dbg ? launch_v5<3, true, 0, false, 64>(a, st) : launch_v5<3, false, 0, false, 64>(a, st);
+        return dbg ? launch_v5<true, 0, false, 64>(a, st) : launch_v5<false, 0, false, 64>(a, st);
     }
-    if (a.g_desc) return launch_v5<3, false, 2>(a, st);
-    if (a.topk_mask) return dbg ? launch_v5<3, true, 1>(a, st) : launch_v5<3, false, 1>(a, st);
-    if (a.rope_tab) return dbg ? launch_v5<3, true, 0, true>(a, st) : launch_v5<3, false, 0, true>(a, st);
-    return dbg ? launch_v5<3, true>(a, st) : launch_v5<3, false>(a, st);
+    if (a.g_desc) return launch_v5<false, 2>(a, st);
+    if (a.topk_mask) return dbg ? launch_v5<true, 1>(a, st) : launch_v5<false, 1>(a, st);
+    if (a.rope_tab) return dbg ? launch_v5<true, 0, true>(a, st) : launch_v5<false, 0, true>(a, st);
+    return dbg ? launch_v5<true>(a, st) : launch_v5<false>(a, st);
 }
 
 }  // namespace salad

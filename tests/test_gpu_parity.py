@@ -204,6 +204,25 @@ def test_fp32_tile_edges(oracle, B, H, d, grid, kept):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grid,kept", [
+    ((1, 1, 40), [1, 1]),                        # one block, both halves of it partly past the end
+    ((2, 7, 5), [1, 2]),                         # 70 tokens: the tail block has 6 keys, its second half none
+    ((3, 5, 13), [1, 2, 3, 4]),                  # 195 tokens, 4 blocks
+    ((3, 13, 14), [1, 2, 3, 4, 5, 6, 7, 8, 9]),  # 546 tokens, 9 blocks: lists of 4 to 9 entries, around the 4 blocks fetched ahead
+    ((5, 28, 31), [61, 62, 66, 68]),             # 4340 tokens, 68 blocks: lists of 64 and more entries, read in chunks of 64
+])
+def test_visit_list_lengths(oracle, d, grid, kept):
+    """The attention kernel's pipeline at the ends of its visit lists: fewer entries than it fetches ahead, the wait at the
+    last ones, the second chunk of a list, blocks without keys in their second half; both head orders, bf16."""
+    w = wl.small(f"lists-{d}-{grid[0] * grid[1] * grid[2]}", 1, len(kept), d, *grid, "bf16", 0.5, seed=400 + d + grid[2])
+    inp = wl.make_inputs(w)
+    kinds = wl.head_kinds(w)
+    for dbg in (True, False):
+        res = run_layer(w, inp, upload(w, inp), kept, kinds, dbg=dbg)
+        compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), label=w.name)
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_sixty_four_heads(oracle, d):
     """The largest head count the boundary takes (64: the head-order mask is a 64-bit word, the last head temporal),
     every head with its own window size.  The gate runs over D = 4096 (d = 64) and D = 8192 (d = 128, the widest row the
