@@ -14,7 +14,7 @@
 // The token range of a head is cut into chunks, one workgroup each; the fp32 partial states go to
 // the workspace and are added in chunk order by the finalize kernel (no float atomics, so results
 // are reproducible run to run).
-#include "salad_internal.h"
+#include "gate_part.h"
 
 namespace salad {
 
@@ -60,18 +60,11 @@ __device__ inline uint32_t relu_bf16x2(uint32_t x)
 // ROPE: the rotary linear branch (Sec. 4.1): after the ReLU and the Z sums (which stay unrotated), channel pair
 // (2p, 2p+1) of token n is rotated by the angle whose cosine and sine sit, as two fp16 values in one word, at
 // rope_tab[n * D/2 + p], before it enters the outer products, so the state is sum_j (R_j relu(K_j))^T V_j.
-template <int D, bool ROPE = false>
-__global__ __launch_bounds__(256, 2) void state_partial_kernel(const u16 *__restrict__ k,
-                                                               const u16 *__restrict__ v, int N,
-                                                               int tiles_per_chunk, int P,
-                                                               float *__restrict__ partial,
-                                                               const int32_t *__restrict__ drop, int H,
-                                                               const uint32_t *__restrict__ rope_tab = nullptr)
+template <int D, bool ROPE>
+__device__ inline __attribute__((always_inline)) void state_chunk(const u16 *__restrict__ k, const u16 *__restrict__ v, int N, int tiles_per_chunk,
+                                                                  int P, float *__restrict__ partial, const uint32_t *__restrict__ rope_tab,
+                                                                  int bh, int chunk)
 {
-    // ROPE: the sample-head index runs fastest over the grid, so that the workgroups that read the same rows of the
-    // angle tables (same token chunk, different heads) run at the same time and the tables come from HBM once
-    const int bh = ROPE ? blockIdx.x : blockIdx.y, chunk = ROPE ? blockIdx.y : blockIdx.x;
-    if (drop && drop[bh / H]) return;                  // pruned sample (Sec. 4.3): K, V are not read
     constexpr int CH = D / 8;          // 16-byte chunks per row
     constexpr int TPT = D / 32;        // tokens per thread per tile (4 for d=128, 2 for d=64)
     constexpr int QT = D / 64;         // 32x32 tiles per side of a wave's quadrant
@@ -223,6 +216,64 @@ __global__ __launch_bounds__(256, 2) void state_partial_kernel(const u16 *__rest
     if (tid < D) out[D * D + tid] = (zred[0][tid] + zred[1][tid]) + (zred[2][tid] + zred[3][tid]);
 }
 
+template <int D, bool ROPE = false>
+__global__ __launch_bounds__(256, 2) void state_partial_kernel(const u16 *__restrict__ k,
+                                                               const u16 *__restrict__ v, int N,
+                                                               int tiles_per_chunk, int P,
+                                                               float *__restrict__ partial,
+                                                               const int32_t *__restrict__ drop, int H,
+                                                               const uint32_t *__restrict__ rope_tab = nullptr)
+{
+    // ROPE: the sample-head index runs fastest over the grid, so that the workgroups that read the same rows of the
+    // angle tables (same token chunk, different heads) run at the same time and the tables come from HBM once
+    const int bh = ROPE ? blockIdx.x : blockIdx.y, chunk = ROPE ? blockIdx.y : blockIdx.x;
+    if (drop && drop[bh / H]) return;                  // pruned sample (Sec. 4.3): K, V are not read
+    state_chunk<D, ROPE>(k, v, N, tiles_per_chunk, P, partial, rope_tab, bh, chunk);
+}
+
+// State chunks and gate partial sums in one launch: both are passes over inputs that nothing before them writes, and alone each
+// has a start and an end in which the memory system idles (the state leaves half a CU's wave slots empty, too).  The gate's
+// workgroups come last in the grid and fill in behind the state's.  Layer call at N = 1950, H = 12: 42.9 -> 38.6 us; N = 12480:
+// 320 -> 315; N = 32760: 723 -> 712; N = 75600, H = 40: 11491 -> 11441.  The same bits as the two launches.
+template <int D, int NCH, int TOK, bool ROPE>
+__global__ __launch_bounds__(256, 2) void state_gate_kernel(const u16 *__restrict__ k, const u16 *__restrict__ v, int N, int tiles_per_chunk, int P,
+                                                            float *__restrict__ partial, int BH, GateArgs g,
+                                                            const uint32_t *__restrict__ rope_tab)
+{
+    __shared__ float wave_sum[4];
+    const int i = blockIdx.x, state_blocks = BH * P;
+    // ROPE: heads fastest, see state_partial_kernel
+    if (i < state_blocks) state_chunk<D, ROPE>(k, v, N, tiles_per_chunk, P, partial, rope_tab, ROPE ? i % BH : i / P, ROPE ? i / BH : i % P);
+    else gate_part<true, NCH, TOK>(g.x_t, g.w, g.bias, N, g.D, g.partial, g.nparts, (i - state_blocks) / g.nparts, (i - state_blocks) % g.nparts,
+                                   threadIdx.x >> 6, wave_sum);
+}
+
+// wider rows keep the gate weights in LDS (gate_partial_wide_kernel) and stay a launch of their own
+bool state_gate_fits(int Dm) { return Dm <= 512 * GATE_MAX_CHUNKS; }
+
+hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int D, float *partial, int target_wgs, const GateArgs &g, int B,
+                                  hipStream_t st, const uint32_t *rope_tab)
+{
+    if (rope_tab && D != 128) return hipErrorInvalidValue;
+    const int tpc = state_tiles_per_chunk(BH, N, target_wgs), P = state_num_chunks(BH, N, target_wgs);
+    const int nch = (g.D / 8 + 63) / 64;
+    const dim3 grid(BH * P + g.nparts * B), block(256);
+    auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, st, k, v, N, tpc, P, partial, BH, g, rope_tab); };
+    auto by_width = [&](auto dc, auto rc) {
+        constexpr int DD = decltype(dc)::value;
+        constexpr bool R = decltype(rc)::value;
+        if (nch <= 1) go(state_gate_kernel<DD, 1, 4, R>);
+        else if (nch <= 2) go(state_gate_kernel<DD, 2, 4, R>);
+        else if (nch <= 3) go(state_gate_kernel<DD, 3, 2, R>);
+        else if (nch <= 5) go(state_gate_kernel<DD, 5, 2, R>);
+        else go(state_gate_kernel<DD, GATE_MAX_CHUNKS, 1, R>);
+    };
+    if (rope_tab) by_width(std::integral_constant<int, 128>{}, std::true_type{});
+    else if (D == 128) by_width(std::integral_constant<int, 128>{}, std::false_type{});
+    else by_width(std::integral_constant<int, 64>{}, std::false_type{});
+    return take_launch_status();
+}
+
 hipError_t launch_state_partial_bf16(const u16 *k, const u16 *v, int BH, int N, int D,
                                      float *partial, const int32_t *drop, int H, int target_wgs, hipStream_t st,
                                      const uint32_t *rope_tab)
@@ -270,15 +321,12 @@ hipError_t launch_rope_pack(const float *rope_cos, const float *rope_sin, size_t
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(1024) void state_f32_kernel(const float *__restrict__ k, const float *__restrict__ v,
-                                                         int N, int D, float *__restrict__ Hs, float *__restrict__ Z,
-                                                         const int32_t *__restrict__ drop, int H)
+__device__ inline __attribute__((always_inline)) void state_f32_tile(const float *__restrict__ k, const float *__restrict__ v, int N, int D,
+                                                                     float *__restrict__ Hs, float *__restrict__ Z, int bh, int tile)
 {
     __shared__ float part[16][256], zpart[16][16];
-    const int bh = blockIdx.y;
-    if (drop && drop[bh / H]) return;                  // pruned sample (Sec. 4.3)
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = lane & 15, g = lane >> 4;
-    const int nt = D / 16, a0 = (blockIdx.x / nt) * 16, c0 = (blockIdx.x % nt) * 16;
+    const int nt = D / 16, a0 = (tile / nt) * 16, c0 = (tile % nt) * 16;
     const float *kb = k + (size_t)bh * N * D + a0 + i;
     const float *vb = v + (size_t)bh * N * D + c0 + i;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -318,6 +366,40 @@ __global__ __launch_bounds__(1024) void state_f32_kernel(const float *__restrict
         for (int x = 1; x < 16; ++x) t += zpart[x][e - 256];
         Z[(size_t)bh * D + a0 + e - 256] = t;
     }
+}
+
+__global__ __launch_bounds__(1024) void state_f32_kernel(const float *__restrict__ k, const float *__restrict__ v,
+                                                         int N, int D, float *__restrict__ Hs, float *__restrict__ Z,
+                                                         const int32_t *__restrict__ drop, int H)
+{
+    if (drop && drop[blockIdx.y / H]) return;          // pruned sample (Sec. 4.3)
+    state_f32_tile(k, v, N, D, Hs, Z, blockIdx.y, blockIdx.x);
+}
+
+// fp32 state and gate in one launch: state tiles first, then workgroups of four gate partial sums each.  Layer call at H = 2,
+// N = 1024, d = 64: 19.0 -> 16.9 us.  Rows up to 1024 channels: the gate weights of wider ones do not fit the 128 registers
+// of a 1024-thread workgroup.
+__global__ __launch_bounds__(1024) void state_gate_f32_kernel(const float *__restrict__ k, const float *__restrict__ v, int N, int D,
+                                                              float *__restrict__ Hs, float *__restrict__ Z, int BH, GateArgs g)
+{
+    __shared__ float wave_sum[4][4];
+    const int tiles = (D / 16) * (D / 16), i = blockIdx.x;
+    if (i < tiles * BH) {
+        state_f32_tile(k, v, N, D, Hs, Z, i / tiles, i % tiles);
+        return;
+    }
+    const int per_b = (g.nparts + 3) / 4, x = i - tiles * BH, w = threadIdx.x >> 6;
+    gate_part<false, 2, 1>(g.x_t, g.w, g.bias, N, g.D, g.partial, g.nparts, x / per_b, (x % per_b) * 4 + (w >> 2), w & 3, wave_sum[w >> 2]);
+}
+
+bool state_gate_f32_fits(int Dm) { return Dm <= 1024; }
+
+hipError_t launch_state_gate_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z, const GateArgs &g, int B,
+                                 hipStream_t st)
+{
+    const int blocks = (D / 16) * (D / 16) * BH + (g.nparts + 3) / 4 * B;
+    launch_kernel(state_gate_f32_kernel, dim3(blocks), dim3(1024), 0, st, k, v, N, D, Hs, Z, BH, g);
+    return take_launch_status();
 }
 
 hipError_t launch_state_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z,

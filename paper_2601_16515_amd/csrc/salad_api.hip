@@ -495,7 +495,11 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     int32_t *drop = dropping ? (int32_t *)(ws + w.drop) : nullptr;
     mark(0);
     if (use_linear) {
-        if (need_gate) {
+        // the gate's pass 1 rides in the state's launch, except where its result is needed first (dropping) or each stage is
+        // being timed
+        const bool with_state = need_gate && !dropping && timing != 1 && (bf16 ? state_gate_fits(Dm) : state_gate_f32_fits(Dm));
+        const GateArgs g{p->x_t, p->w_gate, p->b_gate, Dm, (float *)(ws + w.gate_partial), w.nparts};
+        if (need_gate && !with_state) {
             e = launch_gate_partial(p->x_t, p->w_gate, p->b_gate, p->B, p->N, Dm, bf16, (float *)(ws + w.gate_partial), w.nparts, st);
             if (e != hipSuccess) return give_back(), hip_fail(e, "gate launch");
         }
@@ -509,9 +513,9 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         f.s_out = p->s_out; f.s_ws = (float *)(ws + w.s); f.coef = (float *)(ws + w.coef); f.do_gate = 1;
         f.tau = p->drop_threshold; f.drop = drop; f.dropped_out = dropping ? p->dropped_out : nullptr;
         if (dropping) {
-            FinalizeArgs g = f;
-            g.P = 0;                                   // gate part only: s, coefficients, drop flags
-            e = launch_finalize(g, st);
+            FinalizeArgs fg = f;
+            fg.P = 0;                                  // gate part only: s, coefficients, drop flags
+            e = launch_finalize(fg, st);
             if (e != hipSuccess) return give_back(), hip_fail(e, "gate reduce launch");
             f.do_gate = 0;
         }
@@ -522,9 +526,15 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
                 e = launch_rope_pack(p->rope_cos, p->rope_sin, (size_t)p->N * (p->d / 2), (uint32_t *)(ws + w.rope_tab), st);
                 if (e != hipSuccess) return give_back(), hip_fail(e, "rotary table launch");
             }
-            e = launch_state_partial_bf16((const u16 *)p->k, (const u16 *)p->v, BH, p->N, p->d, (float *)(ws + w.state_partial), drop, p->H, state_wgs, st,
-                                          rope ? (const uint32_t *)(ws + w.rope_tab) : nullptr);
+            if (with_state)
+                e = launch_state_gate_bf16((const u16 *)p->k, (const u16 *)p->v, BH, p->N, p->d, (float *)(ws + w.state_partial), state_wgs, g, p->B, st,
+                                           rope ? (const uint32_t *)(ws + w.rope_tab) : nullptr);
+            else
+                e = launch_state_partial_bf16((const u16 *)p->k, (const u16 *)p->v, BH, p->N, p->d, (float *)(ws + w.state_partial), drop, p->H, state_wgs, st,
+                                              rope ? (const uint32_t *)(ws + w.rope_tab) : nullptr);
         }
+        else if (with_state)
+            e = launch_state_gate_f32((const float *)p->k, (const float *)p->v, BH, p->N, p->d, (float *)(ws + w.Hs), (float *)(ws + w.Z), g, p->B, st);
         else
             e = launch_state_f32((const float *)p->k, (const float *)p->v, BH, p->N, p->d, (float *)(ws + w.Hs), (float *)(ws + w.Z), drop, p->H, st);
         if (e != hipSuccess) return give_back(), hip_fail(e, "state launch");

@@ -43,6 +43,15 @@ hipError_t launch_rope_pack(const float *rope_cos, const float *rope_sin, size_t
 hipError_t launch_state_f32(const float *k, const float *v, int BH, int N, int D,
                             float *Hs, float *Z, const int32_t *drop, int H, hipStream_t st);
 
+// The state and the gate's pass 1 as one launch (no dropping).  *_fits: whether the gate's row width Dm goes with it.
+struct GateArgs { const void *x_t; const float *w; float bias; int D; float *partial; int nparts; };
+bool state_gate_fits(int Dm);
+hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int D, float *partial, int target_wgs, const GateArgs &g, int B,
+                                  hipStream_t st, const uint32_t *rope_tab);
+bool state_gate_f32_fits(int Dm);
+hipError_t launch_state_gate_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z, const GateArgs &g, int B,
+                                 hipStream_t st);
+
 // ---- finalize: reduce partials, dynamic scale, coefficients ---------------------------------------
 struct FinalizeArgs {
     int B, H, D;

@@ -222,6 +222,30 @@ def test_visit_list_lengths(oracle, d, grid, kept):
         compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), label=w.name)
 
 
+@pytest.mark.parametrize("B,H,d,grid,dtype", [
+    (2, 1, 64, (1, 3, 5), "bf16"), (1, 5, 128, (3, 7, 11), "bf16"), (3, 12, 128, (2, 5, 13), "bf16"), (1, 16, 128, (1, 1, 1), "bf16"),
+    (1, 40, 128, (2, 9, 9), "bf16"), (1, 41, 128, (2, 3, 3), "bf16"), (2, 2, 64, (2, 9, 11), "f32"), (1, 8, 128, (1, 4, 5), "f32"),
+    (1, 9, 128, (1, 4, 5), "f32"),
+])
+def test_gate_rides_with_the_state(B, H, d, grid, dtype):
+    """Gate and state in one launch (every row width the launch is built for, and the first beyond) give the bits of the two
+    launches that the per-stage timing mode makes."""
+    w = wl.small(f"ride-{H}-{d}", B, H, d, *grid, dtype, 0.5, seed=500 + H)
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    rope = tuple(torch.from_numpy(t).cuda() for t in wl.rope_tables(*grid, d)) if dtype == "bf16" and d == 128 else None
+    kinds, kept = wl.head_kinds(w), [max(1, w.nb // 2)] * H
+    for r in {None, rope}:
+        got = run_layer(w, inp, dev, kept, kinds, dbg=False, rope=r)
+        sb.salad_timing_enable(1)
+        try:
+            ref = run_layer(w, inp, dev, kept, kinds, dbg=False, rope=r)
+        finally:
+            sb.salad_timing_read(True)
+            sb.salad_timing_enable(0)
+        assert np.array_equal(got["s"], ref["s"]) and torch.equal(got["out_t"], ref["out_t"])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_sixty_four_heads(oracle, d):
     """The largest head count the boundary takes (64: the head-order mask is a 64-bit word, the last head temporal),
