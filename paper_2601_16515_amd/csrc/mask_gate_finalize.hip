@@ -155,10 +155,10 @@ hipError_t launch_gate_partial(const void *x_t, const float *w, float bias, int 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Finalize.  Workgroups [0, BH*ceil((D*D+D)/64)) add up the P partial states of one head in chunk
+// Finalize.  All workgroups but the first (the first too without a gate part) add up the P partial states of one head in chunk
 // order (fp32) and emit Hs, Z and Hs rounded to bf16 laid out as MFMA A-operand fragments
 // of Hs^T:  element (a, c) -> ((c/32 * (D/16) + a/16) * 64 + ((a%16)/8)*32 + c%32) * 8 + a%8.
-// The last workgroup reduces the gate partial sums (or takes the caller's s), writes s and the
+// The first workgroup reduces the gate partial sums (or takes the caller's s), writes s and the
 // per-(b, h) coefficient lambda * a_h * s_b of the residual sum (Alg. 1, Sec. 4.2).
 // ------------------------------------------------------------------------------------------------
 __device__ inline u16 f32_to_bf16_rne(float f)
@@ -168,37 +168,44 @@ __device__ inline u16 f32_to_bf16_rne(float f)
     return (u16)(u >> 16);
 }
 
-__global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int state_blocks, int blocks_per_head)
+__global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int gate_blocks, int blocks_per_head)
 {
     const int D = a.D;
-    __shared__ float part[4][64];
-    if ((int)blockIdx.x < state_blocks) {
-        // 64 state elements per workgroup; the P partials are split over 4 thread groups (more loads in
-        // flight), each group adds its share in chunk order, the 4 sums are added in group order
-        const int bh = blockIdx.x / blocks_per_head;
+    __shared__ __attribute__((aligned(16))) float part[4][256];
+    if ((int)blockIdx.x >= gate_blocks) {
+        // 256 state elements per workgroup, 4 per thread; the P partials are split over 4 thread groups (more loads in
+        // flight), each group adds its share in chunk order, the 4 sums are added in group order.  With 64 elements per
+        // workgroup the launch was bound by its own workgroup count: 6192 of them at 24 heads took 10.0 us, 5.0 now
+        // (12 heads 5.9 -> 4.4; the gate's workgroup, once last in the grid, starts first).
+        const int x = blockIdx.x - gate_blocks, bh = x / blocks_per_head;
         if (a.drop && a.drop[bh / a.H]) return;        // pruned sample: its partial states were not computed
-        const int le = threadIdx.x & 63, grp = threadIdx.x >> 6;
-        const int e = (blockIdx.x - bh * blocks_per_head) * 64 + le;
-        const int per = D * D + D;
-        float s = 0.f;
-        if (e < per) {
-            const float *p = a.state_partial + (size_t)bh * a.P * per + e;
+        const int grp = threadIdx.x >> 6, le = (threadIdx.x & 63) * 4;
+        const int e0 = (x - bh * blocks_per_head) * 256;
+        const int per = D * D + D;                     // a multiple of 4: a thread's elements exist together
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (e0 + le < per) {
+            const float *p = a.state_partial + (size_t)bh * a.P * per + e0 + le;
             const int c0 = (a.P * grp) / 4, c1 = (a.P * (grp + 1)) / 4;
-            for (int c = c0; c < c1; ++c) s += p[(size_t)c * per];
+#pragma unroll 6
+            for (int c = c0; c < c1; ++c) {
+                const float4 v = *reinterpret_cast<const float4 *>(p + (size_t)c * per);
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            }
         }
-        part[grp][le] = s;
+        *reinterpret_cast<float4 *>(&part[grp][le]) = s;
         __syncthreads();
-        if (grp != 0 || e >= per) return;
-        s = (part[0][le] + part[1][le]) + (part[2][le] + part[3][le]);
+        const int t = threadIdx.x, e = e0 + t;
+        if (e >= per) return;
+        const float v = (part[0][t] + part[1][t]) + (part[2][t] + part[3][t]);
         if (e < D * D) {
-            a.Hs[(size_t)bh * D * D + e] = s;
+            a.Hs[(size_t)bh * D * D + e] = v;
             if (a.hfrag) {
                 int row = e / D, col = e - row * D;   // Hs[row = a][col = c]
                 int idx = ((col / 32 * (D / 16) + row / 16) * 64 + ((row % 16) / 8) * 32 + col % 32) * 8 + row % 8;
-                a.hfrag[(size_t)bh * D * D + idx] = f32_to_bf16_rne(s);
+                a.hfrag[(size_t)bh * D * D + idx] = f32_to_bf16_rne(v);
             }
         } else {
-            a.Z[(size_t)bh * D + (e - D * D)] = s;
+            a.Z[(size_t)bh * D + (e - D * D)] = v;
         }
         return;
     }
@@ -238,10 +245,9 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int state
 
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st)
 {
-    int per = a.D * a.D + a.D;
-    int blocks_per_head = (per + 63) / 64;
-    int state_blocks = a.P > 0 ? a.B * a.H * blocks_per_head : 0;
-    launch_kernel(finalize_kernel, dim3(state_blocks + (a.do_gate ? 1 : 0)), dim3(256), 0, st, a, state_blocks, blocks_per_head);
+    const int per = a.D * a.D + a.D, blocks_per_head = (per + 255) / 256, gate_blocks = a.do_gate ? 1 : 0;
+    const int state_blocks = a.P > 0 ? a.B * a.H * blocks_per_head : 0;
+    launch_kernel(finalize_kernel, dim3(gate_blocks + state_blocks), dim3(256), 0, st, a, gate_blocks, blocks_per_head);
     return take_launch_status();
 }
 
