@@ -170,7 +170,8 @@ typedef struct salad_fwd_params {
 #define SALAD_FLAG_UNFUSED_EPILOGUE 1
 
 /* Device scratch the forward needs for these shapes (partial states, partial gate sums, the
- * reduced state, per-tile block lists; with w_proj also O_l and the rearranged W_p; with topk the key-block means,
+ * reduced state, per-tile block lists, for shapes whose last round of tiles is cut into pieces the pieces'
+ * results (at most 33 MB); with w_proj also O_l and the rearranged W_p; with topk the key-block means,
  * the masks and per-sample lists).  Reads only B, H, N, d, dtype, topk and whether w_proj and rope_cos are NULL.
  * 0 on invalid shapes. */
 size_t salad_fwd_workspace_bytes(const salad_fwd_params *p);

@@ -37,8 +37,9 @@ salad_status hip_fail(hipError_t e, const char *what)
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
-    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, total;
+    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, total;
     int nparts, P;
+    SplitPlan split;
 };
 
 // tuning knobs (salad_tune): atomics, read once at the top of an entry point and passed down by value, so that a
@@ -62,9 +63,11 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     w.s = off; off = align256(off + sizeof(float) * B);
     w.coef = off; off = align256(off + sizeof(float) * BH);
     w.drop = off; off = align256(off + sizeof(int32_t) * B);
+    bool large_lists = false;
     {   // union lists per (head, 4-block tile) for the large-tile attention kernel
         const int nb = (N + 63) / 64, ntiles = (nb + 3) / 4;
         const bool need = dtype == SALAD_BF16 && (d == 128 || (d == 64 && !topk)) && (size_t)tile_list_cap(nb) * 4 <= 24 * 1024;
+        large_lists = need;
         const size_t nl = topk ? BH : (size_t)H;       // Top-K masks differ between samples
         w.tile_lists = off; off = align256(off + (need ? sizeof(uint32_t) * nl * ntiles * tile_list_cap(nb) : 0));
         w.tile_counts = off; off = align256(off + (need ? sizeof(int32_t) * nl * ntiles : 0));
@@ -90,6 +93,12 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
         w.g_po = off; off = align256(off + (topk ? sizeof(u16) * pairs * d : 0));
     }
     w.rope_tab = off; off = align256(off + (rope ? sizeof(uint32_t) * (size_t)N * (d / 2) : 0));
+    // pieces of the large-tile kernel's last round (CSR masks): at most 256 of them
+    if (dtype == SALAD_BF16 && !topk && large_lists) w.split = split_plan((int)BH, (N + 63) / 64);
+    const size_t np = w.split.pieces > 1 ? (size_t)w.split.rest * w.split.pieces : 0;
+    w.sp_o = off; off = align256(off + sizeof(float) * np * 256 * (size_t)d);
+    w.sp_ml = off; off = align256(off + sizeof(uint64_t) * np * 512);
+    w.sp_count = off; off = align256(off + sizeof(int32_t) * (np ? (size_t)w.split.rest : 0));
     w.total = off;
     return w;
 }
@@ -462,6 +471,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     const int BH = p->B * p->H;
     const bool bf16 = p->dtype == SALAD_BF16;
     hipError_t e;
+    const bool split = w.split.pieces > 1 && large_tile;      // the last round's tiles are cut
 
     CallEvents ev{};
     int timing;
@@ -512,6 +522,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         f.s_dev = p->s_dev; f.lambda = p->lambda; f.head_scale = p->head_scale;
         f.s_out = p->s_out; f.s_ws = (float *)(ws + w.s); f.coef = (float *)(ws + w.coef); f.do_gate = 1;
         f.tau = p->drop_threshold; f.drop = drop; f.dropped_out = dropping ? p->dropped_out : nullptr;
+        f.clear = (int32_t *)(ws + w.sp_count); f.n_clear = split ? w.split.rest : 0;
         if (dropping) {
             FinalizeArgs fg = f;
             fg.P = 0;                                  // gate part only: s, coefficients, drop flags
@@ -546,6 +557,10 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     } else {
         mark(1);
         mark(2);
+        if (split) {
+            e = launch_clear_counts((int32_t *)(ws + w.sp_count), w.split.rest, st);
+            if (e != hipSuccess) return give_back(), hip_fail(e, "counter launch");
+        }
     }
     mark(3);
 
@@ -565,6 +580,10 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     a.write_sparse_only = unfused;
     a.drop = drop;
     a.variant = attn_variant;
+    if (split) {
+        a.sp_full = w.split.full; a.sp_pieces = w.split.pieces;
+        a.sp_o = (uint64_t *)(ws + w.sp_o); a.sp_ml = (uint64_t *)(ws + w.sp_ml); a.sp_count = (int32_t *)(ws + w.sp_count);
+    }
     a.rope_tab = rope_fused && use_linear ? (const uint32_t *)(ws + w.rope_tab) : nullptr;
     if (topk) {
         // App. A.1.2: key-block means -> per-query selection -> per-tile visit lists; the mask never leaves the device

@@ -72,6 +72,7 @@ struct FinalizeArgs {
     float tau;
     int32_t *drop;       // [B] in the workspace
     int32_t *dropped_out;// [B] caller's copy (may be null)
+    int32_t *clear; int n_clear;    // counters that the gate part sets to 0 (n_clear may be 0)
 };
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 
@@ -111,6 +112,10 @@ struct AttnArgs {
     int g_kk, g_bpb, g_max_tiles;
     const uint32_t *rope_tab;       // large-tile kernel, fused epilogue only: [N, 64] angle words (fp16 cos | fp16 sin << 16) of the
                                     // rotary linear branch (the state fragments then hold the rotated state), or null
+    // large-tile kernel, CSR lists, sp_pieces > 1: tiles from sp_full (a multiple of 256) on are cut into up to sp_pieces workgroups.
+    // Per piece: pairs of fp32, O [d * 128], (reference, row sum) [512]; per tile a counter that is 0 at launch
+    int sp_full, sp_pieces;
+    uint64_t *sp_o, *sp_ml; int32_t *sp_count;
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };
 hipError_t launch_sparse_attn_bf16(const AttnArgs &a, hipStream_t st);
@@ -119,6 +124,10 @@ hipError_t launch_sparse_attn_bf16(const AttnArgs &a, hipStream_t st);
 bool attn_takes_large_tile(const AttnArgs &a);
 // union lists of the CSR rows of every 4-query-block tile (input of the large-tile attention kernel)
 int tile_list_cap(int nb);
+// how the large-tile kernel cuts the tiles of its last, partial round (BH sample-heads of nb blocks); pieces < 2: not at all
+struct SplitPlan { int full, rest, pieces; };
+SplitPlan split_plan(int BH, int nb);
+hipError_t launch_clear_counts(int32_t *count, int n, hipStream_t st);
 hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int H, int nb, uint32_t *lists,
                              int32_t *counts, hipStream_t st);
 hipError_t launch_sparse_attn_f32(const AttnArgs &a, hipStream_t st);

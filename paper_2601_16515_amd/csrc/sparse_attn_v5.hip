@@ -45,6 +45,9 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8)
 #define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | (n))
 
+constexpr int SPLIT_MAX_PIECES = 8;
+constexpr int SPLIT_MIN_ENTRIES = 6;     // least entries of a piece: what a cut costs (two passes over 128 KB, a prologue) is about as long
+
 namespace {
 
 __device__ inline int row_of_position5(int kind, int p, int T, int HW, unsigned magic)
@@ -200,7 +203,11 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 // D = 64 (MODE 0 without ROPE only): the same kernel on half-size tiles.  A row is 8 chunks of 16 bytes instead of 16,
 // so one pass of the 512 threads fetches a whole 64-row tile, the swizzles below take the row pair instead of the row
 // (rows 128 bytes apart alternate between the two halves of the banks), and every fragment count halves.
-template <int D, bool DBG, int MODE = 0, bool ROPE = false>
+// SPLIT (MODE 0 only): the tiles from a.sp_full on, which do not fill the chip, are cut along their visit lists into up to a.sp_pieces
+// workgroups each.  Every piece runs its own softmax over its entries, writes O, the reference and the row sum in fp32, and counts
+// itself in; the piece that comes last reads the others back, combines all in piece order (so the result does not depend on which
+// it was) and goes on to the epilogue.  Nobody waits for anybody.
+template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false>
 __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
 {
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
@@ -219,8 +226,22 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     auto kswz = [](int row) INL -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
     auto vswz = [](int row) INL -> int { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); };
     const int g = blockIdx.x;
-    const int L = (g & 7) * per_xcd + (g >> 3);
-    if (L >= total) return;
+    int L, piece = 0, pieces = 1;
+    if (SPLIT) {      // an XCD's share: its run of whole tiles, then its run of pieces
+        const int fx = a.sp_full / 8, r = (g >> 3) - fx, np = (total - a.sp_full) * a.sp_pieces, px = (np + 7) / 8;
+        if (r < 0) {
+            L = (g & 7) * fx + (g >> 3);
+        } else {
+            const int q = (g & 7) * px + r;
+            if (r >= px || q >= np) return;
+            L = a.sp_full + q / a.sp_pieces;
+            piece = q - (L - a.sp_full) * a.sp_pieces;
+            pieces = a.sp_pieces;
+        }
+    } else {
+        L = (g & 7) * per_xcd + (g >> 3);
+        if (L >= total) return;
+    }
     int bh = L / ntiles, tile = L - bh * ntiles;
     int g_J = 0, g_slot0 = 0, g_cnt = 0;
     if (GATHER) {
@@ -267,7 +288,14 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     // ---- this tile's union list (built by the pre-pass): the whole row of list_cap slots is copied, so
     // the copy does not wait for the count (slots past the count hold stale words that are never used)
     const int g_blk0 = g_J * a.g_bpb;
-    const int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile];
+    int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile];
+    int list0 = 0;                       // SPLIT: this piece's first entry
+    if (SPLIT && pieces > 1) {
+        pieces = min(pieces, max(1, n / SPLIT_MIN_ENTRIES));
+        if (piece >= pieces) return;
+        list0 = n * piece / pieces;
+        n = n * (piece + 1) / pieces - list0;
+    }
     uint32_t qm_lo = 0u, qm_hi = 0u;     // TOPK: this lane's query's key-block bits
     if (TOPK && qvalid) {
         const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow];
@@ -278,7 +306,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         for (int i = tid; i < list_cap; i += 512) blist[i] = (uint32_t)min(g_blk0 + i, nb - 1) | 0xff000000u;
     } else {
         const uint32_t *src = a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
-        for (int i = tid; i < list_cap; i += 512) blist[i] = src[i];
+        for (int i = tid; i < list_cap; i += 512) blist[i] = src[SPLIT ? min(i + list0, list_cap - 1) : i];
     }
     __syncthreads();
     // Retire the Q loads here: inside the loop the only vector-memory operations in flight must be the
@@ -597,13 +625,65 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         WAIT_VM(0);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (lin) stage_state();
-        if (ROPE && lin) load_angles();
+        if (lin && !(SPLIT && pieces > 1)) stage_state();
+        if (ROPE && lin && !(SPLIT && pieces > 1)) load_angles();
         {
             int vslot_prev = vslot - 1; if (vslot_prev < 0) vslot_prev += NV;
             v_last = vslot_prev;
             if ((e_prev & mybit) != 0) finish_prev(e_prev, Vb + vslot_prev * TILE);
         }
+    }
+
+    if (SPLIT && pieces > 1) {
+        const int first = (L - a.sp_full) * a.sp_pieces;      // the tile's pieces in the scratch
+        constexpr int PER = NDT * 8 * 512;                    // register pairs of a piece: pair r of thread tid at r * 512 + tid
+        // The pieces of a tile may run on different XCDs, whose L2 caches do not see each other.  Instead of fences, which
+        // write back and invalidate a whole L2 (101 against 37 us for a layer call of N = 1950), the scratch is written and
+        // read with device-scope accesses, which go past it: a piece's stores are at the common level when they are
+        // acknowledged, which every wave waits for before the workgroup counts itself in.
+        auto put = [&](uint64_t *p, float x, float y) INL {
+            __hip_atomic_store(p, (uint64_t)__float_as_uint(x) | (uint64_t)__float_as_uint(y) << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        auto get = [&](const uint64_t *p) INL -> float2 {
+            const uint64_t v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+        };
+        uint64_t *mine = a.sp_o + (size_t)(first + piece) * PER + tid;
+#pragma unroll
+        for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 8; ++r) put(mine + (dt * 8 + r) * 512, o[dt][2 * r], o[dt][2 * r + 1]);
+        // a wave that kept no entry of this piece has no reference, and nothing to add
+        put(a.sp_ml + (size_t)(first + piece) * 512 + tid, have_ref ? m_run : -INFINITY, l_run);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        WAIT_VM(0);
+        __syncthreads();
+        if (tid == 0) blist[0] = (uint32_t)__hip_atomic_fetch_add(a.sp_count + (L - a.sp_full), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if ((int)blist[0] != pieces - 1) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        float mx = -INFINITY;
+        for (int p = 0; p < pieces; ++p) mx = fmaxf(mx, get(a.sp_ml + (size_t)(first + p) * 512 + tid).x);
+#pragma unroll
+        for (int i = 0; i < NDT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
+        l_run = 0.f;
+        for (int p = 0; p < pieces; ++p) {
+            const float2 ml = get(a.sp_ml + (size_t)(first + p) * 512 + tid);
+            const float wt = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - mx);
+            const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + tid;
+            l_run = fmaf(wt, ml.y, l_run);
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const float2 v = get(src + (dt * 8 + r) * 512);
+                    o[dt][2 * r] = fmaf(wt, v.x, o[dt][2 * r]);
+                    o[dt][2 * r + 1] = fmaf(wt, v.y, o[dt][2 * r + 1]);
+                }
+        }
+        m_run = mx;
     }
 
     // ---- epilogue ---------------------------------------------------------------------------------
@@ -612,7 +692,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     f32x16 num[NDT];
     float lin_scale = 0.f, inv_den = 0.f;
     if (lin) {
-        if (n == 0) { stage_state(); if (ROPE) load_angles(); }
+        if (n == 0 || (SPLIT && pieces > 1)) { stage_state(); if (ROPE) load_angles(); }
         float dpart = 0.f;
         const float *Zh = a.Z + (size_t)bh * D;
 #pragma unroll
@@ -727,7 +807,24 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     }
 }
 
-template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128>
+SplitPlan split_plan(int BH, int nb)
+{
+    // 256 workgroups run at a time (one per compute unit).  Whole rounds of 256 tiles stay as they are; the rest, if it leaves at
+    // least half of the chip idle, is cut into as many pieces as there is room for.
+    // Layer call before -> after: 49 tiles of 12 heads (512 + 76 workgroups, 52 entries) 300 -> 269 us; 44 tiles, 42 entries, dense
+    // 79 -> 46; 184 tiles of 2 x 12 heads 675 -> 629; 25 tiles of 5 heads 64 -> 55.  A list of 11 entries cut in two gained nothing
+    // (37.4 -> 38.5), hence SPLIT_MIN_ENTRIES; with it calls that are not cut measure the same as before.
+    const long long total = (long long)BH * ((nb + 3) / 4);
+    SplitPlan p{};
+    p.full = (int)(total / 256 * 256);
+    p.rest = (int)(total - p.full);
+    p.pieces = p.rest ? 256 / p.rest : 1;
+    if (p.pieces > SPLIT_MAX_PIECES) p.pieces = SPLIT_MAX_PIECES;
+    if (nb < 2 * SPLIT_MIN_ENTRIES) p.pieces = 1;             // no list of this length is cut
+    return p;
+}
+
+template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false>
 static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
 {
     const int ntiles = (a.nb + 3) / 4;
@@ -737,22 +834,26 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     const size_t lds = (size_t)9 * 64 * D * 2 + (size_t)list_cap * 4;
     constexpr int kMaxDyn = 160 * 1024 - 2048;   // the static part is rounded up to its 1 KB alignment
     if (lds > (size_t)kMaxDyn) return hipErrorInvalidValue;
-    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE>;
+    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT>;
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), kMaxDyn, attr_done); e != hipSuccess) return e;
-    launch_kernel(kern, dim3(per_xcd * 8), dim3(512), lds, st, a, ntiles, total, per_xcd, list_cap);
+    const int grid = SPLIT ? a.sp_full + ((total - a.sp_full) * a.sp_pieces + 7) / 8 * 8 : per_xcd * 8;
+    launch_kernel(kern, dim3(grid), dim3(512), lds, st, a, ntiles, total, per_xcd, list_cap);
     return take_launch_status();
 }
 
 hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st)
 {
-    const bool dbg = a.o_sparse_dbg || a.o_linear_dbg;
+    const bool dbg = a.o_sparse_dbg || a.o_linear_dbg, split = a.sp_pieces > 1 && !a.g_desc && !a.topk_mask;
     if (a.D == 64) {
         if (a.g_desc || a.topk_mask || a.rope_tab) return hipErrorInvalidValue;
+        if (split) return dbg ? launch_v5<true, 0, false, 64, true>(a, st) : launch_v5<false, 0, false, 64, true>(a, st);
         return dbg ? launch_v5<true, 0, false, 64>(a, st) : launch_v5<false, 0, false, 64>(a, st);
     }
     if (a.g_desc) return launch_v5<false, 2>(a, st);
     if (a.topk_mask) return dbg ? launch_v5<true, 1>(a, st) : launch_v5<false, 1>(a, st);
+    if (split && a.rope_tab) return dbg ? launch_v5<true, 0, true, 128, true>(a, st) : launch_v5<false, 0, true, 128, true>(a, st);
+    if (split) return dbg ? launch_v5<true, 0, false, 128, true>(a, st) : launch_v5<false, 0, false, 128, true>(a, st);
     if (a.rope_tab) return dbg ? launch_v5<true, 0, true>(a, st) : launch_v5<false, 0, true>(a, st);
     return dbg ? launch_v5<true>(a, st) : launch_v5<false>(a, st);
 }

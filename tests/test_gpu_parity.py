@@ -222,6 +222,34 @@ def test_visit_list_lengths(oracle, d, grid, kept):
         compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), label=w.name)
 
 
+@pytest.mark.parametrize("B,H,d,grid,kept", [
+    (1, 3, 128, (5, 13, 17), [18, 5, 13]),       # 15 tiles in up to 8 pieces; lists of 18 (3 pieces), 8 (whole) and 16 (2 pieces) entries
+    (2, 2, 64, (3, 29, 31), [43, 30]),           # 44 tiles in 5 pieces, the last tile of 3 blocks
+    (1, 1, 128, (1, 7, 110), [13]),              # 13 blocks: the shortest list that is cut, one head, spatial
+    (1, 64, 64, (2, 17, 32), [9 + h % 9 for h in range(64)]),   # 320 tiles: a whole round of 256, then 64 in 4 pieces
+])
+def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
+    """Tiles of the last, partial round cut along their visit lists: against the oracle, the same bits on every call (whichever
+    piece comes last combines them) and with the counters cleared by either kernel (with and without the linear branch)."""
+    w = wl.small(f"cut-{d}-{grid[0] * grid[1] * grid[2]}", B, H, d, *grid, "bf16", 0.5, seed=600 + d + grid[2])
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    kinds = wl.head_kinds(w)
+    res = run_layer(w, inp, dev, kept, kinds)
+    compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), label=w.name)
+    row_ptr, col_idx = sb.salad_block_mask(w.T, w.Hh, w.W, w.block, kept)
+    ws = sb.Workspace(B, H, w.N, d, sb.SALAD_BF16)
+    ws.buf.fill_(0x5a)                           # the counters start from whatever the memory holds
+    outs = {}
+    for i in range(8):
+        lam = 0.0 if i % 2 else w.lam
+        out = sb.salad_sparse_linear_attn_fwd(dev["q"], dev["k"], dev["v"], grid, row_ptr, col_idx, kinds, lam=lam, head_scale=dev["head_scale"],
+                                              x_t=dev["x_t"], w_gate=dev["w_gate"], eps=w.eps, workspace=ws)
+        assert torch.equal(out, outs.setdefault(lam, out))
+    assert torch.equal(outs[w.lam], res["out_t"])
+    assert errors(outs[0.0].double().cpu().numpy(), res["o_sparse"])[1] < 4e-3      # one bf16 rounding (2^-9) of each value
+
+
 @pytest.mark.parametrize("B,H,d,grid,dtype", [
     (2, 1, 64, (1, 3, 5), "bf16"), (1, 5, 128, (3, 7, 11), "bf16"), (3, 12, 128, (2, 5, 13), "bf16"), (1, 16, 128, (1, 1, 1), "bf16"),
     (1, 40, 128, (2, 9, 9), "bf16"), (1, 41, 128, (2, 3, 3), "bf16"), (2, 2, 64, (2, 9, 11), "f32"), (1, 8, 128, (1, 4, 5), "f32"),
