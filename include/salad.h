@@ -171,7 +171,7 @@ typedef struct salad_fwd_params {
 
 /* Device scratch the forward needs for these shapes (partial states, partial gate sums, the
  * reduced state, per-tile block lists, for shapes whose last round of tiles is cut into pieces the pieces'
- * results (at most 33 MB); with w_proj also O_l and the rearranged W_p; with topk the key-block means,
+ * results (at most 35 MB); with w_proj also O_l and the rearranged W_p; with topk the key-block means,
  * the masks and per-sample lists).  Reads only B, H, N, d, dtype, topk and whether w_proj and rope_cos are NULL.
  * 0 on invalid shapes. */
 size_t salad_fwd_workspace_bytes(const salad_fwd_params *p);
