@@ -185,7 +185,7 @@ def main():
                      "unit": "TFLOP/s", "frac": flops / (attn_ms * 1e-3) * 1e-12 / PEAK_BF16_TFLOPS,
                      "traffic": measured_attn_traffic() if args.sparsity is None else None,
                      "traffic_source": TRAFFIC_FILE + " (stored rocprofv3 --pmc figure, not collected in this run)",
-                     "kernel": "sparse_attn_v5_kernel<3> alone (visit lists prebuilt with the mask)", "kernel_ms": attn_ms},
+                     "kernel": "sparse_attn_v5_kernel alone (visit lists prebuilt with the mask)", "kernel_ms": attn_ms},
         "kernels_ms": {"gate": gate_ms, "linear_state": state_ms, "finalize": fin_ms, "sparse_attn_fused": attn_ms,
                        "empty_stage_bracket": empty_ms,
                        "pass_with_every_stage_bracketed": {"ms_per_step": ms_all, "sparse_attn_fused": attn_ms_all}},
