@@ -249,7 +249,10 @@ __global__ __launch_bounds__(256, 2) void state_gate_kernel(const u16 *__restric
 }
 
 // wider rows keep the gate weights in LDS (gate_partial_wide_kernel) and stay a launch of their own
-bool state_gate_fits(int Dm) { return Dm <= 512 * GATE_MAX_CHUNKS; }
+bool state_gate_fits(const GateArgs &g, int B, int BH, int P)
+{
+    return g.D <= 512 * GATE_MAX_CHUNKS && grid_dim_fits((long long)BH * P + (long long)g.nparts * B, 256);
+}
 
 hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int D, float *partial, int target_wgs, const GateArgs &g, int B,
                                   hipStream_t st, const uint32_t *rope_tab)
@@ -392,13 +395,20 @@ __global__ __launch_bounds__(1024) void state_gate_f32_kernel(const float *__res
     gate_part<false, 2, 1>(g.x_t, g.w, g.bias, N, g.D, g.partial, g.nparts, x / per_b, (x % per_b) * 4 + (w >> 2), w & 3, wave_sum[w >> 2]);
 }
 
-bool state_gate_f32_fits(int Dm) { return Dm <= 1024; }
+static long long state_gate_f32_blocks(const GateArgs &g, int B, int BH, int D)
+{
+    return (long long)(D / 16) * (D / 16) * BH + (g.nparts + 3) / 4 * (long long)B;
+}
+
+bool state_gate_f32_fits(const GateArgs &g, int B, int BH, int D)
+{
+    return g.D <= 1024 && grid_dim_fits(state_gate_f32_blocks(g, B, BH, D), 1024);
+}
 
 hipError_t launch_state_gate_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z, const GateArgs &g, int B,
                                  hipStream_t st)
 {
-    const int blocks = (D / 16) * (D / 16) * BH + (g.nparts + 3) / 4 * B;
-    launch_kernel(state_gate_f32_kernel, dim3(blocks), dim3(1024), 0, st, k, v, N, D, Hs, Z, BH, g);
+    launch_kernel(state_gate_f32_kernel, dim3((unsigned)state_gate_f32_blocks(g, B, BH, D)), dim3(1024), 0, st, k, v, N, D, Hs, Z, BH, g);
     return take_launch_status();
 }
 

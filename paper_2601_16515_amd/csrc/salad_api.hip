@@ -507,8 +507,9 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     if (use_linear) {
         // the gate's pass 1 rides in the state's launch, except where its result is needed first (dropping) or each stage is
         // being timed
-        const bool with_state = need_gate && !dropping && timing != 1 && (bf16 ? state_gate_fits(Dm) : state_gate_f32_fits(Dm));
         const GateArgs g{p->x_t, p->w_gate, p->b_gate, Dm, (float *)(ws + w.gate_partial), w.nparts};
+        const bool with_state = need_gate && !dropping && timing != 1 &&
+                                (bf16 ? state_gate_fits(g, p->B, BH, w.P) : state_gate_f32_fits(g, p->B, BH, p->d));
         if (need_gate && !with_state) {
             e = launch_gate_partial(p->x_t, p->w_gate, p->b_gate, p->B, p->N, Dm, bf16, (float *)(ws + w.gate_partial), w.nparts, st);
             if (e != hipSuccess) return give_back(), hip_fail(e, "gate launch");

@@ -43,12 +43,13 @@ hipError_t launch_rope_pack(const float *rope_cos, const float *rope_sin, size_t
 hipError_t launch_state_f32(const float *k, const float *v, int BH, int N, int D,
                             float *Hs, float *Z, const int32_t *drop, int H, hipStream_t st);
 
-// The state and the gate's pass 1 as one launch (no dropping).  *_fits: whether the gate's row width Dm goes with it.
+// The state and the gate's pass 1 as one launch (no dropping).  *_fits: whether the gate's row width g.D goes with it and the
+// workgroups of both (B samples, BH sample-heads, P state chunks) go into one grid dimension.
 struct GateArgs { const void *x_t; const float *w; float bias; int D; float *partial; int nparts; };
-bool state_gate_fits(int Dm);
+bool state_gate_fits(const GateArgs &g, int B, int BH, int P);
 hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int D, float *partial, int target_wgs, const GateArgs &g, int B,
                                   hipStream_t st, const uint32_t *rope_tab);
-bool state_gate_f32_fits(int Dm);
+bool state_gate_f32_fits(const GateArgs &g, int B, int BH, int D);
 hipError_t launch_state_gate_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z, const GateArgs &g, int B,
                                  hipStream_t st);
 
@@ -202,12 +203,17 @@ inline hipError_t launch_with(const void *kernel, dim3 grid, dim3 block, size_t 
     void *ptrs[] = {static_cast<void *>(&std::get<I>(vals))...};
     return hipLaunchKernel(kernel, grid, block, ptrs, lds, st);
 }
+// The runtime takes a grid of 2^32 threads or more in one dimension modulo 2^32, without an error: part of the work would be
+// left out.  A launcher that can reach this size splits its grid; launch_kernel refuses the rest.
+inline bool grid_dim_fits(long long blocks, unsigned threads) { return blocks * (long long)threads < (1ll << 32); }
 template <class... P, class... A>
 inline void launch_kernel(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t st, A &&...args)
 {
     static_assert(sizeof...(P) == sizeof...(A), "every kernel parameter needs its argument");
     std::tuple<std::remove_cv_t<P>...> vals(static_cast<P>(std::forward<A>(args))...);   // copies in the parameter types
-    const hipError_t e = launch_with(reinterpret_cast<const void *>(kernel), grid, block, lds, st, vals, std::index_sequence_for<P...>{});
+    const hipError_t e = grid_dim_fits(grid.x, block.x) && grid_dim_fits(grid.y, block.y)
+                             ? launch_with(reinterpret_cast<const void *>(kernel), grid, block, lds, st, vals, std::index_sequence_for<P...>{})
+                             : hipErrorInvalidConfiguration;
     if (e != hipSuccess && launch_status_slot() == hipSuccess) launch_status_slot() = e;
 }
 

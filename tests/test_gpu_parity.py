@@ -250,6 +250,20 @@ def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     assert errors(outs[0.0].double().cpu().numpy(), res["o_sparse"])[1] < 4e-3      # one bf16 rounding (2^-9) of each value
 
 
+def test_fp32_state_and_gate_of_many_samples():
+    """The state and the gate of 247000 samples: 16 state tiles and one gate workgroup of 1024 threads a sample are more than
+    the 2^32 threads that one grid dimension holds (beyond, the runtime drops workgroups without an error)."""
+    B, d = 247000, 64
+    q, k, v, x = (torch.randn(B, 1, 1, d, generator=torch.Generator("cuda").manual_seed(s), device="cuda") for s in range(4))
+    wg = torch.randn(d, generator=torch.Generator("cuda").manual_seed(4), device="cuda") * 0.05
+    row_ptr, col_idx = sb.salad_block_mask(1, 1, 1, 64, [1])
+    out = sb.salad_sparse_linear_attn_fwd(q, k, v, (1, 1, 1), row_ptr, col_idx, lam=1.0, x_t=x.view(B, 1, d), w_gate=wg)
+    q, k, v, x = (t.double().view(B, d) for t in (q, k, v, x))
+    dot = (q.clamp(min=0) * k.clamp(min=0)).sum(1, keepdim=True)
+    want = v + torch.sigmoid(x @ wg.double())[:, None] * v * dot / (dot + 1e-6)
+    assert float((out.view(B, d).double() - want).norm() / want.norm()) < 1e-5
+
+
 @pytest.mark.parametrize("B,H,d,grid,dtype", [
     (2, 1, 64, (1, 3, 5), "bf16"), (1, 5, 128, (3, 7, 11), "bf16"), (3, 12, 128, (2, 5, 13), "bf16"), (1, 16, 128, (1, 1, 1), "bf16"),
     (1, 40, 128, (2, 9, 9), "bf16"), (1, 41, 128, (2, 3, 3), "bf16"), (2, 2, 64, (2, 9, 11), "f32"), (1, 8, 128, (1, 4, 5), "f32"),
