@@ -17,6 +17,8 @@
 // wave and unit at d = 64) with two or three waves per SIMD beyond that.  One wave per query with the dot products on the
 // vector unit took 48.0 us at B = 1, H = 2, N = 1024, d = 64, 4 of 16 blocks kept and 481 us at H = 4, N = 2080, 16 of 33 kept;
 // this takes 8.5 and 44.9 us (50.3 us with K read straight into operand order).
+#include <algorithm>
+
 #include "salad_internal.h"
 
 namespace salad {
@@ -34,9 +36,10 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a, int
     // wave-private: the unit's K rows; after the last unit rows 0..15 take the wave's partial result
     __shared__ __attribute__((aligned(16))) float stage[4][32][PITCH];
     __shared__ float msh[4][16], lsh[4][16];
-    // consecutive workgroups go to the 8 XCDs in turn: give each XCD a contiguous range of (head, tile)
-    const int L = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (L >= total) return;
+    // consecutive workgroups go to the 8 XCDs in turn: give each XCD a contiguous range of a slice's (head, tile)
+    const long long l64 = (long long)blockIdx.y * (8ll * per_xcd) + (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (l64 >= total) return;
+    const int L = (int)l64;
     const int bh = L / ntiles, tile = L - bh * ntiles, h = bh % a.H;
     const int N = a.N, T = a.T, HW = a.HW;
     const int kind = T > 1 ? (int)((a.kind_mask >> h) & 1ull) : 0;
@@ -219,9 +222,10 @@ hipError_t launch_sparse_attn_f32(const AttnArgs &a, hipStream_t st)
 {
     const int ntiles = (a.N + 15) / 16;
     const long long total = (long long)a.B * a.H * ntiles;
-    if (total > 0x7ffffff0ll / 256) return hipErrorInvalidValue;
-    const int per_xcd = (int)((total + 7) / 8);
-    auto go = [&](auto kern) { launch_kernel(kern, dim3(per_xcd * 8), dim3(256), 0, st, a, ntiles, (int)total, per_xcd); };
+    if (total > 0x7fffffffll) return hipErrorInvalidValue;
+    // one grid dimension takes fewer than 2^32 threads: more tiles lie in slices of 2^23 along y
+    const int per_xcd = (int)((std::min(total, 1ll << 23) + 7) / 8), slices = (int)((total + 8ll * per_xcd - 1) / (8ll * per_xcd));
+    auto go = [&](auto kern) { launch_kernel(kern, dim3(per_xcd * 8, slices), dim3(256), 0, st, a, ntiles, (int)total, per_xcd); };
     const bool div = a.kind_mask != 0 && a.T > 1 && a.t_magic == 0;
     if (a.D == 128) div ? go(sparse_attn_f32_kernel<128, true>) : go(sparse_attn_f32_kernel<128, false>);
     else div ? go(sparse_attn_f32_kernel<64, true>) : go(sparse_attn_f32_kernel<64, false>);

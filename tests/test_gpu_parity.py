@@ -264,6 +264,16 @@ def test_fp32_state_and_gate_of_many_samples():
     assert float((out.view(B, d).double() - want).norm() / want.norm()) < 1e-5
 
 
+def test_fp32_tiles_of_many_heads():
+    """8.4 million heads of one token: as many tiles, more than one grid dimension of 256-thread workgroups took."""
+    H, d = 64, 64
+    B = 8388672 // H                                               # 2^31 / 256 tiles are 8388608
+    v = torch.randn(B, H, 1, d, generator=torch.Generator("cuda").manual_seed(5), device="cuda")
+    row_ptr, col_idx = sb.salad_block_mask(1, 1, 1, 64, [1] * H)
+    out = sb.salad_sparse_linear_attn_fwd(v, v, v, (1, 1, 1), row_ptr, col_idx, lam=0.0)
+    assert torch.equal(out, v)                                     # one key: its value
+
+
 @pytest.mark.parametrize("B,H,d,grid,dtype", [
     (2, 1, 64, (1, 3, 5), "bf16"), (1, 5, 128, (3, 7, 11), "bf16"), (3, 12, 128, (2, 5, 13), "bf16"), (1, 16, 128, (1, 1, 1), "bf16"),
     (1, 40, 128, (2, 9, 9), "bf16"), (1, 41, 128, (2, 3, 3), "bf16"), (2, 2, 64, (2, 9, 11), "f32"), (1, 8, 128, (1, 4, 5), "f32"),
