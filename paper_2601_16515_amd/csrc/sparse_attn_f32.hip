@@ -135,6 +135,15 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a, int
                 s[kt][r] = here + kt * 16 + 4 * g + r < N ? __expf(s[kt][r] - mn) : 0.f;
                 l += s[kt][r];
             }
+        if (here + 32 > N) {                // keys past the end are copies of the last row: weight 0 alone would make NaN of an infinity
+#pragma unroll
+            for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (here + kt * 16 + 4 * g + r >= N)
+#pragma unroll
+                        for (int x = 0; x < D / 64; ++x) vv[kt][r][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll

@@ -250,6 +250,20 @@ def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     assert errors(outs[0.0].double().cpu().numpy(), res["o_sparse"])[1] < 4e-3      # one bf16 rounding (2^-9) of each value
 
 
+def test_fp32_infinite_value_in_the_last_row():
+    """Keys past the end of the sequence do not exist: an infinite V element of the last token gives infinity in its channel
+    and nothing anywhere else, whatever part of a 32-key unit the tail fills."""
+    for N in (160, 144, 130):                                      # tails of 32, 16 and 2 keys
+        q, k, v = (torch.from_numpy(wl.normal(643, t, (1, 1, N, 64))).cuda() for t in ("q", "k", "v"))
+        v[0, 0, N - 1, 5] = float("inf")
+        row_ptr, col_idx = sb.salad_block_mask(1, 1, N, 64, [3])
+        out = sb.salad_sparse_linear_attn_fwd(q, k, v, (1, 1, N), row_ptr, col_idx, lam=0.0)
+        v[0, 0, N - 1, 5] = 0.0
+        want = sb.salad_sparse_linear_attn_fwd(q, k, v, (1, 1, N), row_ptr, col_idx, lam=0.0)
+        want[..., 5] = float("inf")
+        assert torch.equal(out, want), N
+
+
 def test_fp32_state_and_gate_of_many_samples():
     """The state and the gate of 247000 samples: 16 state tiles and one gate workgroup of 1024 threads a sample are more than
     the 2^32 threads that one grid dimension holds (beyond, the runtime drops workgroups without an error)."""
