@@ -136,7 +136,7 @@ typedef struct salad_fwd_params {
     float *s_out;             /* optional device [B]: the dynamic scale that was applied          */
     float *o_sparse_dbg;      /* optional device fp32 [B,H,N,d]: sparse branch alone              */
     float *o_linear_dbg;      /* optional device fp32 [B,H,N,d]: unscaled linear branch alone     */
-    void *workspace;          /* device, >= salad_fwd_workspace_bytes(), 256-byte aligned; always needed */
+    void *workspace;          /* device, see salad_fwd_workspace_bytes(), 256-byte aligned; always needed */
     size_t workspace_bytes;
     int32_t flags;            /* SALAD_FLAG_* */
     void *hip_stream;
@@ -169,11 +169,14 @@ typedef struct salad_fwd_params {
  * kernel instead of inside its epilogue (same result up to rounding; bf16 only). */
 #define SALAD_FLAG_UNFUSED_EPILOGUE 1
 
-/* Device scratch the forward needs for these shapes (partial states, partial gate sums, the
+/* Device scratch the forward uses for these shapes (partial states, partial gate sums, the
  * reduced state, per-tile block lists, for shapes whose last round of tiles is cut into pieces the pieces'
  * results (at most 35 MB); with w_proj also O_l and the rearranged W_p; with topk the key-block means,
  * the masks and per-sample lists).  Reads only B, H, N, d, dtype, topk and whether w_proj and rope_cos are NULL.
- * 0 on invalid shapes. */
+ * 0 on invalid shapes.  The pieces' results can be left out: a smaller workspace that has room for the rest is taken and
+ * the tiles are not cut (same result up to rounding order), so that one workspace may serve the largest grid of a program
+ * and all smaller ones, although a small grid with pieces may ask for more than a large one without.
+ * SALAD_ENOSPC: below the rest. */
 size_t salad_fwd_workspace_bytes(const salad_fwd_params *p);
 
 /* Alg. 1 from SparseAttn to the residual sum:
@@ -216,7 +219,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p);
 /* ---- single steps (the same kernels the layer call launches) -------------------------------- */
 
 /* Eq. (3) sums: Hs [B,H,d,d] (Hs[a][c] = sum_j relu(K[j][a]) V[j][c]) and Z [B,H,d], fp32.
- * workspace as for the layer call with the same B, H, N, d, dtype. */
+ * workspace as for the layer call with the same B, H, N, d, dtype (nothing is cut here: no room for pieces needed). */
 salad_status salad_linear_state_fwd(const void *k, const void *v, int32_t B, int32_t H, int32_t N,
                                     int32_t d, int32_t dtype, float *Hs_out, float *Z_out,
                                     void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -37,7 +37,7 @@ salad_status hip_fail(hipError_t e, const char *what)
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
-    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, total;
+    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, base, total;
     int nparts, P;
     SplitPlan split;
 };
@@ -93,6 +93,7 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
         w.g_po = off; off = align256(off + (topk ? sizeof(u16) * pairs * d : 0));
     }
     w.rope_tab = off; off = align256(off + (rope ? sizeof(uint32_t) * (size_t)N * (d / 2) : 0));
+    w.base = off;       // what a call needs; the rest only makes it faster, and a workspace without room for it is taken
     // pieces of the large-tile kernel's last round (CSR masks): at most 256 of them
     if (dtype == SALAD_BF16 && !topk && large_lists) w.split = split_plan((int)BH, (N + 63) / 64);
     const size_t np = w.split.pieces > 1 ? (size_t)w.split.rest * w.split.pieces : 0;
@@ -306,7 +307,7 @@ salad_status salad_linear_state_fwd(const void *k, const void *v, int32_t B, int
     const int state_wgs = g_state_target_wgs.load();
     WsLayout w = ws_layout(B, H, N, d, dtype, state_wgs);
     if (!workspace || ((uintptr_t)workspace & 255)) return fail(SALAD_EINVAL, "salad_linear_state_fwd: workspace null or not 256-byte aligned");
-    if (workspace_bytes < w.total) return fail(SALAD_ENOSPC, "salad_linear_state_fwd: workspace %zu < %zu bytes", workspace_bytes, w.total);
+    if (workspace_bytes < w.base) return fail(SALAD_ENOSPC, "salad_linear_state_fwd: workspace %zu < %zu bytes", workspace_bytes, w.base);
     char *ws = (char *)workspace;
     hipError_t e = launch_state_partial_bf16((const u16 *)k, (const u16 *)v, B * H, N, d, (float *)(ws + w.state_partial), nullptr, H, state_wgs, st);
     if (e != hipSuccess) return hip_fail(e, "state_partial launch");
@@ -457,7 +458,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     const bool need_lists = p->dtype == SALAD_BF16 && (p->d == 128 || p->d == 64) && (size_t)tile_list_cap((p->N + 63) / 64) * 4 <= 24 * 1024;
     if (use_linear || need_lists) {
         if (!p->workspace || ((uintptr_t)p->workspace & 255)) return fail(SALAD_EINVAL, "fwd: workspace null or not 256-byte aligned");
-        if (p->workspace_bytes < w.total) return fail(SALAD_ENOSPC, "fwd: workspace %zu < %zu bytes", p->workspace_bytes, w.total);
+        if (p->workspace_bytes < w.base) return fail(SALAD_ENOSPC, "fwd: workspace %zu < %zu bytes", p->workspace_bytes, w.base);
     }
     uint64_t kind_mask = 0;
     if (p->head_kind_host)
@@ -471,7 +472,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     const int BH = p->B * p->H;
     const bool bf16 = p->dtype == SALAD_BF16;
     hipError_t e;
-    const bool split = w.split.pieces > 1 && large_tile;      // the last round's tiles are cut
+    const bool split = w.split.pieces > 1 && large_tile && p->workspace_bytes >= w.total;      // the last round's tiles are cut
 
     CallEvents ev{};
     int timing;

@@ -250,6 +250,32 @@ def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     assert errors(outs[0.0].double().cpu().numpy(), res["o_sparse"])[1] < 4e-3      # one bf16 rounding (2^-9) of each value
 
 
+def test_workspace_without_room_for_the_pieces(oracle):
+    """The scratch of cut tiles is optional: a workspace sized for a larger grid whose tiles fill whole rounds (no pieces)
+    serves a smaller one, whose tiles then run whole, and the state alone never needs it."""
+    H, d = 32, 64
+    w = wl.small("uncut", 1, H, d, 4, 13, 16, "bf16", 0.5, seed=640)          # N = 832: 128 tiles, 2 pieces each
+    large = sb.Workspace(1, H, 2048, d, sb.SALAD_BF16)                         # 256 tiles
+    assert large.bytes < sb.salad_fwd_workspace_bytes(1, H, w.N, d, sb.SALAD_BF16)
+    large.buf.fill_(0x5a)
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    kinds, kept = wl.head_kinds(w), [13] * H
+    ref = _oracle_layer(oracle, w, inp, kept, kinds)
+    cut = run_layer(w, inp, dev, kept, kinds, dbg=False)
+    row_ptr, col_idx = sb.salad_block_mask(w.T, w.Hh, w.W, w.block, kept)
+    for lists in (None, sb.salad_tile_lists(row_ptr, col_idx, H, w.nb)):
+        out = sb.salad_sparse_linear_attn_fwd(dev["q"], dev["k"], dev["v"], (w.T, w.Hh, w.W), row_ptr, col_idx, kinds, lam=w.lam,
+                                              head_scale=dev["head_scale"], x_t=dev["x_t"], w_gate=dev["w_gate"], eps=w.eps,
+                                              workspace=large, tile_lists=lists)
+        got = out.float().cpu().numpy().astype(np.float64)
+        compare_layer({"out": got}, ref, check_linear=False, label="uncut")
+        assert errors(got, cut["out"])[1] < 4e-3                               # two independently rounded bf16 results
+    Hs, Z = sb.salad_linear_state_fwd(dev["k"], dev["v"], large)
+    assert errors(Hs.cpu().numpy().astype(np.float64), ref["Hs"])[1] < 2e-6
+    assert errors(Z.cpu().numpy().astype(np.float64), ref["Z"])[1] < 2e-6
+
+
 def test_fp32_infinite_value_in_the_last_row():
     """Keys past the end of the sequence do not exist: an infinite V element of the last token gives infinity in its channel
     and nothing anywhere else, whatever part of a 32-key unit the tail fills."""
