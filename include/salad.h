@@ -96,8 +96,8 @@ salad_status salad_block_mask_mode(int32_t T, int32_t Hh, int32_t W, int32_t blo
  * CSR and passed to every layer call as salad_fwd_params.tile_lists; without them the layer call rebuilds them in its
  * workspace each time (a few microseconds).  Works for any CSR with ascending unique block ids per row.
  *   salad_tile_lists_bytes   size of the buffer for H heads and nb = ceil(N/64) blocks; 0 if the shape is invalid or the
- *                            lists of this nb do not fit the kernel (nb > 6144: the layer call then uses another kernel
- *                            and ignores tile_lists)
+ *                            lists of this nb fit no kernel (nb > 6144; at d = 128 the layer call uses another kernel and
+ *                            ignores tile_lists from nb > 3584 on, at d = 64 from nb > 6144 on)
  *   lists_dev                device, 256-byte aligned, >= salad_tile_lists_bytes (written); SALAD_ENOSPC if smaller */
 size_t salad_tile_lists_bytes(int32_t H, int32_t nb);
 salad_status salad_tile_lists(const int32_t *row_ptr_dev, const int32_t *col_idx_dev, int32_t H, int32_t nb,
@@ -151,7 +151,7 @@ typedef struct salad_fwd_params {
                                  largest dot product with it; row_ptr / col_idx are ignored (may be NULL).  Needs
                                  dtype bf16, d = 128.  Key blocks are runs of the head's own token order           */
     int32_t topk_key_block;   /* tokens (positions of the head's order) per key block: a multiple of 64 with
-                                 ceil(N / topk_key_block) <= 64                                                       */
+                                 ceil(N / topk_key_block) <= 64; N up to 229376 (3584 blocks of 64)                   */
     uint64_t *topk_mask_out;  /* optional device uint64 [B,H,N]: bit J set = the query keeps key block J            */
     const float *rope_cos;    /* optional device fp32 [N, d/2] (shared by all samples and heads), with rope_sin: rotary  */
     const float *rope_sin;    /*   position embedding inside the linear branch (Sec. 4.1): cosine and sine of the angle

@@ -66,7 +66,7 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     bool large_lists = false;
     {   // union lists per (head, 4-block tile) for the large-tile attention kernel
         const int nb = (N + 63) / 64, ntiles = (nb + 3) / 4;
-        const bool need = dtype == SALAD_BF16 && (d == 128 || (d == 64 && !topk)) && (size_t)tile_list_cap(nb) * 4 <= 24 * 1024;
+        const bool need = dtype == SALAD_BF16 && (d == 128 || !topk) && large_tile_list_fits(d, nb);
         large_lists = need;
         const size_t nl = topk ? BH : (size_t)H;       // Top-K masks differ between samples
         w.tile_lists = off; off = align256(off + (need ? sizeof(uint32_t) * nl * ntiles * tile_list_cap(nb) : 0));
@@ -246,7 +246,7 @@ salad_status salad_block_mask(int32_t T, int32_t Hh, int32_t W, int32_t block, i
 
 size_t salad_tile_lists_bytes(int32_t H, int32_t nb)
 {
-    if (H < 1 || H > 64 || nb < 1 || (size_t)tile_list_cap(nb) * 4 > 24 * 1024) return 0;
+    if (H < 1 || H > 64 || nb < 1 || tile_list_cap(nb) > LIST_MAX_ENTRIES) return 0;
     const size_t ntiles = ((size_t)nb + 3) / 4;
     return align256(sizeof(uint32_t) * (size_t)H * ntiles * tile_list_cap(nb)) + align256(sizeof(int32_t) * (size_t)H * ntiles);
 }
@@ -408,7 +408,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
                     if (g_topk_variant.load() != 0) return fail(SALAD_ENOTSUP, "fwd: topk_variant 1 works on the stored token order (head %d is TEMPORAL)", h);
                     if ((unsigned long long)p->N * (unsigned long long)p->T >= (1ull << 32)) return fail(SALAD_ENOTSUP, "fwd: topk: N * T too large for a TEMPORAL head");
                 }
-        if ((size_t)tile_list_cap((p->N + 63) / 64) * 4 > 24 * 1024 || (unsigned long long)p->N * 256ull >= (1ull << 32))
+        if (!attn_takes_large_tile(p->d, (p->N + 63) / 64, p->N, p->T, false, 0))
             return fail(SALAD_ENOTSUP, "fwd: topk: N = %d too long for the large-tile kernel", p->N);
     }
     if (p->tile_lists && ((uintptr_t)p->tile_lists & 255)) return fail(SALAD_EINVAL, "fwd: tile_lists not 256-byte aligned");
@@ -435,13 +435,10 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         if (!p->rope_cos || !p->rope_sin) return fail(SALAD_EINVAL, "fwd: rope_cos and rope_sin must be given together");
         if (p->dtype != SALAD_BF16 || p->d != 128) return fail(SALAD_ENOTSUP, "fwd: the rotary linear branch needs dtype bf16 and d = 128");
     }
-    // will the sparse branch run on the large-tile kernel?  (the same conditions as the dispatcher's: see attn_takes_large_tile)
     bool temporal_any = false;
-    if (p->head_kind_host && p->T > 1)
+    if (p->head_kind_host)
         for (int h = 0; h < p->H; ++h) temporal_any |= p->head_kind_host[h] == SALAD_HEAD_TEMPORAL;
-    const bool large_tile = p->dtype == SALAD_BF16 && (p->d == 128 || p->d == 64) && attn_variant == 0 &&
-                            (size_t)tile_list_cap((p->N + 63) / 64) * 4 <= 24 * 1024 && (unsigned long long)p->N * 256ull < (1ull << 32) &&
-                            (!temporal_any || (unsigned long long)p->N * (unsigned long long)p->T < (1ull << 32));
+    const bool large_tile = p->dtype == SALAD_BF16 && attn_takes_large_tile(p->d, (p->N + 63) / 64, p->N, p->T, temporal_any, attn_variant);
     const bool has_proj = p->w_proj != nullptr || p->w_proj_packed != nullptr;
     const bool rope_fused = rope && large_tile && !topk && !has_proj && !(p->flags & SALAD_FLAG_UNFUSED_EPILOGUE);
     const bool unfused = (p->flags & SALAD_FLAG_UNFUSED_EPILOGUE) != 0 || (has_proj && p->lambda != 0.f) ||
@@ -455,7 +452,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         if (p->head_scale) return fail(SALAD_EINVAL, "fwd: w_proj and head_scale exclude each other");
     }
     const WsLayout w = ws_layout(p->B, p->H, p->N, p->d, p->dtype, state_wgs, has_proj, topk ? p->topk : 0, p->rope_cos != nullptr);
-    const bool need_lists = p->dtype == SALAD_BF16 && (p->d == 128 || p->d == 64) && (size_t)tile_list_cap((p->N + 63) / 64) * 4 <= 24 * 1024;
+    const bool need_lists = p->dtype == SALAD_BF16 && large_tile_list_fits(p->d, (p->N + 63) / 64);
     if (use_linear || need_lists) {
         if (!p->workspace || ((uintptr_t)p->workspace & 255)) return fail(SALAD_EINVAL, "fwd: workspace null or not 256-byte aligned");
         if (p->workspace_bytes < w.base) return fail(SALAD_ENOSPC, "fwd: workspace %zu < %zu bytes", p->workspace_bytes, w.base);

@@ -120,11 +120,14 @@ struct AttnArgs {
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };
 hipError_t launch_sparse_attn_bf16(const AttnArgs &a, hipStream_t st);
-// whether launch_sparse_attn_bf16 will take the large-tile kernel for these arguments (the only one whose fused epilogue
-// knows the rotary linear branch)
-bool attn_takes_large_tile(const AttnArgs &a);
 // union lists of the CSR rows of every 4-query-block tile (input of the large-tile attention kernel)
+constexpr int LIST_MAX_ENTRIES = 6144;      // what the pre-pass sorts (13-bit positions, 48 KB of LDS)
 int tile_list_cap(int nb);
+// whether the large-tile kernel of head width d has LDS for the lists of nb blocks (d = 128: 3584, d = 64: LIST_MAX_ENTRIES)
+bool large_tile_list_fits(int d, int nb);
+// whether a bf16 call runs on the large-tile kernel (the only one whose fused epilogue knows the rotary linear branch): its list
+// fits, its 32-bit row offsets hold N rows, and where a head is temporal its multiply-high division by T is exact
+bool attn_takes_large_tile(int d, int nb, int N, int T, bool temporal, int variant);
 // how the large-tile kernel cuts the tiles of its last, partial round (BH sample-heads of nb blocks); pieces < 2: not at all
 struct SplitPlan { int full, rest, pieces; };
 SplitPlan split_plan(int BH, int nb);

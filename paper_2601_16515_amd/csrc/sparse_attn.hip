@@ -311,31 +311,23 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_kernel(AttnArgs a, in
     }
 }
 
-bool attn_takes_large_tile(const AttnArgs &a)
+bool attn_takes_large_tile(int d, int nb, int N, int T, bool temporal, int variant)
 {
-    if ((a.D != 128 && a.D != 64) || !a.tile_lists) return false;
-    if (a.topk_mask) return a.D == 128;
-    const bool temporal = a.kind_mask != 0 && a.T > 1;
-    return a.variant == 0 && (size_t)tile_list_cap(a.nb) * 4 <= 24 * 1024 && (unsigned long long)a.N * 256ull < (1ull << 32) &&
-           (!temporal || a.t_magic != 0);
+    return variant == 0 && large_tile_list_fits(d, nb) && (unsigned long long)N * 256ull < (1ull << 32) &&
+           (!temporal || T == 1 || (unsigned long long)N * (unsigned long long)T < (1ull << 32));
 }
 
 hipError_t launch_sparse_attn_bf16(const AttnArgs &a, hipStream_t st)
 {
-    // d = 128: the large-tile ping-pong kernel unless its block list does not fit in LDS or a variant is
-    // forced (a.variant: 0 = automatic, 1 = double-buffered 128-row kernel, 2 = first-generation kernel)
+    // the large-tile kernel, else (or where a.variant forces it) at d = 128 the double-buffered 128-row kernel, at d = 64 (and
+    // variant 2) the first-generation kernel
     const int variant = a.variant;
     if (a.topk_mask) {   // token-level mask: the large-tile kernel only (the host checks that the shape fits it)
         if (a.D != 128 || !a.tile_lists) return hipErrorInvalidValue;
         return launch_sparse_attn_v5(a, st);
     }
     if (variant != 2) {
-        // the large-tile kernel addresses rows with 32-bit byte offsets and divides by T with a
-        // multiply (t_magic); a T = 1 grid makes the temporal order the identity
-        const bool temporal = a.kind_mask != 0 && a.T > 1;
-        const bool fits = (size_t)tile_list_cap(a.nb) * 4 <= 24 * 1024 && (unsigned long long)a.N * 256ull < (1ull << 32) &&
-                          (!temporal || a.t_magic != 0);
-        if (variant == 0 && fits && a.tile_lists) return launch_sparse_attn_v5(a, st);
+        if (a.tile_lists && attn_takes_large_tile(a.D, a.nb, a.N, a.T, a.kind_mask != 0, variant)) return launch_sparse_attn_v5(a, st);
         if (a.D == 128) return launch_sparse_attn_v2(a, st);
     }
     const int ntiles = (a.nb + 1) / 2;

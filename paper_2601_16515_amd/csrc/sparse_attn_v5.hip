@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64) void tile_lists_kernel(const int32_t *__restric
     // consecutive ids, and for any other list the lowest position wins
     for (int i = lane; i < count; i += 64) {
         const uint32_t key = (lst[i] & 0xffffffu) % (uint32_t)count;
-        atomicMin(&best, (key << 13) | (uint32_t)i);      // at most 6144 entries (list size limit checked on the host)
+        atomicMin(&best, (key << 13) | (uint32_t)i);      // at most LIST_MAX_ENTRIES entries (checked on the host)
     }
     __syncthreads();
     const int rot = count > 0 ? (int)(best & 0x1fffu) : 0;
@@ -179,6 +179,14 @@ __global__ __launch_bounds__(64) void tile_lists_kernel(const int32_t *__restric
 }
 
 int tile_list_cap(int nb) { return (nb + 63) & ~63; }
+
+constexpr int V5_MAX_DYN = 160 * 1024 - 2048;       // the static part is rounded up to its 1 KB alignment
+constexpr int v5_ring_bytes(int d) { return 9 * 64 * d * 2; }     // 5 K and 4 V tiles
+
+bool large_tile_list_fits(int d, int nb)
+{
+    return tile_list_cap(nb) <= LIST_MAX_ENTRIES && v5_ring_bytes(d) + tile_list_cap(nb) * 4 <= V5_MAX_DYN;
+}
 
 hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int H, int nb, uint32_t *lists,
                              int32_t *counts, hipStream_t st)
@@ -830,13 +838,12 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     const int ntiles = (a.nb + 3) / 4;
     const int total = MODE == 2 ? a.g_max_tiles : a.B * a.H * ntiles;
     const int per_xcd = (total + 7) / 8;
-    const int list_cap = (a.nb + 63) & ~63;
-    const size_t lds = (size_t)9 * 64 * D * 2 + (size_t)list_cap * 4;
-    constexpr int kMaxDyn = 160 * 1024 - 2048;   // the static part is rounded up to its 1 KB alignment
-    if (lds > (size_t)kMaxDyn) return hipErrorInvalidValue;
+    if (!large_tile_list_fits(D, a.nb)) return hipErrorInvalidValue;
+    const int list_cap = tile_list_cap(a.nb);
+    const size_t lds = v5_ring_bytes(D) + (size_t)list_cap * 4;
     auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT>;
     static bool attr_done[16] = {};
-    if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), kMaxDyn, attr_done); e != hipSuccess) return e;
+    if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), V5_MAX_DYN, attr_done); e != hipSuccess) return e;
     const int grid = SPLIT ? a.sp_full + ((total - a.sp_full) * a.sp_pieces + 7) / 8 * 8 : per_xcd * 8;
     launch_kernel(kern, dim3(grid), dim3(512), lds, st, a, ntiles, total, per_xcd, list_cap);
     return take_launch_status();

@@ -142,6 +142,8 @@ def _params(**over):
     (dict(topk=4, topk_key_block=0, d=128), sb.SALAD_EINVAL, "multiple of 64"),
     (dict(topk=4, topk_key_block=64, d=128, N=8192, T=32), sb.SALAD_ENOTSUP, "key blocks"),   # 128 key blocks
     (dict(topk=4, topk_key_block=128, d=128, workspace_bytes=1 << 16), sb.SALAD_ENOSPC, "workspace"),
+    (dict(topk=4, topk_key_block=3648, d=128, N=229400, T=40, Hh=155, W=37, workspace_bytes=256), sb.SALAD_ENOTSUP, "too long"),   # 3585 blocks
+    (dict(topk=4, topk_key_block=3648, d=128, N=229320, T=40, Hh=63, W=91, workspace_bytes=256), sb.SALAD_ENOSPC, "workspace"),    # 3584 blocks
     (dict(rope_cos=0xa000, d=128), sb.SALAD_EINVAL, "together"),                          # cosine table without the sine table
     (dict(rope_sin=0xa000, d=128), sb.SALAD_EINVAL, "together"),
     (dict(rope_cos=0xa000, rope_sin=0xb000), sb.SALAD_ENOTSUP, "rotary"),                # d = 64

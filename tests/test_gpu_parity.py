@@ -1172,6 +1172,20 @@ def test_long_sequence_takes_the_fallback_by_itself(oracle, case):
     _sampled_parity(oracle, w, 8, w.name)
 
 
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("nb,grid", [(3584, (40, 63, 91)), (3585, (40, 155, 37)), (3563, (19000, 3, 4))])
+def test_edge_of_the_large_tile_kernel_at_d128(oracle, nb, grid):
+    """d = 128: the large-tile kernel's rings leave room for lists of 3584 entries; the first sequence beyond has to go to the
+    128-row kernel, lists passed in or not, and so does a shorter one whose temporal order it cannot divide (N T >= 2^32).  One
+    spatial and one temporal head, 5 kept blocks per row, ragged last block."""
+    w = wl.small(f"list-{nb}", 1, 2, 128, *grid, "bf16", 1.0 - 5.0 / nb, seed=133)
+    assert w.nb == nb and w.N % 64 and sb.salad_kept_from_sparsity(nb, w.sparsity) == 5
+    assert (w.N * w.T >= 1 << 32) == (nb == 3563)
+    res, _, inp, dev, kinds, kept = _sampled_parity(oracle, w, 8, w.name)
+    pre = run_layer(w, inp, dev, kept, kinds, dbg=False, prebuilt_lists=True)
+    assert np.array_equal(pre["out"], res["out"])
+
+
 @pytest.mark.parametrize("rho", [0.0, 0.5, 0.75, 0.95])
 def test_wan13_480p_sweep_sampled(oracle, rho):
     """The other points of the sparsity sweep at the 480p shape (same seeded inputs)."""
