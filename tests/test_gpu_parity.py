@@ -276,6 +276,28 @@ def test_workspace_without_room_for_the_pieces(oracle):
     assert errors(Z.cpu().numpy().astype(np.float64), ref["Z"])[1] < 2e-6
 
 
+@pytest.mark.parametrize("second_half", [True, False])
+def test_softmax_reference_is_the_first_block_maximum(second_half):
+    """Two keys carry the weight of every query, one in each half of the first block.  The reference is the larger of the two
+    logits wherever it sits, so its weight is 1 and the other one's is rounded to bf16: O_s to fp32 precision (a reference
+    taken from the first half alone rounds the other weight and is 1e-3 off)."""
+    N, d = 64, 128
+    a, b = (9, 41) if second_half else (41, 9)                     # logits 1.0 (key a) and 1.5 (key b), the others -300
+    q = torch.zeros(1, 1, N, d); k = torch.zeros(1, 1, N, d)
+    q[..., 0] = 1.0
+    k[..., 0] = -300.0
+    k[0, 0, a, 0], k[0, 0, b, 0] = 1.0, 1.5
+    v = torch.from_numpy(wl.round_to_bf16(wl.normal(642, "v", (1, 1, N, d))))
+    row_ptr, col_idx = sb.salad_block_mask(1, 8, 8, 64, [1])
+    o_s = torch.empty(1, 1, N, d, device="cuda")
+    sb.salad_sparse_linear_attn_fwd(q.bfloat16().cuda(), k.bfloat16().cuda(), v.bfloat16().cuda(), (1, 8, 8), row_ptr, col_idx, lam=0.0,
+                                    softmax_scale=1.0, o_sparse_dbg=o_s)
+    pa = float(torch.tensor(np.exp(-0.5)).bfloat16())              # 0.60653 lies 0.23 of a spacing from a rounding boundary
+    want = (pa * v[0, 0, a].double() + v[0, 0, b].double()) / (pa + 1.0)
+    got = o_s.double().cpu()[0, 0]
+    assert float((got - want).abs().max()) < 1e-5
+
+
 def test_fp32_infinite_value_in_the_last_row():
     """Keys past the end of the sequence do not exist: an infinite V element of the last token gives infinity in its channel
     and nothing anywhere else, whatever part of a 32-key unit the tail fills."""
