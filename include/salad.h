@@ -176,7 +176,9 @@ typedef struct salad_fwd_params {
  * 0 on invalid shapes.  The pieces' results can be left out: a smaller workspace that has room for the rest is taken and
  * the tiles are not cut (same result up to rounding order), so that one workspace may serve the largest grid of a program
  * and all smaller ones, although a small grid with pieces may ask for more than a large one without.
- * SALAD_ENOSPC: below the rest. */
+ * SALAD_ENOSPC: below the rest.
+ * Nothing in a workspace has to be set or kept between calls, but calls that may overlap (other streams or threads) must
+ * not share one, a call with lambda == 0 and prebuilt tile_lists, which uses it for the pieces alone, included. */
 size_t salad_fwd_workspace_bytes(const salad_fwd_params *p);
 
 /* Alg. 1 from SparseAttn to the residual sum:

@@ -276,7 +276,8 @@ def salad_fwd_workspace_bytes(B: int, H: int, N: int, d: int, dtype: int, full_p
 
 
 class Workspace:
-    """Caller-owned scratch for the layer call, sized by the library's query."""
+    """Caller-owned scratch for the layer call, sized by the library's query.  One for each stream: calls that may
+    overlap must not share it."""
 
     def __init__(self, B: int, H: int, N: int, d: int, dtype: int, device="cuda", full_proj: bool = False,
                  topk: int = 0, rope: bool = False):

@@ -212,7 +212,6 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int gate_
     // dynamic scale and coefficients: one workgroup, fixed summation order
     __shared__ float red[256];
     __shared__ float s_sh;
-    for (int i = threadIdx.x; i < a.n_clear; i += 256) a.clear[i] = 0;
     for (int b = 0; b < a.B; ++b) {
         float s;
         if (a.nparts > 0) {
@@ -242,17 +241,6 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int gate_
             for (int h = threadIdx.x; h < a.H; h += 256)
                 a.coef[b * a.H + h] = dropped ? 0.f : a.lambda * (a.head_scale ? a.head_scale[h] : 1.f) * s;
     }
-}
-
-__global__ __launch_bounds__(256) void clear_counts_kernel(int32_t *count, int n)
-{
-    for (int i = threadIdx.x; i < n; i += 256) count[i] = 0;
-}
-
-hipError_t launch_clear_counts(int32_t *count, int n, hipStream_t st)
-{
-    launch_kernel(clear_counts_kernel, dim3(1), dim3(256), 0, st, count, n);
-    return take_launch_status();
 }
 
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st)

@@ -73,7 +73,6 @@ struct FinalizeArgs {
     float tau;
     int32_t *drop;       // [B] in the workspace
     int32_t *dropped_out;// [B] caller's copy (may be null)
-    int32_t *clear; int n_clear;    // counters that the gate part sets to 0 (n_clear may be 0)
 };
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 
@@ -114,9 +113,10 @@ struct AttnArgs {
     const uint32_t *rope_tab;       // large-tile kernel, fused epilogue only: [N, 64] angle words (fp16 cos | fp16 sin << 16) of the
                                     // rotary linear branch (the state fragments then hold the rotated state), or null
     // large-tile kernel, CSR lists, sp_pieces > 1: tiles from sp_full (a multiple of 256) on are cut into up to sp_pieces workgroups.
-    // Per piece: pairs of fp32, O [d * 128], (reference, row sum) [512]; per tile a counter that is 0 at launch
+    // Per piece: pairs of fp32, O [d * 128], (reference, row sum) [512]; per tile a counter.  A counter holds this call's tag and,
+    // in the low 4 bits, how many pieces have arrived; with any other tag in it (whatever the workspace held) none has
     int sp_full, sp_pieces;
-    uint64_t *sp_o, *sp_ml; int32_t *sp_count;
+    uint64_t *sp_o, *sp_ml, *sp_count, sp_tag;
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };
 hipError_t launch_sparse_attn_bf16(const AttnArgs &a, hipStream_t st);
@@ -131,7 +131,6 @@ bool attn_takes_large_tile(int d, int nb, int N, int T, bool temporal, int varia
 // how the large-tile kernel cuts the tiles of its last, partial round (BH sample-heads of nb blocks); pieces < 2: not at all
 struct SplitPlan { int full, rest, pieces; };
 SplitPlan split_plan(int BH, int nb);
-hipError_t launch_clear_counts(int32_t *count, int n, hipStream_t st);
 hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int H, int nb, uint32_t *lists,
                              int32_t *counts, hipStream_t st);
 hipError_t launch_sparse_attn_f32(const AttnArgs &a, hipStream_t st);

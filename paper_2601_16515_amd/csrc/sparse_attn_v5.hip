@@ -672,9 +672,17 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         WAIT_VM(0);
         __syncthreads();
-        if (tid == 0) blist[0] = (uint32_t)__hip_atomic_fetch_add(a.sp_count + (L - a.sp_full), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) {
+            uint64_t *cnt = a.sp_count + (L - a.sp_full);
+            uint64_t was = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), now;
+            do now = ((was & ~15ull) == a.sp_tag ? was : a.sp_tag) + 1;      // fails only when another piece has counted itself in
+            while (!__hip_atomic_compare_exchange_strong(cnt, &was, now, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            const bool last = (int)(now & 15) == pieces;
+            if (last) __hip_atomic_store(cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            blist[0] = last;
+        }
         __syncthreads();
-        if ((int)blist[0] != pieces - 1) return;
+        if (!blist[0]) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         float mx = -INFINITY;
         for (int p = 0; p < pieces; ++p) mx = fmaxf(mx, get(a.sp_ml + (size_t)(first + p) * 512 + tid).x);

@@ -1,6 +1,8 @@
 """GPU parity: the HIP path, called through the C ABI, against the CPU oracle on the same seeded
 inputs.  Integer work (the mask) must match bit for bit; floating point within max-abs 2e-2 and
 relative L2 5e-3 (bf16 inputs, fp32 accumulation), per branch and combined."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -230,7 +232,7 @@ def test_visit_list_lengths(oracle, d, grid, kept):
 ])
 def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     """Tiles of the last, partial round cut along their visit lists: against the oracle, the same bits on every call (whichever
-    piece comes last combines them) and with the counters cleared by either kernel (with and without the linear branch)."""
+    piece comes last combines them) on a workspace that held anything, with and without the linear branch."""
     w = wl.small(f"cut-{d}-{grid[0] * grid[1] * grid[2]}", B, H, d, *grid, "bf16", 0.5, seed=600 + d + grid[2])
     inp = wl.make_inputs(w)
     dev = upload(w, inp)
@@ -274,6 +276,37 @@ def test_workspace_without_room_for_the_pieces(oracle):
     Hs, Z = sb.salad_linear_state_fwd(dev["k"], dev["v"], large)
     assert errors(Hs.cpu().numpy().astype(np.float64), ref["Hs"])[1] < 2e-6
     assert errors(Z.cpu().numpy().astype(np.float64), ref["Z"])[1] < 2e-6
+
+
+def test_sparse_branch_alone_is_one_launch():
+    """lambda = 0 with prebuilt lists on a grid whose tiles may be cut: the attention kernel and nothing else, counted in a
+    captured graph; replays on a workspace that held anything give the bits of the eager call."""
+    w = wl.small("one-launch", 1, 3, 128, 5, 13, 17, "bf16", 0.5, seed=641)   # N = 1105: 15 tiles in up to 8 pieces
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    grid, kinds, kept = (w.T, w.Hh, w.W), wl.head_kinds(w), [18, 5, 13]
+    row_ptr, col_idx = sb.salad_block_mask(*grid, w.block, kept)
+    lists = sb.salad_tile_lists(row_ptr, col_idx, w.H, w.nb)
+    eager = run_layer(w, inp, dev, kept, kinds, lam=0.0, dbg=False)["out_t"].clone()
+    ws = sb.Workspace(w.B, w.H, w.N, w.d, sb.SALAD_BF16)
+    ws.buf.fill_(0x5a)
+    out = torch.zeros_like(dev["q"])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        p, keep = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, grid, row_ptr, col_idx, kinds, lam=0.0, workspace=ws, tile_lists=lists)
+        sb.salad_fwd_call(p)
+    nodes = C.c_size_t(0)
+    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    assert C.CDLL(hip).hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(nodes)) == 0
+    assert nodes.value == 1
+    g.instantiate()
+    for rep in range(3):
+        out.fill_(float("nan"))
+        (dev["x_t"].float().sum()).item()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager), f"replay {rep} differs from the eager call"
 
 
 @pytest.mark.parametrize("second_half", [True, False])
