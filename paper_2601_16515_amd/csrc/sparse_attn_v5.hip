@@ -294,15 +294,21 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         qf[s].u = *reinterpret_cast<const uint4 *>(qb + (size_t)qrow * D + s * 16 + hh * 8);
 
     // ---- this tile's union list (built by the pre-pass): the whole row of list_cap slots is copied, so
-    // the copy does not wait for the count (slots past the count hold stale words that are never used)
+    // the copy does not wait for the count (slots past the count hold stale words that are never used); only a tile's later
+    // pieces wait, for their first entry
     const int g_blk0 = g_J * a.g_bpb;
+    auto copy_list = [&](int list0) INL {
+        const uint32_t *src = a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
+        for (int i = tid; i < list_cap; i += 512) blist[i] = src[SPLIT ? min(i + list0, list_cap - 1) : i];
+    };
+    if (!GATHER && !(SPLIT && piece)) copy_list(0);
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile];
-    int list0 = 0;                       // SPLIT: this piece's first entry
     if (SPLIT && pieces > 1) {
         pieces = min(pieces, max(1, n / SPLIT_MIN_ENTRIES));
         if (piece >= pieces) return;
-        list0 = n * piece / pieces;
+        const int list0 = n * piece / pieces;      // this piece's first entry
         n = n * (piece + 1) / pieces - list0;
+        if (piece) copy_list(list0);
     }
     uint32_t qm_lo = 0u, qm_hi = 0u;     // TOPK: this lane's query's key-block bits
     if (TOPK && qvalid) {
@@ -310,12 +316,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         qm_lo = (uint32_t)m;
         qm_hi = (uint32_t)(m >> 32);
     }
-    if (GATHER) {
+    if (GATHER)
         for (int i = tid; i < list_cap; i += 512) blist[i] = (uint32_t)min(g_blk0 + i, nb - 1) | 0xff000000u;
-    } else {
-        const uint32_t *src = a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
-        for (int i = tid; i < list_cap; i += 512) blist[i] = src[SPLIT ? min(i + list0, list_cap - 1) : i];
-    }
     __syncthreads();
     // Retire the Q loads here: inside the loop the only vector-memory operations in flight must be the
     // K/V prefetches, whose completion is tracked by hand.
