@@ -252,6 +252,70 @@ def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     assert errors(outs[0.0].double().cpu().numpy(), res["o_sparse"])[1] < 4e-3      # one bf16 rounding (2^-9) of each value
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_cut_tiles_with_the_options_of_the_call(oracle, d):
+    """Lists that are cut (18 and 13 to 16 entries: 3 and 2 pieces) together with what the call can be asked for: branch dropping,
+    the rotary linear branch with and without debug outputs, prebuilt lists, a CSR with empty rows and lists of every length, and
+    replays of a captured graph; always on one workspace that first holds anything and then the last call's leavings."""
+    w = wl.small(f"cut-options-{d}", 2, 2, d, 5, 13, 17, "bf16", 0.5, seed=650 + d)      # N = 1105: 20 tiles in up to 8 pieces
+    inp = wl.make_inputs(w)
+    wg = inp["w_gate"]
+    inp["x_t"] = inp["x_t"].copy()
+    inp["x_t"][1] = wl.round_to_bf16(inp["x_t"][1] + (2.0 * wg / float(np.dot(wg, wg))).astype(np.float32))   # pre-activations of sample 1 up by ~2
+    dev = upload(w, inp)
+    kinds, kept = wl.head_kinds(w), [18, 13]
+    ws = sb.Workspace(w.B, w.H, w.N, d, sb.SALAD_BF16, rope=d == 128)
+    ws.buf.fill_(0x5a)
+
+    def layer(**kw):
+        a = run_layer(w, inp, dev, kept, kinds, workspace=ws, dbg=False, **kw)
+        b = run_layer(w, inp, dev, kept, kinds, workspace=ws, dbg=False, prebuilt_lists=True, **kw)
+        c = run_layer(w, inp, dev, kept, kinds, workspace=ws, **kw)
+        assert torch.equal(a["out_t"], b["out_t"]) and torch.equal(a["out_t"], c["out_t"])
+        return c
+
+    sparse_only = layer(lam=0.0)
+    base = _oracle_layer(oracle, w, inp, kept, kinds, lam=20.0)
+    tau = float(0.5 * (base["s"][0] + base["s"][1]))
+    ref = _oracle_layer(oracle, w, inp, kept, kinds, lam=20.0, drop_threshold=tau)
+    drop = layer(lam=20.0, drop_threshold=tau)
+    assert drop["dropped"].tolist() == [1, 0]
+    compare_layer(drop, ref, check_linear=False, label="cut+drop")
+    assert torch.equal(drop["out_t"][0], sparse_only["out_t"][0]) and not torch.equal(drop["out_t"][1], sparse_only["out_t"][1])
+    if d == 128:
+        cs, sn = wl.rope_tables(w.T, w.Hh, w.W, d)
+        rope = layer(lam=20.0, rope=(torch.from_numpy(cs).cuda(), torch.from_numpy(sn).cuda()))
+        compare_layer(rope, _oracle_layer(oracle, w, inp, kept, kinds, lam=20.0, rope=(cs, sn)), label="cut+rope")
+
+    # rows of 0 to 18 blocks: whole tiles empty, of one entry, with a single row that has any, and cut ones between them
+    rng = np.random.default_rng(d)
+    sizes = [[0, 0, 0, 0], [18, 0, 1, 0], [1, 1, 1, 1], [0, 0, 12, 0], [6, 5]]
+    rows = [np.sort(rng.choice(w.nb, size=sz, replace=False)) for h in range(w.H) for t in (sizes if h else sizes[:4][::-1] + sizes[4:]) for sz in t]
+    csr = (np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32), np.concatenate(rows).astype(np.int32))
+    res = layer(csr=csr)
+    o_s, rws = oracle.sparse_attn(inp["q"], inp["k"], inp["v"], (w.T, w.Hh, w.W), 64, kinds, *csr)
+    got, ok = gather_rows(res["o_sparse"], rws)
+    assert np.isfinite(got[ok]).all() and errors(got[ok], o_s[ok])[1] <= REL_L2
+
+    row_ptr, col_idx = sb.salad_block_mask(w.T, w.Hh, w.W, w.block, kept)
+    out, dropped = torch.zeros_like(dev["q"]), torch.zeros(w.B, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        p, keep = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, (w.T, w.Hh, w.W), row_ptr, col_idx, kinds, lam=20.0,
+                                     head_scale=dev["head_scale"], x_t=dev["x_t"], w_gate=dev["w_gate"], eps=w.eps, workspace=ws,
+                                     drop_threshold=tau, dropped_out=dropped)
+        sb.salad_fwd_call(p)
+    for rep in range(4):
+        out.fill_(float("nan"))
+        if rep == 2:
+            ws.buf.fill_(0x5a)
+        assert torch.equal(layer(lam=0.0)["out_t"], sparse_only["out_t"])          # eager work on the same workspace between the replays
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, drop["out_t"]), f"replay {rep} differs from the eager call"
+
+
 def test_workspace_without_room_for_the_pieces(oracle):
     """The scratch of cut tiles is optional: a workspace sized for a larger grid whose tiles fill whole rounds (no pieces)
     serves a smaller one, whose tiles then run whole, and the state alone never needs it."""
