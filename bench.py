@@ -188,6 +188,7 @@ def main():
                      "kernel": "sparse_attn_v5_kernel alone (visit lists prebuilt with the mask)", "kernel_ms": attn_ms},
         "kernels_ms": {"gate": gate_ms, "linear_state": state_ms, "finalize": fin_ms, "sparse_attn_fused": attn_ms,
                        "empty_stage_bracket": empty_ms,
+                       "note": "gate and linear_state from a pass that brackets every stage and launches them apart; the timed call makes one launch of both",
                        "pass_with_every_stage_bracketed": {"ms_per_step": ms_all, "sparse_attn_fused": attn_ms_all}},
         "hbm_kernels": {"linear_state": hbm(kv_bytes, state_ms), "gate": hbm(x_bytes, gate_ms)},
     }

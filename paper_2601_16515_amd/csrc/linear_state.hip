@@ -233,8 +233,9 @@ __global__ __launch_bounds__(256, 2) void state_partial_kernel(const u16 *__rest
 
 // State chunks and gate partial sums in one launch: both are passes over inputs that nothing before them writes, and alone each
 // has a start and an end in which the memory system idles (the state leaves half a CU's wave slots empty, too).  The gate's
-// workgroups come last in the grid and fill in behind the state's.  Layer call at N = 1950, H = 12: 42.9 -> 38.6 us; N = 12480:
-// 320 -> 315; N = 32760: 723 -> 712; N = 75600, H = 40: 11491 -> 11441.  The same bits as the two launches.
+// workgroups come last in the grid and fill in behind the state's.  Layer call, two launches -> one: N = 1950, H = 12 42.0 -> 37.5 us;
+// N = 12480 292.1 -> 285.9; N = 32760 708.7 -> 703.6 (rotary 735.8 -> 729.3); N = 75600, H = 40 11438 -> 11396; no size where it
+// lost.  The same bits as the two launches.
 template <int D, int NCH, int TOK, bool ROPE>
 __global__ __launch_bounds__(256, 2) void state_gate_kernel(const u16 *__restrict__ k, const u16 *__restrict__ v, int N, int tiles_per_chunk, int P,
                                                             float *__restrict__ partial, int BH, GateArgs g,

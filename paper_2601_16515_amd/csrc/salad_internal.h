@@ -39,7 +39,7 @@ hipError_t launch_state_partial_bf16(const u16 *k, const u16 *v, int BH, int N, 
                                      float *partial, const int32_t *drop, int H, int target_wgs, hipStream_t st,
                                      const uint32_t *rope_tab = nullptr);
 hipError_t launch_rope_pack(const float *rope_cos, const float *rope_sin, size_t n, uint32_t *tab, hipStream_t st);
-// fp32: direct evaluation, one thread per state element (small shapes).
+// fp32 (small shapes): 16 x 16 tiles of the state on the fp32 matrix instruction, the tokens dealt to 16 waves.
 hipError_t launch_state_f32(const float *k, const float *v, int BH, int N, int D,
                             float *Hs, float *Z, const int32_t *drop, int H, hipStream_t st);
 
@@ -135,7 +135,7 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
                              int32_t *counts, hipStream_t st);
 hipError_t launch_sparse_attn_f32(const AttnArgs &a, hipStream_t st);
 hipError_t launch_sparse_attn_v2(const AttnArgs &a, hipStream_t st);   // d = 128 only
-hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st);   // d = 128 only
+hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st);   // large tile; d = 64 with CSR lists only
 
 // ---- Top-K dynamic mask (App. A.1.2), d = 128 bf16 ---------------------------------------------------------
 // means [BH][nbk][128] fp32: mean key of each run of key_block positions of the head's own order (bit h of kind_mask:

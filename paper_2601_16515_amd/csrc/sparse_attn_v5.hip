@@ -96,8 +96,8 @@ __device__ inline unsigned lds_addr_of(const void *p)
     return __builtin_amdgcn_readfirstlane((unsigned)(size_t)LDS_PTR(p));
 }
 
-// max of a value with its copy in the other 32-lane half, on the VALU (v_permlane32_swap): the LDS
-// unit, which a cross-lane shuffle would go through, is saturated by the other group's operand reads.
+// max of a value with its copy in the other 32-lane half, on the VALU (v_permlane32_swap): a cross-lane shuffle would
+// go through the LDS unit, which the operand reads of the CU's waves keep busy.
 __device__ inline float max_with_other_half(float x)
 {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
