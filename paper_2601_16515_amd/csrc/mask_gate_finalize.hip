@@ -212,6 +212,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int gate_
     // dynamic scale and coefficients: one workgroup, fixed summation order
     __shared__ float red[256];
     __shared__ float s_sh;
+    for (int i = threadIdx.x; i < a.sp_n; i += 256) a.sp_count[i] = a.sp_tag;
     for (int b = 0; b < a.B; ++b) {
         float s;
         if (a.nparts > 0) {

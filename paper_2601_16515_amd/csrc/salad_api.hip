@@ -110,7 +110,8 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
 // Tag of a call's piece counters: 60 bits, another for every call, from a random start, so that a word left in the workspace
 // by anything else carries it with a chance of 2^-60.  A captured call keeps its tag: the last piece to arrive sets the
 // counter to 0, which is no call's tag.  Setting the counters to 0 ahead of the attention kernel took a launch more where
-// lambda = 0 and the lists are prebuilt: N = 1950, 12 heads, lists of 6 entries 16.5 -> 15.0 us, 25 entries 37.1 -> 36.8.
+// lambda = 0 and the lists are prebuilt: N = 1950, 12 heads, lists of 6 entries 16.5 -> 15.0 us, 25 entries 37.1 -> 36.8.  With lambda
+// != 0 the reduce sets them to the tag: N = 1248, 8 heads, 40 tiles in 3 pieces 40.1 us, 41.5 where the pieces have to find out.
 uint64_t next_piece_tag()
 {
     static std::atomic<uint64_t> next{[] {
@@ -490,6 +491,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     const bool bf16 = p->dtype == SALAD_BF16;
     hipError_t e;
     const bool split = w.split.pieces > 1 && large_tile && p->workspace_bytes >= w.total;      // the last round's tiles are cut
+    const uint64_t sp_tag = split ? next_piece_tag() : 0;
 
     CallEvents ev{};
     int timing;
@@ -540,6 +542,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         f.gate_partial = (const float *)(ws + w.gate_partial); f.nparts = need_gate ? w.nparts : 0; f.N = p->N;
         f.s_dev = p->s_dev; f.lambda = p->lambda; f.head_scale = p->head_scale;
         f.s_out = p->s_out; f.s_ws = (float *)(ws + w.s); f.coef = (float *)(ws + w.coef); f.do_gate = 1;
+        f.sp_count = (uint64_t *)(ws + w.sp_count); f.sp_tag = sp_tag; f.sp_n = split ? w.split.rest : 0;
         f.tau = p->drop_threshold; f.drop = drop; f.dropped_out = dropping ? p->dropped_out : nullptr;
         if (dropping) {
             FinalizeArgs fg = f;
@@ -597,7 +600,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     if (split) {
         a.sp_full = w.split.full; a.sp_pieces = w.split.pieces;
         a.sp_o = (uint64_t *)(ws + w.sp_o); a.sp_ml = (uint64_t *)(ws + w.sp_ml); a.sp_count = (uint64_t *)(ws + w.sp_count);
-        a.sp_tag = next_piece_tag();
+        a.sp_tag = sp_tag;
     }
     a.rope_tab = rope_fused && use_linear ? (const uint32_t *)(ws + w.rope_tab) : nullptr;
     if (topk) {

@@ -73,6 +73,7 @@ struct FinalizeArgs {
     float tau;
     int32_t *drop;       // [B] in the workspace
     int32_t *dropped_out;// [B] caller's copy (may be null)
+    uint64_t *sp_count, sp_tag; int sp_n;   // counters of cut tiles that the gate part sets to the tag (sp_n may be 0)
 };
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 
@@ -114,7 +115,7 @@ struct AttnArgs {
                                     // rotary linear branch (the state fragments then hold the rotated state), or null
     // large-tile kernel, CSR lists, sp_pieces > 1: tiles from sp_full (a multiple of 256) on are cut into up to sp_pieces workgroups.
     // Per piece: pairs of fp32, O [d * 128], (reference, row sum) [512]; per tile a counter.  A counter holds this call's tag and,
-    // in the low 4 bits, how many pieces have arrived; with any other tag in it (whatever the workspace held) none has
+    // in the low 4 bits, how many pieces have arrived; with any other tag in it (whatever the workspace held) none has.  At the end it is 0
     int sp_full, sp_pieces;
     uint64_t *sp_o, *sp_ml, *sp_count, sp_tag;
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel

@@ -675,10 +675,15 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         WAIT_VM(0);
         __syncthreads();
         if (tid == 0) {
+            // one round trip where the counter carries the call's tag, which the reduce ahead of this launch writes; without that
+            // launch the first piece to arrive puts it there (a failed exchange means that another piece has got further)
             uint64_t *cnt = a.sp_count + (L - a.sp_full);
-            uint64_t was = __hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), now;
-            do now = ((was & ~15ull) == a.sp_tag ? was : a.sp_tag) + 1;      // fails only when another piece has counted itself in
-            while (!__hip_atomic_compare_exchange_strong(cnt, &was, now, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            uint64_t now = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+            while ((now & ~15ull) != a.sp_tag) {
+                const uint64_t first = a.sp_tag + 1;
+                if (__hip_atomic_compare_exchange_strong(cnt, &now, first, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) now = first;
+                else if ((now & ~15ull) == a.sp_tag) now = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+            }
             const bool last = (int)(now & 15) == pieces;
             if (last) __hip_atomic_store(cnt, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             blist[0] = last;
