@@ -520,8 +520,12 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));     // see exp_pack
         settle(hf, TOPK && hf == 0, sel, ps0 + ps1);     // TOPK: a lane's first selected block may come here
     };
-    // the same work unwoven, for blocks that not both of two successive list entries give this wave (first and last entry,
-    // entries that another query block of the tile keeps)
+    // the same work for blocks that not both of two successive list entries give this wave (first and last entry, entries that
+    // another query block of the tile keeps).  In the uncut d = 128 kernels start_cur has the softmax of the first half between the S
+    // products of the second: N = 12480, 24 heads, rows of random blocks at 30 % 954 -> 924 us (945 in the loop before the woven
+    // one), every third block 1159 -> 1066, every second, where no wave ever has two entries in turn, 1188 -> 1144 (1146); windows
+    // as before.  The same in finish_prev loses (962, 1182, 1217), and windows get slower by it where tiles are cut (720p 11395 ->
+    // 11452) and at d = 64 (480p, 90 % 882 -> 895).
     auto finish_prev = [&](uint32_t e, const u16 *Vt) INL {
         mask_tail(1, e);
         const bool sel = selected(e);
@@ -536,15 +540,38 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         }
     };
     auto start_cur = [&](uint32_t e, const u16 *Kt) INL {
-#pragma unroll
-        for (int t = 0; t < 2 * NS; ++t) {
+        auto step_S = [&](int t) INL {
             Frag5 f;
             f.v = *reinterpret_cast<const bf16x8 *>(Kt + (t / NS) * 32 * D + koff[t % NS]);
             mfma_S(t / NS, t % NS, f);
+        };
+        if constexpr (D == 128 && !SPLIT) {
+#pragma unroll
+            for (int t = 0; t < NS; ++t) step_S(t);
+            mask_tail(0, e);
+            const bool sel = selected(e);
+            const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
+            float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+            for (int t = 0; t < NS; ++t) {
+                step_S(NS + t);
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if (q * (NS - 1) / 8 == t - 1) {
+                        const uint32_t w = pair_exp(fmaf(s[0][2 * q], cs, -mref), fmaf(s[0][2 * q + 1], cs, -mref));
+                        pf[q >> 2].w[q & 3] = w;
+                        if (q & 1) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
+                    }
+            }
+            asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));     // see exp_pack
+            settle(0, true, sel, ps0 + ps1);
+        } else {
+#pragma unroll
+            for (int t = 0; t < 2 * NS; ++t) step_S(t);
+            mask_tail(0, e);
+            const bool sel = selected(e);
+            settle(0, true, sel, exp_pack(0, sel));
         }
-        mask_tail(0, e);
-        const bool sel = selected(e);
-        settle(0, true, sel, exp_pack(0, sel));
     };
 
     const bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[bh / a.H]);   // pruned sample (Sec. 4.3): out = O_s
