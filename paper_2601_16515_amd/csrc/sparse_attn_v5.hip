@@ -11,9 +11,7 @@
 //     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
-//     fma / exp / pack / sum of a third half sit between its MFMAs, a few vector instructions after each: alone, this mix
-//     runs at 41 cycles per MFMA with two waves per SIMD (33 without the sums: v_dot2c_f32_bf16 takes 16 cycles of the matrix
-//     pipe).  A block's K and V loads are issued between its two halves.  One barrier per KV block (it also protects
+//     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's K and V loads are issued between its two halves.  One barrier per KV block (it also protects
 //     the rings).  Before, the waves of a SIMD took turns, one multiplying while the other did its softmax, which left the
 //     softmax partly exposed.  B = 1, N = 32760, layer call: 24 heads of 64 at 90 % 917 -> 863 us; 12 heads of 128 dense
 //     5921 -> 5842 us, at 90 % 702 -> 699 us: at d = 128 the cycles fall by 5 % and the clock, which the power limit
@@ -22,8 +20,8 @@
 //     that P never moves between lanes.  LDS operand reads are spread evenly between the MFMAs through a
 //     small ring of fragment registers.
 //   * Softmax with few vector instructions: logits live in the log2 domain (one fma and one v_exp_f32 per
-//     element); row sums are taken from the bf16-rounded probabilities with v_dot2c_f32_bf16; the block
-//     maximum is not computed unless a block's sums show that some logit exceeds the running reference
+//     element); row sums are taken from the bf16-rounded probabilities by a 16x16x32 MFMA against a matrix of zeros and
+//     ones (row_sum); the block maximum is not computed unless a block's sums show that some logit exceeds the running reference
 //     by more than 13 binades (the reference then moves to the true maximum and the block is redone).
 //   * Epilogue: the bf16 fragments of the linear state are staged once per workgroup in LDS.
 #include "salad_internal.h"
@@ -32,6 +30,7 @@ namespace salad {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x2 __attribute__((ext_vector_type(2)));
@@ -102,15 +101,6 @@ __device__ inline float max_with_other_half(float x)
 {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-// acc + lo(w) + hi(w) for a packed pair of bf16 (dot product with (1, 1), fp32 accumulate).  Chains of these
-// on one accumulator need no wait; any other instruction reading the result needs four idle slots first
-// (see the s_nop where the sums are consumed).
-__device__ inline float add_bf16_pair(float acc, uint32_t w)
-{
-    asm("v_dot2c_f32_bf16 %0, %1, %2" : "+v"(acc) : "v"(w), "v"(0x3f803f80u));
-    return acc;
 }
 
 union Frag5 {
@@ -435,21 +425,28 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
                 if (kbase + 16 * (r >> 3) + (r & 7) >= N) s[hf][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
         }
     };
+    // Sums of 16 keys' bf16 probabilities, every lane getting its query's.  As the B operand of a 16x16x32 product a fragment's lanes
+    // 0..15 and 32..47 hold keys of queries 0..15, the others keys of queries 16..31, and a lane's results are the rows 4 (lane / 16)
+    // .. + 3 of column lane % 16: the A operand picks by row which of the two goes there.  Four of these a block take 64 cycles of the
+    // matrix pipe where 16 v_dot2c_f32_bf16 took 256 (plain adds of the unpacked pairs take two more vector instructions per pair,
+    // and the loop is held by the energy of its instructions).  Layer call, B = 1, N = 32760: 12 heads of 128 dense 5830 -> 5712 us, at
+    // 90 % 687 -> 672; 24 heads of 64 at 90 % 858 -> 846; the error against 64 bits is the same to six digits.
+    Frag5 pick;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pick.w[i] = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
+    asm volatile("" : "+v"(pick.w[0]), "+v"(pick.w[1]), "+v"(pick.w[2]), "+v"(pick.w[3]));
+    auto row_sum = [&](int i, f32x4 acc) INL -> f32x4 { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, pf[i].v, acc, 0, 0, 0); };
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
     // P = 2^(S c2 - m) rounded to bf16, pair q of half hf; returns the packed pair
     auto pair_exp = [&](float t0, float t1) INL -> uint32_t { return pack2e(__builtin_amdgcn_exp2f(t0), __builtin_amdgcn_exp2f(t1)); };
     auto exp_pack = [&](int hf, bool sel) INL -> float {
         const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
-        float ps0 = 0.f, ps1 = 0.f;
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const uint32_t w = pair_exp(fmaf(s[hf][2 * q], cs, -mref), fmaf(s[hf][2 * q + 1], cs, -mref));
             pf[hf * 2 + (q >> 2)].w[q & 3] = w;
-            if (q & 1) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
         }
-        // the dot instructions come from inline assembly, so the compiler does not know that another
-        // vector instruction must not read their result in the next four issue slots
-        asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));
-        return ps0 + ps1;
+        return row_sum(hf * 2 + 1, row_sum(hf * 2, zero4))[0];
     };
     // The reference only has to keep 2^S in range, so the maximum is not computed unless the sums say that some logit rose
     // more than 13 binades above the reference (or no reference exists yet): then the reference moves to the true maximum
@@ -491,7 +488,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         const bool sel = selected(e);
         const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
         constexpr int FS = NPS - 3;
-        float t[16], ps0 = 0.f, ps1 = 0.f;
+        float t[16];
+        f32x4 ps = zero4;
 #pragma unroll
         for (int i = 0; i < NPS; ++i) {
             const int g = pt * NPS + i;
@@ -510,15 +508,11 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
                     t[2 * q + 1] = __builtin_amdgcn_exp2f(t[2 * q + 1]);
                 }
                 if (i == at + 2) pf[hf * 2 + (q >> 2)].w[q & 3] = pack2e(t[2 * q], t[2 * q + 1]);
-                if (i == at + 3) {
-                    const uint32_t w = pf[hf * 2 + (q >> 2)].w[q & 3];
-                    if (q & 1) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
-                }
+                if (i == at + 3 && (q & 3) == 3) ps = row_sum(hf * 2 + (q >> 2), ps);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));     // see exp_pack
-        settle(hf, TOPK && hf == 0, sel, ps0 + ps1);     // TOPK: a lane's first selected block may come here
+        settle(hf, TOPK && hf == 0, sel, ps[0]);     // TOPK: a lane's first selected block may come here
     };
     // the same work for blocks that not both of two successive list entries give this wave (first and last entry, entries that
     // another query block of the tile keeps).  In the uncut d = 128 kernels start_cur has the softmax of the first half between the S
@@ -551,7 +545,6 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             mask_tail(0, e);
             const bool sel = selected(e);
             const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
-            float ps0 = 0.f, ps1 = 0.f;
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
                 step_S(NS + t);
@@ -560,11 +553,9 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
                     if (q * (NS - 1) / 8 == t - 1) {
                         const uint32_t w = pair_exp(fmaf(s[0][2 * q], cs, -mref), fmaf(s[0][2 * q + 1], cs, -mref));
                         pf[q >> 2].w[q & 3] = w;
-                        if (q & 1) ps1 = add_bf16_pair(ps1, w); else ps0 = add_bf16_pair(ps0, w);
                     }
             }
-            asm volatile("s_nop 4" : "+v"(ps0), "+v"(ps1));     // see exp_pack
-            settle(0, true, sel, ps0 + ps1);
+            settle(0, true, sel, row_sum(1, row_sum(0, zero4))[0]);
         } else {
 #pragma unroll
             for (int t = 0; t < 2 * NS; ++t) step_S(t);
@@ -743,7 +734,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     }
 
     // ---- epilogue ---------------------------------------------------------------------------------
-    float l_tot = l_run + __shfl_xor(l_run, 32);
+    const float l_tot = l_run;
     const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
     f32x16 num[NDT];
     float lin_scale = 0.f, inv_den = 0.f;
