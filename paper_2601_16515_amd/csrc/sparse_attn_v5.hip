@@ -11,18 +11,23 @@
 //     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
-//     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's K and V loads are issued between its two halves.  One barrier per KV block (it also protects
-//     the rings).  Before, the waves of a SIMD took turns, one multiplying while the other did its softmax, which left the
+//     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's
+//     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).  Before, the waves of a SIMD took turns, one multiplying while the other did its softmax, which left the
 //     softmax partly exposed.  B = 1, N = 32760, layer call: 24 heads of 64 at 90 % 917 -> 863 us; 12 heads of 128 dense
 //     5921 -> 5842 us, at 90 % 702 -> 699 us: at d = 128 the cycles fall by 5 % and the clock, which the power limit
 //     sets (1.95 -> 1.89 GHz on the dense call), takes most of it back.
+//   * What bounds the loop is the energy of its instructions: the chip is at its power limit, and fewer cycles for the same
+//     instructions only lower the clock (dense call: without the barrier 9.94 instead of 10.23 M cycles, 1.625 instead of 1.674
+//     GHz, the same time).  So whatever is the same for a whole wave is on the scalar unit, and the tiles in LDS are laid out so
+//     that operand addresses are one register and an immediate: 22 vector instructions fewer of 128 per block and wave, with the
+//     conditions below 26.  Dense 5752 -> 5575 us, 480p 90 % 668 -> 651, 8 x 30 x 52 at 75 % 267 -> 261, 24 heads of 64 842 -> 833.
 //   * V^T operands come from ds_read_b64_tr_b16, K rows are read through the kappa permutation so
 //     that P never moves between lanes.  LDS operand reads are spread evenly between the MFMAs through a
 //     small ring of fragment registers.
 //   * Softmax with few vector instructions: logits live in the log2 domain (one fma and one v_exp_f32 per
 //     element); row sums are taken from the bf16-rounded probabilities by a 16x16x32 MFMA against a matrix of zeros and
-//     ones (row_sum); the block maximum is not computed unless a block's sums show that some logit exceeds the running reference
-//     by more than 13 binades (the reference then moves to the true maximum and the block is redone).
+//     ones (row_sum); the block maximum is not computed unless a block's sums show that some logit exceeds the running
+//     reference by more than 13 binades (the reference then moves to the true maximum and the block is redone).
 //   * Epilogue: the bf16 fragments of the linear state are staged once per workgroup in LDS.
 #include "salad_internal.h"
 
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
     constexpr int NS = D / 16, NDT = D / 32;     // 16-channel steps of S, 32-channel tiles of O^T
     constexpr int CH = D / 8;                    // 16-byte chunks per row
-    constexpr int RPP = 512 / CH, NPASS = 64 / RPP;   // rows per pass of the 512 threads over a tile, passes per tile
+    constexpr int CG = CH / 4, NPASS = CG / 2;   // groups of 4 chunks per row; loads of a thread per tile
     constexpr int TILE = 64 * D;                 // elements
     constexpr int NK = 5, NV = 4;                // K and V tiles in LDS
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -220,9 +225,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     uint32_t *blist = reinterpret_cast<uint32_t *>(Vb + NV * TILE);      // [list_cap] union list: blk | mask << 24
 
     constexpr bool TOPK = MODE == 1, GATHER = MODE == 2;
-    // chunk swizzles of the K tile, the V tile and the output staging as functions of the row
-    auto kswz = [](int row) INL -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
-    auto vswz = [](int row) INL -> int { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); };
+    // chunk swizzle of the output staging
+    auto oswz = [](int row) INL -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
     const int g = blockIdx.x;
     int L, piece = 0, pieces = 1;
     if (SPLIT) {      // an XCD's share: its run of whole tiles, then its run of pieces
@@ -318,53 +322,62 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
 
     const float c2 = a.scale * 1.44269504088896340736f;   // logits are handled in the log2 domain
 
-    // ---- global -> LDS: thread owns LDS slots (row RPP i + tid/CH, chunk tid%CH), i < NPASS, of a tile.
+    // ---- global -> LDS.  A tile is laid out in pieces of 1 KB, 16 rows by 4 chunks (64 bytes) each, the CG pieces of 16 rows one
+    // after the other; one load of a wave fills a piece.  Within a piece chunk c of row r is at r * 64 + c * 16 for V and
+    // r * 64 + ((c ^ (r / 4 % 4)) * 16) for K (the swap is made in the global address), so that both the 16 rows of a K operand and
+    // the 4 rows by 64 bytes that 32 lanes of a transposing V read take cover all banks once.  Of an operand's address only two bits
+    // of K's chunk depend on both lane and step; all else of the step is an immediate.
     // LDS destinations are wave-uniform scalars; global sources are a uniform base plus a 32-bit offset.
-    const int lr = tid / CH, pc = tid % CH;
-    const unsigned kchunk_b = (unsigned)((pc ^ kswz(lr)) * 16);
-    const unsigned vchunk_b = (unsigned)((pc ^ vswz(lr)) * 16);
     const unsigned wave_u = (unsigned)__builtin_amdgcn_readfirstlane(wave);
-    const unsigned k_lds0 = lds_addr_of(Kb) + wave_u * 1024u;
-    const unsigned v_lds0 = lds_addr_of(Vb) + wave_u * 1024u;
-    // byte offset of this thread's row i of a block: without a branch (a spatial head is location 0, stride 1)
+    const unsigned k_lds0 = lds_addr_of(Kb) + wave_u * (NPASS * 1024u);
+    const unsigned v_lds0 = lds_addr_of(Vb) + wave_u * (NPASS * 1024u);
+    const unsigned Tk = kind ? (unsigned)T : 0x7fffffffu;
+    const int lr = (wave >> 1) * 16 + (lane >> 2);                       // this thread's row of a tile
+    const unsigned vchunk_b = (unsigned)((wave & 1) * NPASS * 64 + (lane & 3) * 16);
+    const unsigned kv_b = (unsigned)((((lane & 3) ^ (lane >> 4)) - (lane & 3)) * 16);     // K's chunk less V's
+    // byte offset of this thread's row of a block and its V chunk.  The division is by a scalar, of the block's first row; a lane's own
+    // part is a constant, but for one wrap of the time axis.  Without a branch on the order (a spatial head is location 0, stride 1).
     const unsigned magic_u = kind ? magic : 0u, stride_b = (unsigned)((kind ? HW : 1) * D * 2), back_b = (unsigned)(D * 2) - (unsigned)T * stride_b;
-    auto row_bytes = [&](int blk, int i) INL -> unsigned {
-        int p = blk * 64 + i * RPP + lr;
-        p = p < N ? p : N - 1;
-        return (unsigned)p * stride_b + __umulhi((unsigned)p, magic_u) * back_b;     // (p - loc T) stride + loc, in rows of 2 D bytes
+    // (p - loc T) stride + loc, in rows of 2 D bytes
+    auto row_bytes = [&](unsigned p) INL -> unsigned { return p * stride_b + __umulhi(p, magic_u) * back_b; };
+    const unsigned ql = __umulhi((unsigned)lr, magic_u), rl = (unsigned)lr - ql * (unsigned)T * (kind ? 1u : 0u);
+    const unsigned lane0 = (unsigned)lr * stride_b + ql * back_b + vchunk_b, lane1 = lane0 + (unsigned)(D * 2) - (unsigned)T * stride_b;
+    auto rows_of = [&](int blk) INL -> unsigned {
+        const unsigned p0 = (unsigned)__builtin_amdgcn_readfirstlane(blk * 64);
+        if ((int)p0 + 64 > N) return row_bytes((unsigned)min((int)p0 + lr, N - 1)) + vchunk_b;
+        const unsigned q0 = __umulhi(p0, magic_u);
+        const unsigned base = p0 * stride_b + q0 * back_b, left = Tk - (kind ? p0 - q0 * (unsigned)T : 0u);
+        return base + (rl >= left ? lane1 : lane0);
     };
-    struct Rows { unsigned b[NPASS]; };
-    auto rows_of = [&](int blk) INL -> Rows {
-        Rows r;
+    auto fetch_k = [&](unsigned r, int slot) INL {
 #pragma unroll
-        for (int i = 0; i < NPASS; ++i) r.b[i] = row_bytes(blk, i);
-        return r;
+        for (int i = 0; i < NPASS; ++i) lds_dma16_base(kb + i * 32, r + kv_b, k_lds0 + (unsigned)slot * (unsigned)(TILE * 2) + i * 1024u);
     };
-    auto fetch_k = [&](const Rows &r, int slot) INL {
+    auto fetch_v = [&](unsigned r, int slot) INL {
 #pragma unroll
-        for (int i = 0; i < NPASS; ++i) lds_dma16_base(kb, r.b[i] + kchunk_b, k_lds0 + (unsigned)slot * (unsigned)(TILE * 2) + i * 8192u);
-    };
-    auto fetch_v = [&](const Rows &r, int slot) INL {
-#pragma unroll
-        for (int i = 0; i < NPASS; ++i) lds_dma16_base(vb, r.b[i] + vchunk_b, v_lds0 + (unsigned)slot * (unsigned)(TILE * 2) + i * 8192u);
+        for (int i = 0; i < NPASS; ++i) lds_dma16_base(vb + i * 32, r, v_lds0 + (unsigned)slot * (unsigned)(TILE * 2) + i * 1024u);
     };
     // list entries travel in a vector register (lane l holds entry 64 c + l of the current 64-entry
     // chunk c) and are picked with v_readlane: no LDS round trip per iteration
     uint32_t ev = blist[lane];
+    const uint32_t tail_blk = (N & 63) ? (uint32_t)(N >> 6) : 0xffffffffu;             // the block that the sequence ends in
     auto entry = [&](int idx) INL -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)ev, idx & 63); };
 
     // ---- LDS operand addresses (element offsets inside a tile)
     const int kappa = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-    int koff[NS];
+    unsigned koff[2];
 #pragma unroll
-    for (int st = 0; st < NS; ++st) koff[st] = kappa * D + (((2 * st + hh) ^ kswz(kappa)) << 3);
-    const int vr = 8 * hh + ((l32 >> 2) & 3);
-    int voff[NDT];
-#pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) {
-        int chunk = 4 * dt + 2 * (l32 >> 4) + ((l32 & 3) >> 1);
-        voff[dt] = vr * D + ((chunk ^ vswz(vr)) << 3) + 4 * (l32 & 1);
-    }
+    for (int p = 0; p < 2; ++p)
+        koff[p] = (unsigned)((kappa >> 4) * (CG * 1024) + (kappa & 15) * 64 + (((2 * p + hh) ^ ((kappa >> 2) & 3)) << 4));
+    const unsigned voff = (unsigned)((8 * hh + ((l32 >> 2) & 3)) * 64 + (2 * (l32 >> 4) + ((l32 & 3) >> 1)) * 16 + 8 * (l32 & 1));
+    auto k_frag = [&](const u16 *Kt, int half, int st) INL -> bf16x8 {
+        return *(const bf16x8 *)(reinterpret_cast<const unsigned char *>(Kt) + koff[st & 1] + half * (2 * CG * 1024) + (st >> 1) * 1024);
+    };
+    auto v_frag = [&](Frag5 &f, const u16 *Vt, int kg, int dt) INL {
+        const unsigned char *p = reinterpret_cast<const unsigned char *>(Vt) + voff + kg * (CG * 1024) + dt * 1024;
+        f.h[0] = TR_READ(p);
+        f.h[1] = TR_READ(p + 256);
+    };
 
     f32x16 o[NDT];
 #pragma unroll
@@ -388,12 +401,9 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         Frag5 &f = ring[i % RING];
         const int pt = i / NPS, t = i % NPS;
         if (t < NS) {
-            const u16 *base = pt < 2 ? Kt : Kn;
-            f.v = *reinterpret_cast<const bf16x8 *>(base + (pt & 1) * 32 * D + koff[t]);
+            f.v = k_frag(pt < 2 ? Kt : Kn, pt & 1, t);
         } else {
-            const u16 *vp = Vt + ((pt & 1) * 2 + (t - NS) / NDT) * 16 * D + voff[(t - NS) % NDT];
-            f.h[0] = TR_READ(vp);
-            f.h[1] = TR_READ(vp + 4 * D);
+            v_frag(f, Vt, (pt & 1) * 2 + (t - NS) / NDT, (t - NS) % NDT);
         }
     };
     auto mfma_S = [&](int pt, int t, const Frag5 &f) INL {
@@ -418,8 +428,10 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     };
     auto mask_tail = [&](int hf, uint32_t e) INL {           // keys past the sequence end (last block only)
         const int blk = (int)(e & BLKMASK);
-        if (blk * 64 + 64 > N) {
-            const int kbase = blk * 64 + hf * 32 + hh * 8;
+        if ((uint32_t)blk == tail_blk) {
+            int first = blk * 64;
+            asm volatile("" : "+s"(first));      // else the compares, the same in every such block, leave the loop and fill the scalar registers
+            const int kbase = first + hf * 32 + hh * 8;
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 if (kbase + 16 * (r >> 3) + (r & 7) >= N) s[hf][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
@@ -454,8 +466,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     // counts, so that a row's first reference is the maximum of 64 keys, whose weight is then exactly 1 (keys past the sequence
     // end need no mask here: their K rows are copies of the last one, which is in the block).
     // With the maximum of the first 32 keys alone the error against 64 bits is up to 3 % larger (N = 1170, 95 %: 2.08e-3 -> 2.14e-3).
-    auto settle = [&](int hf, bool whole, bool sel, float psum) INL {
-        bool redo = sel && !have_ref;
+    auto settle = [&](int hf, bool whole, bool started, bool sel, float psum) INL {
+        bool redo = !started && sel && !have_ref;
         redo = redo || (__any(!(psum <= 8192.f)) && sel);
         if (redo) {
             float mx = s[hf][0];
@@ -465,8 +477,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[1][r]);
             mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run);   // maximum minus reference
-            const float shift = have_ref ? fmaxf(mx, 0.f) : mx;                // new reference minus old reference
-            if (have_ref) {
+            const float shift = started || have_ref ? fmaxf(mx, 0.f) : mx;     // new reference minus old reference
+            if (started || have_ref) {
                 const float alpha = __builtin_amdgcn_exp2f(-shift);
                 l_run *= alpha;
 #pragma unroll
@@ -512,7 +524,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        settle(hf, TOPK && hf == 0, sel, ps[0]);     // TOPK: a lane's first selected block may come here
+        settle(hf, TOPK && hf == 0, !TOPK, sel, ps[0]);     // TOPK: a lane's first selected block may come here
     };
     // the same work for blocks that not both of two successive list entries give this wave (first and last entry, entries that
     // another query block of the tile keeps).  In the uncut d = 128 kernels start_cur has the softmax of the first half between the S
@@ -525,18 +537,16 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         const bool sel = selected(e);
 #pragma unroll
         for (int t = 0; t < 4 * NDT; ++t) {
-            if (t == 2 * NDT) settle(1, false, sel, exp_pack(1, sel));     // after the first half's products: the reference may move here
+            if (t == 2 * NDT) settle(1, false, !TOPK, sel, exp_pack(1, sel));     // after the first half's products: the reference may move here
             Frag5 f;
-            const u16 *vp = Vt + (t / NDT) * 16 * D + voff[t % NDT];
-            f.h[0] = TR_READ(vp);
-            f.h[1] = TR_READ(vp + 4 * D);
+            v_frag(f, Vt, t / NDT, t % NDT);
             mfma_PV(t / (2 * NDT), t % (2 * NDT), f);
         }
     };
     auto start_cur = [&](uint32_t e, const u16 *Kt) INL {
         auto step_S = [&](int t) INL {
             Frag5 f;
-            f.v = *reinterpret_cast<const bf16x8 *>(Kt + (t / NS) * 32 * D + koff[t % NS]);
+            f.v = k_frag(Kt, t / NS, t % NS);
             mfma_S(t / NS, t % NS, f);
         };
         if constexpr (D == 128 && !SPLIT) {
@@ -555,13 +565,13 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
                         pf[q >> 2].w[q & 3] = w;
                     }
             }
-            settle(0, true, sel, row_sum(1, row_sum(0, zero4))[0]);
+            settle(0, true, false, sel, row_sum(1, row_sum(0, zero4))[0]);
         } else {
 #pragma unroll
             for (int t = 0; t < 2 * NS; ++t) step_S(t);
             mask_tail(0, e);
             const bool sel = selected(e);
-            settle(0, true, sel, exp_pack(0, sel));
+            settle(0, true, false, sel, exp_pack(0, sel));
         }
     };
 
@@ -593,9 +603,9 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     if (n > 0) {
         constexpr int AK = NK - 1, AV = NV - 2;     // how far ahead K and V are fetched
         static_assert(AK == 4 && AV == 2, "the waits below count the loads of two iterations");
-        Rows rk[AK - AV + 1];                        // row offsets of blocks j+2 .. j+4, for the V fetches to come
+        unsigned rk[AK - AV + 1];                        // row offsets of blocks j+2 .. j+4, for the V fetches to come
         {
-            Rows r0 = rows_of((int)(entry(0) & BLKMASK)), r1 = rows_of((int)(entry(min(1, n - 1)) & BLKMASK));
+            unsigned r0 = rows_of((int)(entry(0) & BLKMASK)), r1 = rows_of((int)(entry(min(1, n - 1)) & BLKMASK));
             rk[0] = rows_of((int)(entry(min(2, n - 1)) & BLKMASK));
             rk[1] = rows_of((int)(entry(min(3, n - 1)) & BLKMASK));
             fetch_k(r0, 0);
@@ -616,7 +626,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             const int jf = j + AK;
             uint32_t e_f = 0u;
             if (jf < n) {
-                if ((jf & 63) == 0) ev = blist[jf + lane];
+                if ((jf & 63) == 0)      // waited for here, so that the other turns of the loop need not wait for their operand reads
+                    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(ev) : "v"((unsigned)(size_t)LDS_PTR(blist + jf + lane)) : "memory");
                 e_f = entry(jf);
             }
             int kslot_f = kslot + AK; if (kslot_f >= NK) kslot_f -= NK;
@@ -624,7 +635,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             int vslot_f = vslot + AV; if (vslot_f >= NV) vslot_f -= NV;
             int vslot_prev = vslot - 1; if (vslot_prev < 0) vslot_prev += NV;
             const uint32_t e_cur = eq[0];
-            const bool kS = (e_cur & mybit) != 0, kP = (j >= 1) && (e_prev & mybit);
+            const bool kS = (e_cur & mybit) != 0, kP = (e_prev & mybit) != 0;
             const u16 *Kt = Kb + kslot * TILE, *Kn = Kb + kslot_n * TILE;
             const u16 *Vt = Vb + vslot_prev * TILE;
             auto dma = [&]() INL {
@@ -808,7 +819,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
                 uint2 pk;
                 pk.x = pack2e(ov[0], ov[1]);
                 pk.y = pack2e(ov[2], ov[3]);
-                *reinterpret_cast<uint2 *>(stg + l32 * ROWB + (((dt * 4 + g4) ^ kswz(l32)) << 4) + hh * 8) = pk;
+                *reinterpret_cast<uint2 *>(stg + l32 * ROWB + (((dt * 4 + g4) ^ oswz(l32)) << 4) + hh * 8) = pk;
             }
         asm volatile("" ::: "memory");       // the wave's LDS operations execute in order
         // destination of row r: the stored row (or the pair slot) of the lane that owns query r
@@ -819,7 +830,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
 #pragma unroll
         for (int i = 0; i < 32 / RPI; ++i) {
             const int r = RPI * i + r4;
-            const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * ROWB + ((c16 ^ kswz(r)) << 4));
+            const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * ROWB + ((c16 ^ oswz(r)) << 4));
             const int dest = __shfl(dest_mine, r);
             if (dest >= 0) *reinterpret_cast<uint4 *>(dbase + (size_t)dest * D + c16 * 8) = v;
         }
