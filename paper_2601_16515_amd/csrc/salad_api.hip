@@ -97,8 +97,8 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     }
     w.rope_tab = off; off = align256(off + (rope ? sizeof(uint32_t) * (size_t)N * (d / 2) : 0));
     w.base = off;       // what a call needs; the rest only makes it faster, and a workspace without room for it is taken
-    // pieces of the large-tile kernel's last round (CSR masks): at most 256 of them
-    if (dtype == SALAD_BF16 && !topk && large_lists) w.split = split_plan((int)BH, (N + 63) / 64);
+    // pieces of the large-tile kernel's last round (CSR masks): at most 256 of them (d = 64: 512)
+    if (dtype == SALAD_BF16 && !topk && large_lists) w.split = split_plan((int)BH, (N + 63) / 64, d);
     const size_t np = w.split.pieces > 1 ? (size_t)w.split.rest * w.split.pieces : 0;
     w.sp_o = off; off = align256(off + sizeof(float) * np * 256 * (size_t)d);
     w.sp_ml = off; off = align256(off + sizeof(uint64_t) * np * 512);

@@ -2,7 +2,8 @@
 // d = 128 (and d = 64 on half-size tiles).  Large tile, deep LDS prefetch, softmax woven into the matrix stream.
 //
 //   * One workgroup = 8 waves = 256 query positions = 4 CSR rows of one (batch, head); one workgroup
-//     per CU (LDS: 5 K + 4 V tiles of 16 KB plus the block list; registers at d = 64, where the tiles are 8 KB).
+//     per CU (LDS: 5 K + 4 V tiles of 16 KB plus the block list).  d = 64, where the tiles are 8 KB: two workgroups of 4 waves
+//     per CU, a wave owning 64 queries, if there are tiles for both (QS below).
 //   * The ascending union of the 4 rows' kept-block lists is built once per workgroup in LDS (bitmap +
 //     ballot compaction), each entry carrying a 4-bit "kept by query block i" mask.  The main loop
 //     reads one entry per iteration from LDS; no global or scalar load sits on its critical path.
@@ -47,7 +48,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 #define TR_READ(p) __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)LDS_PTR(p))
 #define INL __attribute__((always_inline))
 // s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8)
-#define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | (n))
+#define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | ((n) >> 4) << 14)
 
 constexpr int SPLIT_MAX_PIECES = 8;
 constexpr int SPLIT_MIN_ENTRIES = 6;     // least entries of a piece: what a cut costs (two passes over 128 KB, a prologue) is about as long
@@ -210,13 +211,19 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 // workgroups each.  Every piece runs its own softmax over its entries, writes O, the reference and the row sum in fp32, and counts
 // itself in; the piece that comes last reads the others back, combines all in piece order (so the result does not depend on which
 // it was) and goes on to the epilogue.  Nobody waits for anybody.
-template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false>
-__global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
+// QS: sets of 32 queries that a wave owns.  With 2 every operand fragment read from LDS feeds two products, which halves the energy
+// of the reads, and a workgroup has half the waves.  d = 64 has the registers for it and LDS for two such workgroups per CU, whose
+// barriers are independent: B = 1, N = 32760, 24 heads at 90 % 832 -> 725 us, dense N = 12480 1119 -> 1005; while there is one tile per CU
+// or less the 4 waves alone are slower (N = 1950, 24 heads 28.4 -> 30.9).  At d = 128 it needs 400 registers, so one wave per SIMD, and
+// the loads, which hold a wave for 60 cycles each, and the scalar code have nothing to run under: dense 5421 -> 5564 us.
+template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, int QS = 1>
+__global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
 {
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
     constexpr int NS = D / 16, NDT = D / 32;     // 16-channel steps of S, 32-channel tiles of O^T
     constexpr int CH = D / 8;                    // 16-byte chunks per row
-    constexpr int CG = CH / 4, NPASS = CG / 2;   // groups of 4 chunks per row; loads of a thread per tile
+    constexpr int NW = 8 / QS, NT = 64 * NW;     // waves, threads
+    constexpr int CG = CH / 4, NPASS = 4 * CG / NW;   // groups of 4 chunks per row; loads of a thread per tile
     constexpr int TILE = 64 * D;                 // elements
     constexpr int NK = 5, NV = 4;                // K and V tiles in LDS
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -264,28 +271,30 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     const u16 *kb = reinterpret_cast<const u16 *>(a.k) + (size_t)bh * N * D;
     const u16 *vb = reinterpret_cast<const u16 *>(a.v) + (size_t)bh * N * D;
 
-    const int qsub = wave >> 1;
-    const int qblk = tile * 4 + qsub;
-    unsigned mybit = qblk < nb ? (1u << (24 + (TOPK ? (wave & 7) : qsub))) : 0u;
-    const int qpos = qblk * 64 + (wave & 1) * 32 + l32;
-    bool qvalid = (qblk < nb) && (qpos < N);
-    int qrow;
-    size_t g_slot = 0;                    // GATHER: this lane's (query, key block) pair
-    if (GATHER) {
-        const int qi = wave * 32 + l32;   // position in the run of gathered queries
-        qvalid = qi < g_cnt;
-        mybit = wave * 32 < g_cnt ? (1u << (24 + (wave & 7))) : 0u;
-        g_slot = (size_t)bh * N * a.g_kk + g_slot0 + (qvalid ? qi : 0);
-        qrow = a.g_idx[g_slot];
-        qrow = min(max(qrow, 0), N - 1);
-    } else {
-        qrow = row_of_position5(kind, qvalid ? qpos : N - 1, T, HW, magic);
-    }
-
-    Frag5 qf[NS];
+    unsigned mybit = 0u;
+    bool qvalid[QS];
+    int qrow[QS];
+    size_t g_slot[QS];                    // GATHER: this lane's (query, key block) pairs
+    Frag5 qf[QS][NS];
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-        qf[s].u = *reinterpret_cast<const uint4 *>(qb + (size_t)qrow * D + s * 16 + hh * 8);
+    for (int u = 0; u < QS; ++u) {
+        const int unit = wave * QS + u, qblk = tile * 4 + (unit >> 1), qpos = qblk * 64 + (unit & 1) * 32 + l32;
+        g_slot[u] = 0;
+        if (GATHER) {
+            const int qi = unit * 32 + l32;   // position in the run of gathered queries
+            qvalid[u] = qi < g_cnt;
+            mybit |= unit * 32 < g_cnt ? (1u << (24 + unit)) : 0u;
+            g_slot[u] = (size_t)bh * N * a.g_kk + g_slot0 + (qvalid[u] ? qi : 0);
+            qrow[u] = min(max(a.g_idx[g_slot[u]], 0), N - 1);
+        } else {
+            mybit |= qblk < nb ? (1u << (24 + (TOPK ? unit : unit >> 1))) : 0u;
+            qvalid[u] = (qblk < nb) && (qpos < N);
+            qrow[u] = row_of_position5(kind, qvalid[u] ? qpos : N - 1, T, HW, magic);
+        }
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            qf[u][s].u = *reinterpret_cast<const uint4 *>(qb + (size_t)qrow[u] * D + s * 16 + hh * 8);
+    }
 
     // ---- this tile's union list (built by the pre-pass): the whole row of list_cap slots is copied, so
     // the copy does not wait for the count (slots past the count hold stale words that are never used); only a tile's later
@@ -293,7 +302,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     const int g_blk0 = g_J * a.g_bpb;
     auto copy_list = [&](int list0) INL {
         const uint32_t *src = a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
-        for (int i = tid; i < list_cap; i += 512) blist[i] = src[SPLIT ? min(i + list0, list_cap - 1) : i];
+        for (int i = tid; i < list_cap; i += NT) blist[i] = src[SPLIT ? min(i + list0, list_cap - 1) : i];
     };
     if (!GATHER && !(SPLIT && piece)) copy_list(0);
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile];
@@ -304,21 +313,27 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         n = n * (piece + 1) / pieces - list0;
         if (piece) copy_list(list0);
     }
-    uint32_t qm_lo = 0u, qm_hi = 0u;     // TOPK: this lane's query's key-block bits
-    if (TOPK && qvalid) {
-        const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow];
-        qm_lo = (uint32_t)m;
-        qm_hi = (uint32_t)(m >> 32);
-    }
+    uint32_t qm_lo[QS] = {}, qm_hi[QS] = {};     // TOPK: this lane's queries' key-block bits
+    if (TOPK)
+#pragma unroll
+        for (int u = 0; u < QS; ++u)
+            if (qvalid[u]) {
+                const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow[u]];
+                qm_lo[u] = (uint32_t)m;
+                qm_hi[u] = (uint32_t)(m >> 32);
+            }
     if (GATHER)
-        for (int i = tid; i < list_cap; i += 512) blist[i] = (uint32_t)min(g_blk0 + i, nb - 1) | 0xff000000u;
+        for (int i = tid; i < list_cap; i += NT) blist[i] = (uint32_t)min(g_blk0 + i, nb - 1) | 0xff000000u;
     __syncthreads();
     // Retire the Q loads here: inside the loop the only vector-memory operations in flight must be the
     // K/V prefetches, whose completion is tracked by hand.
 #pragma unroll
-    for (int s = 0; s < NS; ++s)
-        asm volatile("" : "+v"(qf[s].w[0]), "+v"(qf[s].w[1]), "+v"(qf[s].w[2]), "+v"(qf[s].w[3]));
-    asm volatile("" : "+v"(qm_lo), "+v"(qm_hi));
+    for (int u = 0; u < QS; ++u) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            asm volatile("" : "+v"(qf[u][s].w[0]), "+v"(qf[u][s].w[1]), "+v"(qf[u][s].w[2]), "+v"(qf[u][s].w[3]));
+        asm volatile("" : "+v"(qm_lo[u]), "+v"(qm_hi[u]));
+    }
 
     const float c2 = a.scale * 1.44269504088896340736f;   // logits are handled in the log2 domain
 
@@ -332,8 +347,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     const unsigned k_lds0 = lds_addr_of(Kb) + wave_u * (NPASS * 1024u);
     const unsigned v_lds0 = lds_addr_of(Vb) + wave_u * (NPASS * 1024u);
     const unsigned Tk = kind ? (unsigned)T : 0x7fffffffu;
-    const int lr = (wave >> 1) * 16 + (lane >> 2);                       // this thread's row of a tile
-    const unsigned vchunk_b = (unsigned)((wave & 1) * NPASS * 64 + (lane & 3) * 16);
+    const int lr = wave * NPASS / CG * 16 + (lane >> 2);                       // this thread's row of a tile
+    const unsigned vchunk_b = (unsigned)(wave * NPASS % CG * 64 + (lane & 3) * 16);
     const unsigned kv_b = (unsigned)((((lane & 3) ^ (lane >> 4)) - (lane & 3)) * 16);     // K's chunk less V's
     // byte offset of this thread's row of a block and its V chunk.  The division is by a scalar, of the block's first row; a lane's own
     // part is a constant, but for one wrap of the time axis.  Without a branch on the order (a spatial head is location 0, stride 1).
@@ -379,21 +394,26 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         f.h[1] = TR_READ(p + 256);
     };
 
-    f32x16 o[NDT];
+    f32x16 o[QS][NDT];
+    float m_run[QS], l_run[QS];
+    bool have_ref[QS];                     // m_run has been set from a block's true maximum (wave-uniform unless TOPK)
 #pragma unroll
-    for (int i = 0; i < NDT; ++i)
+    for (int u = 0; u < QS; ++u) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
-    float m_run = 0.f, l_run = 0.f;
-    bool have_ref = false;                 // m_run has been set from a block's true maximum (wave-uniform unless TOPK)
-    f32x16 s[2];
-    Frag5 pf[4];
+        for (int i = 0; i < NDT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[u][i][r] = 0.f;
+        m_run[u] = l_run[u] = 0.f;
+        have_ref[u] = false;
+    }
+    f32x16 s[QS][2];
+    Frag5 pf[QS][4];
 
     // The unit of work is half a block (32 keys).  A part = the S products of one half (NS MFMAs, A = K rows) and the O^T
     // products of one half (2 NDT MFMAs, A = V^T, two transposing 8-byte reads), with the softmax of a third half woven
     // between them.  Operand fragments move through a ring of RING register quads: step i takes ring[i % RING] and the read
     // of fragment i + RING is issued right after it; the last steps of a block read the next block's first K fragments.
-    constexpr int RING = 4;                       // 8: 5957 against 5842 us on the dense call
+    constexpr int RING = QS == 2 ? 2 : 4;         // 8: 5957 against 5842 us on the dense call; QS = 2 with 4: 4 spills, 731 against 725 us
     Frag5 ring[RING];
     constexpr int NPS = NS + 2 * NDT;             // steps of a part
     static_assert((2 * NPS) % RING == 0, "a block's fragments go round the ring a whole number of times");
@@ -406,25 +426,25 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             v_frag(f, Vt, (pt & 1) * 2 + (t - NS) / NDT, (t - NS) % NDT);
         }
     };
-    auto mfma_S = [&](int pt, int t, const Frag5 &f) INL {
+    auto mfma_S = [&](int u, int pt, int t, const Frag5 &f) INL {
         if (t == 0) {
             f32x16 z;
 #pragma unroll
             for (int r = 0; r < 16; ++r) z[r] = 0.f;
-            s[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[0].v, z, 0, 0, 0);
+            s[u][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[u][0].v, z, 0, 0, 0);
         } else {
-            s[pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[t].v, s[pt], 0, 0, 0);
+            s[u][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[u][t].v, s[u][pt], 0, 0, 0);
         }
     };
-    auto mfma_PV = [&](int pt, int t, const Frag5 &f) INL {
-        o[t % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, pf[pt * 2 + t / NDT].v, o[t % NDT], 0, 0, 0);
+    auto mfma_PV = [&](int u, int pt, int t, const Frag5 &f) INL {
+        o[u][t % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, pf[u][pt * 2 + t / NDT].v, o[u][t % NDT], 0, 0, 0);
     };
     // TOPK: a lane whose query did not select the entry's key block gets P = 0 (scale 0, reference +inf) and takes no part
     // in the reference updates
-    auto selected = [&](uint32_t e) INL -> bool {
+    auto selected = [&](int u, uint32_t e) INL -> bool {
         if (!TOPK) return true;
         const int J = (int)((e >> 16) & 63u);
-        return (((J & 32) ? qm_hi : qm_lo) >> (J & 31)) & 1u;
+        return (((J & 32) ? qm_hi[u] : qm_lo[u]) >> (J & 31)) & 1u;
     };
     auto mask_tail = [&](int hf, uint32_t e) INL {           // keys past the sequence end (last block only)
         const int blk = (int)(e & BLKMASK);
@@ -433,8 +453,10 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             asm volatile("" : "+s"(first));      // else the compares, the same in every such block, leave the loop and fill the scalar registers
             const int kbase = first + hf * 32 + hh * 8;
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (kbase + 16 * (r >> 3) + (r & 7) >= N) s[hf][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
+            for (int u = 0; u < QS; ++u)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (kbase + 16 * (r >> 3) + (r & 7) >= N) s[u][hf][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
         }
     };
     // Sums of 16 keys' bf16 probabilities, every lane getting its query's.  As the B operand of a 16x16x32 product a fragment's lanes
@@ -447,18 +469,18 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
 #pragma unroll
     for (int i = 0; i < 4; ++i) pick.w[i] = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
     asm volatile("" : "+v"(pick.w[0]), "+v"(pick.w[1]), "+v"(pick.w[2]), "+v"(pick.w[3]));
-    auto row_sum = [&](int i, f32x4 acc) INL -> f32x4 { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, pf[i].v, acc, 0, 0, 0); };
+    auto row_sum = [&](int u, int i, f32x4 acc) INL -> f32x4 { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, pf[u][i].v, acc, 0, 0, 0); };
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
     // P = 2^(S c2 - m) rounded to bf16, pair q of half hf; returns the packed pair
     auto pair_exp = [&](float t0, float t1) INL -> uint32_t { return pack2e(__builtin_amdgcn_exp2f(t0), __builtin_amdgcn_exp2f(t1)); };
-    auto exp_pack = [&](int hf, bool sel) INL -> float {
-        const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
+    auto exp_pack = [&](int u, int hf, bool sel) INL -> float {
+        const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run[u];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const uint32_t w = pair_exp(fmaf(s[hf][2 * q], cs, -mref), fmaf(s[hf][2 * q + 1], cs, -mref));
-            pf[hf * 2 + (q >> 2)].w[q & 3] = w;
+            const uint32_t w = pair_exp(fmaf(s[u][hf][2 * q], cs, -mref), fmaf(s[u][hf][2 * q + 1], cs, -mref));
+            pf[u][hf * 2 + (q >> 2)].w[q & 3] = w;
         }
-        return row_sum(hf * 2 + 1, row_sum(hf * 2, zero4))[0];
+        return row_sum(u, hf * 2 + 1, row_sum(u, hf * 2, zero4))[0];
     };
     // The reference only has to keep 2^S in range, so the maximum is not computed unless the sums say that some logit rose
     // more than 13 binades above the reference (or no reference exists yet): then the reference moves to the true maximum
@@ -466,65 +488,92 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     // counts, so that a row's first reference is the maximum of 64 keys, whose weight is then exactly 1 (keys past the sequence
     // end need no mask here: their K rows are copies of the last one, which is in the block).
     // With the maximum of the first 32 keys alone the error against 64 bits is up to 3 % larger (N = 1170, 95 %: 2.08e-3 -> 2.14e-3).
-    auto settle = [&](int hf, bool whole, bool started, bool sel, float psum) INL {
-        bool redo = !started && sel && !have_ref;
-        redo = redo || (__any(!(psum <= 8192.f)) && sel);
-        if (redo) {
-            float mx = s[hf][0];
+    auto settle = [&](int hf, bool whole, bool started, uint32_t e, const float (&ps)[QS]) INL {
+        float psum[QS];
+        bool redo[QS], any = false;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[hf][r]);
-            if (whole)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[1][r]);
-            mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run);   // maximum minus reference
-            const float shift = started || have_ref ? fmaxf(mx, 0.f) : mx;     // new reference minus old reference
-            if (started || have_ref) {
-                const float alpha = __builtin_amdgcn_exp2f(-shift);
-                l_run *= alpha;
-#pragma unroll
-                for (int i = 0; i < NDT; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
-            }
-            m_run += shift;
-            have_ref = true;
-            psum = exp_pack(hf, sel);
+        for (int u = 0; u < QS; ++u) {
+            const bool sel = selected(u, e);
+            psum[u] = ps[u];
+            redo[u] = !started && sel && !have_ref[u];
+            redo[u] = redo[u] || (__any(!(psum[u] <= 8192.f)) && sel);
+            any = any || redo[u];
         }
-        l_run += psum;
+        if (any) {
+#pragma unroll
+            for (int u = 0; u < QS; ++u)
+                if (redo[u]) {
+                    float mx = s[u][hf][0];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][hf][r]);
+                    if (whole)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][1][r]);
+                    mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run[u]);   // maximum minus reference
+                    const float shift = started || have_ref[u] ? fmaxf(mx, 0.f) : mx;   // new reference minus old reference
+                    if (started || have_ref[u]) {
+                        const float alpha = __builtin_amdgcn_exp2f(-shift);
+                        l_run[u] *= alpha;
+#pragma unroll
+                        for (int i = 0; i < NDT; ++i)
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) o[u][i][r] *= alpha;
+                    }
+                    m_run[u] += shift;
+                    have_ref[u] = true;
+                    psum[u] = exp_pack(u, hf, selected(u, e));
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < QS; ++u) l_run[u] += psum[u];
     };
     // one part: S of half pt of the current block, O of half pt of the previous block, softmax of the other half in flight
     // (pt 0: the previous block's second half, pt 1: the current block's first half; entry e)
     auto part = [&](int pt, uint32_t e, const u16 *Vt, const u16 *Kt, const u16 *Kn) INL {
         const int hf = 1 - pt;
         mask_tail(hf, e);
-        const bool sel = selected(e);
-        const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
-        constexpr int FS = NPS - 3;
-        float t[16];
-        f32x4 ps = zero4;
+        float cs[QS], mref[QS];
+#pragma unroll
+        for (int u = 0; u < QS; ++u) {
+            const bool sel = selected(u, e);
+            cs[u] = (TOPK && !sel) ? 0.f : c2;
+            mref[u] = (TOPK && !sel) ? INFINITY : m_run[u];
+        }
+        constexpr int FS = QS * (NPS - 3);
+        float t[QS][16];
+        f32x4 ps[QS];
+#pragma unroll
+        for (int u = 0; u < QS; ++u) ps[u] = zero4;
 #pragma unroll
         for (int i = 0; i < NPS; ++i) {
             const int g = pt * NPS + i;
-            if (i < NS) mfma_S(pt, i, ring[g % RING]); else mfma_PV(pt, i - NS, ring[g % RING]);
-            read_frag(g + RING, Vt, Kt, Kn);
-            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int at = q * FS / 8;          // step at which pair q's logits are scaled; its exponentials, packing and sum follow one step apart
-                if (i == at) {
-                    t[2 * q] = fmaf(s[hf][2 * q], cs, -mref);
-                    t[2 * q + 1] = fmaf(s[hf][2 * q + 1], cs, -mref);
+            for (int uu = 0; uu < QS; ++uu) {
+                const int u = (i & 1) ? QS - 1 - uu : uu, slot = i * QS + uu;
+                if (i < NS) mfma_S(u, pt, i, ring[g % RING]); else mfma_PV(u, pt, i - NS, ring[g % RING]);
+                if (uu == QS - 1) read_frag(g + RING, Vt, Kt, Kn);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int p = 0; p < 8 * QS; ++p) {
+                    const int q = p / QS, v = p % QS, at = p * FS / (8 * QS);    // pair q of set v; slot at which its logits are scaled, the rest follows one slot apart
+                    if (slot == at) {
+                        t[v][2 * q] = fmaf(s[v][hf][2 * q], cs[v], -mref[v]);
+                        t[v][2 * q + 1] = fmaf(s[v][hf][2 * q + 1], cs[v], -mref[v]);
+                    }
+                    if (slot == at + 1) {
+                        t[v][2 * q] = __builtin_amdgcn_exp2f(t[v][2 * q]);
+                        t[v][2 * q + 1] = __builtin_amdgcn_exp2f(t[v][2 * q + 1]);
+                    }
+                    if (slot == at + 2) pf[v][hf * 2 + (q >> 2)].w[q & 3] = pack2e(t[v][2 * q], t[v][2 * q + 1]);
+                    if (slot == at + 3 && (q & 3) == 3) ps[v] = row_sum(v, hf * 2 + (q >> 2), ps[v]);
                 }
-                if (i == at + 1) {
-                    t[2 * q] = __builtin_amdgcn_exp2f(t[2 * q]);
-                    t[2 * q + 1] = __builtin_amdgcn_exp2f(t[2 * q + 1]);
-                }
-                if (i == at + 2) pf[hf * 2 + (q >> 2)].w[q & 3] = pack2e(t[2 * q], t[2 * q + 1]);
-                if (i == at + 3 && (q & 3) == 3) ps = row_sum(hf * 2 + (q >> 2), ps);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
-        settle(hf, TOPK && hf == 0, !TOPK, sel, ps[0]);     // TOPK: a lane's first selected block may come here
+        float psum[QS];
+#pragma unroll
+        for (int u = 0; u < QS; ++u) psum[u] = ps[u][0];
+        settle(hf, TOPK && hf == 0, !TOPK, e, psum);     // TOPK: a lane's first selected block may come here
     };
     // the same work for blocks that not both of two successive list entries give this wave (first and last entry, entries that
     // another query block of the tile keeps).  In the uncut d = 128 kernels start_cur has the softmax of the first half between the S
@@ -534,45 +583,55 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     // 11452) and at d = 64 (480p, 90 % 882 -> 895).
     auto finish_prev = [&](uint32_t e, const u16 *Vt) INL {
         mask_tail(1, e);
-        const bool sel = selected(e);
 #pragma unroll
         for (int t = 0; t < 4 * NDT; ++t) {
-            if (t == 2 * NDT) settle(1, false, !TOPK, sel, exp_pack(1, sel));     // after the first half's products: the reference may move here
+            if (t == 2 * NDT) {     // after the first half's products: the reference may move here
+                float psum[QS];
+#pragma unroll
+                for (int u = 0; u < QS; ++u) psum[u] = exp_pack(u, 1, selected(u, e));
+                settle(1, false, !TOPK, e, psum);
+            }
             Frag5 f;
             v_frag(f, Vt, t / NDT, t % NDT);
-            mfma_PV(t / (2 * NDT), t % (2 * NDT), f);
+#pragma unroll
+            for (int u = 0; u < QS; ++u) mfma_PV(u, t / (2 * NDT), t % (2 * NDT), f);
         }
     };
     auto start_cur = [&](uint32_t e, const u16 *Kt) INL {
         auto step_S = [&](int t) INL {
             Frag5 f;
             f.v = k_frag(Kt, t / NS, t % NS);
-            mfma_S(t / NS, t % NS, f);
+#pragma unroll
+            for (int u = 0; u < QS; ++u) mfma_S(u, t / NS, t % NS, f);
         };
+        float psum[QS];
         if constexpr (D == 128 && !SPLIT) {
 #pragma unroll
             for (int t = 0; t < NS; ++t) step_S(t);
             mask_tail(0, e);
-            const bool sel = selected(e);
-            const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run;
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
                 step_S(NS + t);
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    if (q * (NS - 1) / 8 == t - 1) {
-                        const uint32_t w = pair_exp(fmaf(s[0][2 * q], cs, -mref), fmaf(s[0][2 * q + 1], cs, -mref));
-                        pf[q >> 2].w[q & 3] = w;
-                    }
+                for (int u = 0; u < QS; ++u) {
+                    const bool sel = selected(u, e);
+                    const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run[u];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        if (q * (NS - 1) / 8 == t - 1)
+                            pf[u][q >> 2].w[q & 3] = pair_exp(fmaf(s[u][0][2 * q], cs, -mref), fmaf(s[u][0][2 * q + 1], cs, -mref));
+                }
             }
-            settle(0, true, false, sel, row_sum(1, row_sum(0, zero4))[0]);
+#pragma unroll
+            for (int u = 0; u < QS; ++u) psum[u] = row_sum(u, 1, row_sum(u, 0, zero4))[0];
         } else {
 #pragma unroll
             for (int t = 0; t < 2 * NS; ++t) step_S(t);
             mask_tail(0, e);
-            const bool sel = selected(e);
-            settle(0, true, false, sel, exp_pack(0, sel));
+#pragma unroll
+            for (int u = 0; u < QS; ++u) psum[u] = exp_pack(u, 0, selected(u, e));
         }
+        settle(0, true, false, e, psum);
     };
 
     const bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[bh / a.H]);   // pruned sample (Sec. 4.3): out = O_s
@@ -580,18 +639,20 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
     // the D x D linear-state fragments (32 KB at d = 128) for the epilogue, staged into the K ring once it is idle
     auto stage_state = [&]() INL {
 #pragma unroll
-        for (int i = 0; i < D * D / (512 * 8); ++i) lds_dma16(hf + (size_t)(i * 512 + tid) * 8, lds_addr_of(Kb + (i * 512 + wave * 64) * 8));
+        for (int i = 0; i < D * D / (NT * 8); ++i) lds_dma16(hf + (size_t)(i * NT + tid) * 8, lds_addr_of(Kb + (i * NT + wave * 64) * 8));
     };
 
     // ROPE: this lane's 32 angle words (its query's row of the table: pairs 8 st + 4 hh + j), fetched under the last
     // PV product of the tile
-    uint4 ang[ROPE ? NS : 1];
+    uint4 ang[QS][ROPE ? NS : 1];
     auto load_angles = [&]() INL {
-        if (ROPE) {
-            const uint32_t *tr = a.rope_tab + (size_t)qrow * (D / 2) + hh * 4;
+        if (ROPE)
 #pragma unroll
-            for (int st = 0; st < NS; ++st) ang[st] = *reinterpret_cast<const uint4 *>(tr + st * 8);
-        }
+            for (int u = 0; u < QS; ++u) {
+                const uint32_t *tr = a.rope_tab + (size_t)qrow[u] * (D / 2) + hh * 4;
+#pragma unroll
+                for (int st = 0; st < NS; ++st) ang[u][st] = *reinterpret_cast<const uint4 *>(tr + st * 8);
+            }
     };
 
     // ---- main loop over the union list.  Iteration j: S(j) and the softmax of its first half, the softmax of the second
@@ -695,11 +756,14 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         };
         uint64_t *mine = a.sp_o + (size_t)(first + piece) * PER + tid;
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt)
+        for (int u = 0; u < QS; ++u) {
 #pragma unroll
-            for (int r = 0; r < 8; ++r) put(mine + (dt * 8 + r) * 512, o[dt][2 * r], o[dt][2 * r + 1]);
-        // a wave that kept no entry of this piece has no reference, and nothing to add
-        put(a.sp_ml + (size_t)(first + piece) * 512 + tid, have_ref ? m_run : -INFINITY, l_run);
+            for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                for (int r = 0; r < 8; ++r) put(mine + (dt * 8 + r) * 512 + u * NT, o[u][dt][2 * r], o[u][dt][2 * r + 1]);
+            // a wave that kept no entry of this piece has no reference, and nothing to add
+            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, have_ref[u] ? m_run[u] : -INFINITY, l_run[u]);
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         WAIT_VM(0);
         __syncthreads();
@@ -720,70 +784,87 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
         __syncthreads();
         if (!blist[0]) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        float mx = -INFINITY;
-        for (int p = 0; p < pieces; ++p) mx = fmaxf(mx, get(a.sp_ml + (size_t)(first + p) * 512 + tid).x);
+        float mx[QS];
 #pragma unroll
-        for (int i = 0; i < NDT; ++i)
+        for (int u = 0; u < QS; ++u) {
+            mx[u] = -INFINITY;
+            for (int p = 0; p < pieces; ++p) mx[u] = fmaxf(mx[u], get(a.sp_ml + (size_t)(first + p) * 512 + u * NT + tid).x);
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[i][r] = 0.f;
-        l_run = 0.f;
-        for (int p = 0; p < pieces; ++p) {
-            const float2 ml = get(a.sp_ml + (size_t)(first + p) * 512 + tid);
-            const float wt = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - mx);
-            const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + tid;
-            l_run = fmaf(wt, ml.y, l_run);
+            for (int i = 0; i < NDT; ++i)
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float2 v = get(src + (dt * 8 + r) * 512);
-                    o[dt][2 * r] = fmaf(wt, v.x, o[dt][2 * r]);
-                    o[dt][2 * r + 1] = fmaf(wt, v.y, o[dt][2 * r + 1]);
-                }
+                for (int r = 0; r < 16; ++r) o[u][i][r] = 0.f;
+            l_run[u] = 0.f;
         }
-        m_run = mx;
+        for (int p = 0; p < pieces; ++p)
+#pragma unroll
+            for (int u = 0; u < QS; ++u) {
+                const float2 ml = get(a.sp_ml + (size_t)(first + p) * 512 + u * NT + tid);
+                const float wt = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - mx[u]);
+                const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + u * NT + tid;
+                l_run[u] = fmaf(wt, ml.y, l_run[u]);
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        const float2 v = get(src + (dt * 8 + r) * 512);
+                        o[u][dt][2 * r] = fmaf(wt, v.x, o[u][dt][2 * r]);
+                        o[u][dt][2 * r + 1] = fmaf(wt, v.y, o[u][dt][2 * r + 1]);
+                    }
+            }
+#pragma unroll
+        for (int u = 0; u < QS; ++u) m_run[u] = mx[u];
     }
 
     // ---- epilogue ---------------------------------------------------------------------------------
-    const float l_tot = l_run;
-    const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    f32x16 num[NDT];
-    float lin_scale = 0.f, inv_den = 0.f;
+    float lin_scale[QS], inv_den[QS];
     if (lin) {
         if (n == 0 || (SPLIT && pieces > 1)) { stage_state(); if (ROPE) load_angles(); }
-        float dpart = 0.f;
         const float *Zh = a.Z + (size_t)bh * D;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
+        for (int u = 0; u < QS; ++u) {
+            float dpart = 0.f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t w = relu2e(qf[st].w[j]);
-                qf[st].w[j] = w;
-                dpart = fmaf(__uint_as_float(w << 16), Zh[st * 16 + hh * 8 + 2 * j], dpart);
-                dpart = fmaf(__uint_as_float(w & 0xffff0000u), Zh[st * 16 + hh * 8 + 2 * j + 1], dpart);
+            for (int st = 0; st < NS; ++st) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t w = relu2e(qf[u][st].w[j]);
+                    qf[u][st].w[j] = w;
+                    dpart = fmaf(__uint_as_float(w << 16), Zh[st * 16 + hh * 8 + 2 * j], dpart);
+                    dpart = fmaf(__uint_as_float(w & 0xffff0000u), Zh[st * 16 + hh * 8 + 2 * j + 1], dpart);
+                }
             }
+            const float den = dpart + __shfl_xor(dpart, 32) + a.eps;
+            inv_den[u] = 1.f / den;
+            lin_scale[u] = a.coef[bh] * inv_den[u];
         }
-        const float den = dpart + __shfl_xor(dpart, 32) + a.eps;
-        inv_den = 1.f / den;
-        lin_scale = a.coef[bh] * inv_den;
         WAIT_VM(0);
         if (ROPE) {
             // numerator operand: R_i relu(Q_i), rounded to bf16 like every MFMA operand (the normaliser above keeps the
             // unrotated features)
 #pragma unroll
-            for (int st = 0; st < NS; ++st) {
-                const uint32_t cw[4] = {ang[st].x, ang[st].y, ang[st].z, ang[st].w};
+            for (int u = 0; u < QS; ++u)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t w = qf[st].w[j];
-                    const float x = __uint_as_float(w << 16), y = __uint_as_float(w & 0xffff0000u);
-                    const f16x2 hcs = __builtin_bit_cast(f16x2, cw[j]);
-                    const float cc = (float)hcs[0], ss = (float)hcs[1];
-                    qf[st].w[j] = pack2e(x * cc - y * ss, x * ss + y * cc);
+                for (int st = 0; st < NS; ++st) {
+                    const uint32_t cw[4] = {ang[u][st].x, ang[u][st].y, ang[u][st].z, ang[u][st].w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t w = qf[u][st].w[j];
+                        const float x = __uint_as_float(w << 16), y = __uint_as_float(w & 0xffff0000u);
+                        const f16x2 hcs = __builtin_bit_cast(f16x2, cw[j]);
+                        const float cc = (float)hcs[0], ss = (float)hcs[1];
+                        qf[u][st].w[j] = pack2e(x * cc - y * ss, x * ss + y * cc);
+                    }
                 }
-            }
         }
         __syncthreads();   // the staged fragments have landed in every wave's view
+    }
+#pragma unroll
+    for (int u = 0; u < QS; ++u) {
+    const int unit = wave * QS + u;
+    const float l_tot = l_run[u];
+    const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    f32x16 num[NDT];
+    if (lin) {
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
 #pragma unroll
@@ -792,20 +873,20 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             for (int st = 0; st < NS; ++st) {
                 const int idx = ((dt * NS + st) * 64 + lane) * 8;
                 bf16x8 hi = *reinterpret_cast<const bf16x8 *>(Kb + idx);
-                num[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, qf[st].v, num[dt], 0, 0, 0);
+                num[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, qf[u][st].v, num[dt], 0, 0, 0);
             }
         }
     }
     if (!DBG) {
         // bf16 results leave through LDS so that every global store is a run of full 256-byte rows: accumulator
-        // layout (lane = query l32; 4 consecutive columns per (dt, g4, hh)) -> a wave-private half of a free tile
+        // layout (lane = query l32; 4 consecutive columns per (dt, g4, hh)) -> half of a free tile of this set's own
         // (K slots 2..4, behind the state, and the V slot after the last block's: nobody reads them any more), 16-byte chunk c of row r at
         // r * 256 + ((c ^ (r & 15)) << 4) -> row layout (4 rows x 16 chunks per instruction).
         int vs = v_last + 1;
         if (vs >= NV) vs -= NV;
-        u16 *free_tile = wave < 6 ? Kb + (2 + (wave >> 1)) * TILE : Vb + vs * TILE;
+        u16 *free_tile = unit < 6 ? Kb + (2 + (unit >> 1)) * TILE : Vb + vs * TILE;
         constexpr int ROWB = D * 2;          // bytes of a row
-        unsigned char *stg = reinterpret_cast<unsigned char *>(free_tile) + (wave & 1) * (32 * ROWB);
+        unsigned char *stg = reinterpret_cast<unsigned char *>(free_tile) + (unit & 1) * (32 * ROWB);
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
@@ -813,8 +894,8 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
                 float ov[4];
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
-                    const float os = o[dt][g4 * 4 + t] * inv_l;
-                    ov[t] = lin ? fmaf(num[dt][g4 * 4 + t], lin_scale, os) : os;
+                    const float os = o[u][dt][g4 * 4 + t] * inv_l;
+                    ov[t] = lin ? fmaf(num[dt][g4 * 4 + t], lin_scale[u], os) : os;
                 }
                 uint2 pk;
                 pk.x = pack2e(ov[0], ov[1]);
@@ -823,7 +904,7 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             }
         asm volatile("" ::: "memory");       // the wave's LDS operations execute in order
         // destination of row r: the stored row (or the pair slot) of the lane that owns query r
-        const int dest_mine = !qvalid ? -1 : GATHER ? g_slot0 + wave * 32 + l32 : qrow;
+        const int dest_mine = !qvalid[u] ? -1 : GATHER ? g_slot0 + unit * 32 + l32 : qrow[u];
         constexpr int RPI = 64 / CH;          // rows per store instruction (4 rows x 16 chunks, or 8 x 8)
         const int r4 = lane / CH, c16 = lane % CH;
         u16 *dbase = GATHER ? a.g_po + (size_t)bh * N * a.g_kk * D : reinterpret_cast<u16 *>(a.out) + (size_t)bh * N * D;
@@ -834,55 +915,62 @@ __global__ __launch_bounds__(512, 2) void sparse_attn_v5_kernel(AttnArgs a, int 
             const int dest = __shfl(dest_mine, r);
             if (dest >= 0) *reinterpret_cast<uint4 *>(dbase + (size_t)dest * D + c16 * 8) = v;
         }
-        if (GATHER && qvalid && hh == 0) a.g_lse[g_slot] = l_tot > 0.f ? m_run + log2f(l_tot) : -INFINITY;
-    } else {
-    if (!qvalid) return;
-    const size_t obase = ((size_t)bh * N + qrow) * D;
-    u16 *outp = reinterpret_cast<u16 *>(a.out) + obase;
+        if (GATHER && qvalid[u] && hh == 0) a.g_lse[g_slot[u]] = l_tot > 0.f ? m_run[u] + log2f(l_tot) : -INFINITY;
+    } else if (qvalid[u]) {
+        const size_t obase = ((size_t)bh * N + qrow[u]) * D;
+        u16 *outp = reinterpret_cast<u16 *>(a.out) + obase;
 #pragma unroll
-    for (int dt = 0; dt < NDT; ++dt) {
+        for (int dt = 0; dt < NDT; ++dt) {
 #pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            const int col = dt * 32 + 8 * g4 + 4 * hh;
-            float os[4], ol[4], ov[4];
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const int col = dt * 32 + 8 * g4 + 4 * hh;
+                float os[4], ol[4], ov[4];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                os[t] = o[dt][g4 * 4 + t] * inv_l;
-                ol[t] = lin ? num[dt][g4 * 4 + t] : 0.f;
-                ov[t] = lin ? fmaf(ol[t], lin_scale, os[t]) : os[t];
+                for (int t = 0; t < 4; ++t) {
+                    os[t] = o[u][dt][g4 * 4 + t] * inv_l;
+                    ol[t] = lin ? num[dt][g4 * 4 + t] : 0.f;
+                    ov[t] = lin ? fmaf(ol[t], lin_scale[u], os[t]) : os[t];
+                }
+                uint2 pk;
+                pk.x = pack2e(ov[0], ov[1]);
+                pk.y = pack2e(ov[2], ov[3]);
+                *reinterpret_cast<uint2 *>(outp + col) = pk;
+                if (DBG && a.o_sparse_dbg)
+                    *reinterpret_cast<float4 *>(a.o_sparse_dbg + obase + col) = make_float4(os[0], os[1], os[2], os[3]);
+                if (DBG && a.o_linear_dbg && lin)
+                    *reinterpret_cast<float4 *>(a.o_linear_dbg + obase + col) =
+                        make_float4(ol[0] * inv_den[u], ol[1] * inv_den[u], ol[2] * inv_den[u], ol[3] * inv_den[u]);
             }
-            uint2 pk;
-            pk.x = pack2e(ov[0], ov[1]);
-            pk.y = pack2e(ov[2], ov[3]);
-            *reinterpret_cast<uint2 *>(outp + col) = pk;
-            if (DBG && a.o_sparse_dbg)
-                *reinterpret_cast<float4 *>(a.o_sparse_dbg + obase + col) = make_float4(os[0], os[1], os[2], os[3]);
-            if (DBG && a.o_linear_dbg && lin)
-                *reinterpret_cast<float4 *>(a.o_linear_dbg + obase + col) =
-                    make_float4(ol[0] * inv_den, ol[1] * inv_den, ol[2] * inv_den, ol[3] * inv_den);
         }
     }
     }
 }
 
-SplitPlan split_plan(int BH, int nb)
+// Sets of 32 queries of a wave (the kernel's QS): 2 at d = 64 where there are more tiles than compute units and two workgroups' LDS fits one.
+static int query_sets(int d, int nb, long long tiles)
 {
-    // 256 workgroups run at a time (one per compute unit).  Whole rounds of 256 tiles stay as they are; the rest, if it leaves at
-    // least half of the chip idle, is cut into as many pieces as there is room for.
+    return d == 64 && tiles > 256 && 2 * (v5_ring_bytes(d) + tile_list_cap(nb) * 4) <= V5_MAX_DYN ? 2 : 1;
+}
+
+SplitPlan split_plan(int BH, int nb, int d)
+{
+    // One workgroup per compute unit runs at a time, 256 in all, or two.  Whole rounds of tiles stay as they are; the rest, if it leaves
+    // at least half of the chip idle, is cut into as many pieces as there is room for.
     // Layer call before -> after: 49 tiles of 12 heads (512 + 76 workgroups, 52 entries) 300 -> 269 us; 44 tiles, 42 entries, dense
     // 79 -> 46; 184 tiles of 2 x 12 heads 675 -> 629; 25 tiles of 5 heads 64 -> 55.  A list of 11 entries cut in two gained nothing
     // (37.4 -> 38.5), hence SPLIT_MIN_ENTRIES; with it calls that are not cut measure the same as before.
     const long long total = (long long)BH * ((nb + 3) / 4);
+    const int round = 256 * query_sets(d, nb, total);
     SplitPlan p{};
-    p.full = (int)(total / 256 * 256);
+    p.full = (int)(total / round * round);
     p.rest = (int)(total - p.full);
-    p.pieces = p.rest ? 256 / p.rest : 1;
+    p.pieces = p.rest ? round / p.rest : 1;
     if (p.pieces > SPLIT_MAX_PIECES) p.pieces = SPLIT_MAX_PIECES;
     if (nb < 2 * SPLIT_MIN_ENTRIES) p.pieces = 1;             // no list of this length is cut
     return p;
 }
 
-template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false>
+template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false, int QS = 1>
 static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
 {
     const int ntiles = (a.nb + 3) / 4;
@@ -891,11 +979,11 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     if (!large_tile_list_fits(D, a.nb)) return hipErrorInvalidValue;
     const int list_cap = tile_list_cap(a.nb);
     const size_t lds = v5_ring_bytes(D) + (size_t)list_cap * 4;
-    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT>;
+    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT, QS>;
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), V5_MAX_DYN, attr_done); e != hipSuccess) return e;
     const int grid = SPLIT ? a.sp_full + ((total - a.sp_full) * a.sp_pieces + 7) / 8 * 8 : per_xcd * 8;
-    launch_kernel(kern, dim3(grid), dim3(512), lds, st, a, ntiles, total, per_xcd, list_cap);
+    launch_kernel(kern, dim3(grid), dim3(512 / QS), lds, st, a, ntiles, total, per_xcd, list_cap);
     return take_launch_status();
 }
 
@@ -904,6 +992,10 @@ hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st)
     const bool dbg = a.o_sparse_dbg || a.o_linear_dbg, split = a.sp_pieces > 1 && !a.g_desc && !a.topk_mask;
     if (a.D == 64) {
         if (a.g_desc || a.topk_mask || a.rope_tab) return hipErrorInvalidValue;
+        if (query_sets(64, a.nb, (long long)a.B * a.H * ((a.nb + 3) / 4)) == 2) {
+            if (split) return dbg ? launch_v5<true, 0, false, 64, true, 2>(a, st) : launch_v5<false, 0, false, 64, true, 2>(a, st);
+            return dbg ? launch_v5<true, 0, false, 64, false, 2>(a, st) : launch_v5<false, 0, false, 64, false, 2>(a, st);
+        }
         if (split) return dbg ? launch_v5<true, 0, false, 64, true>(a, st) : launch_v5<false, 0, false, 64, true>(a, st);
         return dbg ? launch_v5<true, 0, false, 64>(a, st) : launch_v5<false, 0, false, 64>(a, st);
     }

@@ -224,6 +224,35 @@ def test_visit_list_lengths(oracle, d, grid, kept):
         compare_layer(res, _oracle_layer(oracle, w, inp, kept, kinds), label=w.name)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grid", [(2, 11, 13), (15, 4, 5), (63, 3, 5), (64, 3, 4), (65, 3, 5), (130, 2, 3)])
+def test_time_axis_wraps_inside_a_block(oracle, d, grid):
+    """Rows of a temporal head's block are found from its first row and a lane's own offset, which wraps the time axis at most
+    once when the axis is longer than the 16 rows of a load and many times over the block when it is shorter."""
+    w = wl.small(f"wrap-{d}-{grid}", 1, 2, d, *grid, "bf16", 0.5, seed=900 + d + grid[0])
+    inp = wl.make_inputs(w)
+    kept = [3, 3]
+    for dbg in (True, False):
+        res = run_layer(w, inp, upload(w, inp), kept, [1, 1], dbg=dbg)
+        compare_layer(res, _oracle_layer(oracle, w, inp, kept, [1, 1]), label=w.name)
+
+
+@pytest.mark.parametrize("B,H,grid,keep", [
+    (1, 64, (3, 16, 17), 5),      # 256 tiles: 32 queries a wave
+    (1, 43, (4, 17, 19), 9),      # 258 tiles: 64 queries a wave, one round, the last tile of a head with one block of 12 keys
+    (2, 64, (3, 13, 14), 2),      # 384 tiles, lists shorter than the blocks fetched ahead
+    (3, 43, (3, 16, 17), 13),     # 516 tiles: the last four are cut in two
+])
+def test_d64_sixty_four_queries_a_wave(oracle, B, H, grid, keep):
+    """d = 64 around the number of tiles from which on a wave owns 64 queries; both head orders, guided batches, cut tiles."""
+    w = wl.small(f"d64-{B}-{H}-{grid}", B, H, 64, *grid, "bf16", 0.5, seed=950 + H)
+    inp = wl.make_inputs(w)
+    kinds, kept = wl.head_kinds(w), [keep] * H
+    ref = _oracle_layer(oracle, w, inp, kept, kinds)
+    for dbg in (True, False):
+        compare_layer(run_layer(w, inp, upload(w, inp), kept, kinds, dbg=dbg), ref, label=w.name)
+
+
 @pytest.mark.parametrize("B,H,d,grid,kept", [
     (1, 3, 128, (5, 13, 17), [18, 5, 13]),       # 15 tiles in up to 8 pieces; lists of 18 (3 pieces), 8 (whole) and 16 (2 pieces) entries
     (2, 2, 64, (3, 29, 31), [43, 30]),           # 44 tiles in 5 pieces, the last tile of 3 blocks
