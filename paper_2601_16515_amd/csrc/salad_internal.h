@@ -118,6 +118,7 @@ struct AttnArgs {
     // in the low 4 bits, how many pieces have arrived; with any other tag in it (whatever the workspace held) none has.  At the end it is 0
     int sp_full, sp_pieces;
     uint64_t *sp_o, *sp_ml, *sp_count, sp_tag;
+    unsigned tiles_magic, heads_magic, pieces_magic;   // large-tile kernel: multiply-high inverses, filled in by its launcher
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };
 hipError_t launch_sparse_attn_bf16(const AttnArgs &a, hipStream_t st);

@@ -96,6 +96,22 @@ __device__ inline void lds_dma16_base(const void *base_uniform, unsigned byte_of
                  : "memory", "m0");
 }
 
+// One 4-byte-per-lane global -> LDS load (lane i lands at lds_addr + 4 i).
+__device__ inline void lds_dma4(const void *gptr, unsigned lds_addr_uniform)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
+                 :
+                 : "s"(lds_addr_uniform), "v"(gptr)
+                 : "memory", "m0");
+}
+
+// x / d for any x and d >= 1, magic = floor(2^32 / d) (2^32 - 1 for d = 1): the multiply-high is at most one too small
+__device__ inline unsigned div_by(unsigned x, unsigned d, unsigned magic)
+{
+    const unsigned q = __umulhi(x, magic);
+    return x - q * d >= d ? q + 1 : q;
+}
+
 __device__ inline unsigned lds_addr_of(const void *p)
 {
     return __builtin_amdgcn_readfirstlane((unsigned)(size_t)LDS_PTR(p));
@@ -243,7 +259,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         } else {
             const int q = (g & 7) * px + r;
             if (r >= px || q >= np) return;
-            L = a.sp_full + q / a.sp_pieces;
+            L = a.sp_full + (int)div_by((unsigned)q, (unsigned)a.sp_pieces, a.pieces_magic);
             piece = q - (L - a.sp_full) * a.sp_pieces;
             pieces = a.sp_pieces;
         }
@@ -251,7 +267,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         L = (g & 7) * per_xcd + (g >> 3);
         if (L >= total) return;
     }
-    int bh = L / ntiles, tile = L - bh * ntiles;
+    int bh = (int)div_by((unsigned)L, (unsigned)ntiles, a.tiles_magic), tile = L - bh * ntiles;
     int g_J = 0, g_slot0 = 0, g_cnt = 0;
     if (GATHER) {
         const uint4 dsc = a.g_desc[L];
@@ -259,7 +275,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (g_cnt == 0) return;            // unused descriptor
         tile = 0;
     }
-    const int h = bh % a.H;
+    const int smp = (int)div_by((unsigned)bh, (unsigned)a.H, a.heads_magic), h = bh - smp * a.H;
     const int N = a.N, T = a.T, HW = a.HW, nb = a.nb;
     const int kind = (T > 1 && !TOPK) ? (int)((a.kind_mask >> h) & 1ull) : 0;
     const unsigned magic = a.t_magic;
@@ -271,11 +287,31 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const u16 *kb = reinterpret_cast<const u16 *>(a.k) + (size_t)bh * N * D;
     const u16 *vb = reinterpret_cast<const u16 *>(a.v) + (size_t)bh * N * D;
 
+    // ---- The start of a tile is a chain of memory latencies with nothing to run under them (13000 cycles of 57000 for a 13-entry tile),
+    // so everything whose address is known is asked for at once: the count and the first entries by scalar loads, the queries and
+    // the list straight into LDS, and, as soon as the first entries are there, the first blocks.  Before, list and queries came first, through
+    // registers, and the blocks after a barrier.  Layer call: N = 1950 36.5 -> 35.6 us, N = 640 25.6 -> 24.1, Top-K at N = 32760
+    // (13 entries) 1069 -> 1052, 24 heads of 64 at 90 % 723 -> 717; 12 heads of 128 at 90 % the same (at the power limit a wait costs little).
+    const int g_blk0 = g_J * a.g_bpb;
+    const uint32_t *src = GATHER ? nullptr : a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
+    int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
+    if (SPLIT && pieces > 1) {
+        pieces = min(pieces, max(1, n / SPLIT_MIN_ENTRIES));
+        if (piece >= pieces) return;
+        list0 = n * piece / pieces;      // this piece's first entry
+        n = n * (piece + 1) / pieces - list0;
+    }
+    constexpr int AK = NK - 1, AV = NV - 2;     // how far ahead of an iteration K and V are fetched
+    uint32_t eq[AK];                             // entries j .. j+3 of iteration j; the first one's past the end of the list
+#pragma unroll
+    for (int b = 0; b < AK; ++b) eq[b] = GATHER ? (uint32_t)min(g_blk0 + b, nb - 1) | 0xff000000u : src[SPLIT ? min(list0 + b, list_cap - 1) : b];
+
     unsigned mybit = 0u;
     bool qvalid[QS];
     int qrow[QS];
     size_t g_slot[QS];                    // GATHER: this lane's (query, key block) pairs
     Frag5 qf[QS][NS];
+    uint32_t qm_lo[QS] = {}, qm_hi[QS] = {};     // TOPK: this lane's queries' key-block bits
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
         const int unit = wave * QS + u, qblk = tile * 4 + (unit >> 1), qpos = qblk * 64 + (unit & 1) * 32 + l32;
@@ -285,55 +321,45 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             qvalid[u] = qi < g_cnt;
             mybit |= unit * 32 < g_cnt ? (1u << (24 + unit)) : 0u;
             g_slot[u] = (size_t)bh * N * a.g_kk + g_slot0 + (qvalid[u] ? qi : 0);
-            qrow[u] = min(max(a.g_idx[g_slot[u]], 0), N - 1);
+            qrow[u] = 0;
         } else {
             mybit |= qblk < nb ? (1u << (24 + (TOPK ? unit : unit >> 1))) : 0u;
             qvalid[u] = (qblk < nb) && (qpos < N);
             qrow[u] = row_of_position5(kind, qvalid[u] ? qpos : N - 1, T, HW, magic);
         }
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-            qf[u][s].u = *reinterpret_cast<const uint4 *>(qb + (size_t)qrow[u] * D + s * 16 + hh * 8);
+        if (TOPK && qvalid[u]) {
+            const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow[u]];
+            qm_lo[u] = (uint32_t)m;
+            qm_hi[u] = (uint32_t)(m >> 32);
+        }
     }
-
-    // ---- this tile's union list (built by the pre-pass): the whole row of list_cap slots is copied, so
-    // the copy does not wait for the count (slots past the count hold stale words that are never used); only a tile's later
-    // pieces wait, for their first entry
-    const int g_blk0 = g_J * a.g_bpb;
-    auto copy_list = [&](int list0) INL {
-        const uint32_t *src = a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
-        for (int i = tid; i < list_cap; i += NT) blist[i] = src[SPLIT ? min(i + list0, list_cap - 1) : i];
+    const unsigned wave_u = (unsigned)__builtin_amdgcn_readfirstlane(wave);
+    // Queries go through LDS, too, each wave's own into a part of the ring that nothing else uses yet: read from memory in operand order,
+    // 32 bytes of 32 rows at a time, they pass the 64 bytes a clock of the load path four times.  Laid out like a K tile (below).
+    auto q_lds = [&](int u) INL -> unsigned char * {
+        const int unit = (int)wave_u * QS + u;
+        return reinterpret_cast<unsigned char *>(unit < 6 ? Kb + (2 + (unit >> 1)) * TILE : Vb + (NV - 1) * TILE) + (unit & 1) * (32 * D * 2);
     };
-    if (!GATHER && !(SPLIT && piece)) copy_list(0);
-    int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile];
-    if (SPLIT && pieces > 1) {
-        pieces = min(pieces, max(1, n / SPLIT_MIN_ENTRIES));
-        if (piece >= pieces) return;
-        const int list0 = n * piece / pieces;      // this piece's first entry
-        n = n * (piece + 1) / pieces - list0;
-        if (piece) copy_list(list0);
-    }
-    uint32_t qm_lo[QS] = {}, qm_hi[QS] = {};     // TOPK: this lane's queries' key-block bits
-    if (TOPK)
+    auto fetch_q = [&]() INL {
 #pragma unroll
         for (int u = 0; u < QS; ++u)
-            if (qvalid[u]) {
-                const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow[u]];
-                qm_lo[u] = (uint32_t)m;
-                qm_hi[u] = (uint32_t)(m >> 32);
+#pragma unroll
+            for (int rg = 0; rg < 2; ++rg) {
+                const int i = ((int)wave_u * QS + u) * 32 + rg * 16 + (lane >> 2);      // query of the tile
+                int row;
+                if (GATHER) row = min(max(a.g_idx[(size_t)bh * N * a.g_kk + g_slot0 + (i < g_cnt ? i : 0)], 0), N - 1);
+                else row = row_of_position5(kind, min(tile * 256 + i, N - 1), T, HW, magic);
+                const unsigned off = (unsigned)row * (unsigned)(D * 2) + (unsigned)(((lane & 3) ^ (lane >> 4)) * 16);
+                const unsigned dst = lds_addr_of(q_lds(u)) + (unsigned)(rg * CG * 1024);
+#pragma unroll
+                for (int c = 0; c < CG; ++c) lds_dma16_base(qb + c * 32, off, dst + c * 1024u);
             }
-    if (GATHER)
-        for (int i = tid; i < list_cap; i += NT) blist[i] = (uint32_t)min(g_blk0 + i, nb - 1) | 0xff000000u;
-    __syncthreads();
-    // Retire the Q loads here: inside the loop the only vector-memory operations in flight must be the
-    // K/V prefetches, whose completion is tracked by hand.
-#pragma unroll
-    for (int u = 0; u < QS; ++u) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s)
-            asm volatile("" : "+v"(qf[u][s].w[0]), "+v"(qf[u][s].w[1]), "+v"(qf[u][s].w[2]), "+v"(qf[u][s].w[3]));
-        asm volatile("" : "+v"(qm_lo[u]), "+v"(qm_hi[u]));
-    }
+    };
+    if (!GATHER) fetch_q();
+    // the list's whole row of list_cap slots (built by the pre-pass), without waiting for the count: slots past it hold stale words that are never used
+    if (!GATHER)
+        for (int i = (int)wave_u * 64; i < list_cap; i += NT)
+            lds_dma4(src + (SPLIT ? min(i + lane + list0, list_cap - 1) : i + lane), lds_addr_of(blist + i));
 
     const float c2 = a.scale * 1.44269504088896340736f;   // logits are handled in the log2 domain
 
@@ -343,7 +369,6 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the 4 rows by 64 bytes that 32 lanes of a transposing V read take cover all banks once.  Of an operand's address only two bits
     // of K's chunk depend on both lane and step; all else of the step is an immediate.
     // LDS destinations are wave-uniform scalars; global sources are a uniform base plus a 32-bit offset.
-    const unsigned wave_u = (unsigned)__builtin_amdgcn_readfirstlane(wave);
     const unsigned k_lds0 = lds_addr_of(Kb) + wave_u * (NPASS * 1024u);
     const unsigned v_lds0 = lds_addr_of(Vb) + wave_u * (NPASS * 1024u);
     const unsigned Tk = kind ? (unsigned)T : 0x7fffffffu;
@@ -374,9 +399,22 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     };
     // list entries travel in a vector register (lane l holds entry 64 c + l of the current 64-entry
     // chunk c) and are picked with v_readlane: no LDS round trip per iteration
-    uint32_t ev = blist[lane];
+    uint32_t ev = 0u;
     const uint32_t tail_blk = (N & 63) ? (uint32_t)(N >> 6) : 0xffffffffu;             // the block that the sequence ends in
     auto entry = [&](int idx) INL -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)ev, idx & 63); };
+
+    // first blocks: enough for iteration 0; the rest of what the loop expects in flight follows once these have landed
+    unsigned rk[AK - AV + 1] = {};               // row offsets of blocks j+2 .. j+4, for the V fetches to come
+    unsigned r1 = 0u;
+    if (n > 0) {
+        const unsigned r0 = rows_of((int)(eq[0] & BLKMASK));
+        fetch_k(r0, 0);
+        if (n > 1) {
+            r1 = rows_of((int)(eq[1] & BLKMASK));
+            fetch_k(r1, 1);
+        }
+        fetch_v(r0, 0);
+    }
 
     // ---- LDS operand addresses (element offsets inside a tile)
     const int kappa = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
@@ -634,10 +672,15 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         settle(0, true, false, e, psum);
     };
 
-    const bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[bh / a.H]);   // pruned sample (Sec. 4.3): out = O_s
+    const bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[smp]);   // pruned sample (Sec. 4.3): out = O_s
     const u16 *hf = a.hfrag + (size_t)bh * D * D;
-    // the D x D linear-state fragments (32 KB at d = 128) for the epilogue, staged into the K ring once it is idle
+    const float coef = lin ? a.coef[bh] : 0.f;
+    // the D x D linear-state fragments (32 KB at d = 128) for the epilogue, staged into the K ring once it is idle, and the normaliser's
+    // sums into the V slot two after the last block's
+    int v_last = 0;                         // V-ring slot of the last block: the only tile still read after the loop
+    auto z_lds = [&]() INL -> float * { return reinterpret_cast<float *>(Vb + ((v_last + 2) & (NV - 1)) * TILE); };
     auto stage_state = [&]() INL {
+        if ((int)wave_u * 64 < D) lds_dma4(a.Z + (size_t)bh * D + wave_u * 64 + lane, lds_addr_of(z_lds() + wave_u * 64));
 #pragma unroll
         for (int i = 0; i < D * D / (NT * 8); ++i) lds_dma16(hf + (size_t)(i * NT + tid) * 8, lds_addr_of(Kb + (i * NT + wave * 64) * 8));
     };
@@ -660,25 +703,39 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // K ring and b % NV of the V ring: K(b) is read at the end of iteration b-1 and in b, V(b) in b+1.  The barrier of
     // iteration j says that everything fetched up to iteration j-3 has landed (K(j+1) and V(j-1) among it), so two
     // iterations' loads stay in flight, and that iteration j-1 no longer reads the slots that j fetches into.
-    int v_last = 0;                         // V-ring slot of the last block: the only tile still read after the loop
-    if (n > 0) {
-        constexpr int AK = NK - 1, AV = NV - 2;     // how far ahead K and V are fetched
-        static_assert(AK == 4 && AV == 2, "the waits below count the loads of two iterations");
-        unsigned rk[AK - AV + 1];                        // row offsets of blocks j+2 .. j+4, for the V fetches to come
-        {
-            unsigned r0 = rows_of((int)(entry(0) & BLKMASK)), r1 = rows_of((int)(entry(min(1, n - 1)) & BLKMASK));
-            rk[0] = rows_of((int)(entry(min(2, n - 1)) & BLKMASK));
-            rk[1] = rows_of((int)(entry(min(3, n - 1)) & BLKMASK));
-            fetch_k(r0, 0);
-            if (n > 1) fetch_k(r1, 1);
-            if (n > 2) fetch_k(rk[0], 2);
-            fetch_v(r0, 0);
-            if (n > 3) fetch_k(rk[1], 3);
-            if (n > 1) fetch_v(r1, 1);
-        }
-        uint32_t e_prev = 0u, eq[AK];                // entries j-1; j .. j+3
+    // List, queries and K of block 0 are there, K of block 1 and V of block 0 still on their way; from here on the only vector-memory
+    // operations in flight are the K/V fetches, whose completion is tracked by hand.
+    if (GATHER) fetch_q();
+    if (!GATHER && n > 1) WAIT_VM(2 * NPASS); else WAIT_VM(0);
+    asm volatile("" ::: "memory");
+    {
+        const int q_off = (l32 >> 4) * (CG * 1024) + (l32 & 15) * 64;
 #pragma unroll
-        for (int b = 0; b < AK; ++b) eq[b] = entry(min(b, n - 1));
+        for (int u = 0; u < QS; ++u)
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                qf[u][s].u = *reinterpret_cast<const uint4 *>(q_lds(u) + q_off + (((2 * (s & 1) + hh) ^ ((l32 >> 2) & 3)) << 4) + (s >> 1) * 1024);
+    }
+#pragma unroll
+    for (int u = 0; u < QS; ++u) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            asm volatile("" : "+v"(qf[u][s].w[0]), "+v"(qf[u][s].w[1]), "+v"(qf[u][s].w[2]), "+v"(qf[u][s].w[3]));
+        asm volatile("" : "+v"(qm_lo[u]), "+v"(qm_hi[u]));
+    }
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    auto load_entries = [&](int first) INL {      // entries first .. first + 63
+        if (GATHER) ev = (uint32_t)min(g_blk0 + first + lane, nb - 1) | 0xff000000u;
+        else asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(ev) : "v"((unsigned)(size_t)LDS_PTR(blist + first + lane)) : "memory");
+    };
+    load_entries(0);
+    if (n > 0) {
+        static_assert(AK == 4 && AV == 2, "the waits below count the loads of two iterations");
+        if (n > 2) fetch_k(rk[0] = rows_of((int)(eq[2] & BLKMASK)), 2);
+        if (n > 3) fetch_k(rk[1] = rows_of((int)(eq[3] & BLKMASK)), 3);
+        if (n > 1) fetch_v(r1, 1);
+        uint32_t e_prev = 0u;                     // entry j-1
         int kslot = 0, vslot = 0;                 // j % NK, j % NV
         for (int j = 0; j < n; ++j) {
             if (j + AK <= n) WAIT_VM(4 * NPASS); else WAIT_VM(0);
@@ -687,8 +744,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             const int jf = j + AK;
             uint32_t e_f = 0u;
             if (jf < n) {
-                if ((jf & 63) == 0)      // waited for here, so that the other turns of the loop need not wait for their operand reads
-                    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(ev) : "v"((unsigned)(size_t)LDS_PTR(blist + jf + lane)) : "memory");
+                if ((jf & 63) == 0) load_entries(jf);      // waited for inside, so that the other turns of the loop need not wait for their operand reads
                 e_f = entry(jf);
             }
             int kslot_f = kslot + AK; if (kslot_f >= NK) kslot_f -= NK;
@@ -731,13 +787,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         WAIT_VM(0);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
+        v_last = vslot ? vslot - 1 : NV - 1;
         if (lin && !(SPLIT && pieces > 1)) stage_state();
         if (ROPE && lin && !(SPLIT && pieces > 1)) load_angles();
-        {
-            int vslot_prev = vslot - 1; if (vslot_prev < 0) vslot_prev += NV;
-            v_last = vslot_prev;
-            if ((e_prev & mybit) != 0) finish_prev(e_prev, Vb + vslot_prev * TILE);
-        }
+        if ((e_prev & mybit) != 0) finish_prev(e_prev, Vb + v_last * TILE);
     }
 
     if (SPLIT && pieces > 1) {
@@ -819,25 +872,35 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     float lin_scale[QS], inv_den[QS];
     if (lin) {
         if (n == 0 || (SPLIT && pieces > 1)) { stage_state(); if (ROPE) load_angles(); }
-        const float *Zh = a.Z + (size_t)bh * D;
 #pragma unroll
-        for (int u = 0; u < QS; ++u) {
-            float dpart = 0.f;
+        for (int u = 0; u < QS; ++u)
 #pragma unroll
-            for (int st = 0; st < NS; ++st) {
+            for (int st = 0; st < NS; ++st)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) qf[u][st].w[j] = relu2e(qf[u][st].w[j]);
+        WAIT_VM(0);
+        __syncthreads();   // the staged fragments have landed in every wave's view
+        float dpart[QS] = {};
+        const float *Zh = z_lds() + hh * 8;
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            const float4 z0 = *reinterpret_cast<const float4 *>(Zh + st * 16), z1 = *reinterpret_cast<const float4 *>(Zh + st * 16 + 4);
+            const float zz[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
+#pragma unroll
+            for (int u = 0; u < QS; ++u)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    uint32_t w = relu2e(qf[u][st].w[j]);
-                    qf[u][st].w[j] = w;
-                    dpart = fmaf(__uint_as_float(w << 16), Zh[st * 16 + hh * 8 + 2 * j], dpart);
-                    dpart = fmaf(__uint_as_float(w & 0xffff0000u), Zh[st * 16 + hh * 8 + 2 * j + 1], dpart);
+                    const uint32_t w = qf[u][st].w[j];
+                    dpart[u] = fmaf(__uint_as_float(w << 16), zz[2 * j], dpart[u]);
+                    dpart[u] = fmaf(__uint_as_float(w & 0xffff0000u), zz[2 * j + 1], dpart[u]);
                 }
-            }
-            const float den = dpart + __shfl_xor(dpart, 32) + a.eps;
-            inv_den[u] = 1.f / den;
-            lin_scale[u] = a.coef[bh] * inv_den[u];
         }
-        WAIT_VM(0);
+#pragma unroll
+        for (int u = 0; u < QS; ++u) {
+            const float den = dpart[u] + __shfl_xor(dpart[u], 32) + a.eps;
+            inv_den[u] = 1.f / den;
+            lin_scale[u] = coef * inv_den[u];
+        }
         if (ROPE) {
             // numerator operand: R_i relu(Q_i), rounded to bf16 like every MFMA operand (the normaliser above keeps the
             // unrotated features)
@@ -856,7 +919,6 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                     }
                 }
         }
-        __syncthreads();   // the staged fragments have landed in every wave's view
     }
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
@@ -983,7 +1045,10 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), V5_MAX_DYN, attr_done); e != hipSuccess) return e;
     const int grid = SPLIT ? a.sp_full + ((total - a.sp_full) * a.sp_pieces + 7) / 8 * 8 : per_xcd * 8;
-    launch_kernel(kern, dim3(grid), dim3(512 / QS), lds, st, a, ntiles, total, per_xcd, list_cap);
+    auto magic = [](int d) { return d > 1 ? (unsigned)((1ull << 32) / (unsigned)d) : ~0u; };
+    AttnArgs b = a;
+    b.tiles_magic = magic(ntiles); b.heads_magic = magic(a.H); b.pieces_magic = magic(a.sp_pieces);
+    launch_kernel(kern, dim3(grid), dim3(512 / QS), lds, st, b, ntiles, total, per_xcd, list_cap);
     return take_launch_status();
 }
 
