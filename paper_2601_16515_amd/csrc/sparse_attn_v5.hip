@@ -384,7 +384,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const unsigned lane0 = (unsigned)lr * stride_b + ql * back_b + vchunk_b, lane1 = lane0 + (unsigned)(D * 2) - (unsigned)T * stride_b;
     auto rows_of = [&](int blk) INL -> unsigned {
         const unsigned p0 = (unsigned)__builtin_amdgcn_readfirstlane(blk * 64);
-        if ((int)p0 + 64 > N) return row_bytes((unsigned)min((int)p0 + lr, N - 1)) + vchunk_b;
+        if (__builtin_expect((int)p0 + 64 > N, 0)) return row_bytes((unsigned)min((int)p0 + lr, N - 1)) + vchunk_b;
         const unsigned q0 = __umulhi(p0, magic_u);
         const unsigned base = p0 * stride_b + q0 * back_b, left = Tk - (kind ? p0 - q0 * (unsigned)T : 0u);
         return base + (rl >= left ? lane1 : lane0);
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     };
     auto mask_tail = [&](int hf, uint32_t e) INL {           // keys past the sequence end (last block only)
         const int blk = (int)(e & BLKMASK);
-        if ((uint32_t)blk == tail_blk) {
+        if (__builtin_expect((uint32_t)blk == tail_blk, 0)) {
             int first = blk * 64;
             asm volatile("" : "+s"(first));      // else the compares, the same in every such block, leave the loop and fill the scalar registers
             const int kbase = first + hf * 32 + hh * 8;
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             redo[u] = redo[u] || (__any(!(psum[u] <= 8192.f)) && sel);
             any = any || redo[u];
         }
-        if (any) {
+        if (__builtin_expect(any, 0)) {
 #pragma unroll
             for (int u = 0; u < QS; ++u)
                 if (redo[u]) {
@@ -737,32 +737,32 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (n > 1) fetch_v(r1, 1);
         uint32_t e_prev = 0u;                     // entry j-1
         int kslot = 0, vslot = 0;                 // j % NK, j % NV
+        // The expectations keep the usual way through an iteration free of taken branches: dense 5525 -> 5455 us, 480p 90 % 652 -> 644.
         for (int j = 0; j < n; ++j) {
-            if (j + AK <= n) WAIT_VM(4 * NPASS); else WAIT_VM(0);
+            if (__builtin_expect(j + AK <= n, 1)) WAIT_VM(4 * NPASS); else WAIT_VM(0);
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
             const int jf = j + AK;
             uint32_t e_f = 0u;
-            if (jf < n) {
-                if ((jf & 63) == 0) load_entries(jf);      // waited for inside, so that the other turns of the loop need not wait for their operand reads
+            if (__builtin_expect(jf < n, 1)) {
+                if (__builtin_expect((jf & 63) == 0, 0)) load_entries(jf);      // waited for inside, so that the other turns of the loop need not wait for their operand reads
                 e_f = entry(jf);
             }
-            int kslot_f = kslot + AK; if (kslot_f >= NK) kslot_f -= NK;
+            int kslot_f = kslot - 1; if (kslot_f < 0) kslot_f += NK;
             int kslot_n = kslot + 1; if (kslot_n >= NK) kslot_n -= NK;
-            int vslot_f = vslot + AV; if (vslot_f >= NV) vslot_f -= NV;
-            int vslot_prev = vslot - 1; if (vslot_prev < 0) vslot_prev += NV;
+            const int vslot_f = vslot ^ AV, vslot_prev = (vslot - 1) & (NV - 1);
             const uint32_t e_cur = eq[0];
             const bool kS = (e_cur & mybit) != 0, kP = (e_prev & mybit) != 0;
             const u16 *Kt = Kb + kslot * TILE, *Kn = Kb + kslot_n * TILE;
             const u16 *Vt = Vb + vslot_prev * TILE;
             auto dma = [&]() INL {
-                if (jf < n) {
+                if (__builtin_expect(jf < n, 1)) {
                     rk[2] = rows_of((int)(e_f & BLKMASK));
                     fetch_k(rk[2], kslot_f);
                 }
-                if (j + AV < n) fetch_v(rk[0], vslot_f);
+                if (__builtin_expect(j + AV < n, 1)) fetch_v(rk[0], vslot_f);
             };
-            if (kP && kS) {
+            if (__builtin_expect(kP && kS, 1)) {
                 part(0, e_prev, Vt, Kt, Kn);
                 dma();
                 part(1, e_cur, Vt, Kt, Kn);
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             for (int b = 0; b + 1 < AK; ++b) eq[b] = eq[b + 1];
             eq[AK - 1] = e_f;
             kslot = kslot_n;
-            ++vslot; if (vslot >= NV) vslot = 0;
+            vslot = (vslot + 1) & (NV - 1);
         }
         // tail: the last block's second half and its O products.  The K ring is idle from here on, so the epilogue's
         // state fragments are fetched into it under these MFMAs.
