@@ -16,6 +16,8 @@
 // are reproducible run to run).
 #include "gate_part.h"
 
+#include <cmath>
+
 namespace salad {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -31,7 +33,14 @@ int state_tiles_per_chunk(int BH, int N, int target_wgs)
     int want = target_wgs / (BH > 0 ? BH : 1);
     if (want < 1) want = 1;
     if (want > tiles) want = tiles;
-    return (tiles + want - 1) / want;
+    // A chunk's partial state, written and read again, is as many bytes as two to four tiles of K and V (d = 64: one or two), and all of a
+    // head's are added up in the next launch, so a chunk of one tile costs more than it saves: with t us per tile and r per partial state
+    // the time tiles t + BH chunks r is least at sqrt(BH tiles r / t) tiles per chunk; r / t = 1/32 fits best (1/12 and 1/20 measured, too).
+    // Layer call: N = 1950, 12 heads 35.6 -> 34.4 us; N = 640 26.6 -> 25.0; N = 1280, 5 heads 26.6 -> 25.7; N = 720, 40 heads
+    // 38.0 -> 35.0; from N = 12480 on the other term decides, as before.
+    const int spread = (tiles + want - 1) / want;
+    const int least = (int)std::ceil(std::sqrt((double)BH * tiles / 32));
+    return spread > least ? spread : least < tiles ? least : tiles;
 }
 
 int state_num_chunks(int BH, int N, int target_wgs)
