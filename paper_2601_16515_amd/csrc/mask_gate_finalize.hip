@@ -114,8 +114,6 @@ __global__ __launch_bounds__(256) void gate_partial_wide_kernel(const void *x_t,
         partial[(size_t)b * nparts + blockIdx.x] = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
 }
 
-constexpr int GATE_MAX_PARTS = 512;
-
 int gate_num_parts(int N)
 {
     int parts = (N + 15) / 16;          // a workgroup step covers 16 tokens (4 waves x up to 4 tokens)

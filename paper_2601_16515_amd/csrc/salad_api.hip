@@ -523,6 +523,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     // gate is reduced first (finalize in gate-only form) and the later kernels skip the pruned samples.
     const bool dropping = use_linear && p->drop_threshold > 0.f;
     int32_t *drop = dropping ? (int32_t *)(ws + w.drop) : nullptr;
+    bool gate_here = false;                            // the attention kernel reduces the gate
     mark(0);
     if (use_linear) {
         // the gate's pass 1 rides in the state's launch, except where its result is needed first (dropping) or each stage is
@@ -571,7 +572,8 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
             e = launch_state_f32((const float *)p->k, (const float *)p->v, BH, p->N, p->d, (float *)(ws + w.Hs), (float *)(ws + w.Z), drop, p->H, st);
         if (e != hipSuccess) return give_back(), hip_fail(e, "state launch");
         mark(2);
-        if (bf16 || f.do_gate) {                       // fp32: the state kernel wrote Hs, Z directly
+        gate_here = !bf16 && !dropping && timing != 1;
+        if (!gate_here && (bf16 || f.do_gate)) {       // fp32: the state kernel wrote Hs, Z directly
             e = launch_finalize(f, st);
             if (e != hipSuccess) return give_back(), hip_fail(e, "finalize launch");
         }
@@ -596,6 +598,11 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     a.o_sparse_dbg = p->o_sparse_dbg; a.o_linear_dbg = unfused ? nullptr : p->o_linear_dbg;
     a.write_sparse_only = unfused;
     a.drop = drop;
+    if (gate_here) {
+        a.gate_here = 1; a.gate_nparts = need_gate ? w.nparts : 0;
+        a.gate_partial = (const float *)(ws + w.gate_partial); a.s_dev = p->s_dev; a.head_scale = p->head_scale;
+        a.lambda = p->lambda; a.s_out = p->s_out;
+    }
     a.variant = attn_variant;
     if (split) {
         a.sp_full = w.split.full; a.sp_pieces = w.split.pieces;

@@ -26,6 +26,7 @@ hipError_t launch_block_mask(const MaskArgs &a, hipStream_t st);
 // Pass 1: per-workgroup partial sums of sigmoid(x.w + b) -> partial[b * nparts + part].
 hipError_t launch_gate_partial(const void *x_t, const float *w, float bias, int B, int N, int D,
                                int is_bf16, float *partial, int nparts, hipStream_t st);
+constexpr int GATE_MAX_PARTS = 512;
 int gate_num_parts(int N);
 
 // ---- linear state (Eq. (3) sums) ----------------------------------------------------------------
@@ -118,6 +119,11 @@ struct AttnArgs {
     // in the low 4 bits, how many pieces have arrived; with any other tag in it (whatever the workspace held) none has.  At the end it is 0
     int sp_full, sp_pieces;
     uint64_t *sp_o, *sp_ml, *sp_count, sp_tag;
+    // fp32 kernel, gate_here: it reduces the gate (gate_nparts partial sums per sample, or none: s_dev) and scales by lambda, head_scale
+    // itself instead of reading coef, and writes s_out (may be null)
+    int gate_here, gate_nparts;
+    const float *gate_partial, *s_dev, *head_scale;
+    float lambda, *s_out;
     unsigned tiles_magic, heads_magic, pieces_magic;   // large-tile kernel: multiply-high inverses, filled in by its launcher
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };

@@ -424,6 +424,23 @@ def test_softmax_reference_is_the_first_block_maximum(second_half):
     assert float((got - want).abs().max()) < 1e-5
 
 
+@pytest.mark.parametrize("B,H,grid", [(2, 2, (1, 1, 7)), (1, 3, (5, 16, 51)), (2, 1, (5, 16, 52)), (1, 2, (7, 24, 49))])
+def test_fp32_gate_reduced_by_the_attention_kernel(B, H, grid):
+    """1 to 512 partial sums, around the 255 and 261 where a second one falls to the same place: the dynamic scale of the layer
+    call has the bits of the gate called alone, and a call that is given it the bits of the one that finds it."""
+    N, d = grid[0] * grid[1] * grid[2], 64
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda") for _ in range(3))
+    x, wg = torch.randn(B, N, H * d, generator=g, device="cuda"), torch.randn(H * d, generator=g, device="cuda") * 0.1
+    rp, ci = sb.salad_block_mask(*grid, 64, [1] * H)
+    hs, s = torch.rand(H, generator=g, device="cuda"), torch.full((B,), float("nan"), device="cuda")
+    kw = dict(lam=0.5, head_scale=hs, eps=1e-6)
+    out = sb.salad_sparse_linear_attn_fwd(q, k, v, grid, rp, ci, [h % 2 for h in range(H)], x_t=x, w_gate=wg, s_out=s, **kw)
+    alone = sb.salad_gate_fwd(x, wg)
+    given = sb.salad_sparse_linear_attn_fwd(q, k, v, grid, rp, ci, [h % 2 for h in range(H)], s=alone, **kw)
+    assert torch.equal(s, alone) and torch.equal(out, given)
+
+
 def test_fp32_infinite_value_in_the_last_row():
     """Keys past the end of the sequence do not exist: an infinite V element of the last token gives infinity in its channel
     and nothing anywhere else, whatever part of a 32-key unit the tail fills."""
