@@ -99,7 +99,7 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     w.base = off;       // what a call needs; the rest only makes it faster, and a workspace without room for it is taken
     // pieces of the large-tile kernel's last round (CSR masks): at most 256 of them (d = 64: 512)
     if (dtype == SALAD_BF16 && !topk && large_lists) w.split = split_plan((int)BH, (N + 63) / 64, d);
-    const size_t np = w.split.pieces > 1 ? (size_t)w.split.rest * w.split.pieces : 0;
+    const size_t np = w.split.cut ? (size_t)w.split.rest * w.split.pieces : 0;
     w.sp_o = off; off = align256(off + sizeof(float) * np * 256 * (size_t)d);
     w.sp_ml = off; off = align256(off + sizeof(uint64_t) * np * 512);
     w.sp_count = off; off = align256(off + sizeof(uint64_t) * (np ? (size_t)w.split.rest : 0));
@@ -543,7 +543,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         f.gate_partial = (const float *)(ws + w.gate_partial); f.nparts = need_gate ? w.nparts : 0; f.N = p->N;
         f.s_dev = p->s_dev; f.lambda = p->lambda; f.head_scale = p->head_scale;
         f.s_out = p->s_out; f.s_ws = (float *)(ws + w.s); f.coef = (float *)(ws + w.coef); f.do_gate = 1;
-        f.sp_count = (uint64_t *)(ws + w.sp_count); f.sp_tag = sp_tag; f.sp_n = split ? w.split.rest : 0;
+        f.sp_count = (uint64_t *)(ws + w.sp_count); f.sp_tag = sp_tag; f.sp_n = split && w.split.cut ? w.split.rest : 0;
         f.tau = p->drop_threshold; f.drop = drop; f.dropped_out = dropping ? p->dropped_out : nullptr;
         if (dropping) {
             FinalizeArgs fg = f;

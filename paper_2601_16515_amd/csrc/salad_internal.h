@@ -136,8 +136,9 @@ bool large_tile_list_fits(int d, int nb);
 // whether a bf16 call runs on the large-tile kernel (the only one whose fused epilogue knows the rotary linear branch): its list
 // fits, its 32-bit row offsets hold N rows, and where a head is temporal its multiply-high division by T is exact
 bool attn_takes_large_tile(int d, int nb, int N, int T, bool temporal, int variant);
-// how the large-tile kernel cuts the tiles of its last, partial round (BH sample-heads of nb blocks, width d); pieces < 2: not at all
-struct SplitPlan { int full, rest, pieces; };
+// how the large-tile kernel cuts the tiles of its last, partial round (BH sample-heads of nb blocks, width d); pieces < 2: not at all;
+// cut: lists may be long enough to be cut (which needs scratch), else only rows are dealt
+struct SplitPlan { int full, rest, pieces; bool cut; };
 SplitPlan split_plan(int BH, int nb, int d);
 hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int H, int nb, uint32_t *lists,
                              int32_t *counts, hipStream_t st);

@@ -224,7 +224,7 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 // so one pass of the 512 threads fetches a whole 64-row tile, the swizzles below take the row pair instead of the row
 // (rows 128 bytes apart alternate between the two halves of the banks), and every fragment count halves.
 // SPLIT (MODE 0 only): the tiles from a.sp_full on, which do not fill the chip, are cut along their visit lists into up to a.sp_pieces
-// workgroups each.  Every piece runs its own softmax over its entries, writes O, the reference and the row sum in fp32, and counts
+// workgroups each, or, where the list is too short for that, by rows into two.  Every piece runs its own softmax over its entries, writes O, the reference and the row sum in fp32, and counts
 // itself in; the piece that comes last reads the others back, combines all in piece order (so the result does not depend on which
 // it was) and goes on to the epilogue.  Nobody waits for anybody.
 // QS: sets of 32 queries that a wave owns.  With 2 every operand fragment read from LDS feeds two products, which halves the energy
@@ -292,14 +292,26 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the list straight into LDS, and, as soon as the first entries are there, the first blocks.  Before, list and queries came first, through
     // registers, and the blocks after a barrier.  Layer call: N = 1950 36.5 -> 35.6 us, N = 640 25.6 -> 24.1, Top-K at N = 32760
     // (13 entries) 1069 -> 1052, 24 heads of 64 at 90 % 723 -> 717; 12 heads of 128 at 90 % the same (at the power limit a wait costs little).
+    // A list too short to be cut: two workgroups take two of the tile's rows each.  All waves fetch, but with one computing wave per SIMD
+    // an iteration is 2100 cycles long instead of 2900.  N = 1950, 12 heads, 11 entries 33.7 -> 29.8 us; N = 1280, 5 heads 25.2 -> 22.4; 12 heads of 64
+    // 22.1 -> 20.2.  Not with two sets of queries a wave: the two workgroups of a compute unit are one computing wave per SIMD each as it is.
+    constexpr bool ROW_PAIRS = SPLIT && QS == 1;
+    int my_rows = -1;                            // ROW_PAIRS: which two, or all
     const int g_blk0 = g_J * a.g_bpb;
     const uint32_t *src = GATHER ? nullptr : a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
     if (SPLIT && pieces > 1) {
-        pieces = min(pieces, max(1, n / SPLIT_MIN_ENTRIES));
-        if (piece >= pieces) return;
-        list0 = n * piece / pieces;      // this piece's first entry
-        n = n * (piece + 1) / pieces - list0;
+        const int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
+        if (by_length > 1) {
+            pieces = by_length;
+            if (piece >= pieces) return;
+            list0 = n * piece / pieces;      // this piece's first entry
+            n = n * (piece + 1) / pieces - list0;
+        } else {                             // too short to be cut
+            pieces = 1;
+            if (piece >= (ROW_PAIRS ? 2 : 1)) return;
+            if (ROW_PAIRS) my_rows = piece;
+        }
     }
     constexpr int AK = NK - 1, AV = NV - 2;     // how far ahead of an iteration K and V are fetched
     uint32_t eq[AK];                             // entries j .. j+3 of iteration j; the first one's past the end of the list
@@ -323,9 +335,11 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             g_slot[u] = (size_t)bh * N * a.g_kk + g_slot0 + (qvalid[u] ? qi : 0);
             qrow[u] = 0;
         } else {
-            mybit |= qblk < nb ? (1u << (24 + (TOPK ? unit : unit >> 1))) : 0u;
+            const bool active = !ROW_PAIRS || my_rows < 0 || my_rows == unit >> 2;
+            mybit |= qblk < nb && active ? (1u << (24 + (TOPK ? unit : unit >> 1))) : 0u;
             qvalid[u] = (qblk < nb) && (qpos < N);
             qrow[u] = row_of_position5(kind, qvalid[u] ? qpos : N - 1, T, HW, magic);
+            if (ROW_PAIRS) qvalid[u] = qvalid[u] && active;
         }
         if (TOPK && qvalid[u]) {
             const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow[u]];
@@ -920,6 +934,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 }
         }
     }
+    if (ROW_PAIRS && my_rows >= 0 && mybit == 0u) return;      // a wave of the other rows, no barrier follows
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
     const int unit = wave * QS + u;
@@ -1028,7 +1043,8 @@ SplitPlan split_plan(int BH, int nb, int d)
     p.rest = (int)(total - p.full);
     p.pieces = p.rest ? round / p.rest : 1;
     if (p.pieces > SPLIT_MAX_PIECES) p.pieces = SPLIT_MAX_PIECES;
-    if (nb < 2 * SPLIT_MIN_ENTRIES) p.pieces = 1;             // no list of this length is cut
+    p.cut = p.pieces > 1 && nb >= 2 * SPLIT_MIN_ENTRIES;
+    if (!p.cut) p.pieces = p.pieces > 1 && round == 256 ? 2 : 1;      // no list of this length is cut, but rows can be dealt to two workgroups
     return p;
 }
 

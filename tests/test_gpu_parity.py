@@ -281,6 +281,24 @@ def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     assert errors(outs[0.0].double().cpu().numpy(), res["o_sparse"])[1] < 4e-3      # one bf16 rounding (2^-9) of each value
 
 
+@pytest.mark.parametrize("B,H,d,grid,keep", [
+    (1, 2, 128, (1, 1, 40), 1),       # one row of 40 tokens: the second workgroup of the tile has no rows
+    (1, 3, 64, (2, 7, 9), 2),         # 2 rows, the second of 62 tokens
+    (2, 3, 128, (3, 5, 13), 3),       # 4 rows, the last of 3 tokens: alone in its workgroup with the third
+    (1, 12, 128, (5, 15, 26), 8),     # 31 rows, lists of 8 to 11 entries: not cut, though longer ones would be
+    (1, 4, 64, (3, 13, 14), 9),       # all of 9 blocks
+    (3, 43, 128, (3, 16, 17), 3),     # 512 whole tiles, four dealt by rows
+])
+def test_rows_of_a_tile_dealt_to_two_workgroups(oracle, B, H, d, grid, keep):
+    """Tiles beyond a full round whose lists are too short to be cut; both head orders."""
+    w = wl.small(f"rows-{d}-{grid}", B, H, d, *grid, "bf16", 0.5, seed=970 + H)
+    inp = wl.make_inputs(w)
+    kinds, kept = wl.head_kinds(w), [keep] * H
+    ref = _oracle_layer(oracle, w, inp, kept, kinds)
+    for dbg in (True, False):
+        compare_layer(run_layer(w, inp, upload(w, inp), kept, kinds, dbg=dbg), ref, label=w.name)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_cut_tiles_with_the_options_of_the_call(oracle, d):
     """Lists that are cut (18 and 13 to 16 entries: 3 and 2 pieces) together with what the call can be asked for: branch dropping,
