@@ -596,7 +596,12 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     a.coef = use_linear ? (const float *)(ws + w.coef) : nullptr;
     a.eps = p->eps;
     a.o_sparse_dbg = p->o_sparse_dbg; a.o_linear_dbg = unfused ? nullptr : p->o_linear_dbg;
-    a.write_sparse_only = unfused;
+    // full projection: the attention kernel's epilogue writes O_l, in the projection's operand order, next to O_s.  A pass of its own over Q
+    // took 51-55 us at N = 32760, 12 heads: layer call 872 -> 849 us.
+    const bool emit_in_attn = full_proj && large_tile && !topk && !rope && !p->o_sparse_dbg && !p->o_linear_dbg &&
+                              !(p->flags & SALAD_FLAG_UNFUSED_EPILOGUE);
+    a.write_sparse_only = unfused && !emit_in_attn;
+    a.emit_ol = emit_in_attn ? (u16 *)(ws + w.ol) : nullptr;
     a.drop = drop;
     if (gate_here) {
         a.gate_here = 1; a.gate_nparts = need_gate ? w.nparts : 0;
@@ -679,8 +684,10 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
             ap.m_po = a.g_po; ap.m_lse = a.g_lse; ap.m_slot_of = (const int32_t *)(ws + w.g_slot);
             ap.m_mask = a.topk_mask; ap.m_kk = a.g_kk;
         }
-        e = launch_linear_apply_bf16(ap, st);
-        if (e != hipSuccess) return give_back(), hip_fail(e, "linear apply launch");
+        if (!emit_in_attn) {
+            e = launch_linear_apply_bf16(ap, st);
+            if (e != hipSuccess) return give_back(), hip_fail(e, "linear apply launch");
+        }
         mark(5);
         if (full_proj) {
             // Alg. 1 "Proj" as one GEMM over the concatenated heads, fused with the residual sum

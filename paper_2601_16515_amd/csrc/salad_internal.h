@@ -93,6 +93,7 @@ struct AttnArgs {
     const float *coef;              // [BH]
     float eps;
     float *o_sparse_dbg, *o_linear_dbg;
+    u16 *emit_ol;                   // large-tile kernel, d = 128, block lists, no debug outputs: where O_l goes for the full projection, or null
     int write_sparse_only;          // bf16: store O_s (rounded) to out and skip the linear part
     unsigned t_magic;               // floor(2^32 / T) + 1 when N * T < 2^32, else 0
     // per (head, 4-query-block tile): ascending union of the 4 CSR rows, entry = block | keep-mask << 24

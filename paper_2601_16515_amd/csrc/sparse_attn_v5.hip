@@ -232,7 +232,8 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 // barriers are independent: B = 1, N = 32760, 24 heads at 90 % 832 -> 725 us, dense N = 12480 1119 -> 1005; while there is one tile per CU
 // or less the 4 waves alone are slower (N = 1950, 24 heads 28.4 -> 30.9).  At d = 128 it needs 400 registers, so one wave per SIMD, and
 // the loads, which hold a wave for 60 cycles each, and the scalar code have nothing to run under: dense 5421 -> 5564 us.
-template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, int QS = 1>
+// EMIT (d = 128, MODE 0 without ROPE and DBG): the linear branch goes, unscaled, to a.emit_ol instead of being added to O_s.
+template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, int QS = 1, bool EMIT = false>
 __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
 {
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
@@ -972,7 +973,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     const float os = o[u][dt][g4 * 4 + t] * inv_l;
-                    ov[t] = lin ? fmaf(num[dt][g4 * 4 + t], lin_scale[u], os) : os;
+                    ov[t] = lin && !EMIT ? fmaf(num[dt][g4 * 4 + t], lin_scale[u], os) : os;
                 }
                 uint2 pk;
                 pk.x = pack2e(ov[0], ov[1]);
@@ -991,6 +992,28 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * ROWB + ((c16 ^ oswz(r)) << 4));
             const int dest = __shfl(dest_mine, r);
             if (dest >= 0) *reinterpret_cast<uint4 *>(dbase + (size_t)dest * D + c16 * 8) = v;
+        }
+        if (EMIT && lin) {
+            // the unscaled linear branch, for the full projection: through the same staging into 16-byte pieces of the lane's own row, the
+            // order that the projection's operand wants (blocks of 32 stored rows x 128 channels, piece c of row r at
+            // (c / 2 * 64 + c % 2 * 32 + r) * 16 bytes; whole kilobytes for a head in the stored order)
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    uint2 pk;
+                    pk.x = pack2e(num[dt][g4 * 4] * inv_den[u], num[dt][g4 * 4 + 1] * inv_den[u]);
+                    pk.y = pack2e(num[dt][g4 * 4 + 2] * inv_den[u], num[dt][g4 * 4 + 3] * inv_den[u]);
+                    *reinterpret_cast<uint2 *>(stg + l32 * ROWB + (((dt * 4 + g4) ^ oswz(l32)) << 4) + hh * 8) = pk;
+                }
+            asm volatile("" ::: "memory");
+            u16 *blk = a.emit_ol + ((((size_t)smp * ((N + 31) >> 5) + (qrow[u] >> 5)) * a.H + h) << 12) + (hh * 32 + (qrow[u] & 31)) * 8;
+#pragma unroll
+            for (int i = 0; i < CH / 2; ++i) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(stg + l32 * ROWB + (((2 * i + hh) ^ oswz(l32)) << 4));
+                if (qvalid[u]) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
+            }
         }
         if (GATHER && qvalid[u] && hh == 0) a.g_lse[g_slot[u]] = l_tot > 0.f ? m_run[u] + log2f(l_tot) : -INFINITY;
     } else if (qvalid[u]) {
@@ -1048,7 +1071,7 @@ SplitPlan split_plan(int BH, int nb, int d)
     return p;
 }
 
-template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false, int QS = 1>
+template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false, int QS = 1, bool EMIT = false>
 static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
 {
     const int ntiles = (a.nb + 3) / 4;
@@ -1057,7 +1080,7 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     if (!large_tile_list_fits(D, a.nb)) return hipErrorInvalidValue;
     const int list_cap = tile_list_cap(a.nb);
     const size_t lds = v5_ring_bytes(D) + (size_t)list_cap * 4;
-    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT, QS>;
+    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT, QS, EMIT>;
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), V5_MAX_DYN, attr_done); e != hipSuccess) return e;
     const int grid = SPLIT ? a.sp_full + ((total - a.sp_full) * a.sp_pieces + 7) / 8 * 8 : per_xcd * 8;
@@ -1082,6 +1105,10 @@ hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st)
     }
     if (a.g_desc) return launch_v5<false, 2>(a, st);
     if (a.topk_mask) return dbg ? launch_v5<true, 1>(a, st) : launch_v5<false, 1>(a, st);
+    if (a.emit_ol) {
+        if (dbg || a.rope_tab) return hipErrorInvalidValue;
+        return split ? launch_v5<false, 0, false, 128, true, 1, true>(a, st) : launch_v5<false, 0, false, 128, false, 1, true>(a, st);
+    }
     if (split && a.rope_tab) return dbg ? launch_v5<true, 0, true, 128, true>(a, st) : launch_v5<false, 0, true, 128, true>(a, st);
     if (split) return dbg ? launch_v5<true, 0, false, 128, true>(a, st) : launch_v5<false, 0, false, 128, true>(a, st);
     if (a.rope_tab) return dbg ? launch_v5<true, 0, true>(a, st) : launch_v5<false, 0, true>(a, st);

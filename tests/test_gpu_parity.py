@@ -978,6 +978,33 @@ def test_full_projection(oracle, w):
     assert res_dr["dropped"].tolist() == [1, 1] and torch.equal(res_dr["out_t"], sparse_only)
 
 
+@pytest.mark.parametrize("B,H,grid,keep", [
+    (1, 2, (1, 1, 40), 1),            # a block of 32 rows and one of 8
+    (2, 3, (3, 5, 13), 3),            # 195 rows, tiles dealt by rows, two samples
+    (1, 4, (5, 15, 26), 31),          # 1950 rows, tiles cut along their lists
+    (1, 13, (21, 12, 20), 8),    # 5040 rows, 260 tiles: whole ones and dealt ones
+])
+def test_full_projection_input_from_the_attention_epilogue(oracle, B, H, grid, keep):
+    """Without debug outputs the attention kernel itself writes the projection's operand: both head orders, ragged last blocks,
+    whole, cut and dealt tiles against the oracle; a pruned sample stays the sparse branch bit for bit."""
+    w = wl.small(f"emit-{B}-{H}-{grid}", B, H, 128, *grid, "bf16", 0.5, seed=130 + H)
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    kinds, kept, D = wl.head_kinds(w), [keep] * H, H * 128
+    wp = wl.round_to_bf16((wl.normal(131, "w_proj", (D, D)) / np.sqrt(D)).astype(np.float32))
+    wp_dev = torch.from_numpy(wp).cuda().to(torch.bfloat16)
+    # lambda 5: outputs stay below 2 in magnitude, where the two bf16 roundings are at most 2 x 2^-8 = 0.8e-2 of the 2e-2 bar; with 25
+    # those of the first shape reach 6.7, where one rounding alone can take 2^-6 = 1.6e-2
+    lam = 5.0
+    sel = None if w.nb <= 31 else list(range(0, w.nb, 9)) + [w.nb - 1]
+    ref = _oracle_layer(oracle, w, inp, kept, kinds, sel=sel, lam=lam, w_proj=wp.astype(np.float64))
+    res = run_layer(w, inp, dev, kept, kinds, lam=lam, head_scale=None, w_proj=wp_dev, dbg=False)
+    assert np.abs(ref["out"][ref["rows"] >= 0]).max() < 2
+    compare_layer(res, ref, check_linear=False, label=w.name)
+    pruned = run_layer(w, inp, dev, kept, kinds, lam=lam, head_scale=None, w_proj=wp_dev, dbg=False, drop_threshold=2.0)
+    assert torch.equal(pruned["out_t"], run_layer(w, inp, dev, kept, kinds, lam=0.0, dbg=False)["out_t"])
+
+
 @pytest.mark.parametrize("variant", [0, 1], ids=["regrouped", "token-mask"])
 @pytest.mark.parametrize("wi,key_block,topk", [(1, 64, 4), (7, 128, 2), (0, 64, 8), (6, 64, 1), (4, 64, 3)],
                          ids=["N693-B2-kb64-k4", "N1170-kb128-k2", "N270-all-blocks", "single-token", "N512-k3"])
