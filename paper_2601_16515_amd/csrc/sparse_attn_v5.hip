@@ -293,9 +293,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the list straight into LDS, and, as soon as the first entries are there, the first blocks.  Before, list and queries came first, through
     // registers, and the blocks after a barrier.  Layer call: N = 1950 36.5 -> 35.6 us, N = 640 25.6 -> 24.1, Top-K at N = 32760
     // (13 entries) 1069 -> 1052, 24 heads of 64 at 90 % 723 -> 717; 12 heads of 128 at 90 % the same (at the power limit a wait costs little).
-    // A list too short to be cut: two workgroups take two of the tile's rows each.  All waves fetch, but with one computing wave per SIMD
+    // Where a list is not worth cutting, two workgroups take two of the tile's rows each.  All waves fetch, but with one computing wave per SIMD
     // an iteration is 2100 cycles long instead of 2900.  N = 1950, 12 heads, 11 entries 33.7 -> 29.8 us; N = 1280, 5 heads 25.2 -> 22.4; 12 heads of 64
-    // 22.1 -> 20.2.  Not with two sets of queries a wave: the two workgroups of a compute unit are one computing wave per SIMD each as it is.
+    // 22.1 -> 20.2.  Cutting in p costs 19000 cycles (scratch, merge; d = 64: 12000), so it takes n 2900 / p + 19000 < n 2100: two pieces
+    // from 30 entries on (d = 64: 19), three always.  12 entries 35.5 (cut in two) -> 30.6 us, 17 entries 39.5 -> 35.6; 25 entries 42.8 (rows) -> 38.8 (cut in four).  Not with two sets of queries a wave: the two workgroups of a compute unit are one computing wave per SIMD each as it is.
     constexpr bool ROW_PAIRS = SPLIT && QS == 1;
     int my_rows = -1;                            // ROW_PAIRS: which two, or all
     const int g_blk0 = g_J * a.g_bpb;
@@ -303,12 +304,12 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
     if (SPLIT && pieces > 1) {
         const int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
-        if (by_length > 1) {
+        if (by_length > 1 && (!ROW_PAIRS || n * (21 * by_length - 29) > (D == 64 ? 120 : 190) * by_length)) {
             pieces = by_length;
             if (piece >= pieces) return;
             list0 = n * piece / pieces;      // this piece's first entry
             n = n * (piece + 1) / pieces - list0;
-        } else {                             // too short to be cut
+        } else {                             // not worth cutting
             pieces = 1;
             if (piece >= (ROW_PAIRS ? 2 : 1)) return;
             if (ROW_PAIRS) my_rows = piece;

@@ -285,7 +285,10 @@ def test_last_round_cut_into_pieces(oracle, B, H, d, grid, kept):
     (1, 2, 128, (1, 1, 40), 1),       # one row of 40 tokens: the second workgroup of the tile has no rows
     (1, 3, 64, (2, 7, 9), 2),         # 2 rows, the second of 62 tokens
     (2, 3, 128, (3, 5, 13), 3),       # 4 rows, the last of 3 tokens: alone in its workgroup with the third
-    (1, 12, 128, (5, 15, 26), 8),     # 31 rows, lists of 8 to 11 entries: not cut, though longer ones would be
+    (1, 12, 128, (5, 15, 26), 8),     # 31 rows, lists of 8 to 11 entries
+    (1, 12, 128, (5, 15, 26), 25),    # lists of 25 to 28: two pieces would not pay
+    (1, 4, 128, (5, 15, 26), 9),      # lists of 9 to 12: room for 8 pieces, worth 2
+    (1, 12, 128, (5, 15, 26), 31),    # lists of 31: two pieces do pay
     (1, 4, 64, (3, 13, 14), 9),       # all of 9 blocks
     (3, 43, 128, (3, 16, 17), 3),     # 512 whole tiles, four dealt by rows
 ])
