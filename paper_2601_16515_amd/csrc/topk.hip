@@ -17,8 +17,9 @@ constexpr int D = 128;
 
 // grid (nbk, BH), 64 threads: thread c sums channels 2 c and 2 c + 1 of the block's keys in the order of the head's positions
 // (App. A.1.1: position p of a temporal head is stored row (p mod T) HW + p div T; a spatial head's is row p).
-// A read of K: what counts is the bytes in flight, 64 rows or 16 KB per workgroup.  With 16 rows of 2-byte loads it took 55.9 us at
-// N = 32760, 12 heads, 40 key blocks, now 40.5 (100 MB; with 128 rows 41.0).
+// A read of K by 480 single waves: what counts is the bytes in flight, 64 rows or 16 KB each, and few instructions per row, so a row
+// number is one lane's and is read from it (stepping the position row by row took 37.6 us).  At N = 32760, 12 heads, 40 key blocks
+// 21.3 us for either order = 4.7 TB/s; with 16 rows of 2-byte loads in flight 29.2 us spatial and 52.7 temporal.
 __global__ __launch_bounds__(64) void kblock_mean_kernel(const u16 *__restrict__ k, int N, int key_block, int nbk,
                                                          float *__restrict__ means, unsigned long long kind_mask, int H,
                                                          int T, int HW)
@@ -26,19 +27,16 @@ __global__ __launch_bounds__(64) void kblock_mean_kernel(const u16 *__restrict__
     const int J = blockIdx.x, bh = blockIdx.y, c = threadIdx.x;
     const int t0 = J * key_block, t1 = min(N, t0 + key_block);
     const bool temporal = T > 1 && ((kind_mask >> (bh % H)) & 1ull);
-    // position p = loc T + f (location loc, frame f) is stored row f HW + loc; the pair is stepped, not divided (spatial: one frame)
-    const int frames = temporal ? T : 1, step = temporal ? HW : 0;
-    int loc = t0 / frames, f = t0 - loc * frames;
-    const u16 *base = k + (size_t)bh * N * D;
+    // position p = loc T + f (location loc, frame f) is stored row f HW + loc (spatial: one frame): lane c holds it for position t + c
+    const int frames = temporal ? T : 1, step = temporal ? HW : 0, df = 64 % frames, dloc = 64 / frames;
+    int loc = (t0 + c) / frames, f = t0 + c - loc * frames;
+    const uint32_t *base = reinterpret_cast<const uint32_t *>(k + (size_t)bh * N * D);
     float s0 = 0.f, s1 = 0.f;
-    auto add_rows = [&](auto count) __attribute__((always_inline)) {
+    auto add_rows = [&](auto count, int row, int first) __attribute__((always_inline)) {
         constexpr int U = decltype(count)::value;
         uint32_t x[U];
 #pragma unroll
-        for (int i = 0; i < U; ++i) {
-            x[i] = reinterpret_cast<const uint32_t *>(base + (size_t)(f * step + loc) * D)[c];
-            if (++f == frames) { f = 0; ++loc; }
-        }
+        for (int i = 0; i < U; ++i) x[i] = (base + (size_t)__builtin_amdgcn_readlane(row, first + i) * (D / 2))[c];
 #pragma unroll
         for (int i = 0; i < U; ++i) {
             s0 = __fadd_rn(s0, __uint_as_float(x[i] << 16));
@@ -46,9 +44,16 @@ __global__ __launch_bounds__(64) void kblock_mean_kernel(const u16 *__restrict__
         }
     };
     int t = t0;
-    for (; t + 64 <= t1; t += 64) add_rows(std::integral_constant<int, 64>{});
-    for (; t + 8 <= t1; t += 8) add_rows(std::integral_constant<int, 8>{});
-    for (; t < t1; ++t) add_rows(std::integral_constant<int, 1>{});
+    for (; t + 64 <= t1; t += 64) {
+        add_rows(std::integral_constant<int, 64>{}, f * step + loc, 0);
+        f += df;
+        loc += dloc;
+        if (f >= frames) { f -= frames; ++loc; }
+    }
+    const int row = f * step + loc;
+    int i = 0;
+    for (; t + i + 8 <= t1; i += 8) add_rows(std::integral_constant<int, 8>{}, row, i);
+    for (; t + i < t1; ++i) add_rows(std::integral_constant<int, 1>{}, row, i);
     float2 *out = reinterpret_cast<float2 *>(means + ((size_t)bh * nbk + J) * D);
     out[c] = make_float2(__fdiv_rn(s0, (float)(t1 - t0)), __fdiv_rn(s1, (float)(t1 - t0)));
 }

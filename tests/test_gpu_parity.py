@@ -1125,6 +1125,22 @@ def test_wan13_480p_rotary_sampled(oracle):
     assert np.isfinite(res["out"]).all()
 
 
+@pytest.mark.parametrize("grid,key_block", [((70, 2, 3), 192), ((64, 3, 5), 320), ((21, 5, 6), 192), ((2, 15, 17), 128)],
+                         ids=["frames-over-64-tail36", "64-frames", "21-frames-tail54", "2-frames-tail126"])
+def test_topk_means_walk_the_temporal_order(oracle, grid, key_block):
+    """Mean keys over several steps of 64 positions, where the frame count is above, equal to and below the step, with last
+    key blocks whose remainder goes by eights and ones; the selection turns on every bit of the means, so masks are exact."""
+    w = wl.small("topk-means", 1, 2, 128, *grid, "bf16", 0.5, seed=307)
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    kinds = np.array([0, 1], dtype=np.uint8)
+    kept = [1] * w.H
+    ref = _oracle_layer(oracle, w, inp, kept, kinds, topk=1, key_block=key_block)
+    res = run_layer(w, inp, dev, kept, kinds, topk=1, topk_key_block=key_block)
+    assert np.array_equal(res["topk_mask"], ref["topk_mask"])
+    compare_layer(res, ref, label=f"topk-means-T{w.T}")
+
+
 @pytest.mark.parametrize("grid,key_block,topk", [((10, 10, 20), 64, 5), ((10, 20, 20), 64, 4), ((7, 11, 13), 192, 6),
                                                  ((16, 16, 16), 64, 8), ((4, 33, 31), 64, 8)],
                          ids=["32-key-blocks-k5", "63-key-blocks-k4", "6-key-blocks-k6-all", "64-key-blocks-k8",
