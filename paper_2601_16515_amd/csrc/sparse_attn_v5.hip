@@ -4,17 +4,16 @@
 //   * One workgroup = 8 waves = 256 query positions = 4 CSR rows of one (batch, head); one workgroup
 //     per CU (LDS: 5 K + 4 V tiles of 16 KB plus the block list).  d = 64, where the tiles are 8 KB: two workgroups of 4 waves
 //     per CU, a wave owning 64 queries, if there are tiles for both (QS below).
-//   * The ascending union of the 4 rows' kept-block lists is built once per workgroup in LDS (bitmap +
-//     ballot compaction), each entry carrying a 4-bit "kept by query block i" mask.  The main loop
-//     reads one entry per iteration from LDS; no global or scalar load sits on its critical path.
+//   * The union of the 4 rows' kept-block lists comes from a pre-pass (tile_lists_kernel), each entry carrying a 4-bit "kept by
+//     query block i" mask, and is copied to LDS; no global or scalar load sits on the main loop's critical path.
 //   * K and V tiles go straight from global memory into two rings of LDS slots, K four and V two blocks ahead
 //     (global_load_lds_dwordx4, bank swizzle applied on the global side).  The wait before the
 //     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
 //     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's
-//     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).  Before, the waves of a SIMD took turns, one multiplying while the other did its softmax, which left the
-//     softmax partly exposed.  B = 1, N = 32760, layer call: 24 heads of 64 at 90 % 917 -> 863 us; 12 heads of 128 dense
+//     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).  Before, the
+//     waves of a SIMD took turns, one multiplying while the other did its softmax, which left the softmax partly exposed.  B = 1, N = 32760, layer call: 24 heads of 64 at 90 % 917 -> 863 us; 12 heads of 128 dense
 //     5921 -> 5842 us, at 90 % 702 -> 699 us: at d = 128 the cycles fall by 5 % and the clock, which the power limit
 //     sets (1.95 -> 1.89 GHz on the dense call), takes most of it back.
 //   * What bounds the loop is the energy of its instructions: the chip is at its power limit, and fewer cycles for the same
@@ -221,11 +220,10 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 //   (2p, 2p+1) of the query's stored row n by the angle word a.rope_tab[n * 64 + p] = fp16 cos | fp16 sin << 16) after
 //   the normaliser has been taken from the unrotated features.
 // D = 64 (MODE 0 without ROPE only): the same kernel on half-size tiles.  A row is 8 chunks of 16 bytes instead of 16,
-// so one pass of the 512 threads fetches a whole 64-row tile, the swizzles below take the row pair instead of the row
-// (rows 128 bytes apart alternate between the two halves of the banks), and every fragment count halves.
+// so a tile is half as many 1 KB pieces, and every fragment count halves.
 // SPLIT (MODE 0 only): the tiles from a.sp_full on, which do not fill the chip, are cut along their visit lists into up to a.sp_pieces
-// workgroups each, or, where the list is too short for that, by rows into two.  Every piece runs its own softmax over its entries, writes O, the reference and the row sum in fp32, and counts
-// itself in; the piece that comes last reads the others back, combines all in piece order (so the result does not depend on which
+// workgroups each, or, where that does not pay, by rows into two.  Every piece runs its own softmax over its entries, writes O, the
+// reference and the row sum in fp32, and counts itself in; the piece that comes last reads the others back, combines all in piece order (so the result does not depend on which
 // it was) and goes on to the epilogue.  Nobody waits for anybody.
 // QS: sets of 32 queries that a wave owns.  With 2 every operand fragment read from LDS feeds two products, which halves the energy
 // of the reads, and a workgroup has half the waves.  d = 64 has the registers for it and LDS for two such workgroups per CU, whose
