@@ -540,21 +540,25 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // counts, so that a row's first reference is the maximum of 64 keys, whose weight is then exactly 1 (keys past the sequence
     // end need no mask here: their K rows are copies of the last one, which is in the block).
     // With the maximum of the first 32 keys alone the error against 64 bits is up to 3 % larger (N = 1170, 95 %: 2.08e-3 -> 2.14e-3).
+    // The sums are products over 32 lanes, so the way here is the whole wave's, and what differs between lanes is selected, not branched on
+    // (TOPK: a lane that did not select the entry keeps its reference and adds nothing, whatever the product put into its sum).
     auto settle = [&](int hf, bool whole, bool started, uint32_t e, const float (&ps)[QS]) INL {
         float psum[QS];
-        bool redo[QS], any = false;
+        bool risen[QS], redo[QS], any = false;
 #pragma unroll
         for (int u = 0; u < QS; ++u) {
-            const bool sel = selected(u, e);
             psum[u] = ps[u];
-            redo[u] = !started && sel && !have_ref[u];
-            redo[u] = redo[u] || (__any(!(psum[u] <= 8192.f)) && sel);
+            redo[u] = !started && !have_ref[u];
+            if (TOPK) redo[u] = __any(selected(u, e) && redo[u]);
+            risen[u] = __any(!(psum[u] <= 8192.f));
+            redo[u] = redo[u] || risen[u];
             any = any || redo[u];
         }
         if (__builtin_expect(any, 0)) {
 #pragma unroll
             for (int u = 0; u < QS; ++u)
                 if (redo[u]) {
+                    const bool known = started || have_ref[u], moves = !TOPK || (selected(u, e) && (risen[u] || !known));
                     float mx = s[u][hf][0];
 #pragma unroll
                     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][hf][r]);
@@ -562,9 +566,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
                         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][1][r]);
                     mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run[u]);   // maximum minus reference
-                    const float shift = started || have_ref[u] ? fmaxf(mx, 0.f) : mx;   // new reference minus old reference
-                    if (started || have_ref[u]) {
-                        const float alpha = __builtin_amdgcn_exp2f(-shift);
+                    const float shift = !moves ? 0.f : known ? fmaxf(mx, 0.f) : mx;   // new reference minus old reference
+                    if (TOPK || known) {
+                        const float alpha = TOPK && !known ? 1.f : __builtin_amdgcn_exp2f(-shift);
                         l_run[u] *= alpha;
 #pragma unroll
                         for (int i = 0; i < NDT; ++i)
@@ -572,12 +576,12 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                             for (int r = 0; r < 16; ++r) o[u][i][r] *= alpha;
                     }
                     m_run[u] += shift;
-                    have_ref[u] = true;
+                    have_ref[u] = moves || have_ref[u];
                     psum[u] = exp_pack(u, hf, selected(u, e));
                 }
         }
 #pragma unroll
-        for (int u = 0; u < QS; ++u) l_run[u] += psum[u];
+        for (int u = 0; u < QS; ++u) l_run[u] += !TOPK || selected(u, e) ? psum[u] : 0.f;
     };
     // one part: S of half pt of the current block, O of half pt of the previous block, softmax of the other half in flight
     // (pt 0: the previous block's second half, pt 1: the current block's first half; entry e)

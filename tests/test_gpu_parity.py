@@ -1037,6 +1037,31 @@ def test_topk_mask_layer(oracle, topk_variant, wi, key_block, topk, variant):
         assert errors(res["out"], dense["out"])[1] < 5e-3   # two independently rounded bf16 results
 
 
+def test_token_mask_rows_beside_a_row_out_of_range(oracle, topk_variant):
+    """Before a query has a softmax reference, logits 150 to 300 binades above 0 make its first sum infinite; the queries next to it
+    in the wave did not select that block and must not notice.  Neighbours take different blocks, whose keys point along a
+    channel of their own; the same call on the regrouped path, which never has both in one tile."""
+    w = wl.small("beside", 2, 2, 128, 4, 12, 16, "bf16", 0.5, seed=645)      # N = 768: 12 blocks
+    inp = wl.make_inputs(w)
+    blk = np.arange(w.N) // 64
+    inp["k"] = inp["k"] * np.float32(0.25)
+    inp["k"][:, :, np.arange(w.N), blk] += 32 + 4.0 * (blk % 3)
+    for i in range(2):                                     # two blocks of its own for every query, others for the next 15 and for the one 16 on
+        inp["q"][:, :, np.arange(w.N), (np.arange(w.N) % 16 + np.arange(w.N) // 16 * 3 + 5 * i) % w.nb] += 48 - 8 * i
+    for t in ("q", "k"):
+        inp[t] = wl.round_to_bf16(inp[t].astype(np.float32))
+    inp["v"] = inp["v"] * np.float32(0.25)                 # two bf16 roundings of values up to 4.5 would take the absolute bar; exact in bf16
+    dev = upload(w, inp)
+    kinds = np.zeros(w.H, dtype=np.uint8)
+    ref = _oracle_layer(oracle, w, inp, [1] * w.H, kinds, topk=2, key_block=64)
+    for variant in (0, 1):
+        topk_variant(variant)
+        for dbg in (True, False):
+            res = run_layer(w, inp, dev, [1] * w.H, kinds, topk=2, topk_key_block=64, dbg=dbg)
+            assert np.array_equal(res["topk_mask"], ref["topk_mask"])
+            compare_layer(res, ref, label=f"variant {variant}")
+
+
 @pytest.mark.parametrize("wi,key_block,topk", [(1, 64, 4), (7, 128, 2), (5, 64, 3), (0, 64, 2)],
                          ids=["N693-B2-kb64-k4", "N1170-kb128-k2", "T70-gt-block-k3", "N270-tail14-k2"])
 def test_topk_mask_temporal_heads(oracle, wi, key_block, topk):
