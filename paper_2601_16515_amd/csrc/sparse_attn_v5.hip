@@ -523,6 +523,28 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     asm volatile("" : "+v"(pick.w[0]), "+v"(pick.w[1]), "+v"(pick.w[2]), "+v"(pick.w[3]));
     auto row_sum = [&](int u, int i, f32x4 acc) INL -> f32x4 { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, pf[u][i].v, acc, 0, 0, 0); };
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    // The same for both pieces of a half, with the same bits, but each row by itself: in row_sum a probability that is not finite (a NaN or an
+    // infinity in a query, a logit far above the reference) times the zeros that part the rows makes the sum 16 lanes away a NaN as well.
+    auto sums_apart = [&](int u, int hf) INL -> float {
+        int l = lane;
+        asm volatile("" : "+v"(l));                  // else the two masks live in registers all through the loop
+        const uint32_t odd = (uint32_t)((int)((unsigned)l << 27) >> 31);       // all ones for the rows 16 .. 31
+        uint32_t sum = 0u;
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {       // the rows of the other side are zeros here
+            const uint32_t mine = side ? odd : ~odd;
+            f32x4 acc = zero4;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                Frag5 p;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) p.w[j] = pf[u][hf * 2 + i].w[j] & mine;
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, p.v, acc, 0, 0, 0);
+            }
+            sum |= __float_as_uint(acc[0]) & mine;
+        }
+        return __uint_as_float(sum);
+    };
     // P = 2^(S c2 - m) rounded to bf16, pair q of half hf; returns the packed pair
     auto pair_exp = [&](float t0, float t1) INL -> uint32_t { return pack2e(__builtin_amdgcn_exp2f(t0), __builtin_amdgcn_exp2f(t1)); };
     auto exp_pack = [&](int u, int hf, bool sel) INL -> float {
@@ -542,6 +564,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // With the maximum of the first 32 keys alone the error against 64 bits is up to 3 % larger (N = 1170, 95 %: 2.08e-3 -> 2.14e-3).
     // The sums are products over 32 lanes, so the way here is the whole wave's, and what differs between lanes is selected, not branched on
     // (TOPK: a lane that did not select the entry keeps its reference and adds nothing, whatever the product put into its sum).
+    // A sum that is not finite says so for its own row or for the one 16 lanes away; sums_apart tells which, only rows that did rise move, and
+    // the new sums are taken apart, too, so that a row's result does not depend on the others of its wave.
     auto settle = [&](int hf, bool whole, bool started, uint32_t e, const float (&ps)[QS]) INL {
         float psum[QS];
         bool risen[QS], redo[QS], any = false;
@@ -558,7 +582,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
             for (int u = 0; u < QS; ++u)
                 if (redo[u]) {
-                    const bool known = started || have_ref[u], moves = !TOPK || (selected(u, e) && (risen[u] || !known));
+                    const bool known = started || have_ref[u];
+                    float own = 0.f;
+                    if (risen[u] && (TOPK || known)) own = sums_apart(u, hf);
+                    const bool rises = !known | !(own <= 8192.f), moves = TOPK ? rises & selected(u, e) : rises;
                     float mx = s[u][hf][0];
 #pragma unroll
                     for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][hf][r]);
@@ -578,6 +605,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                     m_run[u] += shift;
                     have_ref[u] = moves || have_ref[u];
                     psum[u] = exp_pack(u, hf, selected(u, e));
+                    if (__builtin_expect(__any(!(psum[u] <= 8192.f)), 0)) psum[u] = sums_apart(u, hf);
                 }
         }
 #pragma unroll

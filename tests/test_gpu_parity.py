@@ -1037,6 +1037,48 @@ def test_topk_mask_layer(oracle, topk_variant, wi, key_block, topk, variant):
         assert errors(res["out"], dense["out"])[1] < 5e-3   # two independently rounded bf16 results
 
 
+@pytest.mark.parametrize("B,H,d,grid,keep,topk", [
+    (1, 43, 128, (3, 15, 16), 5, 0),      # 129 whole tiles
+    (1, 2, 128, (2, 7, 19), 4, 0),        # dealt by rows
+    (1, 3, 128, (5, 13, 17), 18, 0),      # cut along their lists
+    (1, 43, 64, (3, 15, 16), 5, 0), (1, 2, 64, (2, 7, 19), 4, 0), (1, 3, 64, (5, 13, 17), 18, 0),
+    (1, 43, 64, (4, 17, 19), 9, 0),       # 64 queries a wave: whole
+    (1, 58, 64, (4, 23, 25), 36, 0),      # and cut
+    (1, 3, 128, (5, 13, 17), 1, 3), (1, 3, 128, (5, 13, 17), 1, -3),     # Top-K: regrouped, token mask
+], ids=lambda x: str(x).replace(" ", ""))
+def test_non_finite_query_rows_stay_alone(topk_variant, B, H, d, grid, keep, topk):
+    """A query row with a NaN, an infinity or values that overflow costs nobody else anything: every other row has the bits of
+    the same call without it.  Key magnitudes rise and fall between blocks, so that references move in good rows as well."""
+    N = grid[0] * grid[1] * grid[2]
+    g = torch.Generator(device="cuda").manual_seed(N + d)
+    q, k, v = (torch.randn(B, H, N, d, generator=g, device="cuda") for _ in range(3))
+    k *= torch.tensor([1.0, 12.0, 2.0, 20.0, 5.0], device="cuda")[(torch.arange(N, device="cuda") // 64 * 7 + 3) % 5][:, None]
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    x, wg = torch.randn(B, N, H * d, generator=g, device="cuda").to(torch.bfloat16), torch.randn(H * d, generator=g, device="cuda") * 0.02
+    bad = torch.zeros(B, H, N, dtype=torch.bool, device="cuda")
+    q_bad = q.clone()
+    for h in range(H):
+        for first, value in ((3, float("nan")), (40, float("inf")), (71, -float("inf")), (101, 3e38), (N - 1, float("nan"))):
+            n = (first + 5 * h) % N
+            q_bad[:, h, n, (7 * h) % d:(7 * h) % d + 2] = value
+            bad[:, h, n] = True
+    rp, ci = sb.salad_block_mask(*grid, 64, [keep] * H)
+    kw = dict(x_t=x, w_gate=wg, lam=0.5, eps=1e-6)
+    kinds = [0 if topk else h % 2 for h in range(H)]
+    if topk:
+        topk_variant(0 if topk > 0 else 1)
+        kw.update(topk=abs(topk), topk_key_block=64)
+    for dbg in (False, True):
+        outs = []
+        for t in (q, q_bad):
+            more = dict(o_sparse_dbg=torch.zeros(B, H, N, d, device="cuda"), o_linear_dbg=torch.zeros(B, H, N, d, device="cuda")) if dbg else {}
+            outs.append([sb.salad_sparse_linear_attn_fwd(t, k, v, grid, rp, ci, kinds, **kw, **more)] + list(more.values()))
+        for clean, got in zip(*outs):
+            assert bool(torch.isfinite(clean).all())
+            assert torch.equal(got[~bad], clean[~bad]), int((got[~bad] != clean[~bad]).any(-1).sum())
+        assert bool(torch.isnan(outs[1][0][:, torch.arange(H), (3 + 5 * torch.arange(H)) % N]).any(-1).all())
+
+
 def test_token_mask_rows_beside_a_row_out_of_range(oracle, topk_variant):
     """Before a query has a softmax reference, logits 150 to 300 binades above 0 make its first sum infinite; the queries next to it
     in the wave did not select that block and must not notice.  Neighbours take different blocks, whose keys point along a
