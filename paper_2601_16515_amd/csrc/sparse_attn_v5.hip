@@ -568,14 +568,13 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the new sums are taken apart, too, so that a row's result does not depend on the others of its wave.
     auto settle = [&](int hf, bool whole, bool started, uint32_t e, const float (&ps)[QS]) INL {
         float psum[QS];
-        bool risen[QS], redo[QS], any = false;
+        bool redo[QS], any = false;
 #pragma unroll
         for (int u = 0; u < QS; ++u) {
             psum[u] = ps[u];
             redo[u] = !started && !have_ref[u];
             if (TOPK) redo[u] = __any(selected(u, e) && redo[u]);
-            risen[u] = __any(!(psum[u] <= 8192.f));
-            redo[u] = redo[u] || risen[u];
+            redo[u] = redo[u] || __any(!(psum[u] <= 8192.f));
             any = any || redo[u];
         }
         if (__builtin_expect(any, 0)) {
@@ -584,7 +583,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 if (redo[u]) {
                     const bool known = started || have_ref[u];
                     float own = 0.f;
-                    if (risen[u] && (TOPK || known)) own = sums_apart(u, hf);
+                    if (TOPK || known) own = sums_apart(u, hf);
                     const bool rises = !known | !(own <= 8192.f), moves = TOPK ? rises & selected(u, e) : rises;
                     float mx = s[u][hf][0];
 #pragma unroll
@@ -603,7 +602,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                             for (int r = 0; r < 16; ++r) o[u][i][r] *= alpha;
                     }
                     m_run[u] += shift;
-                    have_ref[u] = moves || have_ref[u];
+                    have_ref[u] = !TOPK || moves || have_ref[u];      // TOPK apart the same for all lanes, which the compiler is to see
                     psum[u] = exp_pack(u, hf, selected(u, e));
                     if (__builtin_expect(__any(!(psum[u] <= 8192.f)), 0)) psum[u] = sums_apart(u, hf);
                 }
