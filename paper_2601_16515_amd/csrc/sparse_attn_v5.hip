@@ -252,10 +252,19 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const int g = blockIdx.x;
     int L, piece = 0, pieces = 1;
     if (SPLIT) {      // an XCD's share: its run of whole tiles, then its run of pieces
-        const int fx = a.sp_full / 8, r = (g >> 3) - fx, np = (total - a.sp_full) * a.sp_pieces, px = (np + 7) / 8;
+        const int fx = a.sp_full / 8, np = (total - a.sp_full) * a.sp_pieces, px = (np + 7) / 8;
+        int r = (g >> 3) - fx;
         if (r < 0) {
             L = (g & 7) * fx + (g >> 3);
         } else {
+            // QS 2: every sp_pieces-th of the run first, then the next ones.  Workgroups go to the compute units in turn, two to each, and those
+            // without work leave at once; in plain order the first pieces, all that a short list has, came to lie in pairs on half of the
+            // units.  24 heads of 64, 768 tiles, 6 entries 65.8 -> 60.9 us, 40 heads, 640 tiles, 6 entries 63.7 -> 56.9.  With one workgroup a
+            // unit there is nothing to pair.
+            if (QS == 2) {
+                const int col = (int)div_by((unsigned)r, (unsigned)a.sp_rows, a.rows_magic);
+                r = (r - col * a.sp_rows) * a.sp_pieces + col;
+            }
             const int q = (g & 7) * px + r;
             if (r >= px || q >= np) return;
             L = a.sp_full + (int)div_by((unsigned)q, (unsigned)a.sp_pieces, a.pieces_magic);
@@ -1113,10 +1122,12 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT, QS, EMIT>;
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), V5_MAX_DYN, attr_done); e != hipSuccess) return e;
-    const int grid = SPLIT ? a.sp_full + ((total - a.sp_full) * a.sp_pieces + 7) / 8 * 8 : per_xcd * 8;
+    const int px = SPLIT ? ((total - a.sp_full) * a.sp_pieces + 7) / 8 : 0;      // pieces of an XCD
     auto magic = [](int d) { return d > 1 ? (unsigned)((1ull << 32) / (unsigned)d) : ~0u; };
     AttnArgs b = a;
     b.tiles_magic = magic(ntiles); b.heads_magic = magic(a.H); b.pieces_magic = magic(a.sp_pieces);
+    if (SPLIT) { b.sp_rows = (px + a.sp_pieces - 1) / a.sp_pieces; b.rows_magic = magic(b.sp_rows); }
+    const int grid = SPLIT ? a.sp_full + (QS == 2 ? b.sp_rows * a.sp_pieces : px) * 8 : per_xcd * 8;
     launch_kernel(kern, dim3(grid), dim3(512 / QS), lds, st, b, ntiles, total, per_xcd, list_cap);
     return take_launch_status();
 }

@@ -241,7 +241,10 @@ def test_time_axis_wraps_inside_a_block(oracle, d, grid):
     (1, 64, (3, 16, 17), 5),      # 256 tiles: 32 queries a wave
     (1, 43, (4, 17, 19), 9),      # 258 tiles: 64 queries a wave, one round, the last tile of a head with one block of 12 keys
     (2, 64, (3, 13, 14), 2),      # 384 tiles, lists shorter than the blocks fetched ahead
-    (3, 43, (3, 16, 17), 13),     # 516 tiles: the last four are cut in two
+    (3, 43, (3, 16, 17), 13),     # 516 tiles: the last four have room for 8 pieces each, and lists for one or two
+    (1, 62, (6, 18, 21), 8),      # 558 tiles, 46 of them with room for 5 pieces: an XCD's run of pieces starts in the middle of a tile and ends short
+    (1, 64, (3, 29, 32), 4),      # 704 tiles, 192 with room for two, lists too short to be cut
+    (1, 53, (3, 37, 25), 30),     # 583 tiles, 71 with room for 7
 ])
 def test_d64_sixty_four_queries_a_wave(oracle, B, H, grid, keep):
     """d = 64 around the number of tiles from which on a wave owns 64 queries; both head orders, guided batches, cut tiles."""
