@@ -125,8 +125,9 @@ struct AttnArgs {
     int gate_here, gate_nparts;
     const float *gate_partial, *s_dev, *head_scale;
     float lambda, *s_out;
-    // filled in by the large-tile kernel's launcher: an XCD's pieces over the pieces of a tile, rounded up; multiply-high inverses
-    int sp_rows;
+    // filled in by the large-tile kernel's launcher: pieces a tile for which each has a compute unit to itself; an XCD's pieces over the
+    // pieces of a tile, rounded up; multiply-high inverses
+    int sp_alone, sp_rows;
     unsigned tiles_magic, heads_magic, pieces_magic, rows_magic;
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };

@@ -310,7 +310,15 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const uint32_t *src = GATHER ? nullptr : a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
     if (SPLIT && pieces > 1) {
-        const int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
+        int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
+        if (QS == 2) {
+            // A piece alone on its compute unit takes 0.9 us an entry, one that shares it 1.6, a cut costs 4.8 and 11 us (fitted to calls of 520
+            // to 768 tiles): the best of no cut, as many pieces as have a unit each, and all that there is room for.  Cut wherever pieces had
+            // 6 entries: 24 heads, 768 tiles, 12 entries 84.4 -> 75.7 us; 40 heads, 640 tiles, 40 entries 147.1 -> 138.3 (in two, not four).
+            const int own = min(a.sp_alone, by_length);
+            const int p = own > 1 && 18 * n * (own - 1) > 95 * own ? own : 1;
+            if (by_length <= own || (18 * n + (p > 1 ? 95 * p : 0)) * by_length < (32 * n + 220 * by_length) * p) by_length = p;
+        }
         if (by_length > 1 && (!ROW_PAIRS || n * (21 * by_length - 29) > (D == 64 ? 120 : 190) * by_length)) {
             pieces = by_length;
             if (piece >= pieces) return;
@@ -1126,7 +1134,10 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     auto magic = [](int d) { return d > 1 ? (unsigned)((1ull << 32) / (unsigned)d) : ~0u; };
     AttnArgs b = a;
     b.tiles_magic = magic(ntiles); b.heads_magic = magic(a.H); b.pieces_magic = magic(a.sp_pieces);
-    if (SPLIT) { b.sp_rows = (px + a.sp_pieces - 1) / a.sp_pieces; b.rows_magic = magic(b.sp_rows); }
+    if (SPLIT) {
+        b.sp_alone = 256 / (total - a.sp_full);
+        b.sp_rows = (px + a.sp_pieces - 1) / a.sp_pieces; b.rows_magic = magic(b.sp_rows);
+    }
     const int grid = SPLIT ? a.sp_full + (QS == 2 ? b.sp_rows * a.sp_pieces : px) * 8 : per_xcd * 8;
     launch_kernel(kern, dim3(grid), dim3(512 / QS), lds, st, b, ntiles, total, per_xcd, list_cap);
     return take_launch_status();

@@ -244,7 +244,8 @@ def test_time_axis_wraps_inside_a_block(oracle, d, grid):
     (3, 43, (3, 16, 17), 13),     # 516 tiles: the last four have room for 8 pieces each, and lists for one or two
     (1, 62, (6, 18, 21), 8),      # 558 tiles, 46 of them with room for 5 pieces: an XCD's run of pieces starts in the middle of a tile and ends short
     (1, 64, (3, 29, 32), 4),      # 704 tiles, 192 with room for two, lists too short to be cut
-    (1, 53, (3, 37, 25), 30),     # 583 tiles, 71 with room for 7
+    (1, 53, (3, 37, 25), 30),     # 583 tiles, 71 with room for 7, of which 3 have a compute unit each
+    (1, 55, (4, 24, 32), 40),     # 660 tiles, 148 cut in three that share units, but for those whose lists are short
 ])
 def test_d64_sixty_four_queries_a_wave(oracle, B, H, grid, keep):
     """d = 64 around the number of tiles from which on a wave owns 64 queries; both head orders, guided batches, cut tiles."""
