@@ -1094,9 +1094,12 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 }
 
 // Sets of 32 queries of a wave (the kernel's QS): 2 at d = 64 where there are more tiles than compute units and two workgroups' LDS fits one.
+// Up to half a round more than that, with 32 queries a wave the rest is cut in two or more and pairs of tiles on one unit are avoided: 64
+// queries a wave against that take 98 % at 12 entries, 100 at 20, 106 at 32, 109 to 117 at 50, 124 at 104 (260 to 350 tiles).  A list holds
+// at most nb entries, so with few of them 64 queries stay (280 tiles of 28 blocks: 96 to 101 %).
 static int query_sets(int d, int nb, long long tiles)
 {
-    return d == 64 && tiles > 256 && 2 * (v5_ring_bytes(d) + tile_list_cap(nb) * 4) <= V5_MAX_DYN ? 2 : 1;
+    return d == 64 && tiles > (nb > 28 ? 384 : 256) && 2 * (v5_ring_bytes(d) + tile_list_cap(nb) * 4) <= V5_MAX_DYN ? 2 : 1;
 }
 
 SplitPlan split_plan(int BH, int nb, int d)

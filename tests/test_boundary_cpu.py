@@ -191,6 +191,15 @@ def test_workspace_query(lib):
     assert sb.salad_fwd_workspace_bytes(1, 2, 1024, 64, sb.SALAD_BF16) % 256 == 0
 
 
+def test_d64_tiles_just_past_a_round_are_cut(lib):
+    """d = 64, 344 tiles: with lists of more than 28 blocks the 88 beyond a round of 256 are cut in two and the workspace has room for the
+    pieces' results; with shorter lists, and from 385 tiles on, a round is 512 tiles and nothing is cut."""
+    room = 88 * 2 * (256 * 64 * 4 + 512 * 8)
+    long_lists, short_lists = (sb.salad_fwd_workspace_bytes(1, 43, nb * 64, 64, sb.SALAD_BF16) for nb in (29, 28))
+    assert long_lists > room > short_lists
+    assert sb.salad_fwd_workspace_bytes(1, 43, 36 * 64, 64, sb.SALAD_BF16) < room      # 387 tiles
+
+
 def test_step_entry_points_reject_bad_arguments(lib):
     fake = 0x1000
     assert lib.salad_linear_state_fwd(None, fake, 1, 2, 64, 64, sb.SALAD_BF16, fake, fake, fake, 1 << 30, None) == sb.SALAD_EINVAL

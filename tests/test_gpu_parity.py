@@ -240,6 +240,8 @@ def test_time_axis_wraps_inside_a_block(oracle, d, grid):
 @pytest.mark.parametrize("B,H,grid,keep", [
     (1, 64, (3, 16, 17), 5),      # 256 tiles: 32 queries a wave
     (1, 43, (4, 17, 19), 9),      # 258 tiles: 64 queries a wave, one round, the last tile of a head with one block of 12 keys
+    (1, 43, (4, 16, 29), 20),     # 344 tiles of 29 blocks: 32 queries a wave, 88 tiles cut in two
+    (1, 43, (4, 16, 28), 20),     # of 28 blocks: 64 queries a wave
     (2, 64, (3, 13, 14), 2),      # 384 tiles, lists shorter than the blocks fetched ahead
     (3, 43, (3, 16, 17), 13),     # 516 tiles: the last four have room for 8 pieces each, and lists for one or two
     (1, 62, (6, 18, 21), 8),      # 558 tiles, 46 of them with room for 5 pieces: an XCD's run of pieces starts in the middle of a tile and ends short
