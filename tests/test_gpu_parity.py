@@ -398,6 +398,13 @@ def test_workspace_without_room_for_the_pieces(oracle):
     assert errors(Z.cpu().numpy().astype(np.float64), ref["Z"])[1] < 2e-6
 
 
+def _graph_nodes(g):
+    nodes = C.c_size_t(0)
+    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    assert C.CDLL(hip).hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(nodes)) == 0
+    return nodes.value
+
+
 def test_sparse_branch_alone_is_one_launch():
     """lambda = 0 with prebuilt lists on a grid whose tiles may be cut: the attention kernel and nothing else, counted in a
     captured graph; replays on a workspace that held anything give the bits of the eager call."""
@@ -416,10 +423,7 @@ def test_sparse_branch_alone_is_one_launch():
     with torch.cuda.graph(g):
         p, keep = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, grid, row_ptr, col_idx, kinds, lam=0.0, workspace=ws, tile_lists=lists)
         sb.salad_fwd_call(p)
-    nodes = C.c_size_t(0)
-    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
-    assert C.CDLL(hip).hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(nodes)) == 0
-    assert nodes.value == 1
+    assert _graph_nodes(g) == 1
     g.instantiate()
     for rep in range(3):
         out.fill_(float("nan"))
@@ -466,6 +470,30 @@ def test_fp32_gate_reduced_by_the_attention_kernel(B, H, grid):
     alone = sb.salad_gate_fwd(x, wg)
     given = sb.salad_sparse_linear_attn_fwd(q, k, v, grid, rp, ci, [h % 2 for h in range(H)], s=alone, **kw)
     assert torch.equal(s, alone) and torch.equal(out, given)
+
+
+@pytest.mark.parametrize("H,grid,nodes", [(1, (1, 1, 40), 2), (2, (8, 64, 32), 2), (2, (41, 20, 20), 3)])
+def test_fp32_gate_has_a_launch_of_its_own_in_large_calls(H, grid, nodes):
+    """Up to 2048 query tiles of 16 the attention kernel reduces the gate (two launches), beyond that (here 2050) a third one does; a call
+    that is given the scale needs no reduce at any size."""
+    N, d = grid[0] * grid[1] * grid[2], 64
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn(1, H, N, d, generator=g, device="cuda") for _ in range(3))
+    x, wg = torch.randn(1, N, H * d, generator=g, device="cuda"), torch.randn(H * d, generator=g, device="cuda") * 0.1
+    rp, ci = sb.salad_block_mask(*grid, 64, [1] * H)
+    ws, out = sb.Workspace(1, H, N, d, sb.SALAD_F32), torch.empty_like(q)
+    alone = sb.salad_gate_fwd(x, wg)
+    outs = []
+    for kw, want in ((dict(x_t=x, w_gate=wg), nodes), (dict(s=alone), 2)):
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph):
+            p, keep = sb.make_fwd_params(q, k, v, out, grid, rp, ci, [h % 2 for h in range(H)], lam=0.5, workspace=ws, **kw)
+            sb.salad_fwd_call(p)
+        assert _graph_nodes(graph) == want
+        graph.instantiate()
+        graph.replay()
+        outs.append(out.clone())
+    assert torch.equal(*outs)
 
 
 def test_fp32_infinite_value_in_the_last_row():
