@@ -271,7 +271,8 @@ salad_status salad_timing_read(salad_kernel_times *out, int32_t reset);
  * each once at its start, so a concurrent salad_tune cannot change a call half way through.  A thread that changes
  * "state_wgs" between salad_fwd_workspace_bytes and the call gets SALAD_ENOSPC from the call's own size check.
  *   "state_wgs"     1..65536 (default 256): target workgroup count of the linear-state kernel (changes the workspace
- *                   size: query salad_fwd_workspace_bytes again after setting it).
+ *                   size: query salad_fwd_workspace_bytes again after setting it).  The default aims lower for short
+ *                   sequences, any other value is taken as it is.
  *   "attn_variant"  0 (default): the bf16 attention kernel is chosen by shape (256-query tiles for d = 128 and
  *                   d = 64, falling back to 128-query tiles at d = 128, to the first-generation kernel at d = 64,
  *                   when the block list does not fit); 1: never 256-query tiles; 2: the first-generation kernel.

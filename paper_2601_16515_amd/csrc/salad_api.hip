@@ -47,7 +47,7 @@ struct WsLayout {
 
 // tuning knobs (salad_tune): atomics, read once at the top of an entry point and passed down by value, so that a
 // concurrent salad_tune on another thread cannot change a call half way through
-std::atomic<int> g_state_target_wgs{256};
+std::atomic<int> g_state_target_wgs{STATE_WGS};
 std::atomic<int> g_topk_variant{0};
 std::atomic<int> g_attn_variant{0};
 
@@ -56,7 +56,7 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     WsLayout w{};
     const size_t BH = (size_t)B * H;
     w.nparts = gate_num_parts(N);
-    w.P = dtype == SALAD_BF16 ? state_num_chunks((int)BH, N, state_wgs) : 0;
+    w.P = dtype == SALAD_BF16 ? state_num_chunks((int)BH, N, d, state_wgs) : 0;
     size_t off = 0;
     w.gate_partial = off; off = align256(off + sizeof(float) * (size_t)B * w.nparts);
     w.state_partial = off; off = align256(off + sizeof(float) * BH * (size_t)w.P * ((size_t)d * d + d));

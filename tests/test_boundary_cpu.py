@@ -191,6 +191,23 @@ def test_workspace_query(lib):
     assert sb.salad_fwd_workspace_bytes(1, 2, 1024, 64, sb.SALAD_BF16) % 256 == 0
 
 
+def test_state_chunks(lib):
+    """The workspace holds one partial state per chunk of tokens: as many chunks as the knob asks for, except that its default leaves
+    out those too short to be worth one, which depends on the head width."""
+    def partial(BH, chunks, d):
+        return BH * chunks * (d * d + d) * 4
+
+    small = sb.salad_fwd_workspace_bytes(1, 12, 1950, 128, sb.SALAD_BF16)         # 31 tiles of 64 tokens, 4 a chunk
+    try:
+        sb.salad_tune("state_wgs", 12 * 31)
+        assert sb.salad_fwd_workspace_bytes(1, 12, 1950, 128, sb.SALAD_BF16) - small >= partial(12, 31 - 8, 128)
+    finally:
+        sb.salad_tune("state_wgs", 256)
+    assert sb.salad_fwd_workspace_bytes(1, 12, 1950, 128, sb.SALAD_BF16) == small
+    for d in (64, 128):                                                           # 128 tiles: 4 a chunk spread 8 heads over 256 workgroups
+        assert sb.salad_fwd_workspace_bytes(1, 8, 8192, d, sb.SALAD_BF16) > partial(8, 32, d)
+
+
 def test_d64_tiles_just_past_a_round_are_cut(lib):
     """d = 64, 344 tiles: with lists of more than 28 blocks the 88 beyond a round of 256 are cut in two and the workspace has room for the
     pieces' results; with shorter lists, and from 385 tiles on, a round is 512 tiles and nothing is cut."""
