@@ -398,13 +398,6 @@ def test_workspace_without_room_for_the_pieces(oracle):
     assert errors(Z.cpu().numpy().astype(np.float64), ref["Z"])[1] < 2e-6
 
 
-def _graph_nodes(g):
-    nodes = C.c_size_t(0)
-    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
-    assert C.CDLL(hip).hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(nodes)) == 0
-    return nodes.value
-
-
 def test_sparse_branch_alone_is_one_launch():
     """lambda = 0 with prebuilt lists on a grid whose tiles may be cut: the attention kernel and nothing else, counted in a
     captured graph; replays on a workspace that held anything give the bits of the eager call."""
@@ -423,7 +416,10 @@ def test_sparse_branch_alone_is_one_launch():
     with torch.cuda.graph(g):
         p, keep = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, grid, row_ptr, col_idx, kinds, lam=0.0, workspace=ws, tile_lists=lists)
         sb.salad_fwd_call(p)
-    assert _graph_nodes(g) == 1
+    nodes = C.c_size_t(0)
+    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    assert C.CDLL(hip).hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(nodes)) == 0
+    assert nodes.value == 1
     g.instantiate()
     for rep in range(3):
         out.fill_(float("nan"))
@@ -470,6 +466,13 @@ def test_fp32_gate_reduced_by_the_attention_kernel(B, H, grid):
     alone = sb.salad_gate_fwd(x, wg)
     given = sb.salad_sparse_linear_attn_fwd(q, k, v, grid, rp, ci, [h % 2 for h in range(H)], s=alone, **kw)
     assert torch.equal(s, alone) and torch.equal(out, given)
+
+
+def _graph_nodes(g):
+    nodes = C.c_size_t(0)
+    hip = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
+    assert C.CDLL(hip).hipGraphGetNodes(C.c_void_p(g.raw_cuda_graph()), None, C.byref(nodes)) == 0
+    return nodes.value
 
 
 @pytest.mark.parametrize("H,grid,nodes", [(1, (1, 1, 40), 2), (2, (8, 64, 32), 2), (2, (41, 20, 20), 3)])
@@ -660,6 +663,32 @@ def test_softmax_reference_moves_across_blocks(oracle, profile, kept_n):
             compare_layer(res_t, ref_t, label=f"{profile}/topk-variant{tv}: ")
 
 
+@pytest.mark.parametrize("H,grid,keep", [(43, (4, 17, 19), 21), (43, (4, 17, 19), 6), (58, (4, 23, 25), 36)], ids=["whole", "whole-window-6", "cut"])
+@pytest.mark.parametrize("profile", ["rising", "mixed"])
+def test_references_of_two_query_sets_move_apart(oracle, profile, H, grid, keep):
+    """64 queries a wave (d = 64, more than 256 tiles): the references of its two sets of 32 move independently.  Queries of one set, the
+    second in every other head, are so small that they never move after the first block, those of the other rise or jump by
+    tens of binades between blocks; in the last head both sets do."""
+    w = wl.small(f"sets-{H}", 1, H, 64, *grid, "bf16", 0.5, seed=118)
+    inp = wl.make_inputs(w)
+    kinds = wl.head_kinds(w)
+    blk = np.arange(w.N) // 64
+    g = 1.0 + 3.0 * blk if profile == "rising" else np.array([1.0, 30.0, 2.0, 55.0, 8.0])[(blk * 7 + 3) % 5]
+    small = np.arange(w.N) // 32 % 2
+    for h in range(H):
+        row = np.array([oracle.row_of_position(int(kinds[h]), p, w.T, w.Hh, w.W) for p in range(w.N)])
+        inp["k"][:, h, row] *= g[:, None].astype(np.float32)
+        if h < H - 1:
+            inp["q"][:, h, row] *= np.where(small == h // 2 % 2, 0.02, 1.0)[:, None].astype(np.float32)
+    for t in ("q", "k"):
+        inp[t] = wl.round_to_bf16(inp[t])
+    inp["v"] = inp["v"] * np.float32(0.25)                 # the softmax is close to one-hot: see test_softmax_reference_moves_across_blocks
+    dev = upload(w, inp)
+    ref = _oracle_layer(oracle, w, inp, [keep] * H, kinds)
+    for dbg in (True, False):
+        compare_layer(run_layer(w, inp, dev, [keep] * H, kinds, dbg=dbg), ref, label=f"{profile}/{H}/{keep}: ")
+
+
 def test_precomputed_s_and_bias_and_scale_arguments(oracle):
     w = SMALL[2]
     inp = wl.make_inputs(w)
@@ -720,6 +749,34 @@ def test_arbitrary_csr(oracle):
     a, r = errors(got[ok], o_s[ok])
     say(f"  arbitrary CSR: o_sparse max_abs={a:.3e} rel_l2={r:.3e}")
     assert r <= REL_L2
+
+
+@pytest.mark.parametrize("H,grid,longest", [
+    (43, (4, 17, 19), 21),            # 258 tiles of 21 blocks
+    (58, (4, 23, 25), 30),            # 522 tiles of 36 blocks, the last ten cut
+])
+def test_arbitrary_csr_with_two_query_sets_a_wave(oracle, H, grid, longest):
+    """The same for 64 queries a wave (d = 64, more than 256 tiles), with a whole tile of empty rows in the last head."""
+    w = wl.small(f"csr-{H}", 1, H, 64, *grid, "bf16", 0.5, seed=108)
+    inp = wl.make_inputs(w)
+    dev = upload(w, inp)
+    kinds = wl.head_kinds(w)
+    u = wl.uniform(108, "pick", (w.H * w.nb, w.nb))
+    row_ptr, col_idx = [0], []
+    for r in range(w.H * w.nb):
+        cnt = 1 + (r * 7) % longest
+        if r == 3 or (w.H - 1) * w.nb + 4 <= r < (w.H - 1) * w.nb + 8:
+            cnt = 0
+        cols = sorted(np.argsort(u[r])[:cnt].tolist())
+        col_idx += cols
+        row_ptr.append(len(col_idx))
+    csr = (np.array(row_ptr, np.int32), np.array(col_idx, np.int32))
+    o_s, rows = oracle.sparse_attn(inp["q"], inp["k"], inp["v"], (w.T, w.Hh, w.W), 64, kinds, *csr)
+    for got in (run_layer(w, inp, dev, None, kinds, csr=csr)["o_sparse"], run_layer(w, inp, dev, None, kinds, csr=csr, lam=0.0, dbg=False)["out"]):
+        got, ok = gather_rows(got, rows)
+        a, r = errors(got[ok], o_s[ok])
+        say(f"  arbitrary CSR: o_sparse max_abs={a:.3e} rel_l2={r:.3e}")
+        assert r <= REL_L2
 
 
 def test_unfused_epilogue_matches(oracle):
