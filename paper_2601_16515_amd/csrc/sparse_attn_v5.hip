@@ -3,7 +3,7 @@
 //
 //   * One workgroup = 8 waves = 256 query positions = 4 CSR rows of one (batch, head); one workgroup
 //     per CU (LDS: 5 K + 4 V tiles of 16 KB plus the block list).  d = 64, where the tiles are 8 KB: two workgroups of 4 waves
-//     per CU, a wave owning 64 queries, if there are tiles for both (QS below).
+//     per CU, a wave owning 64 queries, where there are tiles enough for both (query_sets).
 //   * The union of the 4 rows' kept-block lists comes from a pre-pass (tile_lists_kernel), each entry carrying a 4-bit "kept by
 //     query block i" mask, and is copied to LDS; no global or scalar load sits on the main loop's critical path.
 //   * K and V tiles go straight from global memory into two rings of LDS slots, K four and V two blocks ahead
@@ -12,15 +12,12 @@
 //     L2 / fabric latency is covered without a second resident workgroup.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
 //     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's
-//     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).  Before, the
-//     waves of a SIMD took turns, one multiplying while the other did its softmax, which left the softmax partly exposed.  B = 1, N = 32760, layer call: 24 heads of 64 at 90 % 917 -> 863 us; 12 heads of 128 dense
-//     5921 -> 5842 us, at 90 % 702 -> 699 us: at d = 128 the cycles fall by 5 % and the clock, which the power limit
-//     sets (1.95 -> 1.89 GHz on the dense call), takes most of it back.
+//     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).
 //   * What bounds the loop is the energy of its instructions: the chip is at its power limit, and fewer cycles for the same
-//     instructions only lower the clock (dense call: without the barrier 9.94 instead of 10.23 M cycles, 1.625 instead of 1.674
-//     GHz, the same time).  So whatever is the same for a whole wave is on the scalar unit, and the tiles in LDS are laid out so
-//     that operand addresses are one register and an immediate: 22 vector instructions fewer of 128 per block and wave, with the
-//     conditions below 26.  Dense 5752 -> 5575 us, 480p 90 % 668 -> 651, 8 x 30 x 52 at 75 % 267 -> 261, 24 heads of 64 842 -> 833.
+//     instructions only lower the clock.  So whatever is the same for a whole wave is on the scalar unit, and the tiles in LDS
+//     are laid out so that operand addresses are one register and an immediate.  Layer calls at B = 1, N = 32760 with that, the row
+//     sums on the matrix pipe and, for 64-wide heads, two query sets a wave: 12 heads of 128 dense 5863 -> 5477 us (1.20 PFLOP/s),
+//     at 90 % 694 -> 664, 24 heads of 64 at 90 % 862 -> 712.
 //   * V^T operands come from ds_read_b64_tr_b16, K rows are read through the kappa permutation so
 //     that P never moves between lanes.  LDS operand reads are spread evenly between the MFMAs through a
 //     small ring of fragment registers.
@@ -221,14 +218,13 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 //   the normaliser has been taken from the unrotated features.
 // D = 64 (MODE 0 without ROPE only): the same kernel on half-size tiles.  A row is 8 chunks of 16 bytes instead of 16,
 // so a tile is half as many 1 KB pieces, and every fragment count halves.
-// SPLIT (MODE 0 only): the tiles from a.sp_full on, which do not fill the chip, are cut along their visit lists into up to a.sp_pieces
-// workgroups each, or, where that does not pay, by rows into two.  Every piece runs its own softmax over its entries, writes O, the
-// reference and the row sum in fp32, and counts itself in; the piece that comes last reads the others back, combines all in piece order (so the result does not depend on which
-// it was) and goes on to the epilogue.  Nobody waits for anybody.
+// SPLIT (MODE 0 only): the tiles from a.sp_full on, which do not fill the chip, are cut along their visit lists into up to
+// a.sp_pieces workgroups each, or, where that does not pay, by rows into two.  Every piece runs its own softmax over its entries,
+// writes O, the reference and the row sum in fp32, and counts itself in; the piece that comes last reads the others back, combines
+// all in piece order (so the result does not depend on which it was) and goes on to the epilogue.  Nobody waits for anybody.
 // QS: sets of 32 queries that a wave owns.  With 2 every operand fragment read from LDS feeds two products, which halves the energy
 // of the reads, and a workgroup has half the waves.  d = 64 has the registers for it and LDS for two such workgroups per CU, whose
-// barriers are independent: B = 1, N = 32760, 24 heads at 90 % 832 -> 725 us, dense N = 12480 1119 -> 1005; while there is one tile per CU
-// or less the 4 waves alone are slower (N = 1950, 24 heads 28.4 -> 30.9).  At d = 128 it needs 400 registers, so one wave per SIMD, and
+// barriers are independent: N = 32760, 24 heads at 90 % 832 -> 725 us.  At d = 128 it needs 400 registers, so one wave per SIMD, and
 // the loads, which hold a wave for 60 cycles each, and the scalar code have nothing to run under: dense 5421 -> 5564 us.
 // EMIT (d = 128, MODE 0 without ROPE and DBG): the linear branch goes, unscaled, to a.emit_ol instead of being added to O_s.
 template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, int QS = 1, bool EMIT = false>
@@ -295,15 +291,14 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const u16 *kb = reinterpret_cast<const u16 *>(a.k) + (size_t)bh * N * D;
     const u16 *vb = reinterpret_cast<const u16 *>(a.v) + (size_t)bh * N * D;
 
-    // ---- The start of a tile is a chain of memory latencies with nothing to run under them (13000 cycles of 57000 for a 13-entry tile),
-    // so everything whose address is known is asked for at once: the count and the first entries by scalar loads, the queries and
-    // the list straight into LDS, and, as soon as the first entries are there, the first blocks.  Before, list and queries came first, through
-    // registers, and the blocks after a barrier.  Layer call: N = 1950 36.5 -> 35.6 us, N = 640 25.6 -> 24.1, Top-K at N = 32760
-    // (13 entries) 1069 -> 1052, 24 heads of 64 at 90 % 723 -> 717; 12 heads of 128 at 90 % the same (at the power limit a wait costs little).
-    // Where a list is not worth cutting, two workgroups take two of the tile's rows each.  All waves fetch, but with one computing wave per SIMD
-    // an iteration is 2100 cycles long instead of 2900.  N = 1950, 12 heads, 11 entries 33.7 -> 29.8 us; N = 1280, 5 heads 25.2 -> 22.4; 12 heads of 64
-    // 22.1 -> 20.2.  Cutting in p costs 19000 cycles (scratch, merge; d = 64: 12000), so it takes n 2900 / p + 19000 < n 2100: two pieces
-    // from 30 entries on (d = 64: 19), three always.  12 entries 35.5 (cut in two) -> 30.6 us, 17 entries 39.5 -> 35.6; 25 entries 42.8 (rows) -> 38.8 (cut in four).  Not with two sets of queries a wave: the two workgroups of a compute unit are one computing wave per SIMD each as it is.
+    // ---- The start of a tile is a chain of memory latencies with nothing to run under them (9000 cycles of 57000 for a 13-entry
+    // tile), so everything whose address is known is asked for at once: the count and the first entries by scalar loads, the
+    // queries and the list straight into LDS, and, as soon as the first entries are there, the first blocks.
+    // Where a list is not worth cutting, two workgroups take two of the tile's rows each.  All waves fetch, but with one computing
+    // wave per SIMD an iteration is 2100 cycles long instead of 2900.  Cutting in p costs 19000 cycles (scratch, merge; d = 64: 12000),
+    // so it takes n 2900 / p + 19000 < n 2100: two pieces from 30 entries on (d = 64: 19), three always.  N = 1950, 12 heads, 11 entries
+    // 33.7 -> 29.8 us, 17 entries 39.5 (in two) -> 35.6 (rows); 25 entries 42.8 (rows) -> 38.8 (in four).  Not with two sets of
+    // queries a wave: the two workgroups of a compute unit are one computing wave per SIMD each as it is.
     constexpr bool ROW_PAIRS = SPLIT && QS == 1;
     int my_rows = -1;                            // ROW_PAIRS: which two, or all
     const int g_blk0 = g_J * a.g_bpb;
@@ -387,7 +382,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             }
     };
     if (!GATHER) fetch_q();
-    // the list's whole row of list_cap slots (built by the pre-pass), without waiting for the count: slots past it hold stale words that are never used
+    // the list's whole row of list_cap slots (built by the pre-pass), without waiting for the count: slots past it hold stale words
+    // that are never used
     if (!GATHER)
         for (int i = (int)wave_u * 64; i < list_cap; i += NT)
             lds_dma4(src + (SPLIT ? min(i + lane + list0, list_cap - 1) : i + lane), lds_addr_of(blist + i));
@@ -482,7 +478,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // products of one half (2 NDT MFMAs, A = V^T, two transposing 8-byte reads), with the softmax of a third half woven
     // between them.  Operand fragments move through a ring of RING register quads: step i takes ring[i % RING] and the read
     // of fragment i + RING is issued right after it; the last steps of a block read the next block's first K fragments.
-    constexpr int RING = QS == 2 ? 2 : 4;         // 8: 5957 against 5842 us on the dense call; QS = 2 with 4: 4 spills, 731 against 725 us
+    constexpr int RING = QS == 2 ? 2 : 4;         // 8: 5957 against 5842 us on the dense call; QS = 2 with 4: 731 against 725 us
     Frag5 ring[RING];
     constexpr int NPS = NS + 2 * NDT;             // steps of a part
     static_assert((2 * NPS) % RING == 0, "a block's fragments go round the ring a whole number of times");
@@ -533,7 +529,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // .. + 3 of column lane % 16: the A operand picks by row which of the two goes there.  Four of these a block take 64 cycles of the
     // matrix pipe where 16 v_dot2c_f32_bf16 took 256 (plain adds of the unpacked pairs take two more vector instructions per pair,
     // and the loop is held by the energy of its instructions).  Layer call, B = 1, N = 32760: 12 heads of 128 dense 5830 -> 5712 us, at
-    // 90 % 687 -> 672; 24 heads of 64 at 90 % 858 -> 846; the error against 64 bits is the same to six digits.
+    // 90 % 687 -> 672; 24 heads of 64 at 90 % 858 -> 846; the error against 64 bits is the same to six digits.  Two rows share a column and
+    // are told apart by zeros only, which is good for finite probabilities: see sums_apart.
     Frag5 pick;
 #pragma unroll
     for (int i = 0; i < 4; ++i) pick.w[i] = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
@@ -655,7 +652,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int p = 0; p < 8 * QS; ++p) {
-                    const int q = p / QS, v = p % QS, at = p * FS / (8 * QS);    // pair q of set v; slot at which its logits are scaled, the rest follows one slot apart
+                    // pair q of set v; slot at which its logits are scaled, the rest follows one slot apart
+                    const int q = p / QS, v = p % QS, at = p * FS / (8 * QS);
                     if (slot == at) {
                         t[v][2 * q] = fmaf(s[v][hf][2 * q], cs[v], -mref[v]);
                         t[v][2 * q + 1] = fmaf(s[v][hf][2 * q + 1], cs[v], -mref[v]);
@@ -676,11 +674,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         settle(hf, TOPK && hf == 0, !TOPK, e, psum);     // TOPK: a lane's first selected block may come here
     };
     // the same work for blocks that not both of two successive list entries give this wave (first and last entry, entries that
-    // another query block of the tile keeps).  In the uncut d = 128 kernels start_cur has the softmax of the first half between the S
-    // products of the second: N = 12480, 24 heads, rows of random blocks at 30 % 954 -> 924 us (945 in the loop before the woven
-    // one), every third block 1159 -> 1066, every second, where no wave ever has two entries in turn, 1188 -> 1144 (1146); windows
-    // as before.  The same in finish_prev loses (962, 1182, 1217), and windows get slower by it where tiles are cut (720p 11395 ->
-    // 11452) and at d = 64 (480p, 90 % 882 -> 895).
+    // another query block of the tile keeps).  Lists of random or strided blocks live on it, so in the uncut d = 128 kernels start_cur has
+    // the softmax of the first half between the S products of the second: every third block 1159 -> 1066 us at N = 12480, 24 heads.
+    // The same in finish_prev lost (1182), and windows got slower by it where tiles are cut and at d = 64 (480p, 90 % 882 -> 895).
+    // Layer calls there, every second / third / a random 30 % of the blocks: 1138 / 1049 / 879 us; 24 heads of 64 593 / 553 / 514.
     auto finish_prev = [&](uint32_t e, const u16 *Vt) INL {
         mask_tail(1, e);
 #pragma unroll
@@ -807,7 +804,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             const int jf = j + AK;
             uint32_t e_f = 0u;
             if (__builtin_expect(jf < n, 1)) {
-                if (__builtin_expect((jf & 63) == 0, 0)) load_entries(jf);      // waited for inside, so that the other turns of the loop need not wait for their operand reads
+                // waited for inside, so that the other turns of the loop need not wait for their operand reads
+                if (__builtin_expect((jf & 63) == 0, 0)) load_entries(jf);
                 e_f = entry(jf);
             }
             int kslot_f = kslot - 1; if (kslot_f < 0) kslot_f += NK;
