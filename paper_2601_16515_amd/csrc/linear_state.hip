@@ -27,7 +27,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-int state_tiles_per_chunk(int BH, int N, int D, int target_wgs)
+int state_tiles_per_chunk(int BH, int N, int target_wgs)
 {
     int tiles = (N + 63) / 64;
     int want = target_wgs / (BH > 0 ? BH : 1);
@@ -37,19 +37,20 @@ int state_tiles_per_chunk(int BH, int N, int D, int target_wgs)
     if (target_wgs != STATE_WGS) return spread;
     // A chunk's partial state, written and read again, is as many bytes as four tiles of K and V (d = 64: two), and all of a head's are
     // added up in the next launch, so a chunk of one tile costs more than it saves: with t us per tile and r per partial state the
-    // time tiles t + BH chunks r is least at sqrt(BH tiles r / t) tiles per chunk.  r / t = 1/80 (d = 64: 1/120), rounded up to an even number,
-    // since the kernel goes by two tiles, lost to the spread alone in 2 of 262 shapes of 640 to 75600 tokens (4 %); 1/32 for both
-    // widths lost up to 8 % in 24.  From BH tiles = 768 on the spread decides.  State and reduce of 1 head at N = 16384
-    // 17.3 -> 12.7 us, 8 heads, N = 4096 18.9 -> 14.0, 12 heads, N = 1950 13.6 -> 12.2; d = 64: 11.5 -> 8.7, 8 heads, N = 8192 11.1 as before.
-    const double worth = std::sqrt((double)BH * tiles / (D == 128 ? 80 : 120));
+    // time tiles t + BH chunks r is least at sqrt(BH tiles r / t) tiles per chunk.  r / t = 1/80 for either width, rounded up to an even
+    // number, since the kernel goes by two tiles: against the spread alone 0.97 of the time at d = 64 and 0.95 at d = 128 in the mean of 131
+    // shapes each (640 to 75600 tokens, 1 to 80 heads), more than 2 % slower in two, by 4 and 5 %; 1/32 without the rounding was in 24, by up
+    // to 8 %.  1/120 for d = 64: 0.976.  From BH tiles = 768 on the spread decides.  State and reduce of 1 head at N = 16384 16.8 -> 12.6 us,
+    // 8 heads, N = 4096 15.5 -> 12.3, 12 heads, N = 1950 12.9 -> 12.1; d = 64: 11.5 -> 8.6, 8 heads, N = 8192 9.8 as before.
+    const double worth = std::sqrt((double)BH * tiles / 80);
     const int least = worth > 1 ? 2 * (int)std::ceil(worth / 2) : 1;
     return spread > least ? spread : least < tiles ? least : tiles;
 }
 
-int state_num_chunks(int BH, int N, int D, int target_wgs)
+int state_num_chunks(int BH, int N, int target_wgs)
 {
     int tiles = (N + 63) / 64;
-    int tpc = state_tiles_per_chunk(BH, N, D, target_wgs);
+    int tpc = state_tiles_per_chunk(BH, N, target_wgs);
     return (tiles + tpc - 1) / tpc;
 }
 
@@ -271,7 +272,7 @@ hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int
                                   hipStream_t st, const uint32_t *rope_tab)
 {
     if (rope_tab && D != 128) return hipErrorInvalidValue;
-    const int tpc = state_tiles_per_chunk(BH, N, D, target_wgs), P = state_num_chunks(BH, N, D, target_wgs);
+    const int tpc = state_tiles_per_chunk(BH, N, target_wgs), P = state_num_chunks(BH, N, target_wgs);
     const int nch = (g.D / 8 + 63) / 64;
     const dim3 grid(BH * P + g.nparts * B), block(256);
     auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, st, k, v, N, tpc, P, partial, BH, g, rope_tab); };
@@ -294,8 +295,8 @@ hipError_t launch_state_partial_bf16(const u16 *k, const u16 *v, int BH, int N, 
                                      float *partial, const int32_t *drop, int H, int target_wgs, hipStream_t st,
                                      const uint32_t *rope_tab)
 {
-    int tpc = state_tiles_per_chunk(BH, N, D, target_wgs);
-    int P = state_num_chunks(BH, N, D, target_wgs);
+    int tpc = state_tiles_per_chunk(BH, N, target_wgs);
+    int P = state_num_chunks(BH, N, target_wgs);
     dim3 grid(P, BH), block(256);
     if (rope_tab) {
         if (D != 128) return hipErrorInvalidValue;

@@ -193,7 +193,7 @@ def test_workspace_query(lib):
 
 def test_state_chunks(lib):
     """The workspace holds one partial state per chunk of tokens: as many chunks as the knob asks for, except that its default leaves
-    out those too short to be worth one, which depends on the head width."""
+    out those too short to be worth one."""
     def partial(BH, chunks, d):
         return BH * chunks * (d * d + d) * 4
 
