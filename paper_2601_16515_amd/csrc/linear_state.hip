@@ -27,7 +27,7 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-int state_tiles_per_chunk(int BH, int N, int target_wgs)
+int state_tiles_per_chunk(int BH, int N, int D, int target_wgs)
 {
     int tiles = (N + 63) / 64;
     int want = target_wgs / (BH > 0 ? BH : 1);
@@ -35,22 +35,21 @@ int state_tiles_per_chunk(int BH, int N, int target_wgs)
     if (want > tiles) want = tiles;
     const int spread = (tiles + want - 1) / want;
     if (target_wgs != STATE_WGS) return spread;
-    // A chunk's partial state, written and read again, is as many bytes as four tiles of K and V (d = 64: two), and all of a head's are
-    // added up in the next launch, so a chunk of one tile costs more than it saves: with t us per tile and r per partial state the
-    // time tiles t + BH chunks r is least at sqrt(BH tiles r / t) tiles per chunk.  r / t = 1/80 for either width, rounded up to an even
-    // number, since the kernel goes by two tiles: against the spread alone 0.97 of the time at d = 64 and 0.95 at d = 128 in the mean of 131
-    // shapes each (640 to 75600 tokens, 1 to 80 heads), more than 2 % slower in two, by 4 and 5 %; 1/32 without the rounding was in 24, by up
-    // to 8 %.  1/120 for d = 64: 0.976.  From BH tiles = 768 on the spread decides.  State and reduce of 1 head at N = 16384 16.8 -> 12.6 us,
-    // 8 heads, N = 4096 15.5 -> 12.3, 12 heads, N = 1950 12.9 -> 12.1; d = 64: 11.5 -> 8.6, 8 heads, N = 8192 9.8 as before.
-    const double worth = std::sqrt((double)BH * tiles / 80);
-    const int least = worth > 1 ? 2 * (int)std::ceil(worth / 2) : 1;
+    // A chunk's partial state, written and read again, is as many bytes as four tiles of K and V (d = 64: two), all of a head's are added
+    // up in the next launch, and the gate's workgroups ride in this one, so short chunks cost more than they save: with t us per tile
+    // and r per partial state the time tiles t + BH chunks r is least at sqrt(BH tiles r / t) tiles per chunk.  r / t = 1/32, d = 64 1/48, by
+    // layer calls of 98 shapes each (640 to 32760 tokens, 2 to 80 heads, 2 kept blocks): 0.967 and 0.983 of the time with the spread
+    // alone in the mean, slower than it by up to 4 and 2.5 %; 1/32 at d = 64 0.983, slower by up to 4 %, 1/80 at d = 128 0.977.  From BH tiles =
+    // 2048 (1365) on the spread decides.  State and reduce alone, without the gate, like chunks to be shorter: 1/80 for both.
+    // N = 1280, 12 heads 27.0 -> 24.1 us, N = 1950, 16 heads 29.9 -> 26.4, N = 6000, 5 heads 29.8 -> 26.0; d = 64: 18.8 -> 16.6, 20.9 -> 18.8.
+    const int least = (int)std::ceil(std::sqrt((double)BH * tiles / (D == 128 ? 32 : 48)));
     return spread > least ? spread : least < tiles ? least : tiles;
 }
 
-int state_num_chunks(int BH, int N, int target_wgs)
+int state_num_chunks(int BH, int N, int D, int target_wgs)
 {
     int tiles = (N + 63) / 64;
-    int tpc = state_tiles_per_chunk(BH, N, target_wgs);
+    int tpc = state_tiles_per_chunk(BH, N, D, target_wgs);
     return (tiles + tpc - 1) / tpc;
 }
 
@@ -272,7 +271,7 @@ hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int
                                   hipStream_t st, const uint32_t *rope_tab)
 {
     if (rope_tab && D != 128) return hipErrorInvalidValue;
-    const int tpc = state_tiles_per_chunk(BH, N, target_wgs), P = state_num_chunks(BH, N, target_wgs);
+    const int tpc = state_tiles_per_chunk(BH, N, D, target_wgs), P = state_num_chunks(BH, N, D, target_wgs);
     const int nch = (g.D / 8 + 63) / 64;
     const dim3 grid(BH * P + g.nparts * B), block(256);
     auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, st, k, v, N, tpc, P, partial, BH, g, rope_tab); };
@@ -295,8 +294,8 @@ hipError_t launch_state_partial_bf16(const u16 *k, const u16 *v, int BH, int N, 
                                      float *partial, const int32_t *drop, int H, int target_wgs, hipStream_t st,
                                      const uint32_t *rope_tab)
 {
-    int tpc = state_tiles_per_chunk(BH, N, target_wgs);
-    int P = state_num_chunks(BH, N, target_wgs);
+    int tpc = state_tiles_per_chunk(BH, N, D, target_wgs);
+    int P = state_num_chunks(BH, N, D, target_wgs);
     dim3 grid(P, BH), block(256);
     if (rope_tab) {
         if (D != 128) return hipErrorInvalidValue;

@@ -56,7 +56,7 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     WsLayout w{};
     const size_t BH = (size_t)B * H;
     w.nparts = gate_num_parts(N);
-    w.P = dtype == SALAD_BF16 ? state_num_chunks((int)BH, N, state_wgs) : 0;
+    w.P = dtype == SALAD_BF16 ? state_num_chunks((int)BH, N, d, state_wgs) : 0;
     size_t off = 0;
     w.gate_partial = off; off = align256(off + sizeof(float) * (size_t)B * w.nparts);
     w.state_partial = off; off = align256(off + sizeof(float) * BH * (size_t)w.P * ((size_t)d * d + d));

@@ -34,8 +34,8 @@ int gate_num_parts(int N);
 // target_wgs: workgroups the launch aims for (the caller reads the tuning knob once per call); fewer where chunks would get too short to be
 // worth their partial states, unless the knob was moved from its default
 constexpr int STATE_WGS = 256;
-int state_tiles_per_chunk(int BH, int N, int target_wgs);
-int state_num_chunks(int BH, int N, int target_wgs);
+int state_tiles_per_chunk(int BH, int N, int D, int target_wgs);
+int state_num_chunks(int BH, int N, int D, int target_wgs);
 // drop (may be null): int32 [B], workgroups of a sample with drop[b] != 0 return at once (H heads per sample)
 // rope_tab (d = 128 only): [N, d/2] words (fp16 cos | fp16 sin << 16) of the rotary linear branch, or null
 hipError_t launch_state_partial_bf16(const u16 *k, const u16 *v, int BH, int N, int D,

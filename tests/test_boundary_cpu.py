@@ -193,19 +193,22 @@ def test_workspace_query(lib):
 
 def test_state_chunks(lib):
     """The workspace holds one partial state per chunk of tokens: as many chunks as the knob asks for, except that its default leaves
-    out those too short to be worth one."""
+    out those too short to be worth one, which depends on the head width."""
     def partial(BH, chunks, d):
         return BH * chunks * (d * d + d) * 4
 
-    small = sb.salad_fwd_workspace_bytes(1, 12, 1950, 128, sb.SALAD_BF16)         # 31 tiles of 64 tokens, 4 a chunk
-    try:
-        sb.salad_tune("state_wgs", 12 * 31)
-        assert sb.salad_fwd_workspace_bytes(1, 12, 1950, 128, sb.SALAD_BF16) - small >= partial(12, 31 - 8, 128)
-    finally:
-        sb.salad_tune("state_wgs", 256)
-    assert sb.salad_fwd_workspace_bytes(1, 12, 1950, 128, sb.SALAD_BF16) == small
-    for d in (64, 128):                                                           # 128 tiles: 4 a chunk spread 8 heads over 256 workgroups
-        assert sb.salad_fwd_workspace_bytes(1, 8, 8192, d, sb.SALAD_BF16) > partial(8, 32, d)
+    def more_chunks(BH, N, d, wgs, chunks):      # the workspace with the knob at wgs is larger by so many partial states a head
+        rest = sb.salad_fwd_workspace_bytes(1, BH, N, d, sb.SALAD_BF16)
+        try:
+            sb.salad_tune("state_wgs", wgs)
+            return abs(sb.salad_fwd_workspace_bytes(1, BH, N, d, sb.SALAD_BF16) - rest - partial(BH, chunks, d)) < 256
+        finally:
+            sb.salad_tune("state_wgs", 256)
+
+    assert more_chunks(12, 1950, 128, 12 * 31, 31 - 8)            # 31 tiles, 4 a chunk by default
+    assert more_chunks(12, 1950, 64, 12 * 31, 31 - 11)            # 3 a chunk
+    assert more_chunks(2, 2000, 128, 4096, 32 - 16)
+    assert more_chunks(40, 4096, 128, 257, 0)                     # 11 a chunk: what spreads 40 heads over the chip is longer already
 
 
 def test_d64_tiles_just_past_a_round_are_cut(lib):
