@@ -15,6 +15,7 @@
 // the workspace and are added in chunk order by the finalize kernel (no float atomics, so results
 // are reproducible run to run).
 #include "gate_part.h"
+#include "linear_ride.h"
 
 #include <cmath>
 
@@ -307,6 +308,33 @@ hipError_t launch_state_partial_bf16(const u16 *k, const u16 *v, int BH, int N, 
     else
         launch_kernel((state_partial_kernel<64, false>), grid, block, 0, st, k, v, N, tpc, P, partial, drop, H, nullptr);
     return take_launch_status();
+}
+
+// Short sequences (linear_ride.h), where the slices do not ride with the attention because each stage is being timed.
+template <int D, bool ROPE>
+__global__ __launch_bounds__(512) void state_direct_kernel(const u16 *__restrict__ k, const u16 *__restrict__ v, int N, int BH, int H, const int32_t *__restrict__ drop,
+                                                           const uint32_t *__restrict__ rope_tab, u16 *__restrict__ hfrag, float *__restrict__ Z)
+{
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ float small[DIRECT_WAVES][32];
+    const int bh = slice_head(BH, slices_per_head(D), blockIdx.x), slice = slice_of(BH, slices_per_head(D), blockIdx.x);
+    if (drop && drop[bh / H]) return;                  // pruned sample (Sec. 4.3): K, V are not read
+    state_slice<D, ROPE>(k, v, N, rope_tab, hfrag, Z, bh, slice, smem, small);
+}
+
+hipError_t launch_state_direct(const u16 *k, const u16 *v, int B, int H, int N, int D, const int32_t *drop, const uint32_t *rope_tab, u16 *hfrag, float *Z,
+                               hipStream_t st)
+{
+    auto go = [&](auto dc, auto rc) -> hipError_t {
+        constexpr int DD = decltype(dc)::value;
+        auto kern = state_direct_kernel<DD, decltype(rc)::value>;
+        static bool attr_done[16] = {};
+        if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), direct_lds(DD), attr_done); e != hipSuccess) return e;
+        launch_kernel(kern, dim3(B * H * slices_per_head(DD)), dim3(512), (size_t)direct_lds(DD), st, k, v, N, B * H, H, drop, rope_tab, hfrag, Z);
+        return take_launch_status();
+    };
+    if (D == 64) return rope_tab ? hipErrorInvalidValue : go(std::integral_constant<int, 64>{}, std::false_type{});
+    return rope_tab ? go(std::integral_constant<int, 128>{}, std::true_type{}) : go(std::integral_constant<int, 128>{}, std::false_type{});
 }
 
 // (cos, sin) tables of the rotary linear branch, fp32 [n] each -> one word per angle: fp16 cos | fp16 sin << 16

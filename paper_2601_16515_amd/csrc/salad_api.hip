@@ -4,6 +4,7 @@
 #include <sys/random.h>
 #include <unistd.h>
 
+#include <algorithm>
 #include <array>
 #include <atomic>
 #include <chrono>
@@ -40,9 +41,10 @@ salad_status hip_fail(hipError_t e, const char *what)
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
-    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, base, total;
+    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, ride_words, ride_gate, base, total;
     int nparts, P;
     SplitPlan split;
+    RidePlan ride;
 };
 
 // tuning knobs (salad_tune): atomics, read once at the top of an entry point and passed down by value, so that a
@@ -103,6 +105,10 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     w.sp_o = off; off = align256(off + sizeof(float) * np * 256 * (size_t)d);
     w.sp_ml = off; off = align256(off + sizeof(uint64_t) * np * 512);
     w.sp_count = off; off = align256(off + sizeof(uint64_t) * (np ? (size_t)w.split.rest : 0));
+    // state and gate within the attention's launch
+    if (dtype == SALAD_BF16 && !topk && large_lists) w.ride = ride_plan(B, H, N, d, w.split);
+    w.ride_words = off; off = align256(off + (w.ride.wgs ? sizeof(uint64_t) * RIDE_STRIDE * (BH + B) : 0));
+    w.ride_gate = off; off = align256(off + (w.ride.wgs ? sizeof(float) * 4 * (size_t)B * w.nparts : 0));
     w.total = off;
     return w;
 }
@@ -187,6 +193,10 @@ salad_status static_scratch_ptr(void **out)
 }  // namespace
 
 extern "C" {
+
+// The layer call with its own bound on how often a tile looks whether riders have done the linear branch's state before it does it itself
+// (0: always itself).  Not part of the interface: for the test of that.
+salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls);
 
 const char *salad_last_error(void) { return g_err; }
 
@@ -401,6 +411,11 @@ salad_status salad_gate_fwd_static(const void *x_t, const float *w_gate, float b
 
 salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
 {
+    return salad_fwd_with_polls(p, RIDE_POLLS);
+}
+
+salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls)
+{
     if (!p) return fail(SALAD_EINVAL, "salad_sparse_linear_attn_fwd: null params");
     if (p->B < 1 || p->H < 1 || p->N < 1) return fail(SALAD_EINVAL, "fwd: B=%d H=%d N=%d must be positive", p->B, p->H, p->N);
     if (p->dtype != SALAD_BF16 && p->dtype != SALAD_F32) return fail(SALAD_EINVAL, "fwd: dtype %d", p->dtype);
@@ -493,6 +508,11 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     const bool split = w.split.pieces > 1 && large_tile && p->workspace_bytes >= w.total;      // the last round's tiles are cut
     const uint64_t sp_tag = split ? next_piece_tag() : 0;
 
+    // full projection: the attention kernel's epilogue writes O_l, in the projection's operand order, next to O_s.  A pass of its own over Q
+    // took 51-55 us at N = 32760, 12 heads: layer call 872 -> 849 us.
+    const bool emit_in_attn = full_proj && large_tile && !topk && !rope && !p->o_sparse_dbg && !p->o_linear_dbg &&
+                              !(p->flags & SALAD_FLAG_UNFUSED_EPILOGUE);
+
     CallEvents ev{};
     int timing;
     auto give_back = [&]() {                       // an error path returns the events it took to the pool
@@ -525,11 +545,32 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     int32_t *drop = dropping ? (int32_t *)(ws + w.drop) : nullptr;
     bool gate_here = false;                            // the attention kernel reduces the gate
     mark(0);
-    if (use_linear) {
+    AttnArgs a{};
+    // short sequences: state and gate in the attention's launch, unless some other kernel wants them, or in launches of their own with the
+    // same bits where each stage is being timed
+    const bool direct = w.ride.wgs && state_wgs == STATE_WGS && use_linear && large_tile && !topk && (!unfused || emit_in_attn) && p->workspace_bytes >= w.total;
+    const bool ride = direct && timing != 1;
+    if (ride && rope) {
+        e = launch_rope_pack(p->rope_cos, p->rope_sin, (size_t)p->N * (p->d / 2), (uint32_t *)(ws + w.rope_tab), st);
+        if (e != hipSuccess) return give_back(), hip_fail(e, "rotary table launch");
+    }
+    if (ride) {
+        RideArgs &r = a.ride;
+        const int chunks = (Dm + 511) / 512;
+        r.wgs = w.ride.wgs; r.nparts = need_gate ? w.nparts : 0; r.gate_tasks = need_gate ? w.ride.gate_tasks : 0;
+        r.riders = (p->d == 128 ? 8 : 2) + (need_gate ? 1 : 0); r.polls = polls;
+        r.crowded = w.ride.crowded;
+        r.full = (uint64_t)r.riders + 1024ull * (2 * (((p->N + 63) / 64 + 3) / 4));
+        r.tag = next_piece_tag() << 18; r.words = (uint64_t *)(ws + w.ride_words);
+        r.x_t = p->x_t; r.w_gate = p->w_gate; r.b_gate = p->b_gate; r.gate_tok = chunks <= 2 ? 4 : chunks <= 5 ? 2 : 1;
+        r.gate_sums = (float *)(ws + w.ride_gate); r.hfrag = (u16 *)(ws + w.hfrag); r.Z = (float *)(ws + w.Z);
+        r.tau = dropping ? p->drop_threshold : 0.f; r.drop = drop; r.dropped_out = dropping ? p->dropped_out : nullptr;
+        gate_here = true;
+    } else if (use_linear) {
         // the gate's pass 1 rides in the state's launch, except where its result is needed first (dropping) or each stage is
         // being timed
         const GateArgs g{p->x_t, p->w_gate, p->b_gate, Dm, (float *)(ws + w.gate_partial), w.nparts};
-        const bool with_state = need_gate && !dropping && timing != 1 &&
+        const bool with_state = need_gate && !dropping && timing != 1 && !direct &&
                                 (bf16 ? state_gate_fits(g, p->B, BH, w.P) : state_gate_f32_fits(g, p->B, BH, p->d));
         if (need_gate && !with_state) {
             e = launch_gate_partial(p->x_t, p->w_gate, p->b_gate, p->B, p->N, Dm, bf16, (float *)(ws + w.gate_partial), w.nparts, st);
@@ -559,7 +600,11 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
                 e = launch_rope_pack(p->rope_cos, p->rope_sin, (size_t)p->N * (p->d / 2), (uint32_t *)(ws + w.rope_tab), st);
                 if (e != hipSuccess) return give_back(), hip_fail(e, "rotary table launch");
             }
-            if (with_state)
+            if (direct) {
+                e = launch_state_direct((const u16 *)p->k, (const u16 *)p->v, p->B, p->H, p->N, p->d, drop, rope ? (const uint32_t *)(ws + w.rope_tab) : nullptr,
+                                        (u16 *)(ws + w.hfrag), (float *)(ws + w.Z), st);
+                f.P = 0;
+            } else if (with_state)
                 e = launch_state_gate_bf16((const u16 *)p->k, (const u16 *)p->v, BH, p->N, p->d, (float *)(ws + w.state_partial), state_wgs, g, p->B, st,
                                            rope ? (const uint32_t *)(ws + w.rope_tab) : nullptr);
             else
@@ -575,7 +620,7 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
         // fp32: a launch saved against every workgroup of the attention adding up the gate's partial sums.  2048 workgroups (16 queries each):
         // 71.2 -> 70.6 us at H = 2, N = 16384, one kept block; 3072, H = 12, N = 4096: 54.6 -> 54.9; 4096, H = 8, N = 8192: 73.9 -> 76.8
         gate_here = !bf16 && !dropping && timing != 1 && (!need_gate || (int64_t)BH * ((p->N + 15) / 16) <= 2048);
-        if (!gate_here && (bf16 || f.do_gate)) {       // fp32: the state kernel wrote Hs, Z directly
+        if (!gate_here && (f.do_gate || f.P)) {        // no part of the state where its kernel wrote Hs, Z directly
             e = launch_finalize(f, st);
             if (e != hipSuccess) return give_back(), hip_fail(e, "finalize launch");
         }
@@ -585,7 +630,6 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     }
     mark(3);
 
-    AttnArgs a{};
     a.q = p->q; a.k = p->k; a.v = p->v; a.out = p->out;
     a.row_ptr = p->row_ptr; a.col_idx = p->col_idx;
     a.B = p->B; a.H = p->H; a.N = p->N; a.nb = (p->N + 63) / 64; a.T = p->T; a.HW = p->Hh * p->W; a.D = p->d;
@@ -598,21 +642,19 @@ salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p)
     a.coef = use_linear ? (const float *)(ws + w.coef) : nullptr;
     a.eps = p->eps;
     a.o_sparse_dbg = p->o_sparse_dbg; a.o_linear_dbg = unfused ? nullptr : p->o_linear_dbg;
-    // full projection: the attention kernel's epilogue writes O_l, in the projection's operand order, next to O_s.  A pass of its own over Q
-    // took 51-55 us at N = 32760, 12 heads: layer call 872 -> 849 us.
-    const bool emit_in_attn = full_proj && large_tile && !topk && !rope && !p->o_sparse_dbg && !p->o_linear_dbg &&
-                              !(p->flags & SALAD_FLAG_UNFUSED_EPILOGUE);
     a.write_sparse_only = unfused && !emit_in_attn;
     a.emit_ol = emit_in_attn ? (u16 *)(ws + w.ol) : nullptr;
-    a.drop = drop;
+    a.drop = ride ? nullptr : drop;          // riding: the kernel finds out itself
     if (gate_here) {
         a.gate_here = 1; a.gate_nparts = need_gate ? w.nparts : 0;
         a.gate_partial = (const float *)(ws + w.gate_partial); a.s_dev = p->s_dev; a.head_scale = p->head_scale;
-        a.lambda = p->lambda; a.s_out = p->s_out;
+        a.lambda = p->lambda; a.s_out = p->s_out; a.coef_out = bf16 ? (float *)(ws + w.coef) : nullptr;
     }
     a.variant = attn_variant;
     if (split) {
         a.sp_full = w.split.full; a.sp_pieces = w.split.pieces;
+        // riders' compute units are not there for pieces (but for calls that may drop the linear branch, whose sparse branch has the bits that it has alone)
+        if (ride && !dropping) a.sp_pieces = std::min(a.sp_pieces, std::max(2, (256 - std::min(w.ride.wgs, 256)) / w.split.rest));
         a.sp_o = (uint64_t *)(ws + w.sp_o); a.sp_ml = (uint64_t *)(ws + w.sp_ml); a.sp_count = (uint64_t *)(ws + w.sp_count);
         a.sp_tag = sp_tag;
     }

@@ -52,6 +52,9 @@ struct GateArgs { const void *x_t; const float *w; float bias; int D; float *par
 bool state_gate_fits(const GateArgs &g, int B, int BH, int P);
 hipError_t launch_state_gate_bf16(const u16 *k, const u16 *v, int BH, int N, int D, float *partial, int target_wgs, const GateArgs &g, int B,
                                   hipStream_t st, const uint32_t *rope_tab);
+// Short sequences (ride_plan): Hs as fragments and Z in one launch, without partial states.  The sums' order is its own.
+hipError_t launch_state_direct(const u16 *k, const u16 *v, int B, int H, int N, int D, const int32_t *drop, const uint32_t *rope_tab, u16 *hfrag, float *Z,
+                               hipStream_t st);
 bool state_gate_f32_fits(const GateArgs &g, int B, int BH, int D);
 hipError_t launch_state_gate_f32(const float *k, const float *v, int BH, int N, int D, float *Hs, float *Z, const GateArgs &g, int B,
                                  hipStream_t st);
@@ -80,8 +83,25 @@ struct FinalizeArgs {
 };
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 
+// ---- state and gate by workgroups of the attention's launch (linear_ride.h) ---------------------------
+constexpr int RIDE_STRIDE = 16;
+constexpr int RIDE_POLLS = 1 << 14;         // about 20 ms
+struct RideArgs {
+    int wgs, gate_tasks;            // workgroups, a multiple of 8 (0: none ride); shares of a sample's gate among them
+    int crowded;                    // tiles that are not cut stay whole, too: there are no compute units for two workgroups each
+    int riders, polls;              // that count in a head's word (the last of a sample's gate tasks for all of them); how often a tile looks before it does their work
+    uint64_t full, tag, *words;     // count of a head's word at the end; this call's tag; [B H + B], RIDE_STRIDE apart
+    const void *x_t; const float *w_gate; float b_gate;
+    int gate_tok, nparts;           // tokens that a wave of gate_part takes at a time; its partial sums (0: s_dev has the scale)
+    float *gate_sums;               // [B][4 nparts]: its waves'
+    u16 *hfrag; float *Z;
+    float tau;                      // > 0: samples whose scale is below it have no linear branch; drop, dropped_out [B] (may be null) say so
+    int32_t *drop, *dropped_out;
+};
+
 // ---- sparse attention + fused linear apply / scale / sum -------------------------------------------
 struct AttnArgs {
+    RideArgs ride;
     const void *q, *k, *v;
     void *out;
     const int32_t *row_ptr, *col_idx;
@@ -123,10 +143,10 @@ struct AttnArgs {
     int sp_full, sp_pieces;
     uint64_t *sp_o, *sp_ml, *sp_count, sp_tag;
     // fp32 kernel, gate_here: it reduces the gate (gate_nparts partial sums per sample, or none: s_dev) and scales by lambda, head_scale
-    // itself instead of reading coef, and writes s_out (may be null)
+    // itself instead of reading coef, and writes s_out (may be null).  Riders in the large-tile kernel's launch: the same, and coef_out.
     int gate_here, gate_nparts;
     const float *gate_partial, *s_dev, *head_scale;
-    float lambda, *s_out;
+    float lambda, *s_out, *coef_out;
     // filled in by the large-tile kernel's launcher: pieces a tile for which each has a compute unit to itself; an XCD's pieces over the
     // pieces of a tile, rounded up; multiply-high inverses
     int sp_alone, sp_rows;
@@ -146,6 +166,9 @@ bool attn_takes_large_tile(int d, int nb, int N, int T, bool temporal, int varia
 // cut: lists may be long enough to be cut (which needs scratch), else only rows are dealt
 struct SplitPlan { int full, rest, pieces; bool cut; };
 SplitPlan split_plan(int BH, int nb, int d);
+// which workgroups ride in the large-tile kernel's launch, if any (wgs 0: none)
+struct RidePlan { int wgs, gate_tasks, crowded; };
+RidePlan ride_plan(int B, int H, int N, int d, const SplitPlan &split);
 hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int H, int nb, uint32_t *lists,
                              int32_t *counts, hipStream_t st);
 hipError_t launch_sparse_attn_f32(const AttnArgs &a, hipStream_t st);

@@ -26,7 +26,7 @@
 //     ones (row_sum); the block maximum is not computed unless a block's sums show that some logit exceeds the running
 //     reference by more than 13 binades (the reference then moves to the true maximum and the block is redone).
 //   * Epilogue: the bf16 fragments of the linear state are staged once per workgroup in LDS.
-#include "salad_internal.h"
+#include "linear_ride.h"
 
 namespace salad {
 
@@ -99,6 +99,16 @@ __device__ inline void lds_dma4(const void *gptr, unsigned lds_addr_uniform)
                  :
                  : "s"(lds_addr_uniform), "v"(gptr)
                  : "memory", "m0");
+}
+
+// The same past the L2 of this XCD: for what a workgroup on another one has written in the same launch.
+__device__ inline void lds_dma4_device(const void *gptr, unsigned lds_addr_uniform)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off sc1" : : "s"(lds_addr_uniform), "v"(gptr) : "memory", "m0");
+}
+__device__ inline void lds_dma16_device(const void *gptr, unsigned lds_addr_uniform)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off sc1" : : "s"(lds_addr_uniform), "v"(gptr) : "memory", "m0");
 }
 
 // x / d for any x and d >= 1, magic = floor(2^32 / d) (2^32 - 1 for d = 1): the multiply-high is at most one too small
@@ -227,7 +237,9 @@ hipError_t launch_tile_lists(const int32_t *row_ptr, const int32_t *col_idx, int
 // barriers are independent: N = 32760, 24 heads at 90 % 832 -> 725 us.  At d = 128 it needs 400 registers, so one wave per SIMD, and
 // the loads, which hold a wave for 60 cycles each, and the scalar code have nothing to run under: dense 5421 -> 5564 us.
 // EMIT (d = 128, MODE 0 without ROPE and DBG): the linear branch goes, unscaled, to a.emit_ol instead of being added to O_s.
-template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, int QS = 1, bool EMIT = false>
+// RIDE (MODE 0, QS = 1): the launch's first workgroups compute the linear branch's state and gate (linear_ride.h), for which the
+// epilogue waits.
+template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, int QS = 1, bool EMIT = false, bool RIDE = false>
 __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
 {
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
@@ -245,7 +257,17 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     constexpr bool TOPK = MODE == 1, GATHER = MODE == 2;
     // chunk swizzle of the output staging
     auto oswz = [](int row) INL -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
-    const int g = blockIdx.x;
+    float (*ride_small)[32] = nullptr;
+    if constexpr (RIDE) {
+        static_assert(MODE == 0 && QS == 1, "the riders are 512 threads, and have no use in the modes of the dynamic mask");
+        __shared__ float small[DIRECT_WAVES][32];
+        ride_small = small;
+        if ((int)blockIdx.x < a.ride.wgs) {
+            if ((int)blockIdx.x < a.B * (a.H * slices_per_head(D) + a.ride.gate_tasks)) ride<D, ROPE>(blockIdx.x, smem, small);
+            return;
+        }
+    }
+    const int g = blockIdx.x - (RIDE ? a.ride.wgs : 0);
     int L, piece = 0, pieces = 1;
     if (SPLIT) {      // an XCD's share: its run of whole tiles, then its run of pieces
         const int fx = a.sp_full / 8, np = (total - a.sp_full) * a.sp_pieces, px = (np + 7) / 8;
@@ -256,8 +278,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             // QS 2: every sp_pieces-th of the run first, then the next ones.  Workgroups go to the compute units in turn, two to each, and those
             // without work leave at once; in plain order the first pieces, all that a short list has, came to lie in pairs on half of the
             // units.  24 heads of 64, 768 tiles, 6 entries 65.8 -> 60.9 us, 40 heads, 640 tiles, 6 entries 63.7 -> 56.9.  With one workgroup a
-            // unit there is nothing to pair.
-            if (QS == 2) {
+            // unit there is nothing to pair, but behind riders those with work have to come first.
+            if (QS == 2 || RIDE) {
                 const int col = (int)div_by((unsigned)r, (unsigned)a.sp_rows, a.rows_magic);
                 r = (r - col * a.sp_rows) * a.sp_pieces + col;
             }
@@ -320,9 +342,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             list0 = n * piece / pieces;      // this piece's first entry
             n = n * (piece + 1) / pieces - list0;
         } else {                             // not worth cutting
+            const bool rows = ROW_PAIRS && !(RIDE && a.ride.crowded);
             pieces = 1;
-            if (piece >= (ROW_PAIRS ? 2 : 1)) return;
-            if (ROW_PAIRS) my_rows = piece;
+            if (piece >= (rows ? 2 : 1)) return;
+            if (rows) my_rows = piece;
         }
     }
     constexpr int AK = NK - 1, AV = NV - 2;     // how far ahead of an iteration K and V are fetched
@@ -731,14 +754,64 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         settle(0, true, false, e, psum);
     };
 
-    const bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[smp]);   // pruned sample (Sec. 4.3): out = O_s
+    bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[smp]);   // pruned sample (Sec. 4.3): out = O_s
     const u16 *hf = a.hfrag + (size_t)bh * D * D;
-    const float coef = lin ? a.coef[bh] : 0.f;
+    float coef = lin && !RIDE ? a.coef[bh] : 0.f;
+    // RIDE: the sample's scale from the gate's partial sums, every wave for itself, in the order of finalize_kernel; tile 0 of a head writes it down
+    auto reduce_gate = [&]() INL {
+        CallRef c = call_args();
+        float t[4] = {};
+        const int nparts = c.ride.nparts;
+        const float *p = c.ride.gate_sums + (size_t)smp * nparts * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            for (int j = i * 64 + lane; j < nparts; j += 256)
+                t[i] += (ride_loadf(p + j * 4) + ride_loadf(p + j * 4 + 1)) + (ride_loadf(p + j * 4 + 2) + ride_loadf(p + j * 4 + 3));
+        float sum = (t[0] + t[2]) + (t[1] + t[3]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        const float sc = nparts > 0 ? sum / (float)N : c.s_dev[smp];
+        const bool dropped = c.ride.tau > 0.f && sc < c.ride.tau;      // Sec. 4.3: out = O_s
+        coef = dropped ? 0.f : c.lambda * (c.head_scale ? c.head_scale[h] : 1.f) * sc;
+        if (tile == 0 && tid == 0) {
+            if (h == 0 && c.s_out) c.s_out[smp] = sc;
+            c.coef_out[bh] = coef;
+            if (h == 0 && c.ride.tau > 0.f) {
+                c.ride.drop[smp] = dropped;
+                if (c.ride.dropped_out) c.ride.dropped_out[smp] = dropped;
+            }
+        }
+        if (__builtin_amdgcn_readfirstlane(dropped)) lin = false;
+    };
     // the D x D linear-state fragments (32 KB at d = 128) for the epilogue, staged into the K ring once it is idle, and the normaliser's
     // sums into the V slot two after the last block's
     int v_last = 0;                         // V-ring slot of the last block: the only tile still read after the loop
     auto z_lds = [&]() INL -> float * { return reinterpret_cast<float *>(Vb + ((v_last + 2) & (NV - 1)) * TILE); };
     auto stage_state = [&]() INL {
+        if constexpr (RIDE) {
+            // counted at once: the word can go back to 0 before the riders are seen in it, which says the same
+            if (tid == 0) {
+                CallRef c = call_args();
+                const uint64_t now = ride_count(c, bh, RIDE_TILE * (my_rows < 0 ? 2 : 1), c.ride.full), tag = c.ride.tag;
+                const int riders = c.ride.riders;
+                bool there = (int)(now & (RIDE_TILE - 1)) == riders;
+                for (int i = c.ride.polls; !there && i > 0; --i) {
+                    __builtin_amdgcn_s_sleep(2);
+                    const uint64_t x = ride_load(ride_word(c, bh));
+                    there = (x & ~RIDE_COUNT) != tag || (int)(x & (RIDE_TILE - 1)) == riders;
+                }
+                ride_small[0][0] = there ? 1.f : 0.f;
+            }
+            __syncthreads();
+            if (__builtin_expect(__builtin_amdgcn_readfirstlane(ride_small[0][0] == 0.f), 0)) {
+                __syncthreads();
+                ride_alone<D, ROPE>(bh, smem, ride_small);
+            }
+            if ((int)wave_u * 64 < D) lds_dma4_device(a.Z + (size_t)bh * D + wave_u * 64 + lane, lds_addr_of(z_lds() + wave_u * 64));
+#pragma unroll
+            for (int i = 0; i < D * D / (NT * 8); ++i) lds_dma16_device(hf + (size_t)(i * NT + tid) * 8, lds_addr_of(Kb + (i * NT + wave * 64) * 8));
+            return;
+        }
         if ((int)wave_u * 64 < D) lds_dma4(a.Z + (size_t)bh * D + wave_u * 64 + lane, lds_addr_of(z_lds() + wave_u * 64));
 #pragma unroll
         for (int i = 0; i < D * D / (NT * 8); ++i) lds_dma16(hf + (size_t)(i * NT + tid) * 8, lds_addr_of(Kb + (i * NT + wave * 64) * 8));
@@ -848,7 +921,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         v_last = vslot ? vslot - 1 : NV - 1;
-        if (lin && !(SPLIT && pieces > 1)) stage_state();
+        if (lin && !RIDE && !(SPLIT && pieces > 1)) stage_state();
         if (ROPE && lin && !(SPLIT && pieces > 1)) load_angles();
         if ((e_prev & mybit) != 0) finish_prev(e_prev, Vb + v_last * TILE);
     }
@@ -931,7 +1004,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // ---- epilogue ---------------------------------------------------------------------------------
     float lin_scale[QS], inv_den[QS];
     if (lin) {
-        if (n == 0 || (SPLIT && pieces > 1)) { stage_state(); if (ROPE) load_angles(); }
+        if (RIDE || n == 0 || (SPLIT && pieces > 1)) { stage_state(); if (ROPE) load_angles(); }
+        if (RIDE) reduce_gate();
 #pragma unroll
         for (int u = 0; u < QS; ++u)
 #pragma unroll
@@ -1115,11 +1189,35 @@ SplitPlan split_plan(int BH, int nb, int d)
     p.pieces = p.rest ? round / p.rest : 1;
     if (p.pieces > SPLIT_MAX_PIECES) p.pieces = SPLIT_MAX_PIECES;
     p.cut = p.pieces > 1 && nb >= 2 * SPLIT_MIN_ENTRIES;
+    if (p.cut && p.pieces > nb / SPLIT_MIN_ENTRIES) p.pieces = nb / SPLIT_MIN_ENTRIES;      // no list has entries for more
     if (!p.cut) p.pieces = p.pieces > 1 && round == 256 ? 2 : 1;      // no list of this length is cut, but rows can be dealt to two workgroups
     return p;
 }
 
-template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false, int QS = 1, bool EMIT = false>
+RidePlan ride_plan(int B, int H, int N, int d, const SplitPlan &split)
+{
+    // Where all tiles fit one round and riders, who read 192 bytes a token at some 30 GB/s, are not much later than the tiles come to their epilogues.
+    // Layer calls, three launches -> one (us): 12 heads, N = 256 19.2 -> 11.5, 1024 23.8 -> 14.1, 1950 29.8 -> 24.8, 3000 32.4 -> 24.6, dense 83.7 -> 74.0;
+    // 2 heads, N = 4000 32.0 -> 24.8, 6400 30.8 -> 28.7, 9000 35.7 -> 39.0; 40 heads, N = 256 31.6 -> 18.9, 1000 37.6 -> 25.2, 1500 42.7 -> 37.2; 64 heads, N = 512
+    // 44.6 -> 35.4, 1000 (768 riders and tiles) 53.8 -> 53.7; 24 heads of 64, N = 1000 20.2 -> 13.8, 40 heads of 64, N = 512 20.2 -> 13.3.
+    RidePlan p{};
+    const int BH = B * H, nparts = gate_num_parts(N);
+    const long long slices = (long long)BH * slices_per_head(d);
+    if (N > 6400 || split.full || slices + split.rest > 640 || query_sets(d, (N + 63) / 64, split.rest) != 1) return p;
+    // 32 shares of the gate, or 16 at the least where that gives every workgroup with work a compute unit: those of tiles dealt by rows, or else of
+    // whole tiles (12 heads, N = 1500: 17.0 us with 16 and rows, 19.8 with 32 and whole tiles; 24 heads of 64, N = 1950: 18.7 and 24.5)
+    int shares = 256 - (int)slices - 2 * split.rest;
+    if (shares < 16) shares = 256 - (int)slices - split.rest;
+    if (shares < 16 || shares > 32) shares = 32;
+    p.gate_tasks = shares / B < 1 ? 1 : shares / B;
+    if (p.gate_tasks > (nparts + 1) / 2) p.gate_tasks = (nparts + 1) / 2;
+    const int riders = (int)slices + B * p.gate_tasks;
+    p.wgs = (riders + 7) & ~7;
+    p.crowded = p.wgs + 2 * split.rest > 256 && p.wgs + split.rest <= 256;
+    return p;
+}
+
+template <bool DBG, int MODE = 0, bool ROPE = false, int D = 128, bool SPLIT = false, int QS = 1, bool EMIT = false, bool RIDE = false>
 static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
 {
     const int ntiles = (a.nb + 3) / 4;
@@ -1128,7 +1226,7 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     if (!large_tile_list_fits(D, a.nb)) return hipErrorInvalidValue;
     const int list_cap = tile_list_cap(a.nb);
     const size_t lds = v5_ring_bytes(D) + (size_t)list_cap * 4;
-    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT, QS, EMIT>;
+    auto kern = sparse_attn_v5_kernel<D, DBG, MODE, ROPE, SPLIT, QS, EMIT, RIDE>;
     static bool attr_done[16] = {};
     if (hipError_t e = dyn_lds_attr_once(reinterpret_cast<const void *>(kern), V5_MAX_DYN, attr_done); e != hipSuccess) return e;
     const int px = SPLIT ? ((total - a.sp_full) * a.sp_pieces + 7) / 8 : 0;      // pieces of an XCD
@@ -1139,8 +1237,8 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
         b.sp_alone = 256 / (total - a.sp_full);
         b.sp_rows = (px + a.sp_pieces - 1) / a.sp_pieces; b.rows_magic = magic(b.sp_rows);
     }
-    const int grid = SPLIT ? a.sp_full + (QS == 2 ? b.sp_rows * a.sp_pieces : px) * 8 : per_xcd * 8;
-    launch_kernel(kern, dim3(grid), dim3(512 / QS), lds, st, b, ntiles, total, per_xcd, list_cap);
+    const int grid = SPLIT ? a.sp_full + (QS == 2 || RIDE ? b.sp_rows * a.sp_pieces : px) * 8 : per_xcd * 8;
+    launch_kernel(kern, dim3(grid + (RIDE ? a.ride.wgs : 0)), dim3(512 / QS), lds, st, b, ntiles, total, per_xcd, list_cap);
     return take_launch_status();
 }
 
@@ -1153,11 +1251,21 @@ hipError_t launch_sparse_attn_v5(const AttnArgs &a, hipStream_t st)
             if (split) return dbg ? launch_v5<true, 0, false, 64, true, 2>(a, st) : launch_v5<false, 0, false, 64, true, 2>(a, st);
             return dbg ? launch_v5<true, 0, false, 64, false, 2>(a, st) : launch_v5<false, 0, false, 64, false, 2>(a, st);
         }
+        if (a.ride.wgs && split) return dbg ? launch_v5<true, 0, false, 64, true, 1, false, true>(a, st) : launch_v5<false, 0, false, 64, true, 1, false, true>(a, st);
+        if (a.ride.wgs) return dbg ? launch_v5<true, 0, false, 64, false, 1, false, true>(a, st) : launch_v5<false, 0, false, 64, false, 1, false, true>(a, st);
         if (split) return dbg ? launch_v5<true, 0, false, 64, true>(a, st) : launch_v5<false, 0, false, 64, true>(a, st);
         return dbg ? launch_v5<true, 0, false, 64>(a, st) : launch_v5<false, 0, false, 64>(a, st);
     }
     if (a.g_desc) return launch_v5<false, 2>(a, st);
     if (a.topk_mask) return dbg ? launch_v5<true, 1>(a, st) : launch_v5<false, 1>(a, st);
+    if (a.ride.wgs) {
+        if (a.emit_ol && (dbg || a.rope_tab)) return hipErrorInvalidValue;
+        if (a.emit_ol) return split ? launch_v5<false, 0, false, 128, true, 1, true, true>(a, st) : launch_v5<false, 0, false, 128, false, 1, true, true>(a, st);
+        if (a.rope_tab && split) return dbg ? launch_v5<true, 0, true, 128, true, 1, false, true>(a, st) : launch_v5<false, 0, true, 128, true, 1, false, true>(a, st);
+        if (a.rope_tab) return dbg ? launch_v5<true, 0, true, 128, false, 1, false, true>(a, st) : launch_v5<false, 0, true, 128, false, 1, false, true>(a, st);
+        if (split) return dbg ? launch_v5<true, 0, false, 128, true, 1, false, true>(a, st) : launch_v5<false, 0, false, 128, true, 1, false, true>(a, st);
+        return dbg ? launch_v5<true, 0, false, 128, false, 1, false, true>(a, st) : launch_v5<false, 0, false, 128, false, 1, false, true>(a, st);
+    }
     if (a.emit_ol) {
         if (dbg || a.rope_tab) return hipErrorInvalidValue;
         return split ? launch_v5<false, 0, false, 128, true, 1, true>(a, st) : launch_v5<false, 0, false, 128, false, 1, true>(a, st);

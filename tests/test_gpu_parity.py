@@ -398,6 +398,66 @@ def test_workspace_without_room_for_the_pieces(oracle):
     assert errors(Z.cpu().numpy().astype(np.float64), ref["Z"])[1] < 2e-6
 
 
+@pytest.mark.parametrize("B,H,d,grid,keep,opt", [
+    (1, 2, 128, (1, 1, 40), 1, ""),            # one block, its riders with 3 of 8 waves' tokens; one gate share
+    (3, 5, 128, (3, 5, 17), 2, "drop"),        # 255 tokens, a last group of 15; samples pruned and not
+    (1, 12, 128, (4, 16, 16), 4, ""),          # whole groups, tiles dealt by rows
+    (1, 12, 128, (5, 15, 26), 31, ""),         # lists that are cut, with riders on the compute units of other pieces
+    (1, 16, 128, (5, 15, 26), 6, ""),          # more riders and tiles than compute units
+    (1, 40, 128, (2, 9, 9), 2, "rope"),        # a row of 5120 channels
+    (1, 64, 128, (1, 7, 9), 1, ""),            # 8192
+    (2, 3, 128, (3, 5, 13), 3, "proj"),
+    (1, 3, 64, (3, 13, 14), 9, "drop"),        # 64-wide heads; a row of 192 channels, a ragged chunk
+    (1, 40, 64, (2, 16, 16), 8, "given"),      # the scale is given: no gate
+    (1, 1, 64, (5, 32, 40), 20, ""),           # the longest sequence (6400)
+])
+def test_state_and_gate_within_the_attention_launch(B, H, d, grid, keep, opt):
+    """Short sequences: riders in the attention's launch give the bits of the launches of their own that the per-stage timing mode makes, on a
+    workspace that holds anything, then another call's leavings; and so does a tile that does not wait for them (a bound of 0 on its wait)."""
+    w = wl.small(f"within-{H}-{d}", B, H, d, *grid, "bf16", 0.5, seed=700 + H)
+    kinds, kept = wl.head_kinds(w), [min(keep, w.nb)] * H
+    row_ptr, col_idx = sb.salad_block_mask(*grid, w.block, kept)
+    ws = sb.Workspace(B, H, w.N, d, sb.SALAD_BF16, full_proj=opt == "proj", rope=opt == "rope")
+    ws.buf.fill_(0x5a)
+    for seed in (1, 2):
+        inp = {k: v.copy() for k, v in wl.make_inputs(wl.small("x", B, H, d, *grid, "bf16", 0.5, seed=700 + H + seed)).items()}
+        dev = upload(w, inp)
+        s_out, dropped = torch.zeros(B, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
+        kw = dict(lam=20.0, eps=w.eps, workspace=ws, s_out=s_out, head_scale=dev["head_scale"])
+        if opt == "given":
+            kw["s"] = torch.rand(B, device="cuda")
+        else:
+            kw.update(x_t=dev["x_t"], w_gate=dev["w_gate"])
+        if opt == "drop":
+            s = sb.salad_gate_fwd(dev["x_t"], dev["w_gate"])
+            kw.update(drop_threshold=float(s.max()) if B > 1 else 1e-6, dropped_out=dropped)       # all but the largest, or none
+        if opt == "rope":
+            kw.update(zip(("rope_cos", "rope_sin"), (torch.from_numpy(t).cuda() for t in wl.rope_tables(*grid, d))))
+        if opt == "proj":
+            kw.update(head_scale=None, w_proj=torch.randn(H * d, H * d, device="cuda").bfloat16() / (H * d) ** 0.5)
+
+        def call(polls=None):
+            out = torch.full_like(dev["q"], float("nan"))
+            s_out.fill_(float("nan"))
+            dropped.fill_(-1)
+            p, keepalive = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, grid, row_ptr, col_idx, kinds, **kw)
+            sb._check(sb.lib().salad_sparse_linear_attn_fwd(C.byref(p)) if polls is None else sb.lib().salad_fwd_with_polls(C.byref(p), polls))
+            torch.cuda.synchronize()
+            return out, s_out.clone(), dropped.clone()
+
+        sb.salad_timing_enable(1)
+        try:
+            ref = call()
+        finally:
+            sb.salad_timing_read(True)
+            sb.salad_timing_enable(0)
+        for polls in (None, 0, None):
+            for got, want in zip(call(polls), ref):
+                assert torch.equal(got, want), (opt, polls, seed)
+        if opt == "drop" and B > 1:
+            assert sorted(ref[2].tolist()) == [0] + [1] * (B - 1)
+
+
 def test_sparse_branch_alone_is_one_launch():
     """lambda = 0 with prebuilt lists on a grid whose tiles may be cut: the attention kernel and nothing else, counted in a
     captured graph; replays on a workspace that held anything give the bits of the eager call."""
