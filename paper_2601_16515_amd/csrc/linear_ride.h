@@ -175,7 +175,7 @@ __device__ inline __attribute__((always_inline)) void ride_gate(const void *x_t,
 // LDS), so a wave has a ring of its own, waits for its own loads only and meets the others once, at the end, where the 8 accumulators are
 // added in wave order.  Operands come out of LDS transposed (ds_read_b64_tr_b16): the contraction is over tokens, the rows of the
 // stored tensors.  Bound by what a compute unit reads, about 30 GB/s whatever is in flight: 192 bytes a token.  Slices of 32 x 32 are twice as
-// many workgroups for two thirds of the bytes: 5 heads, N = 4000 33.8 us a call in place of 26.3.
+// many workgroups for two thirds of the bytes: 12 heads, N = 1950 28.8 us a call in place of 24.8, 8 heads, N = 5000 37.1 and 26.2, 2 heads the same.
 // ------------------------------------------------------------------------------------------------
 constexpr int DIRECT_WAVES = 8;
 constexpr int SLICE_COLS = 2;             // times 32 columns of a slice

@@ -1198,12 +1198,13 @@ RidePlan ride_plan(int B, int H, int N, int d, const SplitPlan &split)
 {
     // Where all tiles fit one round and riders, who read 192 bytes a token at some 30 GB/s, are not much later than the tiles come to their epilogues.
     // Layer calls, three launches -> one (us): 12 heads, N = 256 19.2 -> 11.5, 1024 23.8 -> 14.1, 1950 29.8 -> 24.8, 3000 32.4 -> 24.6, dense 83.7 -> 74.0;
-    // 2 heads, N = 4000 32.0 -> 24.8, 6400 30.8 -> 28.7, 9000 35.7 -> 39.0; 40 heads, N = 256 31.6 -> 18.9, 1000 37.6 -> 25.2, 1500 42.7 -> 37.2; 64 heads, N = 512
+    // 8 heads, N = 5200 37.2 -> 27.5, 6400 41.3 -> 43.2, dense 167 -> 171; 2 heads, N = 4000 32.0 -> 24.8, 9000 35.7 -> 39.0;
+    // 40 heads, N = 256 31.6 -> 18.9, 1000 37.6 -> 25.2, 1500 42.7 -> 37.2; 64 heads, N = 512
     // 44.6 -> 35.4, 1000 (768 riders and tiles) 53.8 -> 53.7; 24 heads of 64, N = 1000 20.2 -> 13.8, 40 heads of 64, N = 512 20.2 -> 13.3.
     RidePlan p{};
     const int BH = B * H, nparts = gate_num_parts(N);
     const long long slices = (long long)BH * slices_per_head(d);
-    if (N > 6400 || split.full || slices + split.rest > 640 || query_sets(d, (N + 63) / 64, split.rest) != 1) return p;
+    if (N > 5400 || split.full || slices + split.rest > 640 || query_sets(d, (N + 63) / 64, split.rest) != 1) return p;
     // 32 shares of the gate, or 16 at the least where that gives every workgroup with work a compute unit: those of tiles dealt by rows, or else of
     // whole tiles (12 heads, N = 1500: 17.0 us with 16 and rows, 19.8 with 32 and whole tiles; 24 heads of 64, N = 1950: 18.7 and 24.5)
     int shares = 256 - (int)slices - 2 * split.rest;

@@ -409,7 +409,7 @@ def test_workspace_without_room_for_the_pieces(oracle):
     (2, 3, 128, (3, 5, 13), 3, "proj"),
     (1, 3, 64, (3, 13, 14), 9, "drop"),        # 64-wide heads; a row of 192 channels, a ragged chunk
     (1, 40, 64, (2, 16, 16), 8, "given"),      # the scale is given: no gate
-    (1, 1, 64, (5, 32, 40), 20, ""),           # the longest sequence (6400)
+    (1, 1, 64, (5, 30, 36), 20, ""),           # the longest sequence (5400)
 ])
 def test_state_and_gate_within_the_attention_launch(B, H, d, grid, keep, opt):
     """Short sequences: riders in the attention's launch give the bits of the launches of their own that the per-stage timing mode makes, on a
