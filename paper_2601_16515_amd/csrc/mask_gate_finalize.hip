@@ -159,13 +159,6 @@ hipError_t launch_gate_partial(const void *x_t, const float *w, float bias, int 
 // The first workgroup reduces the gate partial sums (or takes the caller's s), writes s and the
 // per-(b, h) coefficient lambda * a_h * s_b of the residual sum (Alg. 1, Sec. 4.2).
 // ------------------------------------------------------------------------------------------------
-__device__ inline u16 f32_to_bf16_rne(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (u16)(u >> 16);
-}
-
 __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a, int gate_blocks, int blocks_per_head)
 {
     const int D = a.D;

@@ -11,6 +11,13 @@ namespace salad {
 
 typedef unsigned short u16;
 
+__device__ inline u16 f32_to_bf16_rne(float f)
+{
+    uint32_t u = __float_as_uint(f);
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (u16)(u >> 16);
+}
+
 // ---- block mask -------------------------------------------------------------------------------
 struct MaskArgs {
     int32_t nb, H;

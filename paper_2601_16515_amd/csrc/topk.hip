@@ -6,7 +6,8 @@
 // The selection is an integer decided by floating point, so its arithmetic is fixed: fp32 throughout, a block's sum
 // taken token by token in ascending order and divided by the token count, a score accumulated over the channels in
 // ascending order with a fused multiply-add, a block replaces a kept one only on a strictly larger score (ties go
-// to the lower index).  No fast-math: the division and the fused multiply-adds are the IEEE ones.
+// to the lower index).  No fast-math: the division and the fused multiply-adds are the IEEE ones.  (Scores from the matrix cores decide where they
+// differ by more than they can be off; see topk_select_kernel.)
 #include "salad_internal.h"
 
 namespace salad {
@@ -65,104 +66,265 @@ hipError_t launch_kblock_mean(const u16 *k, int BH, int N, int key_block, int nb
     return take_launch_status();
 }
 
-// grid (ceil(N / 256), BH), 256 threads: a thread owns one query and keeps one score accumulator per key block
-// (NBK of them, the smallest instantiation >= nbk: the chains are independent, each runs over the channels in
-// ascending order).  The head's block means sit in LDS; every lane reads the same word (broadcast).  The best SLOTS
-// (4 or 8, >= topk) scores are then collected in descending order, blocks in ascending order; the first topk of them
-// are the selection.
-template <int NBK, int SLOTS>
-__global__ __launch_bounds__(256) void topk_select_kernel(const u16 *__restrict__ q, const float *__restrict__ means,
-                                                          int N, int nbk, int topk,
-                                                          unsigned long long *__restrict__ mask)
-{
-    __shared__ float sm[NBK * D];
-    const int bh = blockIdx.y;
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    const int nr = n < N ? n : N - 1;
-    for (int i = threadIdx.x; i < NBK * D; i += 256) sm[i] = i < nbk * D ? means[(size_t)bh * nbk * D + i] : 0.f;
-    __syncthreads();
-    float sc[NBK];
-#pragma unroll
-    for (int J = 0; J < NBK; ++J) sc[J] = 0.f;
-    const uint4 *src = reinterpret_cast<const uint4 *>(q + ((size_t)bh * N + nr) * D);
-#pragma unroll 1
-    for (int c64 = 0; c64 < D / 64; ++c64) {           // 64 channels = one 128-byte line of the query row at a time:
-        uint4 u[8];                                    // its 8 loads go out together, so the line is fetched once
-#pragma unroll
-        for (int i = 0; i < 8; ++i) u[i] = src[c64 * 8 + i];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t w[4] = {u[i].x, u[i].y, u[i].z, u[i].w};
-            float qv[8];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                qv[2 * j] = __uint_as_float(w[j] << 16);
-                qv[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-            }
-            const float *mc = sm + c64 * 64 + i * 8;
-#pragma unroll
-            for (int J = 0; J < NBK; ++J) {
-                const float4 m0 = *reinterpret_cast<const float4 *>(mc + J * D);
-                const float4 m1 = *reinterpret_cast<const float4 *>(mc + J * D + 4);
-                float x = sc[J];
-                x = __fmaf_rn(qv[0], m0.x, x); x = __fmaf_rn(qv[1], m0.y, x);
-                x = __fmaf_rn(qv[2], m0.z, x); x = __fmaf_rn(qv[3], m0.w, x);
-                x = __fmaf_rn(qv[4], m1.x, x); x = __fmaf_rn(qv[5], m1.y, x);
-                x = __fmaf_rn(qv[6], m1.z, x); x = __fmaf_rn(qv[7], m1.w, x);
-                sc[J] = x;
-            }
-        }
-    }
-    float best[SLOTS];                                 // SLOTS >= topk: 4 or 8
+// Selection for more than topk key blocks.  The definition's scores, 128-step chains of fp32 multiply-adds, are 5120 vector instructions a wave at 40
+// blocks (91 us at N = 32760, 12 heads); here scores come off the matrix cores first: a mean is the sum of three bf16 values (24 bits; the last
+// part is below 2^-26 of it), a query is bf16 as it is, products are exact and sums fp32.  Such a score is off the definition's by less than
+//   2e-5 |q| |m| + 2^-17 of itself:  8 products of 16 channels onto sums that grow to |q| |m| (the two small parts go first) at 17 roundings of
+//   2^-23 each 0.9e-5, the chain's 128 roundings 0.4e-5, twice the small parts' 0.1e-5; the block's number in the six low bits
+// so where the topk-th and the next score are further apart than twice that, the selection is the definition's.  Queries where they are not (ties
+// and values that are not finite among them) have their scores computed as defined, one lane a block, and selected with the definition's rules;
+// a workgroup with a wave that has many of them does all of its queries the definition's way.
+typedef __bf16 sel_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float sel_f32x16 __attribute__((ext_vector_type(16)));
+constexpr int SELECT_FEW = 6;           // queries of 64 that are done one by one (about 2 us each)
+
+// the best SLOTS of scores offered in ascending order of blocks: a strict comparison keeps earlier blocks ahead on ties; an empty slot (index
+// -1) always gives way; once placed, the displaced pairs all move down one slot
+template <int SLOTS> struct BestBlocks {
+    float best[SLOTS];
     int bidx[SLOTS];
+    __device__ inline void clear()
+    {
 #pragma unroll
-    for (int i = 0; i < SLOTS; ++i) { best[i] = -INFINITY; bidx[i] = -1; }
+        for (int i = 0; i < SLOTS; ++i) { best[i] = -INFINITY; bidx[i] = -1; }
+    }
+    __device__ inline void offer(float v, int id)
+    {
+        bool carry = false;
 #pragma unroll
-    for (int J = 0; J < NBK; ++J) {
-        if (J < nbk) {
-            // bubble the pair down the descending list; a strict comparison keeps earlier blocks ahead on ties; an
-            // empty slot (index -1) always gives way; once placed, the displaced pairs all move down one slot
-            float v = sc[J];
-            int id = J;
-            bool carry = false;
-#pragma unroll
-            for (int i = 0; i < SLOTS; ++i) {
-                const bool take = (id >= 0) && (carry || bidx[i] < 0 || v > best[i]);
-                carry = carry || take;
-                const float tv = best[i];
-                const int ti = bidx[i];
-                best[i] = take ? v : tv;
-                bidx[i] = take ? id : ti;
-                v = take ? tv : v;
-                id = take ? ti : id;
-            }
+        for (int i = 0; i < SLOTS; ++i) {
+            const bool take = (id >= 0) && (carry || bidx[i] < 0 || v > best[i]);
+            carry = carry || take;
+            const float tv = best[i];
+            const int ti = bidx[i];
+            best[i] = take ? v : tv;
+            bidx[i] = take ? id : ti;
+            v = take ? tv : v;
+            id = take ? ti : id;
         }
     }
-    unsigned long long m = 0ull;
+    __device__ inline unsigned long long mask(int topk) const
+    {
+        unsigned long long m = 0ull;
 #pragma unroll
-    for (int i = 0; i < SLOTS; ++i)
-        if (i < topk && bidx[i] >= 0) m |= 1ull << bidx[i];
-    if (n < N) mask[(size_t)bh * N + n] = m;
+        for (int i = 0; i < SLOTS; ++i)
+            if (i < topk && bidx[i] >= 0) m |= 1ull << bidx[i];
+        return m;
+    }
+};
+
+// grid (ceil(N / 256), BH), 256 threads: a wave owns 64 queries, two column sets of the products; JT tiles of 32 key blocks.  N = 32760, 12 heads (us, all
+// mask steps): 4 of 40 blocks 152 -> 122, 8 of 64 251 -> 160; 5 heads, N = 7800, 1 of 61 96 -> 47; where every query is doubtful 152 -> 220.  Two to four turns
+// of 256 queries a workgroup, for which the means are taken apart once, gave 135.
+template <int JT, int SLOTS>
+__global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restrict__ q, const float *__restrict__ means, int N, int nbk, int topk,
+                                                             unsigned long long *__restrict__ mask)
+{
+    constexpr int NS = D / 16;
+    __shared__ __attribute__((aligned(16))) uint4 frag[3][JT][NS][64];          // operand order: lane (row l32, channels 8 hh ..)
+    __shared__ float norm[JT * 32];
+    const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+    const float *mb = means + (size_t)bh * nbk * D;
+    if (nbk <= topk) {                      // every block
+        const int n = blockIdx.x * 256 + tid;
+        if (n < N) mask[(size_t)bh * N + n] = ~0ull >> (64 - nbk);
+        return;
+    }
+    if (tid < JT * 32) norm[tid] = 0.f;
+    __syncthreads();
+    // the three parts of the means, largest last
+    for (int x = tid; x < JT * NS * 64; x += 256) {
+        const int jt = x / (NS * 64), st = x / 64 % NS, J = jt * 32 + (x & 31), c = st * 16 + ((x >> 5) & 1) * 8;
+        uint32_t w[3][4];
+        float v[8], t = 0.f;
+        const float4 *m = reinterpret_cast<const float4 *>(mb + min(J, nbk - 1) * D + c);
+        *reinterpret_cast<float4 *>(v) = m[0];
+        *reinterpret_cast<float4 *>(v + 4) = m[1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float a = J < nbk ? v[2 * e] : 0.f, b = J < nbk ? v[2 * e + 1] : 0.f;
+            t = fmaf(a, a, fmaf(b, b, t));
+#pragma unroll
+            for (int s = 2; s >= 0; --s) {
+                const uint32_t ha = f32_to_bf16_rne(a), hb = f32_to_bf16_rne(b);
+                w[s][e] = ha | hb << 16;
+                a -= __uint_as_float(ha << 16);
+                b -= __uint_as_float(hb << 16);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) frag[s][jt][st][x & 63] = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
+        atomicAdd(&norm[J], t);            // for a bound: the order does not matter
+    }
+    __syncthreads();
+    float mm = norm[lane & (JT * 32 - 1)];                       // largest |m|^2; a NaN in it is one in the scores, too
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mm = fmaxf(mm, __shfl_xor(mm, o));
+    const int n0 = blockIdx.x * 256 + (tid >> 6) * 64;
+    uint4 qf[2][NS];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const uint4 *src = reinterpret_cast<const uint4 *>(q + ((size_t)bh * N + min(n0 + u * 32 + l32, N - 1)) * D) + hh;
+#pragma unroll
+        for (int st = 0; st < NS; ++st) qf[u][st] = src[st * 2];
+    }
+    sel_f32x16 acc[2][JT];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[u][jt][r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+        for (int st = 0; st < NS; ++st)
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) {
+                const sel_bf16x8 a = __builtin_bit_cast(sel_bf16x8, frag[s][jt][st][lane]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+                    acc[u][jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(sel_bf16x8, qf[u][st]), acc[u][jt], 0, 0, 0);
+            }
+    unsigned long long doubtful = 0ull;                            // bit i: query n0 + i
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        float qq = 0.f;
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            const uint32_t w[4] = {qf[u][st].x, qf[u][st].y, qf[u][st].z, qf[u][st].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = __uint_as_float(w[e] << 16), y = __uint_as_float(w[e] & 0xffff0000u);
+                qq = fmaf(x, x, fmaf(y, y, qq));
+            }
+        }
+        qq += __shfl_xor(qq, 32);
+        // the lane's half of its query's scores (rows 8 g + 4 hh + t of a tile), each with its block's number; the SLOTS + 1 largest, descending
+        float b[SLOTS + 1];
+#pragma unroll
+        for (int i = 0; i <= SLOTS; ++i) b[i] = -INFINITY;
+        bool finite = true;
+        auto put = [&](float v) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i <= SLOTS; ++i) {
+                const float hi = fmaxf(b[i], v);
+                v = fminf(b[i], v);
+                b[i] = hi;
+            }
+        };
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int J = jt * 32 + 8 * (r >> 2) + 4 * hh + (r & 3);
+                const float v = acc[u][jt][r];
+                finite = finite && (fabsf(v) < INFINITY || J >= nbk);
+                put(J < nbk ? __uint_as_float((__float_as_uint(v) & ~63u) | (uint32_t)J) : -INFINITY);
+            }
+        float other[SLOTS + 1];
+#pragma unroll
+        for (int i = 0; i <= SLOTS; ++i) other[i] = __shfl_xor(b[i], 32);
+#pragma unroll
+        for (int i = 0; i <= SLOTS; ++i) put(other[i]);
+        unsigned long long m = 0ull;
+        float last = b[0], next = b[0];
+#pragma unroll
+        for (int i = 0; i <= SLOTS; ++i) {
+            if (i < topk) {
+                m |= 1ull << (__float_as_uint(b[i]) & 63u);
+                last = b[i];
+            }
+            if (i == topk) next = b[i];
+        }
+        // (tiny norms: the parts of the means, or the queries, may be below what a product takes)
+        const bool sure = finite && qq > 1e-30f && mm > 1e-30f && last - next > 4.1e-5f * sqrtf(qq * mm) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
+        const unsigned long long no = __ballot(!sure);
+        doubtful |= (unsigned long long)((uint32_t)no | (uint32_t)(no >> 32)) << (u * 32);
+        const int n = n0 + u * 32 + l32;
+        if (hh == 0 && n < N) mask[(size_t)bh * N + n] = m;
+    }
+    if (N - n0 < 64) doubtful &= N > n0 ? (1ull << (N - n0)) - 1ull : 0ull;
+    if (__builtin_expect(__syncthreads_or(__popcll(doubtful) > SELECT_FEW), 0)) {
+        // the definition, a thread a query, the means as broadcast words in LDS, GROUP blocks' chains at a time
+        constexpr int GROUP = 20;
+        float *sm = reinterpret_cast<float *>(frag);
+        for (int i = tid; i < nbk * D; i += 256) sm[i] = mb[i];
+        __syncthreads();
+        const int n = blockIdx.x * 256 + tid;
+        const uint4 *row = reinterpret_cast<const uint4 *>(q + ((size_t)bh * N + min(n, N - 1)) * D);
+        BestBlocks<SLOTS> best;
+        best.clear();
+#pragma unroll 1
+        for (int J = 0; J < nbk; J += GROUP) {
+            float x[GROUP] = {};
+            const float *m[GROUP];
+#pragma unroll
+            for (int i = 0; i < GROUP; ++i) m[i] = sm + min(J + i, nbk - 1) * D;
+            uint4 v = row[0];
+#pragma unroll 1
+            for (int c = 0; c < D / 8; ++c) {
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+                v = row[min(c + 1, D / 8 - 1)];
+                float qv[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) qv[e] = (e & 1) ? __uint_as_float(w[e >> 1] & 0xffff0000u) : __uint_as_float(w[e >> 1] << 16);
+#pragma unroll
+                for (int i = 0; i < GROUP; ++i) {
+                    const float4 m0 = *reinterpret_cast<const float4 *>(m[i] + c * 8), m1 = *reinterpret_cast<const float4 *>(m[i] + c * 8 + 4);
+                    x[i] = __fmaf_rn(qv[0], m0.x, x[i]); x[i] = __fmaf_rn(qv[1], m0.y, x[i]);
+                    x[i] = __fmaf_rn(qv[2], m0.z, x[i]); x[i] = __fmaf_rn(qv[3], m0.w, x[i]);
+                    x[i] = __fmaf_rn(qv[4], m1.x, x[i]); x[i] = __fmaf_rn(qv[5], m1.y, x[i]);
+                    x[i] = __fmaf_rn(qv[6], m1.z, x[i]); x[i] = __fmaf_rn(qv[7], m1.w, x[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < GROUP; ++i)
+                if (J + i < nbk) best.offer(x[i], J + i);
+        }
+        if (n < N) mask[(size_t)bh * N + n] = best.mask(topk);
+        return;
+    }
+    while (doubtful) {
+        const int i = __builtin_ctzll(doubtful);
+        doubtful &= doubtful - 1ull;
+        const u16 *row = q + ((size_t)bh * N + n0 + i) * D;
+        const float *m = mb + (size_t)min(lane, nbk - 1) * D;
+        float x = 0.f;
+#pragma unroll 4
+        for (int c = 0; c < D; c += 8) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(row + c);
+            const float4 m0 = *reinterpret_cast<const float4 *>(m + c), m1 = *reinterpret_cast<const float4 *>(m + c + 4);
+            x = __fmaf_rn(__uint_as_float(v.x << 16), m0.x, x); x = __fmaf_rn(__uint_as_float(v.x & 0xffff0000u), m0.y, x);
+            x = __fmaf_rn(__uint_as_float(v.y << 16), m0.z, x); x = __fmaf_rn(__uint_as_float(v.y & 0xffff0000u), m0.w, x);
+            x = __fmaf_rn(__uint_as_float(v.z << 16), m1.x, x); x = __fmaf_rn(__uint_as_float(v.z & 0xffff0000u), m1.y, x);
+            x = __fmaf_rn(__uint_as_float(v.w << 16), m1.z, x); x = __fmaf_rn(__uint_as_float(v.w & 0xffff0000u), m1.w, x);
+        }
+        unsigned long long chosen;
+        if (__all(fabsf(x) < INFINITY)) {              // a block is chosen if fewer than topk are ahead of it
+            int ahead = 0;
+            for (int J = 0; J < nbk; ++J) {
+                const float y = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), J));
+                ahead += y > x || (y == x && J < lane);
+            }
+            chosen = __ballot(lane < nbk && ahead < topk);
+        } else {
+            BestBlocks<SLOTS> best;
+            best.clear();
+            for (int J = 0; J < nbk; ++J) best.offer(__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), J)), J);
+            chosen = best.mask(topk);
+        }
+        if (lane == 0) mask[(size_t)bh * N + n0 + i] = chosen;
+    }
 }
 
 hipError_t launch_topk_select(const u16 *q, const float *means, int BH, int N, int nbk, int topk,
                               unsigned long long *mask, hipStream_t st)
 {
     const dim3 grid((N + 255) / 256, BH), block(256);
-#define SALAD_TOPK_SELECT(NBK_)                                                                                              \
-    do {                                                                                                                     \
-        if (topk <= 4) launch_kernel((topk_select_kernel<NBK_, 4>), grid, block, 0, st, q, means, N, nbk, topk, mask);  \
-        else launch_kernel((topk_select_kernel<NBK_, 8>), grid, block, 0, st, q, means, N, nbk, topk, mask);            \
-    } while (0)
-    if (nbk <= 8) SALAD_TOPK_SELECT(8);
-    else if (nbk <= 16) SALAD_TOPK_SELECT(16);
-    else if (nbk <= 24) SALAD_TOPK_SELECT(24);
-    else if (nbk <= 32) SALAD_TOPK_SELECT(32);
-    else if (nbk <= 40) SALAD_TOPK_SELECT(40);
-    else if (nbk <= 48) SALAD_TOPK_SELECT(48);
-    else if (nbk <= 56) SALAD_TOPK_SELECT(56);
-    else SALAD_TOPK_SELECT(64);
-#undef SALAD_TOPK_SELECT
+    auto go = [&](auto kern) { launch_kernel(kern, grid, block, 0, st, q, means, N, nbk, topk, mask); };
+    if (nbk <= 32) topk <= 4 ? go(topk_select_kernel<1, 4>) : go(topk_select_kernel<1, 8>);
+    else topk <= 4 ? go(topk_select_kernel<2, 4>) : go(topk_select_kernel<2, 8>);
     return take_launch_status();
 }
 

@@ -1378,6 +1378,42 @@ def test_topk_selection_kernel_instantiations(oracle, grid, key_block, topk):
     compare_layer(res, ref, label=f"topk-N{w.N}-kb{key_block}-k{topk}")
 
 
+@pytest.mark.parametrize("H,grid,key_block,topk", [
+    (2, (1, 5, 100), 64, 4),          # 8 blocks
+    (1, (3, 9, 13), 64, 5),           # 6 blocks: one is left out; 5 of 8 slots; a last workgroup of 95 queries
+    (2, (1, 4, 128), 64, 8),          # all of 8 blocks
+    (1, (4, 16, 33), 64, 4),          # 33 blocks: a second tile of one row
+    (2, (4, 32, 32), 64, 1),          # 64 blocks
+])
+@pytest.mark.parametrize("kind", ["normal", "ties", "one block in all", "zero queries", "wide range", "infinite"])
+def test_topk_scores_from_the_matrix_cores(oracle, H, grid, key_block, topk, kind):
+    """Masks bit for bit where scores from the matrix cores cannot decide, for a few queries of a wave and for all of them: equal means, zero
+    queries, values at both ends of bf16, infinite ones."""
+    N, d = grid[0] * grid[1] * grid[2], 128
+    q, k = (wl.round_to_bf16(wl.normal(77 + N, t, (1, H, N, d))) for t in ("q", "k"))
+    if kind == "ties":
+        k[:, :, key_block:2 * key_block] = k[:, :, :key_block]        # the first two blocks, for every query that one of them is last for
+        q[:, :, ::17] = np.round(q[:, :, ::17])
+    elif kind == "one block in all":
+        k[:] = np.resize(k[0, 0, 0], k.shape)
+    elif kind == "zero queries":
+        q[:, :, 5:300] = 0
+    elif kind == "wide range":
+        q *= np.where(np.arange(N) % 3 == 0, 1e-30, 1e18).astype(np.float32)[:, None]
+        k *= np.where(np.arange(N) // key_block % 2 == 0, 1e-19, 1e-3).astype(np.float32)[:, None]
+        q, k = wl.round_to_bf16(q), wl.round_to_bf16(k)
+    elif kind == "infinite":
+        k[0, 0, N // 2, 3] = np.inf
+        q[0, 0, 70:90, 3] = np.inf                                      # the same channel: scores are infinite, none is a NaN
+    ref = oracle.topk_select(q, k, key_block, topk, [0] * H, grid)
+    got = torch.zeros((1, H, N), dtype=torch.int64, device="cuda")
+    qd, kd = (torch.from_numpy(x).cuda().bfloat16() for x in (q, k))
+    sb.salad_sparse_linear_attn_fwd(qd, kd, kd, grid, None, None, [0] * H, lam=0.0, topk=topk, topk_key_block=key_block, topk_mask_out=got)
+    torch.cuda.synchronize()
+    same = got.cpu().numpy().view(np.uint64) == ref
+    assert same.all(), (kind, int((~same).sum()), np.argwhere(~same)[:4].tolist())
+
+
 def test_topk_rotary_dropping_together(oracle):
     """The widened pieces in one call: Top-K mask for the sparse branch, rotary linear branch, and branch dropping
     with a threshold between the two samples' dynamic scales (sample 0 keeps its branch, sample 1 loses it)."""
