@@ -255,8 +255,9 @@ typedef struct salad_kernel_times {
 
 /* on = 1: the layer call brackets each of its stages with HIP events on its stream (eight records per call; every
  * record is a dependency between two kernels that would otherwise start back to back, and the gate and the state, one
- * launch otherwise, are launched apart; the call itself gets some 5 % slower).  on = 2: only the attention stage (pre-pass + attention kernel, Top-K: + the merge kernel when the
- * linear-apply pass does not merge) is bracketed, two
+ * launch otherwise, are launched apart; the call itself gets some 5 % slower, one of a short sequence, whose gate, state and
+ * reduce are part of the attention's launch otherwise, up to twice as slow; the same results).  on = 2: only the attention stage (pre-pass + attention kernel, Top-K: + the merge kernel when the
+ * linear-apply pass does not merge; short sequences: everything) is bracketed, two
  * records per call; salad_timing_read then fills attn_ms and calls only.  on = 0: no events.  Other values:
  * SALAD_EINVAL. */
 salad_status salad_timing_enable(int32_t on);
