@@ -237,8 +237,9 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
             }
             if (i == topk) next = b[i];
         }
-        // (tiny norms: the parts of the means, or the queries, may be below what a product takes)
-        const bool sure = finite && qq > 1e-30f && mm > 1e-30f && last - next > 4.1e-5f * sqrtf(qq * mm) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
+        // tiny norms: the parts of the means, or the queries, may be below what a product takes.  From 1e-13 on all that is lost below 2^-126 is
+        // less than 2e-5 of the bound.  The product of the two squares may be below 2^-149 then, that of the norms is not.
+        const bool sure = finite && qq > 1e-26f && mm > 1e-26f && last - next > 4.1e-5f * (sqrtf(qq) * sqrtf(mm)) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
         const unsigned long long no = __ballot(!sure);
         doubtful |= (unsigned long long)((uint32_t)no | (uint32_t)(no >> 32)) << (u * 32);
         const int n = n0 + u * 32 + l32;

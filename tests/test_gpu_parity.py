@@ -1385,10 +1385,11 @@ def test_topk_selection_kernel_instantiations(oracle, grid, key_block, topk):
     (1, (4, 16, 33), 64, 4),          # 33 blocks: a second tile of one row
     (2, (4, 32, 32), 64, 1),          # 64 blocks
 ])
-@pytest.mark.parametrize("kind", ["normal", "ties", "one block in all", "zero queries", "wide range", "infinite"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "one block in all", "zero queries", "wide range", "infinite", "cancelling", "cancelling, small"])
 def test_topk_scores_from_the_matrix_cores(oracle, H, grid, key_block, topk, kind):
     """Masks bit for bit where scores from the matrix cores cannot decide, for a few queries of a wave and for all of them: equal means, zero
-    queries, values at both ends of bf16, infinite ones."""
+    queries, values at both ends of bf16, infinite ones; scores that are nothing but rounding, also where the product of the squared norms is
+    below what fp32 holds."""
     N, d = grid[0] * grid[1] * grid[2], 128
     q, k = (wl.round_to_bf16(wl.normal(77 + N, t, (1, H, N, d))) for t in ("q", "k"))
     if kind == "ties":
@@ -1405,6 +1406,10 @@ def test_topk_scores_from_the_matrix_cores(oracle, H, grid, key_block, topk, kin
     elif kind == "infinite":
         k[0, 0, N // 2, 3] = np.inf
         q[0, 0, 70:90, 3] = np.inf                                      # the same channel: scores are infinite, none is a NaN
+    elif kind.startswith("cancelling"):                                 # channel c + 64 of the product is minus channel c
+        scale = np.float32(1e-13 if kind.endswith("small") else 1)
+        q[..., 64:], k[..., 64:] = q[..., :64], -k[..., :64]
+        q, k = wl.round_to_bf16(q * scale), wl.round_to_bf16(k * scale)
     ref = oracle.topk_select(q, k, key_block, topk, [0] * H, grid)
     got = torch.zeros((1, H, N), dtype=torch.int64, device="cuda")
     qd, kd = (torch.from_numpy(x).cuda().bfloat16() for x in (q, k))
