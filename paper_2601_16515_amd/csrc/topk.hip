@@ -68,12 +68,14 @@ hipError_t launch_kblock_mean(const u16 *k, int BH, int N, int key_block, int nb
 
 // Selection for more than topk key blocks.  The definition's scores, 128-step chains of fp32 multiply-adds, are 5120 vector instructions a wave at 40
 // blocks (91 us at N = 32760, 12 heads); here scores come off the matrix cores first: a mean is the sum of three bf16 values (24 bits; the last
-// part is below 2^-26 of it), a query is bf16 as it is, products are exact and sums fp32.  Such a score is off the definition's by less than
-//   2e-5 |q| |m| + 2^-17 of itself:  8 products of 16 channels onto sums that grow to |q| |m| (the two small parts go first) at 17 roundings of
-//   2^-23 each 0.9e-5, the chain's 128 roundings 0.4e-5, twice the small parts' 0.1e-5; the block's number in the six low bits
+// part is below 2^-26 of it), a query is bf16 as it is, products are exact and sums fp32.  Such a score is off the definition's by no more than
+//   (SELECT_MATRIX + SELECT_CHAIN) |q| |m| + 2^-17 of itself:  8 products of 16 channels, 17 additions each that may cut at 2^-23 of sums up to
+//   |q| |m|, the two small parts, which go first, at 2^-9 of that, and what the three parts leave; the chain's 128 roundings of 2^-24 of sums up to
+//   |q| |m| (both reached only where the first channels have all of it); the block's number in the six low bits
 // so where the topk-th and the next score are further apart than twice that, the selection is the definition's.  Queries where they are not (ties
 // and values that are not finite among them) have their scores computed as defined, one lane a block, and selected with the definition's rules;
 // a workgroup with a wave that has many of them does all of its queries the definition's way.
+constexpr float SELECT_MATRIX = (8 * 17 + 2) * 0x1p-23f, SELECT_CHAIN = (128 + 1) * 0x1p-24f;
 typedef __bf16 sel_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sel_f32x16 __attribute__((ext_vector_type(16)));
 constexpr int SELECT_FEW = 6;           // queries of 64 that are done one by one (about 2 us each)
@@ -239,7 +241,8 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
         }
         // tiny norms: the parts of the means, or the queries, may be below what a product takes.  From 1e-13 on all that is lost below 2^-126 is
         // less than 2e-5 of the bound.  The product of the two squares may be below 2^-149 then, that of the norms is not.
-        const bool sure = finite && qq > 1e-26f && mm > 1e-26f && last - next > 4.1e-5f * (sqrtf(qq) * sqrtf(mm)) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
+        const bool sure = finite && qq > 1e-26f && mm > 1e-26f &&
+                          last - next > 2 * (SELECT_MATRIX + SELECT_CHAIN) * (sqrtf(qq) * sqrtf(mm)) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
         const unsigned long long no = __ballot(!sure);
         doubtful |= (unsigned long long)((uint32_t)no | (uint32_t)(no >> 32)) << (u * 32);
         const int n = n0 + u * 32 + l32;
