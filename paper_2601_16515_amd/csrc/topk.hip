@@ -72,13 +72,15 @@ hipError_t launch_kblock_mean(const u16 *k, int BH, int N, int key_block, int nb
 //   (SELECT_MATRIX + SELECT_CHAIN) |q| |m| + 2^-17 of itself:  8 products of 16 channels, 17 additions each that may cut at 2^-23 of sums up to
 //   |q| |m|, the two small parts, which go first, at 2^-9 of that, and what the three parts leave; the chain's 128 roundings of 2^-24 of sums up to
 //   |q| |m| (both reached only where the first channels have all of it); the block's number in the six low bits
-// so where the topk-th and the next score are further apart than twice that, the selection is the definition's.  Queries where they are not (ties
-// and values that are not finite among them) have their scores computed as defined, one lane a block, and selected with the definition's rules;
-// a workgroup with a wave that has many of them does all of its queries the definition's way.
+// so where the topk-th and the next score are further apart than twice that, the selection is the definition's.  Where they are not (ties and
+// values that are not finite among them), the scores that are open, within that of both, are computed as defined, a lane each, and selected
+// with the definition's rules; a workgroup with a wave that has many of them does all of its queries the definition's way.
 constexpr float SELECT_MATRIX = (8 * 17 + 2) * 0x1p-23f, SELECT_CHAIN = (128 + 1) * 0x1p-24f;
 typedef __bf16 sel_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float sel_f32x16 __attribute__((ext_vector_type(16)));
-constexpr int SELECT_FEW = 6;           // queries of 64 that are done one by one (about 2 us each)
+// Open scores that a wave computes, for each tile of 32 key blocks: what fits the products' LDS with the means, and about where all scores of the
+// workgroup's queries the definition's way are no more work
+constexpr int SELECT_PAIRS = 320;
 
 // the best SLOTS of scores offered in ascending order of blocks: a strict comparison keeps earlier blocks ahead on ties; an empty slot (index
 // -1) always gives way; once placed, the displaced pairs all move down one slot
@@ -116,13 +118,16 @@ template <int SLOTS> struct BestBlocks {
 };
 
 // grid (ceil(N / 256), BH), 256 threads: a wave owns 64 queries, two column sets of the products; JT tiles of 32 key blocks.  N = 32760, 12 heads (us, all
-// mask steps): 4 of 40 blocks 152 -> 122, 8 of 64 251 -> 160; 5 heads, N = 7800, 1 of 61 96 -> 47; where every query is doubtful 152 -> 220.  Two to four turns
-// of 256 queries a workgroup, for which the means are taken apart once, gave 135.
+// mask steps; before: the definition alone): 4 of 40 blocks 147 -> 110, 8 of 64 251 -> 141; 5 heads, N = 7800, 1 of 61 97 -> 43.  Two to four turns
+// of 256 queries a workgroup, for which the means are taken apart once, gave 135 where one gave 122.
+// What all keys have in common widens the bound and leaves the scores' differences as they are.  4 of 40 blocks of normal keys with as much as 1, 3, 10, 30
+// of it in every channel: 113, 116, 123, 145 (before 141; each doubtful query's 40 scores, one query at a time: 201, 208, 208).  All keys equal, so that
+// every score is open: 212 (144).  Less the average of 8 means it was 131, and 133, 135, 142, 180 there, with fewer waves for its registers.
 template <int JT, int SLOTS>
 __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restrict__ q, const float *__restrict__ means, int N, int nbk, int topk,
                                                              unsigned long long *__restrict__ mask)
 {
-    constexpr int NS = D / 16;
+    constexpr int NS = D / 16, PAIRS = JT * SELECT_PAIRS;
     __shared__ __attribute__((aligned(16))) uint4 frag[3][JT][NS][64];          // operand order: lane (row l32, channels 8 hh ..)
     __shared__ float norm[JT * 32];
     const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
@@ -188,7 +193,9 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
                 for (int u = 0; u < 2; ++u)
                     acc[u][jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(sel_bf16x8, qf[u][st]), acc[u][jt], 0, 0, 0);
             }
+    const unsigned long long every = ~0ull >> (64 - nbk);
     unsigned long long doubtful = 0ull;                            // bit i: query n0 + i
+    unsigned long long chosen = 0ull, open = 0ull;                 // of query n0 + lane, if it is doubtful
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         float qq = 0.f;
@@ -241,15 +248,47 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
         }
         // tiny norms: the parts of the means, or the queries, may be below what a product takes.  From 1e-13 on all that is lost below 2^-126 is
         // less than 2e-5 of the bound.  The product of the two squares may be below 2^-149 then, that of the norms is not.
-        const bool sure = finite && qq > 1e-26f && mm > 1e-26f &&
-                          last - next > 2 * (SELECT_MATRIX + SELECT_CHAIN) * (sqrtf(qq) * sqrtf(mm)) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
+        const bool bounded = finite && __shfl_xor((int)finite, 32) && qq > 1e-26f && mm > 1e-26f;
+        const float margin = 2 * (SELECT_MATRIX + SELECT_CHAIN) * (sqrtf(qq) * sqrtf(mm)) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
+        const bool sure = bounded && last - next > margin;
         const unsigned long long no = __ballot(!sure);
-        doubtful |= (unsigned long long)((uint32_t)no | (uint32_t)(no >> 32)) << (u * 32);
+        doubtful |= (no & 0xffffffffull) << (u * 32);
         const int n = n0 + u * 32 + l32;
-        if (hh == 0 && n < N) mask[(size_t)bh * N + n] = m;
+        if (hh == 0 && sure && n < N) mask[(size_t)bh * N + n] = m;
+        if (no) {
+            // ahead of the first left out by more than the margin: chosen; behind the last chosen by more: not; the others are open
+            unsigned long long yes = 0ull, may = 0ull;
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float v = acc[u][jt][r];
+                    const unsigned long long bit = 1ull << (jt * 32 + 8 * (r >> 2) + (r & 3));
+                    if (v > next + margin) yes |= bit;
+                    else if (!(v < last - margin)) may |= bit;
+                }
+            yes <<= 4 * hh;
+            may <<= 4 * hh;
+            if (!bounded) { yes = 0ull; may = ~0ull; }
+            yes |= __shfl_xor(yes, 32);
+            may |= __shfl_xor(may, 32);
+            if (hh == u) {
+                chosen = yes & every;
+                open = may & every;
+            }
+        }
     }
     if (N - n0 < 64) doubtful &= N > n0 ? (1ull << (N - n0)) - 1ull : 0ull;
-    if (__builtin_expect(__syncthreads_or(__popcll(doubtful) > SELECT_FEW), 0)) {
+    if (!(doubtful >> lane & 1ull)) open = 0ull;
+    const int count = __popcll(open);
+    int end = count;                        // of this lane's pairs in the wave's list
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int x = __shfl_up(end, o);
+        if (lane >= o) end += x;
+    }
+    const int pairs = __shfl(end, 63);
+    if (__builtin_expect(__syncthreads_or(pairs > PAIRS), 0)) {
         // the definition, a thread a query, the means as broadcast words in LDS, GROUP blocks' chains at a time
         constexpr int GROUP = 20;
         float *sm = reinterpret_cast<float *>(frag);
@@ -289,36 +328,49 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
         if (n < N) mask[(size_t)bh * N + n] = best.mask(topk);
         return;
     }
-    while (doubtful) {
-        const int i = __builtin_ctzll(doubtful);
-        doubtful &= doubtful - 1ull;
-        const u16 *row = q + ((size_t)bh * N + n0 + i) * D;
-        const float *m = mb + (size_t)min(lane, nbk - 1) * D;
-        float x = 0.f;
+    // the open scores as defined, a lane a (query, block) pair; where a wave has many, which read many rows of means at once, from LDS, chunk c of
+    // row J at c ^ (J % 16)
+    const bool stage = __syncthreads_or(pairs > 64);
+    float4 *lm = reinterpret_cast<float4 *>(frag);
+    if (stage) {
+        for (int i = tid; i < nbk * (D / 4); i += 256) lm[i ^ (i / (D / 4) & 15)] = reinterpret_cast<const float4 *>(mb)[i];
+        __syncthreads();
+    }
+    if (!doubtful) return;                  // (by the numbers of the blocks in the scores a query can be doubtful and no score be open)
+    u16 *list = reinterpret_cast<u16 *>(lm + JT * 32 * (D / 4)) + (tid >> 6) * (PAIRS * 3);
+    float *score = reinterpret_cast<float *>(list + PAIRS);
+    static_assert(sizeof(frag) >= JT * 32 * D * 4 + 4 * PAIRS * 6, "LDS");
+    {
+        int i = end - count;
+        for (unsigned long long o = open; o; o &= o - 1ull) list[i++] = (u16)(lane << 6 | __builtin_ctzll(o));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    auto compute = [&](auto mean) __attribute__((always_inline)) {
+        for (int i = lane; i < pairs; i += 64) {
+            const int p = list[i];
+            const u16 *row = q + ((size_t)bh * N + n0 + (p >> 6)) * D;
+            float x = 0.f;
 #pragma unroll 4
-        for (int c = 0; c < D; c += 8) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(row + c);
-            const float4 m0 = *reinterpret_cast<const float4 *>(m + c), m1 = *reinterpret_cast<const float4 *>(m + c + 4);
-            x = __fmaf_rn(__uint_as_float(v.x << 16), m0.x, x); x = __fmaf_rn(__uint_as_float(v.x & 0xffff0000u), m0.y, x);
-            x = __fmaf_rn(__uint_as_float(v.y << 16), m0.z, x); x = __fmaf_rn(__uint_as_float(v.y & 0xffff0000u), m0.w, x);
-            x = __fmaf_rn(__uint_as_float(v.z << 16), m1.x, x); x = __fmaf_rn(__uint_as_float(v.z & 0xffff0000u), m1.y, x);
-            x = __fmaf_rn(__uint_as_float(v.w << 16), m1.z, x); x = __fmaf_rn(__uint_as_float(v.w & 0xffff0000u), m1.w, x);
-        }
-        unsigned long long chosen;
-        if (__all(fabsf(x) < INFINITY)) {              // a block is chosen if fewer than topk are ahead of it
-            int ahead = 0;
-            for (int J = 0; J < nbk; ++J) {
-                const float y = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), J));
-                ahead += y > x || (y == x && J < lane);
+            for (int c = 0; c < D / 8; ++c) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(row + c * 8);
+                const float4 m0 = mean(p & 63, 2 * c), m1 = mean(p & 63, 2 * c + 1);
+                x = __fmaf_rn(__uint_as_float(v.x << 16), m0.x, x); x = __fmaf_rn(__uint_as_float(v.x & 0xffff0000u), m0.y, x);
+                x = __fmaf_rn(__uint_as_float(v.y << 16), m0.z, x); x = __fmaf_rn(__uint_as_float(v.y & 0xffff0000u), m0.w, x);
+                x = __fmaf_rn(__uint_as_float(v.z << 16), m1.x, x); x = __fmaf_rn(__uint_as_float(v.z & 0xffff0000u), m1.y, x);
+                x = __fmaf_rn(__uint_as_float(v.w << 16), m1.z, x); x = __fmaf_rn(__uint_as_float(v.w & 0xffff0000u), m1.w, x);
             }
-            chosen = __ballot(lane < nbk && ahead < topk);
-        } else {
-            BestBlocks<SLOTS> best;
-            best.clear();
-            for (int J = 0; J < nbk; ++J) best.offer(__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), J)), J);
-            chosen = best.mask(topk);
+            score[i] = x;
         }
-        if (lane == 0) mask[(size_t)bh * N + n0 + i] = chosen;
+    };
+    if (stage) compute([&](int J, int c) __attribute__((always_inline)) { return lm[J * (D / 4) + (c ^ (J & 15))]; });
+    else compute([&](int J, int c) __attribute__((always_inline)) { return reinterpret_cast<const float4 *>(mb)[J * (D / 4) + c]; });
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (doubtful >> lane & 1ull) {
+        BestBlocks<SLOTS> best;
+        best.clear();
+        int i = end - count;
+        for (unsigned long long o = open; o; o &= o - 1ull) best.offer(score[i++], __builtin_ctzll(o));
+        mask[(size_t)bh * N + n0 + lane] = chosen | best.mask(topk - __popcll(chosen));
     }
 }
 

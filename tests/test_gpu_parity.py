@@ -1386,11 +1386,11 @@ def test_topk_selection_kernel_instantiations(oracle, grid, key_block, topk):
     (2, (4, 32, 32), 64, 1),          # 64 blocks
 ])
 @pytest.mark.parametrize("kind", ["normal", "ties", "one block in all", "zero queries", "wide range", "infinite", "cancelling", "cancelling, small",
-                                  "leading channel"])
+                                  "leading channel", "common part"])
 def test_topk_scores_from_the_matrix_cores(oracle, H, grid, key_block, topk, kind):
     """Masks bit for bit where scores from the matrix cores cannot decide, for a few queries of a wave and for all of them: equal means, zero
     queries, values at both ends of bf16, infinite ones; scores that are nothing but rounding, also where the product of the squared norms is
-    below what fp32 holds; partial sums that are at full size from the first channel on."""
+    below what fp32 holds; partial sums that are at full size from the first channel on; means that differ little from each other."""
     N, d = grid[0] * grid[1] * grid[2], 128
     q, k = (wl.round_to_bf16(wl.normal(77 + N, t, (1, H, N, d))) for t in ("q", "k"))
     if kind == "ties":
@@ -1412,13 +1412,17 @@ def test_topk_scores_from_the_matrix_cores(oracle, H, grid, key_block, topk, kin
         q[..., 64:], k[..., 64:] = q[..., :64], -k[..., :64]
         q, k = wl.round_to_bf16(q * scale), wl.round_to_bf16(k * scale)
     elif kind == "leading channel":
-        # the first product is 1, and each of the next 126 is a little more (even blocks, which the chain rounds up) or less (odd blocks, down)
-        # than half a unit in the last place; odd blocks are ahead by the last one, up to 6e-5, of which the chain takes away 1.5e-5
-        J = np.arange(N) // key_block
-        q[:], k[:] = 2.0 ** -12, (2.0 ** -12 * (1 + np.where(J % 2 == 0, 1, -1) / 64))[:, None]
+        # the first product is 1, and each of the next 126 is a little more than half a unit in the last place (the chain rounds up) or, where the
+        # block is among the first topk, less (down); those are ahead by the last one, up to 1.2e-4, the same for the 64 queries of a wave, of which
+        # the chain takes away 1.5e-5
+        J, n = np.arange(N) // key_block, np.arange(N)
+        ahead = J < topk
+        q[:], k[:] = 2.0 ** -12, (2.0 ** -12 * (1 + np.where(ahead, -1, 1) / 64))[:, None]
         q[..., 0], k[..., 0] = 1, 1
-        q[..., 127], k[..., 127] = 2.0 ** -12 * 6 * np.arange(N) / N, np.where(J % 2 == 0, 0, 0.04 * (1 - J / 80))
+        q[..., 127], k[..., 127] = 2.0 ** -12 * 12 * (n // 64 * 64 / N), np.where(ahead, 0.04, 0)
         q, k = wl.round_to_bf16(q), wl.round_to_bf16(k)
+    elif kind == "common part":
+        k = wl.round_to_bf16(k + np.float32(10) * np.sign(np.sin(np.arange(d) * 1.7 + 0.5)).astype(np.float32))
     ref = oracle.topk_select(q, k, key_block, topk, [0] * H, grid)
     got = torch.zeros((1, H, N), dtype=torch.int64, device="cuda")
     qd, kd = (torch.from_numpy(x).cuda().bfloat16() for x in (q, k))
