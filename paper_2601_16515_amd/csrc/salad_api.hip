@@ -653,8 +653,9 @@ salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls)
     a.variant = attn_variant;
     if (split) {
         a.sp_full = w.split.full; a.sp_pieces = w.split.pieces;
-        // riders' compute units are not there for pieces (but for calls that may drop the linear branch, whose sparse branch has the bits that it has alone)
-        if (ride && !dropping) a.sp_pieces = std::min(a.sp_pieces, std::max(2, (256 - std::min(w.ride.wgs, 256)) / w.split.rest));
+        // riders' compute units are not there for pieces (but for calls that may drop the linear branch, whose sparse branch has the bits that it has
+        // alone); as many where each stage is being timed, for the same bits
+        if (direct && !dropping) a.sp_pieces = std::min(a.sp_pieces, std::max(2, (256 - std::min(w.ride.wgs, 256)) / w.split.rest));
         a.sp_o = (uint64_t *)(ws + w.sp_o); a.sp_ml = (uint64_t *)(ws + w.sp_ml); a.sp_count = (uint64_t *)(ws + w.sp_count);
         a.sp_tag = sp_tag;
     }

@@ -403,6 +403,8 @@ def test_workspace_without_room_for_the_pieces(oracle):
     (3, 5, 128, (3, 5, 17), 2, "drop"),        # 255 tokens, a last group of 15; samples pruned and not
     (1, 12, 128, (4, 16, 16), 4, ""),          # whole groups, tiles dealt by rows
     (1, 12, 128, (5, 15, 26), 31, ""),         # lists that are cut, with riders on the compute units of other pieces
+    (1, 8, 128, (5, 15, 26), 31, ""),          # cut in two, without riders in four
+    (1, 2, 128, (4, 25, 40), 48, ""),          # in six and eight; a last block of 32
     (1, 16, 128, (5, 15, 26), 6, ""),          # more riders and tiles than compute units
     (1, 40, 128, (2, 9, 9), 2, "rope"),        # a row of 5120 channels
     (1, 64, 128, (1, 7, 9), 1, ""),            # 8192
