@@ -174,7 +174,8 @@ typedef struct salad_fwd_params {
  * results (at most 35 MB); with w_proj also O_l and the rearranged W_p; with topk the key-block means,
  * the masks and per-sample lists).  Reads only B, H, N, d, dtype, topk and whether w_proj and rope_cos are NULL.
  * 0 on invalid shapes.  The pieces' results can be left out: a smaller workspace that has room for the rest is taken and
- * the tiles are not cut (same result up to rounding order), so that one workspace may serve the largest grid of a program
+ * the tiles are not cut (same result up to rounding order); and so can what short sequences need for state and gate within
+ * the attention's launch, which lies behind the pieces (those are launches of their own then).  So one workspace may serve the largest grid of a program
  * and all smaller ones, although a small grid with pieces may ask for more than a large one without.
  * SALAD_ENOSPC: below the rest.
  * Nothing in a workspace has to be set or kept between calls, but calls that may overlap (other streams or threads) must

@@ -41,7 +41,7 @@ salad_status hip_fail(hipError_t e, const char *what)
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
-    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, ride_words, ride_gate, base, total;
+    size_t gate_partial, state_partial, Hs, Z, hfrag, s, coef, drop, tile_lists, tile_counts, ol, wfrag, kmeans, topk_mask, g_counts, g_ccnt, g_seg, g_total, g_desc, g_idx, g_slot, g_lse, g_po, rope_tab, sp_o, sp_ml, sp_count, ride_words, ride_gate, base, pieces, total;
     int nparts, P;
     SplitPlan split;
     RidePlan ride;
@@ -105,6 +105,7 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     w.sp_o = off; off = align256(off + sizeof(float) * np * 256 * (size_t)d);
     w.sp_ml = off; off = align256(off + sizeof(uint64_t) * np * 512);
     w.sp_count = off; off = align256(off + sizeof(uint64_t) * (np ? (size_t)w.split.rest : 0));
+    w.pieces = off;     // room for those, but not for what follows
     // state and gate within the attention's launch
     if (dtype == SALAD_BF16 && !topk && large_lists) w.ride = ride_plan(B, H, N, d, w.split);
     w.ride_words = off; off = align256(off + (w.ride.wgs ? sizeof(uint64_t) * RIDE_STRIDE * (BH + B) : 0));
@@ -505,7 +506,7 @@ salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls)
     const int BH = p->B * p->H;
     const bool bf16 = p->dtype == SALAD_BF16;
     hipError_t e;
-    const bool split = w.split.pieces > 1 && large_tile && p->workspace_bytes >= w.total;      // the last round's tiles are cut
+    const bool split = w.split.pieces > 1 && large_tile && p->workspace_bytes >= w.pieces;      // the last round's tiles are cut
     const uint64_t sp_tag = split ? next_piece_tag() : 0;
 
     // full projection: the attention kernel's epilogue writes O_l, in the projection's operand order, next to O_s.  A pass of its own over Q

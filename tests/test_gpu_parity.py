@@ -460,6 +460,25 @@ def test_state_and_gate_within_the_attention_launch(B, H, d, grid, keep, opt):
             assert sorted(ref[2].tolist()) == [0] + [1] * (B - 1)
 
 
+def test_workspace_with_room_for_the_pieces_only():
+    """A workspace with room for the pieces of cut tiles but not for state and gate within the attention's launch: tiles are cut as they
+    are where the sparse branch runs alone."""
+    H, d, grid = 2, 128, (4, 25, 40)
+    w = wl.small("pieces-only", 1, H, d, *grid, "bf16", 0.5, seed=641)
+    dev = upload(w, wl.make_inputs(w))
+    kinds = wl.head_kinds(w)
+    row_ptr, col_idx = sb.salad_block_mask(*grid, w.block, [48] * H)
+    args = (dev["q"], dev["k"], dev["v"], grid, row_ptr, col_idx, kinds)
+    alone = sb.salad_sparse_linear_attn_fwd(*args, lam=0.0)
+    ws = sb.Workspace(1, H, w.N, d, sb.SALAD_BF16)
+    kw = dict(lam=20.0, head_scale=dev["head_scale"], x_t=dev["x_t"], w_gate=dev["w_gate"], eps=w.eps, workspace=ws)
+    whole = sb.salad_sparse_linear_attn_fwd(*args, **kw)
+    ws.bytes -= 256
+    assert torch.equal(sb.salad_sparse_linear_attn_fwd(*args, drop_threshold=2.0, **kw), alone)
+    out = sb.salad_sparse_linear_attn_fwd(*args, **kw)
+    assert errors(out.float().cpu().numpy().astype(np.float64), whole.float().cpu().numpy().astype(np.float64))[1] < 4e-3     # two independently rounded bf16 results
+
+
 def test_sparse_branch_alone_is_one_launch():
     """lambda = 0 with prebuilt lists on a grid whose tiles may be cut: the attention kernel and nothing else, counted in a
     captured graph; replays on a workspace that held anything give the bits of the eager call."""
