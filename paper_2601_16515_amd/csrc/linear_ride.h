@@ -17,7 +17,7 @@
 namespace salad {
 
 // a head's word: riders that are done, tiles that are done with it (two units each), tag
-constexpr uint64_t RIDE_TILE = 1ull << 10, RIDE_COUNT = (1ull << 22) - 1;
+constexpr uint64_t RIDE_TILE = 1ull << 10, RIDE_COUNT = (1ull << RIDE_COUNT_BITS) - 1;
 
 __device__ inline uint64_t ride_load(const uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline void ride_store(uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }

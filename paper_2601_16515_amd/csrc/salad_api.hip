@@ -114,12 +114,12 @@ WsLayout ws_layout(int B, int H, int N, int d, int dtype, int state_wgs, bool fu
     return w;
 }
 
-// Tag of a call's piece counters: 60 bits, another for every call, from a random start, so that a word left in the workspace
-// by anything else carries it with a chance of 2^-60.  A captured call keeps its tag: the last piece to arrive sets the
-// counter to 0, which is no call's tag.  Setting the counters to 0 ahead of the attention kernel took a launch more where
+// Tag of a call's counters in the workspace, above the bits that count: 60 bits for a tile's pieces, 42 for a head's riders and tiles; another for every
+// call, from a random start, so that a word left in the workspace by anything else carries it with a chance of 2^-60 (2^-42).  A captured call
+// keeps its tag: whoever completes the count sets the word to 0, which is no call's tag.  Setting the counters to 0 ahead of the attention kernel took a launch more where
 // lambda = 0 and the lists are prebuilt: N = 1950, 12 heads, lists of 6 entries 16.5 -> 15.0 us, 25 entries 37.1 -> 36.8.  With lambda
 // != 0 the reduce sets them to the tag: N = 1248, 8 heads, 40 tiles in 3 pieces 40.1 us, 41.5 where the pieces have to find out.
-uint64_t next_piece_tag()
+uint64_t next_tag(int count_bits)
 {
     static std::atomic<uint64_t> next{[] {
         uint64_t x = 0;
@@ -128,7 +128,7 @@ uint64_t next_piece_tag()
         return x;
     }()};
     uint64_t t;
-    do t = next.fetch_add(1) << 4; while (!t);
+    do t = next.fetch_add(1) << count_bits; while (!t);
     return t;
 }
 
@@ -507,7 +507,7 @@ salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls)
     const bool bf16 = p->dtype == SALAD_BF16;
     hipError_t e;
     const bool split = w.split.pieces > 1 && large_tile && p->workspace_bytes >= w.pieces;      // the last round's tiles are cut
-    const uint64_t sp_tag = split ? next_piece_tag() : 0;
+    const uint64_t sp_tag = split ? next_tag(4) : 0;
 
     // full projection: the attention kernel's epilogue writes O_l, in the projection's operand order, next to O_s.  A pass of its own over Q
     // took 51-55 us at N = 32760, 12 heads: layer call 872 -> 849 us.
@@ -562,7 +562,7 @@ salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls)
         r.riders = (p->d == 128 ? 8 : 2) + (need_gate ? 1 : 0); r.polls = polls;
         r.crowded = w.ride.crowded;
         r.full = (uint64_t)r.riders + 1024ull * (2 * (((p->N + 63) / 64 + 3) / 4));
-        r.tag = next_piece_tag() << 18; r.words = (uint64_t *)(ws + w.ride_words);
+        r.tag = next_tag(RIDE_COUNT_BITS); r.words = (uint64_t *)(ws + w.ride_words);
         r.x_t = p->x_t; r.w_gate = p->w_gate; r.b_gate = p->b_gate; r.gate_tok = chunks <= 2 ? 4 : chunks <= 5 ? 2 : 1;
         r.gate_sums = (float *)(ws + w.ride_gate); r.hfrag = (u16 *)(ws + w.hfrag); r.Z = (float *)(ws + w.Z);
         r.tau = dropping ? p->drop_threshold : 0.f; r.drop = drop; r.dropped_out = dropping ? p->dropped_out : nullptr;

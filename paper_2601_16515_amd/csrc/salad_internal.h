@@ -92,6 +92,7 @@ hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t st);
 
 // ---- state and gate by workgroups of the attention's launch (linear_ride.h) ---------------------------
 constexpr int RIDE_STRIDE = 16;
+constexpr int RIDE_COUNT_BITS = 22;         // of a word, below the call's tag
 constexpr int RIDE_POLLS = 1 << 14;         // about 20 ms
 struct RideArgs {
     int wgs, gate_tasks;            // workgroups, a multiple of 8 (0: none ride); shares of a sample's gate among them
