@@ -1004,7 +1004,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // ---- epilogue ---------------------------------------------------------------------------------
     float lin_scale[QS], inv_den[QS];
     if (lin) {
-        if (RIDE || n == 0 || (SPLIT && pieces > 1)) { stage_state(); if (ROPE) load_angles(); }
+        const bool late = n == 0 || (SPLIT && pieces > 1);       // not under the last PV product
+        if (RIDE || late) stage_state();
+        if (ROPE && late) load_angles();
         if (RIDE) reduce_gate();
 #pragma unroll
         for (int u = 0; u < QS; ++u)
