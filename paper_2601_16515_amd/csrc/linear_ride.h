@@ -354,6 +354,7 @@ __device__ inline __attribute__((always_inline)) void ride(int i, unsigned char 
     CallRef a = call_args();
     constexpr int SLICES = slices_per_head(D);
     const int H = a.H, BH = a.B * H, tid = threadIdx.x;
+    if (a.ride.polls < 0) return;
     if (i < BH * SLICES) {
         const int bh = slice_head(BH, SLICES, i), slice = slice_of(BH, SLICES, i);
         state_slice<D, ROPE>(reinterpret_cast<const u16 *>(a.k), reinterpret_cast<const u16 *>(a.v), a.N, a.rope_tab, a.ride.hfrag, a.ride.Z, bh, slice, smem, small);

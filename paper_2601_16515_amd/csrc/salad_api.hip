@@ -196,7 +196,7 @@ salad_status static_scratch_ptr(void **out)
 extern "C" {
 
 // The layer call with its own bound on how often a tile looks whether riders have done the linear branch's state before it does it itself
-// (0: always itself).  Not part of the interface: for the test of that.
+// (0: it does not wait; below: riders leave at once, and every tile has to).  Not part of the interface: for the test of that.
 salad_status salad_fwd_with_polls(const salad_fwd_params *p, int32_t polls);
 
 const char *salad_last_error(void) { return g_err; }

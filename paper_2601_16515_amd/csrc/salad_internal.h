@@ -98,6 +98,7 @@ struct RideArgs {
     int wgs, gate_tasks;            // workgroups, a multiple of 8 (0: none ride); shares of a sample's gate among them
     int crowded;                    // tiles that are not cut stay whole, too: there are no compute units for two workgroups each
     int riders, polls;              // that count in a head's word (the last of a sample's gate tasks for all of them); how often a tile looks before it does their work
+                                    // (< 0, in the test of that: riders do nothing)
     uint64_t full, tag, *words;     // count of a head's word at the end; this call's tag; [B H + B], RIDE_STRIDE apart
     const void *x_t; const float *w_gate; float b_gate;
     int gate_tok, nparts;           // tokens that a wave of gate_part takes at a time; its partial sums (0: s_dev has the scale)

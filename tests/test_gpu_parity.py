@@ -414,18 +414,18 @@ def test_workspace_without_room_for_the_pieces(oracle):
     (1, 1, 64, (5, 30, 36), 20, ""),           # the longest sequence (5400)
 ])
 def test_state_and_gate_within_the_attention_launch(B, H, d, grid, keep, opt):
-    """Short sequences: riders in the attention's launch give the bits of the launches of their own that the per-stage timing mode makes, on a
-    workspace that holds anything, then another call's leavings; and so does a tile that does not wait for them (a bound of 0 on its wait)."""
+    """Short sequences: riders in the attention's launch give the bits of the launches of their own that the per-stage timing mode makes (in
+    another workspace), on a workspace that holds anything, then another call's leavings; and so does a tile that does not wait for them (a bound
+    of 0 on its wait) or has none to wait for (-1: they leave at once, and the words of the heads are left as the tiles counted in them)."""
     w = wl.small(f"within-{H}-{d}", B, H, d, *grid, "bf16", 0.5, seed=700 + H)
     kinds, kept = wl.head_kinds(w), [min(keep, w.nb)] * H
     row_ptr, col_idx = sb.salad_block_mask(*grid, w.block, kept)
-    ws = sb.Workspace(B, H, w.N, d, sb.SALAD_BF16, full_proj=opt == "proj", rope=opt == "rope")
-    ws.buf.fill_(0x5a)
+    ws, apart = (sb.Workspace(B, H, w.N, d, sb.SALAD_BF16, full_proj=opt == "proj", rope=opt == "rope") for _ in range(2))
     for seed in (1, 2):
         inp = {k: v.copy() for k, v in wl.make_inputs(wl.small("x", B, H, d, *grid, "bf16", 0.5, seed=700 + H + seed)).items()}
         dev = upload(w, inp)
         s_out, dropped = torch.zeros(B, device="cuda"), torch.zeros(B, dtype=torch.int32, device="cuda")
-        kw = dict(lam=20.0, eps=w.eps, workspace=ws, s_out=s_out, head_scale=dev["head_scale"])
+        kw = dict(lam=20.0, eps=w.eps, s_out=s_out, head_scale=dev["head_scale"])
         if opt == "given":
             kw["s"] = torch.rand(B, device="cuda")
         else:
@@ -438,24 +438,26 @@ def test_state_and_gate_within_the_attention_launch(B, H, d, grid, keep, opt):
         if opt == "proj":
             kw.update(head_scale=None, w_proj=torch.randn(H * d, H * d, device="cuda").bfloat16() / (H * d) ** 0.5)
 
-        def call(polls=None):
+        def call(polls=None, workspace=ws):
             out = torch.full_like(dev["q"], float("nan"))
             s_out.fill_(float("nan"))
             dropped.fill_(-1)
-            p, keepalive = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, grid, row_ptr, col_idx, kinds, **kw)
+            p, keepalive = sb.make_fwd_params(dev["q"], dev["k"], dev["v"], out, grid, row_ptr, col_idx, kinds, workspace=workspace, **kw)
             sb._check(sb.lib().salad_sparse_linear_attn_fwd(C.byref(p)) if polls is None else sb.lib().salad_fwd_with_polls(C.byref(p), polls))
             torch.cuda.synchronize()
             return out, s_out.clone(), dropped.clone()
 
         sb.salad_timing_enable(1)
         try:
-            ref = call()
+            ref = call(workspace=apart)
         finally:
             sb.salad_timing_read(True)
             sb.salad_timing_enable(0)
-        for polls in (None, 0, None):
+        for polls, leavings in ((None, seed > 1), (-1, False), (0, True), (-1, False), (None, True), (None, True), (0, False)):
+            if not leavings:
+                ws.buf.fill_(0x5a)
             for got, want in zip(call(polls), ref):
-                assert torch.equal(got, want), (opt, polls, seed)
+                assert torch.equal(got, want), (opt, polls, leavings, seed)
         if opt == "drop" and B > 1:
             assert sorted(ref[2].tolist()) == [0] + [1] * (B - 1)
 
