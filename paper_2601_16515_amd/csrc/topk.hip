@@ -117,6 +117,22 @@ template <int SLOTS> struct BestBlocks {
     }
 };
 
+// a score as defined; chunk c of the mean at c ^ swap
+__device__ inline __attribute__((always_inline)) float defined_score(const u16 *row, const float4 *m, int swap = 0)
+{
+    float x = 0.f;
+#pragma unroll 4
+    for (int c = 0; c < D / 8; ++c) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(row + c * 8);
+        const float4 m0 = m[(2 * c) ^ swap], m1 = m[(2 * c + 1) ^ swap];
+        x = __fmaf_rn(__uint_as_float(v.x << 16), m0.x, x); x = __fmaf_rn(__uint_as_float(v.x & 0xffff0000u), m0.y, x);
+        x = __fmaf_rn(__uint_as_float(v.y << 16), m0.z, x); x = __fmaf_rn(__uint_as_float(v.y & 0xffff0000u), m0.w, x);
+        x = __fmaf_rn(__uint_as_float(v.z << 16), m1.x, x); x = __fmaf_rn(__uint_as_float(v.z & 0xffff0000u), m1.y, x);
+        x = __fmaf_rn(__uint_as_float(v.w << 16), m1.z, x); x = __fmaf_rn(__uint_as_float(v.w & 0xffff0000u), m1.w, x);
+    }
+    return x;
+}
+
 // grid (ceil(N / 256), BH), 256 threads: a wave owns 64 queries, two column sets of the products; JT tiles of 32 key blocks.  N = 32760, 12 heads (us, all
 // mask steps; before: the definition alone): 4 of 40 blocks 147 -> 110, 8 of 64 251 -> 141; 5 heads, N = 7800, 1 of 61 97 -> 43.  Two to four turns
 // of 256 queries a workgroup, for which the means are taken apart once, gave 135 where one gave 122.
@@ -130,14 +146,17 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
     constexpr int NS = D / 16, PAIRS = JT * SELECT_PAIRS;
     __shared__ __attribute__((aligned(16))) uint4 frag[3][JT][NS][64];          // operand order: lane (row l32, channels 8 hh ..)
     __shared__ float norm[JT * 32];
+    __shared__ int many;                           // a wave has more open scores than lanes (1), than it computes (2)
     const int bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const float *mb = means + (size_t)bh * nbk * D;
+    const float4 *mf = reinterpret_cast<const float4 *>(mb);
     if (nbk <= topk) {                      // every block
         const int n = blockIdx.x * 256 + tid;
         if (n < N) mask[(size_t)bh * N + n] = ~0ull >> (64 - nbk);
         return;
     }
     if (tid < JT * 32) norm[tid] = 0.f;
+    if (tid == 0) many = 0;
     __syncthreads();
     // the three parts of the means, largest last
     for (int x = tid; x < JT * NS * 64; x += 256) {
@@ -195,7 +214,8 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
             }
     const unsigned long long every = ~0ull >> (64 - nbk);
     unsigned long long doubtful = 0ull;                            // bit i: query n0 + i
-    unsigned long long chosen = 0ull, open = 0ull;                 // of query n0 + lane, if it is doubtful
+    float above[2], below[2];
+    bool whole[2];                                                 // nothing is known
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         float qq = 0.f;
@@ -248,47 +268,89 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
         }
         // tiny norms: the parts of the means, or the queries, may be below what a product takes.  From 1e-13 on all that is lost below 2^-126 is
         // less than 2e-5 of the bound.  The product of the two squares may be below 2^-149 then, that of the norms is not.
-        const bool bounded = finite && __shfl_xor((int)finite, 32) && qq > 1e-26f && mm > 1e-26f;
+        const unsigned long long bad = __ballot(!(finite && qq > 1e-26f && mm > 1e-26f));
+        const bool bounded = !(((uint32_t)bad | (uint32_t)(bad >> 32)) >> l32 & 1u);
         const float margin = 2 * (SELECT_MATRIX + SELECT_CHAIN) * (sqrtf(qq) * sqrtf(mm)) + 1.6e-5f * fmaxf(fabsf(last), fabsf(next));
         const bool sure = bounded && last - next > margin;
         const unsigned long long no = __ballot(!sure);
         doubtful |= (no & 0xffffffffull) << (u * 32);
         const int n = n0 + u * 32 + l32;
         if (hh == 0 && sure && n < N) mask[(size_t)bh * N + n] = m;
-        if (no) {
-            // ahead of the first left out by more than the margin: chosen; behind the last chosen by more: not; the others are open
-            unsigned long long yes = 0ull, may = 0ull;
-#pragma unroll
-            for (int jt = 0; jt < JT; ++jt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float v = acc[u][jt][r];
-                    const unsigned long long bit = 1ull << (jt * 32 + 8 * (r >> 2) + (r & 3));
-                    if (v > next + margin) yes |= bit;
-                    else if (!(v < last - margin)) may |= bit;
-                }
-            yes <<= 4 * hh;
-            may <<= 4 * hh;
-            if (!bounded) { yes = 0ull; may = ~0ull; }
-            yes |= __shfl_xor(yes, 32);
-            may |= __shfl_xor(may, 32);
-            if (hh == u) {
-                chosen = yes & every;
-                open = may & every;
-            }
-        }
+        above[u] = next + margin;
+        below[u] = last - margin;
+        whole[u] = !bounded;
     }
     if (N - n0 < 64) doubtful &= N > n0 ? (1ull << (N - n0)) - 1ull : 0ull;
-    if (!(doubtful >> lane & 1ull)) open = 0ull;
-    const int count = __popcll(open);
-    int end = count;                        // of this lane's pairs in the wave's list
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int x = __shfl_up(end, o);
-        if (lane >= o) end += x;
+    // one query in 64, which is usual where there is any: its scores as defined, a lane a block (16 heads, N = 270 10.1 -> 9.0 us against the list below)
+    if (__popcll(doubtful) == 1) {
+        const int i = __builtin_ctzll(doubtful);
+        const u16 *row = q + ((size_t)bh * N + n0 + i) * D;
+        const float x = defined_score(row, mf + min(lane, nbk - 1) * (D / 4));
+        unsigned long long m;
+        if (__all(fabsf(x) < INFINITY)) {              // a block is chosen if fewer than topk are ahead of it
+            int ahead = 0;
+            for (int J = 0; J < nbk; ++J) {
+                const float y = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), J));
+                ahead += y > x || (y == x && J < lane);
+            }
+            m = __ballot(lane < nbk && ahead < topk);
+        } else {
+            BestBlocks<SLOTS> best;
+            best.clear();
+            for (int J = 0; J < nbk; ++J) best.offer(__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), J)), J);
+            m = best.mask(topk);
+        }
+        if (lane == 0) mask[(size_t)bh * N + n0 + i] = m;
+        doubtful = 0ull;
     }
-    const int pairs = __shfl(end, 63);
-    if (__builtin_expect(__syncthreads_or(pairs > PAIRS), 0)) {
+    // of query n0 + lane, if it is doubtful: blocks ahead of the first left out by more than the margin are chosen, those behind the last chosen by more
+    // are not; the others are open
+    unsigned long long chosen = 0ull, open = 0ull;
+    int first = 0, pairs = 0;               // this lane's in the wave's list; all of them
+    const bool mine = doubtful >> lane & 1ull;
+    if (doubtful) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            uint32_t yes[2] = {}, may[2] = {};
+#pragma unroll
+            for (int jt = 0; jt < JT; ++jt) {
+#pragma unroll
+                for (int r = 15; r >= 0; --r) {
+                    const float v = acc[u][jt][r];
+                    yes[jt] += yes[jt] + (v > above[u]);
+                    may[jt] += may[jt] + !(v < below[u]);
+                }
+                may[jt] &= ~yes[jt];
+            }
+            // bit r of these two halves -> bit of the block
+            auto of_blocks = [&](const uint32_t (&x)[2]) __attribute__((always_inline)) -> unsigned long long {
+                uint32_t w[2];
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt) {
+                    uint32_t t = (x[jt] | x[jt] << 8) & 0x00ff00ffu;
+                    t = ((t | t << 4) & 0x0f0f0f0fu) << 4 * hh;
+                    auto both = __builtin_amdgcn_permlane32_swap(t, t, false, false);
+                    w[jt] = both[0] | both[1];
+                }
+                return (unsigned long long)w[1] << 32 | w[0];
+            };
+            const unsigned long long ahead = of_blocks(yes), among = of_blocks(may);
+            if (hh == u && mine) {
+                chosen = whole[u] ? 0ull : ahead & every;
+                open = whole[u] ? every : among & every;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+            const unsigned long long x = __ballot(__popcll(open) >> i & 1);
+            first += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(x >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)x, 0)) << i;
+            pairs += __popcll(x) << i;
+        }
+        if (lane == 0 && pairs > 64) atomicOr(&many, pairs > PAIRS ? 3 : 1);
+    }
+    __syncthreads();
+    const int how = many;
+    if (__builtin_expect(how & 2, 0)) {
         // the definition, a thread a query, the means as broadcast words in LDS, GROUP blocks' chains at a time
         constexpr int GROUP = 20;
         float *sm = reinterpret_cast<float *>(frag);
@@ -330,10 +392,9 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
     }
     // the open scores as defined, a lane a (query, block) pair; where a wave has many, which read many rows of means at once, from LDS, chunk c of
     // row J at c ^ (J % 16)
-    const bool stage = __syncthreads_or(pairs > 64);
     float4 *lm = reinterpret_cast<float4 *>(frag);
-    if (stage) {
-        for (int i = tid; i < nbk * (D / 4); i += 256) lm[i ^ (i / (D / 4) & 15)] = reinterpret_cast<const float4 *>(mb)[i];
+    if (how) {
+        for (int i = tid; i < nbk * (D / 4); i += 256) lm[i ^ (i / (D / 4) & 15)] = mf[i];
         __syncthreads();
     }
     if (!doubtful) return;                  // (by the numbers of the blocks in the scores a query can be doubtful and no score be open)
@@ -341,34 +402,21 @@ __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restri
     float *score = reinterpret_cast<float *>(list + PAIRS);
     static_assert(sizeof(frag) >= JT * 32 * D * 4 + 4 * PAIRS * 6, "LDS");
     {
-        int i = end - count;
+        int i = first;
         for (unsigned long long o = open; o; o &= o - 1ull) list[i++] = (u16)(lane << 6 | __builtin_ctzll(o));
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    auto compute = [&](auto mean) __attribute__((always_inline)) {
-        for (int i = lane; i < pairs; i += 64) {
-            const int p = list[i];
-            const u16 *row = q + ((size_t)bh * N + n0 + (p >> 6)) * D;
-            float x = 0.f;
-#pragma unroll 4
-            for (int c = 0; c < D / 8; ++c) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(row + c * 8);
-                const float4 m0 = mean(p & 63, 2 * c), m1 = mean(p & 63, 2 * c + 1);
-                x = __fmaf_rn(__uint_as_float(v.x << 16), m0.x, x); x = __fmaf_rn(__uint_as_float(v.x & 0xffff0000u), m0.y, x);
-                x = __fmaf_rn(__uint_as_float(v.y << 16), m0.z, x); x = __fmaf_rn(__uint_as_float(v.y & 0xffff0000u), m0.w, x);
-                x = __fmaf_rn(__uint_as_float(v.z << 16), m1.x, x); x = __fmaf_rn(__uint_as_float(v.z & 0xffff0000u), m1.y, x);
-                x = __fmaf_rn(__uint_as_float(v.w << 16), m1.z, x); x = __fmaf_rn(__uint_as_float(v.w & 0xffff0000u), m1.w, x);
-            }
-            score[i] = x;
-        }
-    };
-    if (stage) compute([&](int J, int c) __attribute__((always_inline)) { return lm[J * (D / 4) + (c ^ (J & 15))]; });
-    else compute([&](int J, int c) __attribute__((always_inline)) { return reinterpret_cast<const float4 *>(mb)[J * (D / 4) + c]; });
+    for (int i = lane; i < pairs; i += 64) {
+        const int J = list[i] & 63;
+        const u16 *row = q + ((size_t)bh * N + n0 + (list[i] >> 6)) * D;
+        if (how) score[i] = defined_score(row, lm + J * (D / 4), J & 15);
+        else score[i] = defined_score(row, mf + J * (D / 4));
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (doubtful >> lane & 1ull) {
+    if (mine) {
         BestBlocks<SLOTS> best;
         best.clear();
-        int i = end - count;
+        int i = first;
         for (unsigned long long o = open; o; o &= o - 1ull) best.offer(score[i++], __builtin_ctzll(o));
         mask[(size_t)bh * N + n0 + lane] = chosen | best.mask(topk - __popcll(chosen));
     }
