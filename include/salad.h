@@ -175,8 +175,8 @@ typedef struct salad_fwd_params {
  * the masks and per-sample lists).  Reads only B, H, N, d, dtype, topk and whether w_proj and rope_cos are NULL.
  * 0 on invalid shapes.  The pieces' results can be left out: a smaller workspace that has room for the rest is taken and
  * the tiles are not cut (same result up to rounding order); and so can what short sequences need for state and gate within
- * the attention's launch, which lies behind the pieces (those are launches of their own then).  So one workspace may serve the largest grid of a program
- * and all smaller ones, although a small grid with pieces may ask for more than a large one without.
+ * the attention's launch, which lies behind the pieces (those are launches of their own then).  So one workspace may
+ * serve the largest grid of a program and all smaller ones, although a small grid with pieces may ask for more than a large one without.
  * SALAD_ENOSPC: below the rest.
  * Nothing in a workspace has to be set or kept between calls, but calls that may overlap (other streams or threads) must
  * not share one, a call with lambda == 0 and prebuilt tile_lists, which uses it for the pieces alone, included. */
@@ -214,7 +214,8 @@ size_t salad_fwd_workspace_bytes(const salad_fwd_params *p);
  * Post-tuning branch dropping (Sec. 4.3, App. A.3): with drop_threshold = tau > 0, a sample whose dynamic
  * scale s_b < tau (strict, compared in fp32) loses its linear branch: out[b] = O_s[b], exactly as with
  * lambda == 0.  The decision is taken on the device (no host synchronisation): the gate is reduced first,
- * and the state, reduce and apply kernels skip the pruned samples, so their K, V are not read again.
+ * and the state, reduce and apply kernels skip the pruned samples, so their K, V are not read again (short sequences,
+ * where state and gate are part of the attention's launch: the state is computed, and left out of the sum).
  * bf16: MFMA kernels, fp32 accumulation, one round-to-nearest-even of the sum to bf16.
  * fp32: plain fp32 kernels intended for small shapes. */
 salad_status salad_sparse_linear_attn_fwd(const salad_fwd_params *p);
