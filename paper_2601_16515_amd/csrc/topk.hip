@@ -137,7 +137,8 @@ __device__ inline __attribute__((always_inline)) float defined_score(const u16 *
 // mask steps; before: the definition alone): 4 of 40 blocks 147 -> 110, 8 of 64 251 -> 141; 5 heads, N = 7800, 1 of 61 97 -> 43.  Two to four turns
 // of 256 queries a workgroup, for which the means are taken apart once, gave 135 where one gave 122.
 // What all keys have in common widens the bound and leaves the scores' differences as they are.  4 of 40 blocks of normal keys with as much as 1, 3, 10, 30
-// of it in every channel: 113, 116, 123, 145 (before 141; each doubtful query's 40 scores, one query at a time: 201, 208, 208).  All keys equal, so that
+// of it in every channel: 113, 116, 123, 145 (before 141; where a wave took all scores of
+// its doubtful queries one query at a time, up to 6 of them, 201, 208, 208, -).  All keys equal, so that
 // every score is open: 212 (144).  Less the average of 8 means it was 131, and 133, 135, 142, 180 there, with fewer waves for its registers.
 template <int JT, int SLOTS>
 __global__ __launch_bounds__(256, 2) void topk_select_kernel(const u16 *__restrict__ q, const float *__restrict__ means, int N, int nbk, int topk,
