@@ -159,6 +159,7 @@ struct AttnArgs {
     // filled in by the large-tile kernel's launcher: pieces a tile for which each has a compute unit to itself; an XCD's pieces over the
     // pieces of a tile, rounded up; multiply-high inverses
     int sp_alone, sp_rows;
+    int many;                       // more tiles than a round of one on each compute unit
     unsigned tiles_magic, heads_magic, pieces_magic, rows_magic;
     int variant;                    // 0: automatic choice of the d = 128 kernel; 1: 128-query tiles; 2: first-generation kernel
 };

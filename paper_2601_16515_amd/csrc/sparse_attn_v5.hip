@@ -10,14 +10,16 @@
 //     (global_load_lds_dwordx4, bank swizzle applied on the global side).  The wait before the
 //     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
+//   * Products are 32x32x16 or, for long lists in calls that fill the chip, 16x16x32 ones (LONG_LIST): an instantiation holds both ways from the
+//     queries' operands to the epilogue, and a tile takes one by its list's length.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
 //     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's
 //     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).
 //   * What bounds the loop is the energy of its instructions: the chip is at its power limit, and fewer cycles for the same
 //     instructions only lower the clock.  So whatever is the same for a whole wave is on the scalar unit, and the tiles in LDS
 //     are laid out so that operand addresses are one register and an immediate.  Layer calls at B = 1, N = 32760 with that, the row
-//     sums on the matrix pipe and, for 64-wide heads, two query sets a wave: 12 heads of 128 dense 5863 -> 5477 us (1.20 PFLOP/s),
-//     at 90 % 694 -> 664, 24 heads of 64 at 90 % 862 -> 712.
+//     sums on the matrix pipe and, for 64-wide heads, two query sets a wave: 12 heads of 128 dense 5863 -> 5477 us, at 90 % 694 -> 664, 24 heads
+//     of 64 at 90 % 862 -> 712; with the smaller products (another card) 5604 -> 5257 (1.25 PFLOP/s), 671 -> 645, 737 -> 704.
 //   * V^T operands come from ds_read_b64_tr_b16, K rows are read through the kappa permutation so
 //     that P never moves between lanes.  LDS operand reads are spread evenly between the MFMAs through a
 //     small ring of fragment registers.
@@ -27,6 +29,8 @@
 //     reference by more than 13 binades (the reference then moves to the true maximum and the block is redone).
 //   * Epilogue: the bf16 fragments of the linear state are staged once per workgroup in LDS.
 #include "linear_ride.h"
+#include <type_traits>
+#include <utility>
 
 namespace salad {
 
@@ -46,6 +50,11 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8)
 #define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | ((n) >> 4) << 14)
 
+// Least entries of a list for 16x16x32 products (the kernel's G).  Layer calls of more than 256 tiles with 32x32x16 -> 16x16x32 products (us), by
+// entries: 4 to 9 40 heads, N = 1700 67.4 -> 68.6; 12 12 heads, N = 5500 64.4 -> 64.6; 16 8 heads, N = 16384 102.6 -> 100.8; 27 40 heads, N = 1700 113.0 ->
+// 112.4; 67 8 heads, N = 16384 267.5 -> 260.1; 52 12 heads, N = 12480 271.2 -> 263.0; 54 12 heads, N = 32760 671 -> 645, 512 5604 -> 5257; 64-wide heads: 13 24
+// heads, N = 12480 110.0 -> 124.5, 101 531 -> 488; 54 24 heads, N = 32760 737 -> 704.
+constexpr int LONG_LIST = 20;
 constexpr int SPLIT_MAX_PIECES = 8;
 constexpr int SPLIT_MIN_ENTRIES = 6;     // least entries of a piece: what a cut costs (two passes over 128 KB, a prologue) is about as long
 
@@ -123,13 +132,34 @@ __device__ inline unsigned lds_addr_of(const void *p)
     return __builtin_amdgcn_readfirstlane((unsigned)(size_t)LDS_PTR(p));
 }
 
-// max of a value with its copy in the other 32-lane half, on the VALU (v_permlane32_swap): a cross-lane shuffle would
-// go through the LDS unit, which the operand reads of the CU's waves keep busy.
-__device__ inline float max_with_other_half(float x)
+// max of a value over the lanes that own keys of the same query (every G-th), on the VALU: a cross-lane shuffle would go through the LDS
+// unit, which the operand reads of the CU's waves keep busy.
+template <int G>
+__device__ inline float max_of_query(float x)
 {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    if constexpr (G == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+
+// f(0) .. f(N - 1) with compile-time arguments: where the order of the instructions matters nothing is left for the optimiser to decide (it
+// computes the arms of a condition on an unrolled loop's variable ahead of the loop's other work before it knows the variable).
+template <class F, int... I>
+__device__ inline INL void unrolled_(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ inline INL void unrolled(F &&f)
+{
+    unrolled_(f, std::make_integer_sequence<int, N>{});
+}
+
+// by value: a conditional expression of two array elements selects between their addresses, and the array goes to memory
+__device__ inline float either(bool second, float a, float b) { return second ? b : a; }
 
 union Frag5 {
     bf16x8 v;
@@ -243,7 +273,6 @@ template <int D, bool DBG, int MODE = 0, bool ROPE = false, bool SPLIT = false, 
 __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a, int ntiles, int total, int per_xcd, int list_cap)
 {
     static_assert(D == 128 || (D == 64 && MODE == 0 && !ROPE), "d = 64 has the CSR mode only");
-    constexpr int NS = D / 16, NDT = D / 32;     // 16-channel steps of S, 32-channel tiles of O^T
     constexpr int CH = D / 8;                    // 16-byte chunks per row
     constexpr int NW = 8 / QS, NT = 64 * NW;     // waves, threads
     constexpr int CG = CH / 4, NPASS = 4 * CG / NW;   // groups of 4 chunks per row; loads of a thread per tile
@@ -255,6 +284,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     uint32_t *blist = reinterpret_cast<uint32_t *>(Vb + NV * TILE);      // [list_cap] union list: blk | mask << 24
 
     constexpr bool TOPK = MODE == 1, GATHER = MODE == 2;
+    // Which products the kernel has (G below): calls of one round of tiles and the gathered ones have the larger only.
+    constexpr bool BOTH = MODE == 0 && !RIDE && (D == 128 || QS == 2);
     // chunk swizzle of the output staging
     auto oswz = [](int row) INL -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
     float (*ride_small)[32] = nullptr;
@@ -308,7 +339,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     constexpr uint32_t BLKMASK = TOPK ? 0xffffu : 0xffffffu;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, hh = lane >> 5;
+    const int l32 = lane & 31, hh = lane >> 5;       // a lane's query of a set and half of a row, where rows are read and written
     const u16 *qb = reinterpret_cast<const u16 *>(a.q) + (size_t)bh * N * D;
     const u16 *kb = reinterpret_cast<const u16 *>(a.k) + (size_t)bh * N * D;
     const u16 *vb = reinterpret_cast<const u16 *>(a.v) + (size_t)bh * N * D;
@@ -326,6 +357,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const int g_blk0 = g_J * a.g_bpb;
     const uint32_t *src = GATHER ? nullptr : a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
+    const int n_list = n;
     if (SPLIT && pieces > 1) {
         int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
         if (QS == 2) {
@@ -353,12 +385,59 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
     for (int b = 0; b < AK; ++b) eq[b] = GATHER ? (uint32_t)min(g_blk0 + b, nb - 1) | 0xff000000u : src[SPLIT ? min(list0 + b, list_cap - 1) : b];
 
+    // what chunk c of row r of a K or Q piece is swapped with (below)
+    auto kswz = [](int row) INL -> int { return -(row >> 2) & 3; };
+    const unsigned wave_u = (unsigned)__builtin_amdgcn_readfirstlane(wave);
+    // Queries go through LDS, too, each wave's own into a part of the ring that nothing else uses yet: read from memory in operand order,
+    // 32 bytes of 32 rows at a time, they pass the 64 bytes a clock of the load path four times.  Laid out like a K tile (below).
+    auto q_lds = [&](int u) INL -> unsigned char * {
+        const int unit = (int)wave_u * QS + u;
+        return reinterpret_cast<unsigned char *>(unit < 6 ? Kb + (2 + (unit >> 1)) * TILE : Vb + (NV - 1) * TILE) + (unit & 1) * (32 * D * 2);
+    };
+    auto fetch_q = [&]() INL {
+#pragma unroll
+        for (int u = 0; u < QS; ++u)
+#pragma unroll
+            for (int rg = 0; rg < 2; ++rg) {
+                const int i = ((int)wave_u * QS + u) * 32 + rg * 16 + (lane >> 2);      // query of the tile
+                int row;
+                if (GATHER) row = min(max(a.g_idx[(size_t)bh * N * a.g_kk + g_slot0 + (i < g_cnt ? i : 0)], 0), N - 1);
+                else row = row_of_position5(kind, min(tile * 256 + i, N - 1), T, HW, magic);
+                const unsigned off = (unsigned)row * (unsigned)(D * 2) + (unsigned)(((lane & 3) ^ kswz(lane >> 2)) * 16);
+                const unsigned dst = lds_addr_of(q_lds(u)) + (unsigned)(rg * CG * 1024);
+#pragma unroll
+                for (int c = 0; c < CG; ++c) lds_dma16_base(qb + c * 32, off, dst + c * 1024u);
+            }
+    };
+    if (!GATHER) fetch_q();
+    // the list's whole row of list_cap slots (built by the pre-pass), without waiting for the count: slots past it hold stale words
+    // that are never used
+    if (!GATHER)
+        for (int i = (int)wave_u * 64; i < list_cap; i += NT)
+            lds_dma4(src + (SPLIT ? min(i + lane + list0, list_cap - 1) : i + lane), lds_addr_of(blist + i));
+
+    // ---- All else depends on the products.  16x16x32 ones read and write half the accumulators of 32x32x16 ones for the same work (a loop of
+    // them alone reaches 12 % more at the power limit, with this softmax between them 8 %), and the loop of a call that fills the chip is held by
+    // the power limit.  But each has its own start to line up with the vector instructions: a block takes 3140 cycles instead of 2960, and a
+    // call of one round, or a tile that is half prologue and output, is held by those.  So G = 16 where the list is LONG_LIST entries or more and
+    // the call more than one round (a.many); the whole list's length, so that the pieces of a cut tile are of one kind.
+    auto rest = [&](auto g_) INL {
+    constexpr int G = decltype(g_)::value;
+    constexpr int KD = 512 / G, NS = D / KD;     // channels of a product of S, its steps
+    constexpr int NDT = D / G;                   // G-channel tiles of O^T
+    constexpr int QG = 32 / G * QS;              // groups of G queries that a wave owns: the columns of one product
+    constexpr int NKG = 32 / G;                  // products of S for the 32 keys of a half
+    constexpr int NP = G / 16;                   // P's operands for them
+    constexpr int EL = G / 2;                    // logits of a half that a lane owns, a group
+    constexpr int AR = G * G / 64;               // accumulators of a lane
+    typedef float acc_t __attribute__((ext_vector_type(AR)));
+    const int lq = lane % G, ls = lane / G;          // a lane's query of a group and share of 8 channels or 4 rows in the products
     unsigned mybit = 0u;
     bool qvalid[QS];
     int qrow[QS];
     size_t g_slot[QS];                    // GATHER: this lane's (query, key block) pairs
-    Frag5 qf[QS][NS];
-    uint32_t qm_lo[QS] = {}, qm_hi[QS] = {};     // TOPK: this lane's queries' key-block bits
+    Frag5 qf[QG][NS];
+    uint32_t qm_lo[QG] = {}, qm_hi[QG] = {};     // TOPK: this lane's queries' key-block bits
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
         const int unit = wave * QS + u, qblk = tile * 4 + (unit >> 1), qpos = qblk * 64 + (unit & 1) * 32 + l32;
@@ -376,55 +455,32 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             qrow[u] = row_of_position5(kind, qvalid[u] ? qpos : N - 1, T, HW, magic);
             if (ROW_PAIRS) qvalid[u] = qvalid[u] && active;
         }
-        if (TOPK && qvalid[u]) {
-            const unsigned long long m = a.topk_mask[(size_t)bh * N + qrow[u]];
-            qm_lo[u] = (uint32_t)m;
-            qm_hi[u] = (uint32_t)(m >> 32);
-        }
-    }
-    const unsigned wave_u = (unsigned)__builtin_amdgcn_readfirstlane(wave);
-    // Queries go through LDS, too, each wave's own into a part of the ring that nothing else uses yet: read from memory in operand order,
-    // 32 bytes of 32 rows at a time, they pass the 64 bytes a clock of the load path four times.  Laid out like a K tile (below).
-    auto q_lds = [&](int u) INL -> unsigned char * {
-        const int unit = (int)wave_u * QS + u;
-        return reinterpret_cast<unsigned char *>(unit < 6 ? Kb + (2 + (unit >> 1)) * TILE : Vb + (NV - 1) * TILE) + (unit & 1) * (32 * D * 2);
-    };
-    auto fetch_q = [&]() INL {
+        if (TOPK)
 #pragma unroll
-        for (int u = 0; u < QS; ++u)
-#pragma unroll
-            for (int rg = 0; rg < 2; ++rg) {
-                const int i = ((int)wave_u * QS + u) * 32 + rg * 16 + (lane >> 2);      // query of the tile
-                int row;
-                if (GATHER) row = min(max(a.g_idx[(size_t)bh * N * a.g_kk + g_slot0 + (i < g_cnt ? i : 0)], 0), N - 1);
-                else row = row_of_position5(kind, min(tile * 256 + i, N - 1), T, HW, magic);
-                const unsigned off = (unsigned)row * (unsigned)(D * 2) + (unsigned)(((lane & 3) ^ (lane >> 4)) * 16);
-                const unsigned dst = lds_addr_of(q_lds(u)) + (unsigned)(rg * CG * 1024);
-#pragma unroll
-                for (int c = 0; c < CG; ++c) lds_dma16_base(qb + c * 32, off, dst + c * 1024u);
+            for (int c = 0; c < NKG; ++c) {     // spatial heads only: a position is its row
+                const int row = qblk * 64 + (unit & 1) * 32 + c * G + lq;
+                const unsigned long long m = qblk < nb && row < N ? a.topk_mask[(size_t)bh * N + row] : 0ull;
+                qm_lo[NKG * u + c] = (uint32_t)m;
+                qm_hi[NKG * u + c] = (uint32_t)(m >> 32);
             }
-    };
-    if (!GATHER) fetch_q();
-    // the list's whole row of list_cap slots (built by the pre-pass), without waiting for the count: slots past it hold stale words
-    // that are never used
-    if (!GATHER)
-        for (int i = (int)wave_u * 64; i < list_cap; i += NT)
-            lds_dma4(src + (SPLIT ? min(i + lane + list0, list_cap - 1) : i + lane), lds_addr_of(blist + i));
-
+    }
     const float c2 = a.scale * 1.44269504088896340736f;   // logits are handled in the log2 domain
 
     // ---- global -> LDS.  A tile is laid out in pieces of 1 KB, 16 rows by 4 chunks (64 bytes) each, the CG pieces of 16 rows one
-    // after the other; one load of a wave fills a piece.  Within a piece chunk c of row r is at r * 64 + c * 16 for V and
-    // r * 64 + ((c ^ (r / 4 % 4)) * 16) for K (the swap is made in the global address), so that both the 16 rows of a K operand and
-    // the 4 rows by 64 bytes that 32 lanes of a transposing V read take cover all banks once.  Of an operand's address only two bits
-    // of K's chunk depend on both lane and step; all else of the step is an immediate.
+    // after the other; one load of a wave fills a piece.  Within a piece chunk c of row r is at r * 64 + ((c ^ x(r)) * 16), the swap being
+    // made in the global address, so that each 256 bytes that a read takes at a time cover all banks once.  Those are, for the transposing reads
+    // of V, 32 lanes in a row: 4 rows by 64 bytes (G = 32: no swap) or 8 rows by 32 bytes (G = 16: x = r / 4 % 2 * 2); for the 16-byte reads of
+    // K and Q lanes 0-3, 12-15, 20-23 and 24-27, then 4-7, 8-11, 16-19 and 28-31: x = -(r / 4) % 4 (r / 4 % 4 does for G = 32, but with four
+    // shares of channels side by side it costs twice the cycles of every read).  Of an operand's address only one or two bits of the chunk depend
+    // on both lane and step; all else of the step is an immediate.
     // LDS destinations are wave-uniform scalars; global sources are a uniform base plus a 32-bit offset.
     const unsigned k_lds0 = lds_addr_of(Kb) + wave_u * (NPASS * 1024u);
     const unsigned v_lds0 = lds_addr_of(Vb) + wave_u * (NPASS * 1024u);
     const unsigned Tk = kind ? (unsigned)T : 0x7fffffffu;
     const int lr = wave * NPASS / CG * 16 + (lane >> 2);                       // this thread's row of a tile
-    const unsigned vchunk_b = (unsigned)(wave * NPASS % CG * 64 + (lane & 3) * 16);
-    const unsigned kv_b = (unsigned)((((lane & 3) ^ (lane >> 4)) - (lane & 3)) * 16);     // K's chunk less V's
+    const int vchunk = (lane & 3) ^ (G == 16 ? (lane >> 4 & 1) * 2 : 0);
+    const unsigned vchunk_b = (unsigned)(wave * NPASS % CG * 64 + vchunk * 16);
+    const unsigned kv_b = (unsigned)((((lane & 3) ^ kswz(lane >> 2)) - vchunk) * 16);     // K's chunk less V's
     // byte offset of this thread's row of a block and its V chunk.  The division is by a scalar, of the block's first row; a lane's own
     // part is a constant, but for one wrap of the time axis.  Without a branch on the order (a spatial head is location 0, stride 1).
     const unsigned magic_u = kind ? magic : 0u, stride_b = (unsigned)((kind ? HW : 1) * D * 2), back_b = (unsigned)(D * 2) - (unsigned)T * stride_b;
@@ -466,67 +522,77 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         fetch_v(r0, 0);
     }
 
-    // ---- LDS operand addresses (element offsets inside a tile)
-    const int kappa = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-    unsigned koff[2];
+    // ---- LDS operand addresses.  P never moves between lanes: the logits that a lane gets are those of the keys whose P it has to hold.
+    // G = 32 reads K's rows in the order that swaps bits 2 and 3 of the row (kappa); the accumulators are then the 8-key groups of P's operands.
+    // With G = 16 a lane's logits of a half are keys 16 kg + 4 ls + t (kg the product, t the register), and V is read in that order of keys;
+    // an operand of K is one piece of a tile, of V^T half the width of two.
+    unsigned koff[2], voff[2];
+    if constexpr (G == 16) {
+        koff[0] = koff[1] = (unsigned)(lq * 64 + ((ls ^ kswz(lq)) << 4));
+        voff[0] = (unsigned)((4 * ls + (lq >> 2)) * 64 + ((((lq & 3) >> 1) ^ (ls & 1) * 2) << 4) + 8 * (lq & 1));
+        voff[1] = voff[0] ^ 32u;
+    } else {
+        const int kappa = (l32 & 0x13) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
-        koff[p] = (unsigned)((kappa >> 4) * (CG * 1024) + (kappa & 15) * 64 + (((2 * p + hh) ^ ((kappa >> 2) & 3)) << 4));
-    const unsigned voff = (unsigned)((8 * hh + ((l32 >> 2) & 3)) * 64 + (2 * (l32 >> 4) + ((l32 & 3) >> 1)) * 16 + 8 * (l32 & 1));
-    auto k_frag = [&](const u16 *Kt, int half, int st) INL -> bf16x8 {
-        return *(const bf16x8 *)(reinterpret_cast<const unsigned char *>(Kt) + koff[st & 1] + half * (2 * CG * 1024) + (st >> 1) * 1024);
+        for (int p = 0; p < 2; ++p)
+            koff[p] = (unsigned)((kappa >> 4) * (CG * 1024) + (kappa & 15) * 64 + (((2 * p + hh) ^ kswz(kappa)) << 4));
+        voff[0] = voff[1] = (unsigned)((8 * hh + ((l32 >> 2) & 3)) * 64 + (2 * (l32 >> 4) + ((l32 & 3) >> 1)) * 16 + 8 * (l32 & 1));
+    }
+    // step t of the S products of a half, and of its O^T products
+    auto k_frag = [&](const u16 *Kt, int half, int t) INL -> bf16x8 {
+        const unsigned char *p = reinterpret_cast<const unsigned char *>(Kt) + half * (2 * CG * 1024);
+        if constexpr (G == 16) return *(const bf16x8 *)(p + koff[0] + t / NS * (CG * 1024) + t % NS * 1024);
+        else return *(const bf16x8 *)(p + koff[t & 1] + (t >> 1) * 1024);
     };
-    auto v_frag = [&](Frag5 &f, const u16 *Vt, int kg, int dt) INL {
-        const unsigned char *p = reinterpret_cast<const unsigned char *>(Vt) + voff + kg * (CG * 1024) + dt * 1024;
+    auto v_frag = [&](Frag5 &f, const u16 *Vt, int half, int t) INL {
+        const unsigned char *p = reinterpret_cast<const unsigned char *>(Vt) + half * (2 * CG * 1024);
+        if constexpr (G == 16) p += voff[t & 1] + (t >> 1) * 1024;
+        else p += voff[0] + t / NDT * (CG * 1024) + t % NDT * 1024;
         f.h[0] = TR_READ(p);
-        f.h[1] = TR_READ(p + 256);
+        f.h[1] = TR_READ(p + (G == 16 ? CG * 1024 : 256));
     };
 
-    f32x16 o[QS][NDT];
-    float m_run[QS], l_run[QS];
-    bool have_ref[QS];                     // m_run has been set from a block's true maximum (wave-uniform unless TOPK)
+    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+    acc_t zero;
 #pragma unroll
-    for (int u = 0; u < QS; ++u) {
+    for (int r = 0; r < AR; ++r) zero[r] = 0.f;
+    auto product = [&](const Frag5 &x, const Frag5 &y, acc_t c) INL -> acc_t {
+        if constexpr (G == 16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v, y.v, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(x.v, y.v, c, 0, 0, 0);
+    };
+    acc_t o[QG][NDT];
+    float m_run[QG], l_run[QG];
+    bool have_ref[QG];                     // m_run has been set from a block's true maximum (wave-uniform unless TOPK)
 #pragma unroll
-        for (int i = 0; i < NDT; ++i)
+    for (int u = 0; u < QG; ++u) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) o[u][i][r] = 0.f;
+        for (int i = 0; i < NDT; ++i) o[u][i] = zero;
         m_run[u] = l_run[u] = 0.f;
         have_ref[u] = false;
     }
-    f32x16 s[QS][2];
-    Frag5 pf[QS][4];
-
-    // The unit of work is half a block (32 keys).  A part = the S products of one half (NS MFMAs, A = K rows) and the O^T
-    // products of one half (2 NDT MFMAs, A = V^T, two transposing 8-byte reads), with the softmax of a third half woven
-    // between them.  Operand fragments move through a ring of RING register quads: step i takes ring[i % RING] and the read
+    acc_t s[QG][2][NKG];                   // logits: group, half of the block, G keys of the half
+    Frag5 pf[QG][2][NP];
+    auto logit = [&](int u, int hf, int e) INL -> float { return s[u][hf][e / AR][e % AR]; };
+    auto p_word = [&](int u, int hf, int pair) INL -> uint32_t & { return pf[u][hf][pair >> 2].w[pair & 3]; };
+    // The unit of work is half a block (32 keys).  A part = the S products of one half (NKG NS operands, A = K rows) and the O^T
+    // products of one half (NP NDT operands, A = V^T, two transposing 8-byte reads), each against every group of queries, with the
+    // softmax of a third half woven between them.  Operand fragments move through a ring of RING register quads: step i takes ring[i % RING] and the read
     // of fragment i + RING is issued right after it; the last steps of a block read the next block's first K fragments.
     constexpr int RING = QS == 2 ? 2 : 4;         // 8: 5957 against 5842 us on the dense call; QS = 2 with 4: 731 against 725 us
     Frag5 ring[RING];
-    constexpr int NPS = NS + 2 * NDT;             // steps of a part
+    constexpr int SS = NKG * NS, OS = NP * NDT, NPS = SS + OS;      // steps of a part
     static_assert((2 * NPS) % RING == 0, "a block's fragments go round the ring a whole number of times");
     auto read_frag = [&](int i, const u16 *Vt, const u16 *Kt, const u16 *Kn) INL {     // i counts a block's 2 NPS fragments
         Frag5 &f = ring[i % RING];
         const int pt = i / NPS, t = i % NPS;
-        if (t < NS) {
-            f.v = k_frag(pt < 2 ? Kt : Kn, pt & 1, t);
-        } else {
-            v_frag(f, Vt, (pt & 1) * 2 + (t - NS) / NDT, (t - NS) % NDT);
-        }
+        if (t < SS) f.v = k_frag(pt < 2 ? Kt : Kn, pt & 1, t);
+        else v_frag(f, Vt, pt & 1, t - SS);
     };
     auto mfma_S = [&](int u, int pt, int t, const Frag5 &f) INL {
-        if (t == 0) {
-            f32x16 z;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) z[r] = 0.f;
-            s[u][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[u][0].v, z, 0, 0, 0);
-        } else {
-            s[u][pt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, qf[u][t].v, s[u][pt], 0, 0, 0);
-        }
+        acc_t &acc = s[u][pt][t / NS];
+        acc = product(f, qf[u][t % NS], t % NS == 0 ? zero : acc);
     };
-    auto mfma_PV = [&](int u, int pt, int t, const Frag5 &f) INL {
-        o[u][t % NDT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.v, pf[u][pt * 2 + t / NDT].v, o[u][t % NDT], 0, 0, 0);
-    };
+    auto mfma_PV = [&](int u, int pt, int t, const Frag5 &f) INL { o[u][t % NDT] = product(f, pf[u][pt][t / NDT], o[u][t % NDT]); };
     // TOPK: a lane whose query did not select the entry's key block gets P = 0 (scale 0, reference +inf) and takes no part
     // in the reference updates
     auto selected = [&](int u, uint32_t e) INL -> bool {
@@ -539,29 +605,34 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (__builtin_expect((uint32_t)blk == tail_blk, 0)) {
             int first = blk * 64;
             asm volatile("" : "+s"(first));      // else the compares, the same in every such block, leave the loop and fill the scalar registers
-            const int kbase = first + hf * 32 + hh * 8;
+            const int kbase = first + hf * 32 + ls * (G / 4);
 #pragma unroll
-            for (int u = 0; u < QS; ++u)
+            for (int u = 0; u < QG; ++u)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (kbase + 16 * (r >> 3) + (r & 7) >= N) s[u][hf][r] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
+                for (int e = 0; e < EL; ++e)
+                    if (kbase + 16 * (e / (G / 4)) + e % (G / 4) >= N) s[u][hf][e / AR][e % AR] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
         }
     };
-    // Sums of 16 keys' bf16 probabilities, every lane getting its query's.  As the B operand of a 16x16x32 product a fragment's lanes
-    // 0..15 and 32..47 hold keys of queries 0..15, the others keys of queries 16..31, and a lane's results are the rows 4 (lane / 16)
-    // .. + 3 of column lane % 16: the A operand picks by row which of the two goes there.  Four of these a block take 64 cycles of the
-    // matrix pipe where 16 v_dot2c_f32_bf16 took 256 (plain adds of the unpacked pairs take two more vector instructions per pair,
-    // and the loop is held by the energy of its instructions).  Layer call, B = 1, N = 32760: 12 heads of 128 dense 5830 -> 5712 us, at
-    // 90 % 687 -> 672; 24 heads of 64 at 90 % 858 -> 846; the error against 64 bits is the same to six digits.  Two rows share a column and
-    // are told apart by zeros only, which is good for finite probabilities: see sums_apart.
+    // Sums of bf16 probabilities, every lane getting its query's, by 16x16x32 products.  With G = 16 the other operand is all ones.  With G = 32 a
+    // fragment's lanes 0..15 and 32..47 are, as operand of such a product, keys of queries 0..15, the others keys of queries 16..31, and a
+    // lane's results are the rows 4 (lane / 16) .. + 3 of column lane % 16: the A operand picks by row which of the two goes there.  Two rows
+    // then share a column and are told apart by zeros only, which is good for finite probabilities: see sums_apart.
+    // Four products a block and 32 queries take 64 cycles of the matrix pipe where 16 v_dot2c_f32_bf16 took 256 (plain adds of the unpacked
+    // pairs take two more vector instructions per pair, and the loop is held by the energy of its instructions).  Layer call, B = 1, N = 32760:
+    // 12 heads of 128 dense 5830 -> 5712 us, at 90 % 687 -> 672; the error against 64 bits is the same to six digits.
     Frag5 pick;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) pick.w[i] = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
+    for (int i = 0; i < 4; ++i) pick.w[i] = G == 16 || ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x3f803f80u : 0u;
     asm volatile("" : "+v"(pick.w[0]), "+v"(pick.w[1]), "+v"(pick.w[2]), "+v"(pick.w[3]));
-    auto row_sum = [&](int u, int i, f32x4 acc) INL -> f32x4 { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, pf[u][i].v, acc, 0, 0, 0); };
-    const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-    // The same for both pieces of a half, with the same bits, but each row by itself: in row_sum a probability that is not finite (a NaN or an
-    // infinity in a query, a logit far above the reference) times the zeros that part the rows makes the sum 16 lanes away a NaN as well.
+    auto row_sum = [&](int u, int hf, int i, f32x4 acc) INL -> f32x4 { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, pf[u][hf][i].v, acc, 0, 0, 0); };
+    auto row_sums = [&](int u, int hf) INL -> float {
+        f32x4 acc = zero4;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) acc = row_sum(u, hf, i, acc);
+        return acc[0];
+    };
+    // The sums of a half, with the same bits, but each row by itself: with G = 32 a probability that is not finite (a NaN or an infinity in a
+    // query, a logit far above the reference) times the zeros that part the rows makes the sum 16 lanes away a NaN as well.
     auto sums_apart = [&](int u, int hf) INL -> float {
         int l = lane;
         asm volatile("" : "+v"(l));                  // else the two masks live in registers all through the loop
@@ -572,10 +643,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             const uint32_t mine = side ? odd : ~odd;
             f32x4 acc = zero4;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
+            for (int i = 0; i < NP; ++i) {
                 Frag5 p;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) p.w[j] = pf[u][hf * 2 + i].w[j] & mine;
+                for (int j = 0; j < 4; ++j) p.w[j] = pf[u][hf][i].w[j] & mine;
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick.v, p.v, acc, 0, 0, 0);
             }
             sum |= __float_as_uint(acc[0]) & mine;
@@ -587,11 +658,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     auto exp_pack = [&](int u, int hf, bool sel) INL -> float {
         const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run[u];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const uint32_t w = pair_exp(fmaf(s[u][hf][2 * q], cs, -mref), fmaf(s[u][hf][2 * q + 1], cs, -mref));
-            pf[u][hf * 2 + (q >> 2)].w[q & 3] = w;
-        }
-        return row_sum(u, hf * 2 + 1, row_sum(u, hf * 2, zero4))[0];
+        for (int q = 0; q < EL / 2; ++q) p_word(u, hf, q) = pair_exp(fmaf(logit(u, hf, 2 * q), cs, -mref), fmaf(logit(u, hf, 2 * q + 1), cs, -mref));
+        return row_sums(u, hf);
     };
     // The reference only has to keep 2^S in range, so the maximum is not computed unless the sums say that some logit rose
     // more than 13 binades above the reference (or no reference exists yet): then the reference moves to the true maximum
@@ -599,36 +667,36 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // counts, so that a row's first reference is the maximum of 64 keys, whose weight is then exactly 1 (keys past the sequence
     // end need no mask here: their K rows are copies of the last one, which is in the block).
     // With the maximum of the first 32 keys alone the error against 64 bits is up to 3 % larger (N = 1170, 95 %: 2.08e-3 -> 2.14e-3).
-    // The sums are products over 32 lanes, so the way here is the whole wave's, and what differs between lanes is selected, not branched on
-    // (TOPK: a lane that did not select the entry keeps its reference and adds nothing, whatever the product put into its sum).
-    // A sum that is not finite says so for its own row or for the one 16 lanes away; sums_apart tells which, only rows that did rise move, and
-    // the new sums are taken apart, too, so that a row's result does not depend on the others of its wave.
-    auto settle = [&](int hf, bool whole, bool started, uint32_t e, const float (&ps)[QS]) INL {
-        float psum[QS];
-        bool redo[QS], any = false;
+    // The sums are products over the wave's lanes, so the way here is the whole wave's, and what differs between lanes is selected, not
+    // branched on (TOPK: a lane that did not select the entry keeps its reference and adds nothing, whatever the product put into its sum).
+    // Only rows that did rise move, so that a row's result does not depend on the others of its wave; with G = 32 a sum that is not finite says so
+    // for its own row or for the one 16 lanes away, and sums_apart tells which.
+    auto settle = [&](int hf, bool whole, bool started, uint32_t e, const float (&ps)[QG]) INL {
+        float psum[QG], all = 0.f;
+        bool first[QG], any = false;
 #pragma unroll
-        for (int u = 0; u < QS; ++u) {
+        for (int u = 0; u < QG; ++u) {
             psum[u] = ps[u];
-            redo[u] = !started && !have_ref[u];
-            if (TOPK) redo[u] = __any(selected(u, e) && redo[u]);
-            redo[u] = redo[u] || __any(!(psum[u] <= 8192.f));
-            any = any || redo[u];
+            all += psum[u];                      // none is negative: within the bound only if each is
+            first[u] = !started && !have_ref[u];
+            if (TOPK) first[u] = __any(selected(u, e) && first[u]);
+            any = any || first[u];
         }
-        if (__builtin_expect(any, 0)) {
+        if (__builtin_expect(any || __any(!(all <= 8192.f)), 0)) {
 #pragma unroll
-            for (int u = 0; u < QS; ++u)
-                if (redo[u]) {
+            for (int u = 0; u < QG; ++u)
+                if (first[u] || __any(!(psum[u] <= 8192.f))) {
                     const bool known = started || have_ref[u];
-                    float own = 0.f;
-                    if (TOPK || known) own = sums_apart(u, hf);
+                    float own = psum[u];
+                    if (G == 32 && (TOPK || known)) own = sums_apart(u, hf);
                     const bool rises = !known | !(own <= 8192.f), moves = TOPK ? rises & selected(u, e) : rises;
-                    float mx = s[u][hf][0];
+                    float mx = logit(u, hf, 0);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][hf][r]);
+                    for (int r = 0; r < EL; ++r) mx = fmaxf(mx, logit(u, hf, r));
                     if (whole)
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[u][1][r]);
-                    mx = fmaf(fmaxf(max_with_other_half(mx), -1e30f), c2, -m_run[u]);   // maximum minus reference
+                        for (int r = 0; r < EL; ++r) mx = fmaxf(mx, logit(u, 1, r));
+                    mx = fmaf(fmaxf(max_of_query<G>(mx), -1e30f), c2, -m_run[u]);   // maximum minus reference
                     const float shift = !moves ? 0.f : known ? fmaxf(mx, 0.f) : mx;   // new reference minus old reference
                     if (TOPK || known) {
                         const float alpha = TOPK && !known ? 1.f : __builtin_amdgcn_exp2f(-shift);
@@ -636,64 +704,69 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
                         for (int i = 0; i < NDT; ++i)
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) o[u][i][r] *= alpha;
+                            for (int r = 0; r < AR; ++r) o[u][i][r] *= alpha;
                     }
                     m_run[u] += shift;
                     have_ref[u] = !TOPK || moves || have_ref[u];      // TOPK apart the same for all lanes, which the compiler is to see
                     psum[u] = exp_pack(u, hf, selected(u, e));
-                    if (__builtin_expect(__any(!(psum[u] <= 8192.f)), 0)) psum[u] = sums_apart(u, hf);
+                    if (G == 32 && __builtin_expect(__any(!(psum[u] <= 8192.f)), 0)) psum[u] = sums_apart(u, hf);
                 }
         }
 #pragma unroll
-        for (int u = 0; u < QS; ++u) l_run[u] += !TOPK || selected(u, e) ? psum[u] : 0.f;
+        for (int u = 0; u < QG; ++u) l_run[u] += !TOPK || selected(u, e) ? psum[u] : 0.f;
     };
     // one part: S of half pt of the current block, O of half pt of the previous block, softmax of the other half in flight
     // (pt 0: the previous block's second half, pt 1: the current block's first half; entry e)
-    auto part = [&](int pt, uint32_t e, const u16 *Vt, const u16 *Kt, const u16 *Kn) INL {
-        const int hf = 1 - pt;
+    auto part = [&](auto pt_, uint32_t e, const u16 *Vt, const u16 *Kt, const u16 *Kn) INL {
+        constexpr int hf = 1 - decltype(pt_)::value;
         mask_tail(hf, e);
-        float cs[QS], mref[QS];
+        float cs[QG], mref[QG];
 #pragma unroll
-        for (int u = 0; u < QS; ++u) {
+        for (int u = 0; u < QG; ++u) {
             const bool sel = selected(u, e);
             cs[u] = (TOPK && !sel) ? 0.f : c2;
             mref[u] = (TOPK && !sel) ? INFINITY : m_run[u];
         }
-        constexpr int FS = QS * (NPS - 3);
-        float t[QS][16];
-        f32x4 ps[QS];
-#pragma unroll
-        for (int u = 0; u < QS; ++u) ps[u] = zero4;
-#pragma unroll
-        for (int i = 0; i < NPS; ++i) {
-            const int g = pt * NPS + i;
-#pragma unroll
-            for (int uu = 0; uu < QS; ++uu) {
-                const int u = (i & 1) ? QS - 1 - uu : uu, slot = i * QS + uu;
-                if (i < NS) mfma_S(u, pt, i, ring[g % RING]); else mfma_PV(u, pt, i - NS, ring[g % RING]);
-                if (uu == QS - 1) read_frag(g + RING, Vt, Kt, Kn);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int p = 0; p < 8 * QS; ++p) {
-                    // pair q of set v; slot at which its logits are scaled, the rest follows one slot apart
-                    const int q = p / QS, v = p % QS, at = p * FS / (8 * QS);
-                    if (slot == at) {
-                        t[v][2 * q] = fmaf(s[v][hf][2 * q], cs[v], -mref[v]);
-                        t[v][2 * q + 1] = fmaf(s[v][hf][2 * q + 1], cs[v], -mref[v]);
-                    }
-                    if (slot == at + 1) {
-                        t[v][2 * q] = __builtin_amdgcn_exp2f(t[v][2 * q]);
-                        t[v][2 * q + 1] = __builtin_amdgcn_exp2f(t[v][2 * q + 1]);
-                    }
-                    if (slot == at + 2) pf[v][hf * 2 + (q >> 2)].w[q & 3] = pack2e(t[v][2 * q], t[v][2 * q + 1]);
-                    if (slot == at + 3 && (q & 3) == 3) ps[v] = row_sum(v, hf * 2 + (q >> 2), ps[v]);
+        // Where the softmax's vector instructions stand, pair p of a part's logits: scaled behind product scaled(p), raised and packed after that.
+        // G = 16: two waves a SIMD keep the matrix pipe busy (4 % more cycles than its own) with one exponential or two other instructions behind
+        // every product; with the same ones in bunches, five behind every second product, it takes 53 % more.  So two pairs of logits take
+        // seven products: scale two, exponential, exponential, the same again, pack all four.
+        // G = 32: the steps of a pair one product apart, eight pairs over 13 products.
+        constexpr int SLOTS = NPS * QG, GP = EL / 2, PAIRS = GP * QG;       // products of a part; pairs of a group, of all
+        struct Row {
+            static constexpr int at(int place) { return place * (SLOTS - 4) / (PAIRS / 2 * 7); }
+            static constexpr int scaled(int p) { return G == 16 ? at(p / 2 * 7 + p % 2 * 3) : p * (SLOTS - 3 * QS) / PAIRS; }
+            static constexpr int raised(int p, int b) { return G == 16 ? at(p / 2 * 7 + p % 2 * 3 + 1 + b) : scaled(p) + 1; }
+            static constexpr int packed(int p) { return G == 16 ? at(p / 2 * 7 + 6) : scaled(p) + 2; }
+        };
+        float t[QG][EL];
+        f32x4 ps[QG];
+        unrolled<SLOTS>([&](auto slot_) INL {
+            constexpr int slot = slot_, i = slot / QG, uu = slot % QG, u = (i & 1) ? QG - 1 - uu : uu, pt = decltype(pt_)::value, hf = 1 - pt;
+            constexpr int g = pt * NPS + i;
+            // G = 16: the wave that is behind goes first, so that the two of a SIMD come to the barrier together.  480p, 90 % 3240 -> 3180 cycles a
+            // block (G = 32, where the oldest wave first has always been: 2957).
+            if constexpr (G == 16 && slot == 0) __builtin_amdgcn_s_setprio(pt ? 1 : 3);
+            if constexpr (G == 16 && slot == SLOTS / 2) __builtin_amdgcn_s_setprio(pt ? 0 : 2);
+            if constexpr (i < SS) mfma_S(u, pt, i, ring[g % RING]); else mfma_PV(u, pt, i - SS, ring[g % RING]);
+            if constexpr (uu == QG - 1) read_frag(g + RING, Vt, Kt, Kn);
+            __builtin_amdgcn_sched_barrier(0);
+            unrolled<PAIRS>([&](auto p_) INL {
+                constexpr int p = p_, v = G == 16 ? p / GP : p % QG, q = G == 16 ? p % GP : p / QG, x = 2 * q;
+                if constexpr (slot == Row::scaled(p)) {
+                    t[v][x] = fmaf(logit(v, hf, x), cs[v], -mref[v]);
+                    t[v][x + 1] = fmaf(logit(v, hf, x + 1), cs[v], -mref[v]);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        float psum[QS];
+                if constexpr (slot == Row::raised(p, 0)) t[v][x] = __builtin_amdgcn_exp2f(t[v][x]);
+                if constexpr (slot == Row::raised(p, 1)) t[v][x + 1] = __builtin_amdgcn_exp2f(t[v][x + 1]);
+                if constexpr (slot == Row::packed(p)) p_word(v, hf, q) = pack2e(t[v][x], t[v][x + 1]);
+                if constexpr (slot == Row::packed(p) + 1 && q % 4 == 3) ps[v] = row_sum(v, hf, q / 4, q < 4 ? zero4 : ps[v]);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        float psum[QG];
 #pragma unroll
-        for (int u = 0; u < QS; ++u) psum[u] = ps[u][0];
+        for (int u = 0; u < QG; ++u) psum[u] = ps[u][0];
         settle(hf, TOPK && hf == 0, !TOPK, e, psum);     // TOPK: a lane's first selected block may come here
     };
     // the same work for blocks that not both of two successive list entries give this wave (first and last entry, entries that
@@ -701,55 +774,56 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the softmax of the first half between the S products of the second: every third block 1159 -> 1066 us at N = 12480, 24 heads.
     // The same in finish_prev lost (1182), and windows got slower by it where tiles are cut and at d = 64 (480p, 90 % 882 -> 895).
     // Layer calls there, every second / third / a random 30 % of the blocks: 1138 / 1049 / 879 us; 24 heads of 64 593 / 553 / 514.
-    auto finish_prev = [&](uint32_t e, const u16 *Vt) INL {
-        mask_tail(1, e);
+    // Operands are read four steps ahead here, too; only vector and scalar instructions may pass from one step to another.
+    auto in_turn = [&](auto count, auto read, auto use) INL {
+        Frag5 f[4];
 #pragma unroll
-        for (int t = 0; t < 4 * NDT; ++t) {
-            if (t == 2 * NDT) {     // after the first half's products: the reference may move here
-                float psum[QS];
+        for (int t = 0; t < 4; ++t) read(t, f[t]);
 #pragma unroll
-                for (int u = 0; u < QS; ++u) psum[u] = exp_pack(u, 1, selected(u, e));
-                settle(1, false, !TOPK, e, psum);
-            }
-            Frag5 f;
-            v_frag(f, Vt, t / NDT, t % NDT);
-#pragma unroll
-            for (int u = 0; u < QS; ++u) mfma_PV(u, t / (2 * NDT), t % (2 * NDT), f);
+        for (int t = 0; t < count; ++t) {
+            use(t, f[t % 4]);
+            if (t + 4 < count) read(t + 4, f[t % 4]);
+            __builtin_amdgcn_sched_barrier(0x406);
         }
     };
+    auto finish_prev = [&](uint32_t e, const u16 *Vt) INL {
+        mask_tail(1, e);
+        in_turn(std::integral_constant<int, 2 * OS>{}, [&](int t, Frag5 &f) INL { v_frag(f, Vt, t / OS, t % OS); }, [&](int t, const Frag5 &f) INL {
+            if (t == OS) {          // after the first half's products: the reference may move here
+                float psum[QG];
+#pragma unroll
+                for (int u = 0; u < QG; ++u) psum[u] = exp_pack(u, 1, selected(u, e));
+                settle(1, false, !TOPK, e, psum);
+            }
+#pragma unroll
+            for (int u = 0; u < QG; ++u) mfma_PV(u, t / OS, t % OS, f);
+        });
+    };
     auto start_cur = [&](uint32_t e, const u16 *Kt) INL {
-        auto step_S = [&](int t) INL {
-            Frag5 f;
-            f.v = k_frag(Kt, t / NS, t % NS);
+        constexpr bool woven = D == 128 && !SPLIT;
+        float psum[QG];
+        in_turn(std::integral_constant<int, 2 * SS>{}, [&](int t, Frag5 &f) INL { f.v = k_frag(Kt, t / SS, t % SS); }, [&](int t, const Frag5 &f) INL {
+            if (woven && t == SS) mask_tail(0, e);
 #pragma unroll
-            for (int u = 0; u < QS; ++u) mfma_S(u, t / NS, t % NS, f);
-        };
-        float psum[QS];
-        if constexpr (D == 128 && !SPLIT) {
+            for (int u = 0; u < QG; ++u) mfma_S(u, t / SS, t % SS, f);
+            if (woven && t >= SS)
 #pragma unroll
-            for (int t = 0; t < NS; ++t) step_S(t);
-            mask_tail(0, e);
-#pragma unroll
-            for (int t = 0; t < NS; ++t) {
-                step_S(NS + t);
-#pragma unroll
-                for (int u = 0; u < QS; ++u) {
+                for (int u = 0; u < QG; ++u) {
                     const bool sel = selected(u, e);
                     const float cs = (TOPK && !sel) ? 0.f : c2, mref = (TOPK && !sel) ? INFINITY : m_run[u];
 #pragma unroll
-                    for (int q = 0; q < 8; ++q)
-                        if (q * (NS - 1) / 8 == t - 1)
-                            pf[u][q >> 2].w[q & 3] = pair_exp(fmaf(s[u][0][2 * q], cs, -mref), fmaf(s[u][0][2 * q + 1], cs, -mref));
+                    for (int q = 0; q < EL / 2; ++q)
+                        if ((u * (EL / 2) + q) * (SS - 1) / (EL / 2 * QG) == t - SS - 1)
+                            p_word(u, 0, q) = pair_exp(fmaf(logit(u, 0, 2 * q), cs, -mref), fmaf(logit(u, 0, 2 * q + 1), cs, -mref));
                 }
-            }
+        });
+        if constexpr (woven) {
 #pragma unroll
-            for (int u = 0; u < QS; ++u) psum[u] = row_sum(u, 1, row_sum(u, 0, zero4))[0];
+            for (int u = 0; u < QG; ++u) psum[u] = row_sums(u, 0);
         } else {
-#pragma unroll
-            for (int t = 0; t < 2 * NS; ++t) step_S(t);
             mask_tail(0, e);
 #pragma unroll
-            for (int u = 0; u < QS; ++u) psum[u] = exp_pack(u, 0, selected(u, e));
+            for (int u = 0; u < QG; ++u) psum[u] = exp_pack(u, 0, selected(u, e));
         }
         settle(0, true, false, e, psum);
     };
@@ -817,16 +891,16 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         for (int i = 0; i < D * D / (NT * 8); ++i) lds_dma16(hf + (size_t)(i * NT + tid) * 8, lds_addr_of(Kb + (i * NT + wave * 64) * 8));
     };
 
-    // ROPE: this lane's 32 angle words (its query's row of the table: pairs 8 st + 4 hh + j), fetched under the last
+    // ROPE: this lane's 32 angle words (its queries' rows of the table: pairs KD / 2 st + 4 ls + j), fetched under the last
     // PV product of the tile
-    uint4 ang[QS][ROPE ? NS : 1];
+    uint4 ang[QG][ROPE ? NS : 1];
     auto load_angles = [&]() INL {
         if (ROPE)
 #pragma unroll
-            for (int u = 0; u < QS; ++u) {
-                const uint32_t *tr = a.rope_tab + (size_t)qrow[u] * (D / 2) + hh * 4;
+            for (int u = 0; u < QG; ++u) {
+                const uint32_t *tr = a.rope_tab + (size_t)__shfl(qrow[u / NKG], u % NKG * G + lq) * (D / 2) + ls * 4;
 #pragma unroll
-                for (int st = 0; st < NS; ++st) ang[u][st] = *reinterpret_cast<const uint4 *>(tr + st * 8);
+                for (int st = 0; st < NS; ++st) ang[u][st] = *reinterpret_cast<const uint4 *>(tr + st * (KD / 2));
             }
     };
 
@@ -841,15 +915,16 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     if (!GATHER && n > 1) WAIT_VM(2 * NPASS); else WAIT_VM(0);
     asm volatile("" ::: "memory");
     {
-        const int q_off = (l32 >> 4) * (CG * 1024) + (l32 & 15) * 64;
+        // step st of group u: 8 channels from KD st + 8 ls of row lq of the group
 #pragma unroll
-        for (int u = 0; u < QS; ++u)
+        for (int u = 0; u < QG; ++u)
 #pragma unroll
             for (int s = 0; s < NS; ++s)
-                qf[u][s].u = *reinterpret_cast<const uint4 *>(q_lds(u) + q_off + (((2 * (s & 1) + hh) ^ ((l32 >> 2) & 3)) << 4) + (s >> 1) * 1024);
+                qf[u][s].u = *reinterpret_cast<const uint4 *>(q_lds(u / NKG) + (G == 16 ? u % NKG : lq >> 4) * (CG * 1024) + (lq & 15) * 64 + s * (KD / 8) / 4 * 1024 +
+                                                              (((s * (KD / 8) % 4 + ls) ^ kswz(lq & 15)) << 4));
     }
 #pragma unroll
-    for (int u = 0; u < QS; ++u) {
+    for (int u = 0; u < QG; ++u) {
 #pragma unroll
         for (int s = 0; s < NS; ++s)
             asm volatile("" : "+v"(qf[u][s].w[0]), "+v"(qf[u][s].w[1]), "+v"(qf[u][s].w[2]), "+v"(qf[u][s].w[3]));
@@ -896,9 +971,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 if (__builtin_expect(j + AV < n, 1)) fetch_v(rk[0], vslot_f);
             };
             if (__builtin_expect(kP && kS, 1)) {
-                part(0, e_prev, Vt, Kt, Kn);
+                part(std::integral_constant<int, 0>{}, e_prev, Vt, Kt, Kn);
                 dma();
-                part(1, e_cur, Vt, Kt, Kn);
+                part(std::integral_constant<int, 1>{}, e_cur, Vt, Kt, Kn);
             } else {
                 dma();
                 if (kP) finish_prev(e_prev, Vt);
@@ -928,7 +1003,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 
     if (SPLIT && pieces > 1) {
         const int first = (L - a.sp_full) * a.sp_pieces;      // the tile's pieces in the scratch
-        constexpr int PER = NDT * 8 * 512;                    // register pairs of a piece: pair r of thread tid at r * 512 + tid
+        constexpr int PER = NKG * NDT * (AR / 2) * 512;       // register pairs of a piece: pair r of thread tid at r * 512 + tid
         // The pieces of a tile may run on different XCDs, whose L2 caches do not see each other.  Instead of fences, which
         // write back and invalidate a whole L2 (101 against 37 us for a layer call of N = 1950), the scratch is written and
         // read with device-scope accesses, which go past it: a piece's stores are at the common level when they are
@@ -941,14 +1016,19 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
         };
         uint64_t *mine = a.sp_o + (size_t)(first + piece) * PER + tid;
+        auto pair_at = [&](int u, int dt, int r) INL -> int { return ((u % NKG * NDT + dt) * (AR / 2) + r) * 512 + u / NKG * NT; };
 #pragma unroll
-        for (int u = 0; u < QS; ++u) {
+        for (int u = 0; u < QG; ++u)
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                for (int r = 0; r < 8; ++r) put(mine + (dt * 8 + r) * 512 + u * NT, o[u][dt][2 * r], o[u][dt][2 * r + 1]);
+                for (int r = 0; r < AR / 2; ++r) put(mine + pair_at(u, dt, r), o[u][dt][2 * r], o[u][dt][2 * r + 1]);
+#pragma unroll
+        for (int u = 0; u < QS; ++u) {        // every lane its query of the set, twice
             // a wave that kept no entry of this piece has no reference, and nothing to add
-            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, have_ref[u] ? m_run[u] : -INFINITY, l_run[u]);
+            const int u0 = NKG * u, u1 = NKG * u + NKG - 1;
+            const float m0 = have_ref[u0] ? m_run[u0] : -INFINITY, m1 = have_ref[u1] ? m_run[u1] : -INFINITY;
+            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, either(l32 >= G, m0, m1), either(l32 >= G, l_run[u0], l_run[u1]));
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         WAIT_VM(0);
@@ -970,60 +1050,59 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         __syncthreads();
         if (!blist[0]) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        float mx[QS];
+        const uint64_t *ml_at = a.sp_ml + (size_t)first * 512 + wave * 64 + lq;
+        float mx[QG];
 #pragma unroll
-        for (int u = 0; u < QS; ++u) {
+        for (int u = 0; u < QG; ++u) {
             mx[u] = -INFINITY;
-            for (int p = 0; p < pieces; ++p) mx[u] = fmaxf(mx[u], get(a.sp_ml + (size_t)(first + p) * 512 + u * NT + tid).x);
+            for (int p = 0; p < pieces; ++p) mx[u] = fmaxf(mx[u], get(ml_at + p * 512 + u / NKG * NT + u % NKG * G).x);
 #pragma unroll
-            for (int i = 0; i < NDT; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) o[u][i][r] = 0.f;
+            for (int i = 0; i < NDT; ++i) o[u][i] = zero;
             l_run[u] = 0.f;
         }
         for (int p = 0; p < pieces; ++p)
 #pragma unroll
-            for (int u = 0; u < QS; ++u) {
-                const float2 ml = get(a.sp_ml + (size_t)(first + p) * 512 + u * NT + tid);
+            for (int u = 0; u < QG; ++u) {
+                const float2 ml = get(ml_at + p * 512 + u / NKG * NT + u % NKG * G);
                 const float wt = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - mx[u]);
-                const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + u * NT + tid;
+                const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + tid;
                 l_run[u] = fmaf(wt, ml.y, l_run[u]);
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const float2 v = get(src + (dt * 8 + r) * 512);
+                    for (int r = 0; r < AR / 2; ++r) {
+                        const float2 v = get(src + pair_at(u, dt, r));
                         o[u][dt][2 * r] = fmaf(wt, v.x, o[u][dt][2 * r]);
                         o[u][dt][2 * r + 1] = fmaf(wt, v.y, o[u][dt][2 * r + 1]);
                     }
             }
 #pragma unroll
-        for (int u = 0; u < QS; ++u) m_run[u] = mx[u];
+        for (int u = 0; u < QG; ++u) m_run[u] = mx[u];
     }
 
     // ---- epilogue ---------------------------------------------------------------------------------
-    float lin_scale[QS], inv_den[QS];
+    float lin_scale[QG], inv_den[QG];
     if (lin) {
         const bool late = n == 0 || (SPLIT && pieces > 1);       // not under the last PV product
         if (RIDE || late) stage_state();
         if (ROPE && late) load_angles();
         if (RIDE) reduce_gate();
 #pragma unroll
-        for (int u = 0; u < QS; ++u)
+        for (int u = 0; u < QG; ++u)
 #pragma unroll
             for (int st = 0; st < NS; ++st)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) qf[u][st].w[j] = relu2e(qf[u][st].w[j]);
         WAIT_VM(0);
         __syncthreads();   // the staged fragments have landed in every wave's view
-        float dpart[QS] = {};
-        const float *Zh = z_lds() + hh * 8;
+        float dpart[QG] = {};
+        const float *Zh = z_lds() + ls * 8;
 #pragma unroll
         for (int st = 0; st < NS; ++st) {
-            const float4 z0 = *reinterpret_cast<const float4 *>(Zh + st * 16), z1 = *reinterpret_cast<const float4 *>(Zh + st * 16 + 4);
+            const float4 z0 = *reinterpret_cast<const float4 *>(Zh + st * KD), z1 = *reinterpret_cast<const float4 *>(Zh + st * KD + 4);
             const float zz[8] = {z0.x, z0.y, z0.z, z0.w, z1.x, z1.y, z1.z, z1.w};
 #pragma unroll
-            for (int u = 0; u < QS; ++u)
+            for (int u = 0; u < QG; ++u)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const uint32_t w = qf[u][st].w[j];
@@ -1032,7 +1111,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 }
         }
 #pragma unroll
-        for (int u = 0; u < QS; ++u) {
+        for (int u = 0; u < QG; ++u) {
+            if (G == 16) dpart[u] += __shfl_xor(dpart[u], 16);
             const float den = dpart[u] + __shfl_xor(dpart[u], 32) + a.eps;
             inv_den[u] = 1.f / den;
             lin_scale[u] = coef * inv_den[u];
@@ -1041,7 +1121,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             // numerator operand: R_i relu(Q_i), rounded to bf16 like every MFMA operand (the normaliser above keeps the
             // unrotated features)
 #pragma unroll
-            for (int u = 0; u < QS; ++u)
+            for (int u = 0; u < QG; ++u)
 #pragma unroll
                 for (int st = 0; st < NS; ++st) {
                     const uint32_t cw[4] = {ang[u][st].x, ang[u][st].y, ang[u][st].z, ang[u][st].w};
@@ -1060,25 +1140,31 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
     const int unit = wave * QS + u;
-    const float l_tot = l_run[u];
-    const float inv_l = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    f32x16 num[NDT];
+    const int u0 = NKG * u;                  // this set's groups: u0 .. u0 + NKG - 1
+    float inv_l[NKG];
+#pragma unroll
+    for (int c = 0; c < NKG; ++c) inv_l[c] = l_run[u0 + c] > 0.f ? 1.f / l_run[u0 + c] : 0.f;
+    acc_t num[NKG][NDT];
     if (lin) {
+        // the state's fragments are those of 32x32x16 products: with G = 16 this lane's 8 elements of a 16 x 32 one
+        const int hoff = G == 16 ? (ls >> 1) * 512 + (ls & 1) * 256 + lq * 8 : lane * 8;
 #pragma unroll
         for (int dt = 0; dt < NDT; ++dt) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) num[dt][r] = 0.f;
+            for (int c = 0; c < NKG; ++c) num[c][dt] = zero;
 #pragma unroll
             for (int st = 0; st < NS; ++st) {
-                const int idx = ((dt * NS + st) * 64 + lane) * 8;
-                bf16x8 hi = *reinterpret_cast<const bf16x8 *>(Kb + idx);
-                num[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi, qf[u][st].v, num[dt], 0, 0, 0);
+                const int idx = G == 16 ? ((dt >> 1) * (D / 16) + st * 2) * 512 + (dt & 1) * 128 : (dt * NS + st) * 512;
+                Frag5 hi;
+                hi.v = *reinterpret_cast<const bf16x8 *>(Kb + hoff + idx);
+#pragma unroll
+                for (int c = 0; c < NKG; ++c) num[c][dt] = product(hi, qf[u0 + c][st], num[c][dt]);
             }
         }
     }
     if (!DBG) {
         // bf16 results leave through LDS so that every global store is a run of full 256-byte rows: accumulator
-        // layout (lane = query l32; 4 consecutive columns per (dt, g4, hh)) -> half of a free tile of this set's own
+        // layout (lane = query lq of a group; 4 consecutive columns per (dt, g4, ls)) -> half of a free tile of this set's own
         // (K slots 2..4, behind the state, and the V slot after the last block's: nobody reads them any more), 16-byte chunk c of row r at
         // r * 256 + ((c ^ (r & 15)) << 4) -> row layout (4 rows x 16 chunks per instruction).
         int vs = v_last + 1;
@@ -1086,21 +1172,27 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         u16 *free_tile = unit < 6 ? Kb + (2 + (unit >> 1)) * TILE : Vb + vs * TILE;
         constexpr int ROWB = D * 2;          // bytes of a row
         unsigned char *stg = reinterpret_cast<unsigned char *>(free_tile) + (unit & 1) * (32 * ROWB);
+        auto stage = [&](int c, int dt, int g4, const float (&v)[4]) INL {       // columns dt G + 8 g4 + 4 ls .. + 3 of query lq of group c
+            uint2 pk;
+            pk.x = pack2e(v[0], v[1]);
+            pk.y = pack2e(v[2], v[3]);
+            const int row = c * G + lq;
+            *reinterpret_cast<uint2 *>(stg + row * ROWB + (((dt * (G / 8) + g4 + (ls >> 1)) ^ oswz(row)) << 4) + (ls & 1) * 8) = pk;
+        };
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt)
+        for (int c = 0; c < NKG; ++c)
 #pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-                float ov[4];
+            for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float os = o[u][dt][g4 * 4 + t] * inv_l;
-                    ov[t] = lin && !EMIT ? fmaf(num[dt][g4 * 4 + t], lin_scale[u], os) : os;
+                for (int g4 = 0; g4 < AR / 4; ++g4) {
+                    float ov[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const float os = o[u0 + c][dt][g4 * 4 + t] * inv_l[c];
+                        ov[t] = lin && !EMIT ? fmaf(num[c][dt][g4 * 4 + t], lin_scale[u0 + c], os) : os;
+                    }
+                    stage(c, dt, g4, ov);
                 }
-                uint2 pk;
-                pk.x = pack2e(ov[0], ov[1]);
-                pk.y = pack2e(ov[2], ov[3]);
-                *reinterpret_cast<uint2 *>(stg + l32 * ROWB + (((dt * 4 + g4) ^ oswz(l32)) << 4) + hh * 8) = pk;
-            }
         asm volatile("" ::: "memory");       // the wave's LDS operations execute in order
         // destination of row r: the stored row (or the pair slot) of the lane that owns query r
         const int dest_mine = !qvalid[u] ? -1 : GATHER ? g_slot0 + unit * 32 + l32 : qrow[u];
@@ -1120,14 +1212,16 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             // (c / 2 * 64 + c % 2 * 32 + r) * 16 bytes; whole kilobytes for a head in the stored order)
             asm volatile("" ::: "memory");
 #pragma unroll
-            for (int dt = 0; dt < NDT; ++dt)
+            for (int c = 0; c < NKG; ++c)
 #pragma unroll
-                for (int g4 = 0; g4 < 4; ++g4) {
-                    uint2 pk;
-                    pk.x = pack2e(num[dt][g4 * 4] * inv_den[u], num[dt][g4 * 4 + 1] * inv_den[u]);
-                    pk.y = pack2e(num[dt][g4 * 4 + 2] * inv_den[u], num[dt][g4 * 4 + 3] * inv_den[u]);
-                    *reinterpret_cast<uint2 *>(stg + l32 * ROWB + (((dt * 4 + g4) ^ oswz(l32)) << 4) + hh * 8) = pk;
-                }
+                for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+                    for (int g4 = 0; g4 < AR / 4; ++g4) {
+                        float ol[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) ol[t] = num[c][dt][g4 * 4 + t] * inv_den[u0 + c];
+                        stage(c, dt, g4, ol);
+                    }
             asm volatile("" ::: "memory");
             u16 *blk = a.emit_ol + ((((size_t)smp * ((N + 31) >> 5) + (qrow[u] >> 5)) * a.H + h) << 12) + (hh * 32 + (qrow[u] & 31)) * 8;
 #pragma unroll
@@ -1136,34 +1230,49 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 if (qvalid[u]) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
             }
         }
-        if (GATHER && qvalid[u] && hh == 0) a.g_lse[g_slot[u]] = l_tot > 0.f ? m_run[u] + log2f(l_tot) : -INFINITY;
-    } else if (qvalid[u]) {
-        const size_t obase = ((size_t)bh * N + qrow[u]) * D;
-        u16 *outp = reinterpret_cast<u16 *>(a.out) + obase;
+        if (GATHER && qvalid[u] && hh == 0) {       // lanes 0 .. 31, each for its query of the set
+            const float l_tot = either(l32 >= G, l_run[u0], l_run[u0 + NKG - 1]), m = either(l32 >= G, m_run[u0], m_run[u0 + NKG - 1]);
+            a.g_lse[g_slot[u]] = l_tot > 0.f ? m + log2f(l_tot) : -INFINITY;
+        }
+    } else {
 #pragma unroll
-        for (int dt = 0; dt < NDT; ++dt) {
+        for (int c = 0; c < NKG; ++c) {
+            const int mine = __shfl(qvalid[u] ? qrow[u] : -1, c * G + lq);
+            if (mine >= 0) {
+                const size_t obase = ((size_t)bh * N + mine) * D;
+                u16 *outp = reinterpret_cast<u16 *>(a.out) + obase;
 #pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-                const int col = dt * 32 + 8 * g4 + 4 * hh;
-                float os[4], ol[4], ov[4];
+                for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    os[t] = o[u][dt][g4 * 4 + t] * inv_l;
-                    ol[t] = lin ? num[dt][g4 * 4 + t] : 0.f;
-                    ov[t] = lin ? fmaf(ol[t], lin_scale[u], os[t]) : os[t];
-                }
-                uint2 pk;
-                pk.x = pack2e(ov[0], ov[1]);
-                pk.y = pack2e(ov[2], ov[3]);
-                *reinterpret_cast<uint2 *>(outp + col) = pk;
-                if (DBG && a.o_sparse_dbg)
-                    *reinterpret_cast<float4 *>(a.o_sparse_dbg + obase + col) = make_float4(os[0], os[1], os[2], os[3]);
-                if (DBG && a.o_linear_dbg && lin)
-                    *reinterpret_cast<float4 *>(a.o_linear_dbg + obase + col) =
-                        make_float4(ol[0] * inv_den[u], ol[1] * inv_den[u], ol[2] * inv_den[u], ol[3] * inv_den[u]);
+                    for (int g4 = 0; g4 < AR / 4; ++g4) {
+                        const int col = dt * G + 8 * g4 + 4 * ls;
+                        float os[4], ol[4], ov[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            os[t] = o[u0 + c][dt][g4 * 4 + t] * inv_l[c];
+                            ol[t] = lin ? num[c][dt][g4 * 4 + t] : 0.f;
+                            ov[t] = lin ? fmaf(ol[t], lin_scale[u0 + c], os[t]) : os[t];
+                        }
+                        uint2 pk;
+                        pk.x = pack2e(ov[0], ov[1]);
+                        pk.y = pack2e(ov[2], ov[3]);
+                        *reinterpret_cast<uint2 *>(outp + col) = pk;
+                        if (DBG && a.o_sparse_dbg)
+                            *reinterpret_cast<float4 *>(a.o_sparse_dbg + obase + col) = make_float4(os[0], os[1], os[2], os[3]);
+                        if (DBG && a.o_linear_dbg && lin)
+                            *reinterpret_cast<float4 *>(a.o_linear_dbg + obase + col) =
+                                make_float4(ol[0] * inv_den[u0 + c], ol[1] * inv_den[u0 + c], ol[2] * inv_den[u0 + c], ol[3] * inv_den[u0 + c]);
+                    }
             }
         }
     }
+    }
+    };
+    if constexpr (BOTH) {
+        if (a.many && n_list >= LONG_LIST) rest(std::integral_constant<int, 16>{});
+        else rest(std::integral_constant<int, 32>{});
+    } else {
+        rest(std::integral_constant<int, 32>{});
     }
 }
 
@@ -1235,6 +1344,7 @@ static hipError_t launch_v5(const AttnArgs &a, hipStream_t st)
     const int px = SPLIT ? ((total - a.sp_full) * a.sp_pieces + 7) / 8 : 0;      // pieces of an XCD
     auto magic = [](int d) { return d > 1 ? (unsigned)((1ull << 32) / (unsigned)d) : ~0u; };
     AttnArgs b = a;
+    b.many = total > 256;
     b.tiles_magic = magic(ntiles); b.heads_magic = magic(a.H); b.pieces_magic = magic(a.sp_pieces);
     if (SPLIT) {
         b.sp_alone = 256 / (total - a.sp_full);

@@ -772,6 +772,33 @@ def test_references_of_two_query_sets_move_apart(oracle, profile, H, grid, keep)
         compare_layer(run_layer(w, inp, dev, [keep] * H, kinds, dbg=dbg), ref, label=f"{profile}/{H}/{keep}: ")
 
 
+@pytest.mark.parametrize("H,d,grid,keep", [
+    (43, 128, (4, 17, 19), 16),       # 258 tiles of 21 blocks, lists of at most 19 entries: the larger products
+    (43, 128, (4, 17, 19), 17),       # lists of 17 to 20: both in one call
+    (43, 128, (4, 17, 19), 21),       # 21, the last block of 12 keys
+    (29, 128, (4, 23, 25), 36),       # 261 tiles: a round, and five in pieces
+    (43, 64, (4, 17, 19), 17), (58, 64, (4, 23, 25), 36),
+], ids=lambda x: str(x).replace(" ", ""))
+def test_smaller_products_of_long_lists(oracle, topk_variant, H, d, grid, keep):
+    """Calls of more than one round of tiles around the list length from which on a tile is computed with 16x16x32 products; key magnitudes
+    that move the references of either group of 16 queries, and query rows that are not finite."""
+    w = wl.small(f"columns-{H}-{d}", 1, H, d, *grid, "bf16", 0.5, seed=130 + keep)
+    inp = wl.make_inputs(w)
+    kinds = wl.head_kinds(w)
+    blk = np.arange(w.N) // 64
+    g = np.array([1.0, 30.0, 2.0, 55.0, 8.0])[(blk * 7 + 3) % 5]
+    inp["k"] = wl.round_to_bf16(inp["k"] * g[None, None, :, None].astype(np.float32))
+    inp["q"][:, :, np.arange(w.N) // 16 % 2 == 0] *= np.float32(2.0 ** -6)      # every other group of 16 stored rows stays where it is
+    inp["v"] = inp["v"] * np.float32(0.25)                 # the softmax is close to one-hot: see test_softmax_reference_moves_across_blocks
+    dev = upload(w, inp)
+    ref = _oracle_layer(oracle, w, inp, [keep] * H, kinds)
+    res = [run_layer(w, inp, dev, [keep] * H, kinds, dbg=dbg) for dbg in (True, False)]
+    for r in res:
+        compare_layer(r, ref, label=f"{H}/{d}/{keep}: ")
+    assert torch.equal(res[0]["out_t"], res[1]["out_t"])
+    test_non_finite_query_rows_stay_alone(topk_variant, 1, H, d, grid, keep, 0)
+
+
 def test_precomputed_s_and_bias_and_scale_arguments(oracle):
     w = SMALL[2]
     inp = wl.make_inputs(w)
