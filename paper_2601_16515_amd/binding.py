@@ -182,8 +182,10 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream() -> int:
+    """The current device's current stream.  Asked for by its handle: the object that torch.cuda.current_stream() makes around it takes 2.6 us,
+    which a call of two small kernels waits for (fp32, 2 heads, N = 1024 13.86 -> 13.44 us a call, 6 heads, N = 330 14.4 -> 13.0)."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 # ---------------------------------------------------------------------------------------------
