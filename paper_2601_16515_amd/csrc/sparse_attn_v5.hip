@@ -1223,33 +1223,11 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                         stage(c, dt, g4, ol);
                     }
             asm volatile("" ::: "memory");
-            auto block_of = [&](int row) INL -> u16 * { return a.emit_ol + ((((size_t)smp * ((N + 31) >> 5) + (row >> 5)) * a.H + h) << 12) + (row & 31) * 8; };
-            if (kind && T <= 64) {
-                // A temporal head's rows are HW apart from one position to the next, so a wave's own 32 would leave in pieces of 16 bytes each by
-                // itself.  The tile's rows of one time are neighbours (a position every T): with all waves' rows in LDS, lanes go along
-                // those, 192 bytes in a run at T = 21.  480p, 90 %, layer call 837 -> 813 us; longer time axes leave runs of 64 bytes and less.
-                __syncthreads();
-                static_assert(!EMIT || QS == 1, "a wave stages one set of rows");
-                const int unit0 = ROW_PAIRS && my_rows > 0 ? 4 : 0, waves = ROW_PAIRS && my_rows >= 0 ? min(4, (nb - tile * 4) * 2 - unit0) : NW;      // those that are here
-                const int p0 = tile * 256 + unit0 * 32, p1 = min(p0 + waves * 32, N);
-                const int loc0 = (int)__umulhi((unsigned)p0, magic), nloc = (int)__umulhi((unsigned)(p1 - 1), magic) - loc0 + 1;
-                const unsigned inv = 0xffffffffu / (unsigned)nloc;
-                for (int e = tid - unit0 * 64; e < T * CH * nloc; e += waves * 64) {
-                    const int x = (int)div_by((unsigned)e, (unsigned)nloc, inv), loc = loc0 + e - x * nloc, c = x % CH, t = x / CH, pos = loc * T + t;
-                    if (pos >= p0 && pos < p1) {
-                        const int i = pos - tile * 256, r = i & 31;
-                        const unsigned char *from = reinterpret_cast<const unsigned char *>(i < 192 ? Kb + (2 + (i >> 6)) * TILE : Vb + vs * TILE) + (i & 32) * ROWB;
-                        *reinterpret_cast<uint4 *>(block_of(t * HW + loc) + (c / 2 * 64 + c % 2 * 32) * 8) =
-                            *reinterpret_cast<const uint4 *>(from + r * ROWB + ((c ^ oswz(r)) << 4));
-                    }
-                }
-            } else {
-                u16 *blk = block_of(qrow[u]) + hh * 256;
+            u16 *blk = a.emit_ol + ((((size_t)smp * ((N + 31) >> 5) + (qrow[u] >> 5)) * a.H + h) << 12) + (hh * 32 + (qrow[u] & 31)) * 8;
 #pragma unroll
-                for (int i = 0; i < CH / 2; ++i) {
-                    const uint4 v = *reinterpret_cast<const uint4 *>(stg + l32 * ROWB + (((2 * i + hh) ^ oswz(l32)) << 4));
-                    if (qvalid[u]) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
-                }
+            for (int i = 0; i < CH / 2; ++i) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(stg + l32 * ROWB + (((2 * i + hh) ^ oswz(l32)) << 4));
+                if (qvalid[u]) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
             }
         }
         if (GATHER && qvalid[u] && hh == 0) {       // lanes 0 .. 31, each for its query of the set

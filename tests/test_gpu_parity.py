@@ -1209,15 +1209,6 @@ def test_full_projection_input_from_the_attention_epilogue(oracle, B, H, grid, k
     assert torch.equal(pruned["out_t"], run_layer(w, inp, dev, kept, kinds, lam=0.0, dbg=False)["out_t"])
 
 
-@pytest.mark.parametrize("B,H,grid,keep", [
-    (1, 3, (2, 11, 13), 3),           # 286 rows: the second tile of 30
-    (1, 2, (63, 3, 5), 4), (2, 2, (64, 3, 3), 3), (1, 2, (65, 3, 5), 16),      # around the longest time axis whose rows leave sorted
-    (1, 26, (20, 13, 10), 30),        # 286 tiles, lists long enough for the smaller products, the last one of 10 blocks' 40 rows
-])
-def test_projection_input_of_temporal_heads(oracle, B, H, grid, keep):
-    test_full_projection_input_from_the_attention_epilogue(oracle, B, H, grid, keep)
-
-
 @pytest.mark.parametrize("variant", [0, 1], ids=["regrouped", "token-mask"])
 @pytest.mark.parametrize("wi,key_block,topk", [(1, 64, 4), (7, 128, 2), (0, 64, 8), (6, 64, 1), (4, 64, 3)],
                          ids=["N693-B2-kb64-k4", "N1170-kb128-k2", "N270-all-blocks", "single-token", "N512-k3"])
