@@ -145,6 +145,14 @@ __device__ inline float max_of_query(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// The lane's number, computed where it is asked for: what follows from it is not kept in registers through the loop for a use behind it.
+__device__ inline int lane_again()
+{
+    unsigned all = ~0u;
+    asm volatile("" : "+s"(all));
+    return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+}
+
 // f(0) .. f(N - 1) with compile-time arguments: where the order of the instructions matters nothing is left for the optimiser to decide (it
 // computes the arms of a condition on an unrolled loop's variable ahead of the loop's other work before it knows the variable).
 template <class F, int... I>
@@ -433,28 +441,21 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     typedef float acc_t __attribute__((ext_vector_type(AR)));
     const int lq = lane % G, ls = lane / G;          // a lane's query of a group and share of 8 channels or 4 rows in the products
     unsigned mybit = 0u;
-    bool qvalid[QS];
-    int qrow[QS];
-    size_t g_slot[QS];                    // GATHER: this lane's (query, key block) pairs
     Frag5 qf[QG][NS];
     uint32_t qm_lo[QG] = {}, qm_hi[QG] = {};     // TOPK: this lane's queries' key-block bits
+    auto rows_active = [&](int unit) INL -> bool { return !ROW_PAIRS || my_rows < 0 || my_rows == unit >> 2; };
+    // Stored row of query i of the wave's set u (a valid one also where there is none), and whether there is one.  GATHER: the place in the run.
+    // For the epilogue, and computed there: kept from here on it is a register or two through the loop, of which d = 64 has none to spare.
+    auto query_row = [&](int u, int i, bool &valid) INL -> int {
+        const int unit = (int)wave_u * QS + u, p = GATHER ? unit * 32 + i : tile * 256 + unit * 32 + i;
+        valid = GATHER ? p < g_cnt : p < N && rows_active(unit);
+        return GATHER ? p : row_of_position5(kind, min(p, N - 1), T, HW, magic);
+    };
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
-        const int unit = wave * QS + u, qblk = tile * 4 + (unit >> 1), qpos = qblk * 64 + (unit & 1) * 32 + l32;
-        g_slot[u] = 0;
-        if (GATHER) {
-            const int qi = unit * 32 + l32;   // position in the run of gathered queries
-            qvalid[u] = qi < g_cnt;
-            mybit |= unit * 32 < g_cnt ? (1u << (24 + unit)) : 0u;
-            g_slot[u] = (size_t)bh * N * a.g_kk + g_slot0 + (qvalid[u] ? qi : 0);
-            qrow[u] = 0;
-        } else {
-            const bool active = !ROW_PAIRS || my_rows < 0 || my_rows == unit >> 2;
-            mybit |= qblk < nb && active ? (1u << (24 + (TOPK ? unit : unit >> 1))) : 0u;
-            qvalid[u] = (qblk < nb) && (qpos < N);
-            qrow[u] = row_of_position5(kind, qvalid[u] ? qpos : N - 1, T, HW, magic);
-            if (ROW_PAIRS) qvalid[u] = qvalid[u] && active;
-        }
+        const int unit = wave * QS + u, qblk = tile * 4 + (unit >> 1);
+        if (GATHER) mybit |= unit * 32 < g_cnt ? (1u << (24 + unit)) : 0u;
+        else mybit |= qblk < nb && rows_active(unit) ? (1u << (24 + (TOPK ? unit : unit >> 1))) : 0u;
         if (TOPK)
 #pragma unroll
             for (int c = 0; c < NKG; ++c) {     // spatial heads only: a position is its row
@@ -562,13 +563,16 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     };
     acc_t o[QG][NDT];
     float m_run[QG], l_run[QG];
-    bool have_ref[QG];                     // m_run has been set from a block's true maximum (wave-uniform unless TOPK)
+    // Whether m_run has been set from a block's true maximum.  A wave's queries keep the same list entries but for TOPK, where each lane has its
+    // own: one flag then does for the wave.  With a flag a group 64-wide heads with two query sets a wave had 17 to 32 registers in memory, some
+    // loaded again behind a block's loads, which the wait for them then waits for, too; with one, and what the epilogue and a call's last block alone
+    // need computed there, none.  24 heads of 64, N = 12480: 23 entries 160.8 -> 155.4 us, rows that keep every second block 590 -> 567, a random 10 % 275 -> 263.
+    bool have_ref[TOPK ? QG : 1] = {};
 #pragma unroll
     for (int u = 0; u < QG; ++u) {
 #pragma unroll
         for (int i = 0; i < NDT; ++i) o[u][i] = zero;
         m_run[u] = l_run[u] = 0.f;
-        have_ref[u] = false;
     }
     acc_t s[QG][2][NKG];                   // logits: group, half of the block, G keys of the half
     Frag5 pf[QG][2][NP];
@@ -605,11 +609,11 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (__builtin_expect((uint32_t)blk == tail_blk, 0)) {
             int first = blk * 64;
             asm volatile("" : "+s"(first));      // else the compares, the same in every such block, leave the loop and fill the scalar registers
-            const int kbase = first + hf * 32 + ls * (G / 4);
+            const int kbase = first + hf * 32 + lane_again() / G * (G / 4);
 #pragma unroll
-            for (int u = 0; u < QG; ++u)
+            for (int e = 0; e < EL; ++e)
 #pragma unroll
-                for (int e = 0; e < EL; ++e)
+                for (int u = 0; u < QG; ++u)
                     if (kbase + 16 * (e / (G / 4)) + e % (G / 4) >= N) s[u][hf][e / AR][e % AR] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
         }
     };
@@ -678,7 +682,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         for (int u = 0; u < QG; ++u) {
             psum[u] = ps[u];
             all += psum[u];                      // none is negative: within the bound only if each is
-            first[u] = !started && !have_ref[u];
+            first[u] = !started && !have_ref[TOPK ? u : 0];
             if (TOPK) first[u] = __any(selected(u, e) && first[u]);
             any = any || first[u];
         }
@@ -686,7 +690,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
             for (int u = 0; u < QG; ++u)
                 if (first[u] || __any(!(psum[u] <= 8192.f))) {
-                    const bool known = started || have_ref[u];
+                    const bool known = started || have_ref[TOPK ? u : 0];
                     float own = psum[u];
                     if (G == 32 && (TOPK || known)) own = sums_apart(u, hf);
                     const bool rises = !known | !(own <= 8192.f), moves = TOPK ? rises & selected(u, e) : rises;
@@ -707,10 +711,11 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                             for (int r = 0; r < AR; ++r) o[u][i][r] *= alpha;
                     }
                     m_run[u] += shift;
-                    have_ref[u] = !TOPK || moves || have_ref[u];      // TOPK apart the same for all lanes, which the compiler is to see
+                    if constexpr (TOPK) have_ref[u] = moves || have_ref[u];
                     psum[u] = exp_pack(u, hf, selected(u, e));
                     if (G == 32 && __builtin_expect(__any(!(psum[u] <= 8192.f)), 0)) psum[u] = sums_apart(u, hf);
                 }
+            if (!TOPK) have_ref[0] = true;
         }
 #pragma unroll
         for (int u = 0; u < QG; ++u) l_run[u] += !TOPK || selected(u, e) ? psum[u] : 0.f;
@@ -898,7 +903,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (ROPE)
 #pragma unroll
             for (int u = 0; u < QG; ++u) {
-                const uint32_t *tr = a.rope_tab + (size_t)__shfl(qrow[u / NKG], u % NKG * G + lq) * (D / 2) + ls * 4;
+                bool valid;
+                const uint32_t *tr = a.rope_tab + (size_t)query_row(u / NKG, u % NKG * G + lq, valid) * (D / 2) + ls * 4;
 #pragma unroll
                 for (int st = 0; st < NS; ++st) ang[u][st] = *reinterpret_cast<const uint4 *>(tr + st * (KD / 2));
             }
@@ -1027,7 +1033,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         for (int u = 0; u < QS; ++u) {        // every lane its query of the set, twice
             // a wave that kept no entry of this piece has no reference, and nothing to add
             const int u0 = NKG * u, u1 = NKG * u + NKG - 1;
-            const float m0 = have_ref[u0] ? m_run[u0] : -INFINITY, m1 = have_ref[u1] ? m_run[u1] : -INFINITY;
+            const float m0 = have_ref[0] ? m_run[u0] : -INFINITY, m1 = have_ref[0] ? m_run[u1] : -INFINITY;
             put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, either(l32 >= G, m0, m1), either(l32 >= G, l_run[u0], l_run[u1]));
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1139,7 +1145,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     if (ROW_PAIRS && my_rows >= 0 && mybit == 0u) return;      // a wave of the other rows, no barrier follows
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
-    const int unit = wave * QS + u;
+    const int unit = (int)wave_u * QS + u, lane = lane_again(), lq = lane % G, ls = lane / G, l32 = lane & 31, hh = lane >> 5;
     const int u0 = NKG * u;                  // this set's groups: u0 .. u0 + NKG - 1
     float inv_l[NKG];
 #pragma unroll
@@ -1195,7 +1201,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 }
         asm volatile("" ::: "memory");       // the wave's LDS operations execute in order
         // destination of row r: the stored row (or the pair slot) of the lane that owns query r
-        const int dest_mine = !qvalid[u] ? -1 : GATHER ? g_slot0 + unit * 32 + l32 : qrow[u];
+        bool valid;
+        const int qrow = query_row(u, l32, valid), dest_mine = !valid ? -1 : GATHER ? g_slot0 + qrow : qrow;
         constexpr int RPI = 64 / CH;          // rows per store instruction (4 rows x 16 chunks, or 8 x 8)
         const int r4 = lane / CH, c16 = lane % CH;
         u16 *dbase = GATHER ? a.g_po + (size_t)bh * N * a.g_kk * D : reinterpret_cast<u16 *>(a.out) + (size_t)bh * N * D;
@@ -1223,22 +1230,23 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                         stage(c, dt, g4, ol);
                     }
             asm volatile("" ::: "memory");
-            u16 *blk = a.emit_ol + ((((size_t)smp * ((N + 31) >> 5) + (qrow[u] >> 5)) * a.H + h) << 12) + (hh * 32 + (qrow[u] & 31)) * 8;
+            u16 *blk = a.emit_ol + ((((size_t)smp * ((N + 31) >> 5) + (qrow >> 5)) * a.H + h) << 12) + (hh * 32 + (qrow & 31)) * 8;
 #pragma unroll
             for (int i = 0; i < CH / 2; ++i) {
                 const uint4 v = *reinterpret_cast<const uint4 *>(stg + l32 * ROWB + (((2 * i + hh) ^ oswz(l32)) << 4));
-                if (qvalid[u]) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
+                if (valid) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
             }
         }
-        if (GATHER && qvalid[u] && hh == 0) {       // lanes 0 .. 31, each for its query of the set
+        if (GATHER && valid && hh == 0) {       // lanes 0 .. 31, each for its query of the set
             const float l_tot = either(l32 >= G, l_run[u0], l_run[u0 + NKG - 1]), m = either(l32 >= G, m_run[u0], m_run[u0 + NKG - 1]);
-            a.g_lse[g_slot[u]] = l_tot > 0.f ? m + log2f(l_tot) : -INFINITY;
+            a.g_lse[(size_t)bh * N * a.g_kk + g_slot0 + qrow] = l_tot > 0.f ? m + log2f(l_tot) : -INFINITY;
         }
     } else {
 #pragma unroll
         for (int c = 0; c < NKG; ++c) {
-            const int mine = __shfl(qvalid[u] ? qrow[u] : -1, c * G + lq);
-            if (mine >= 0) {
+            bool valid;
+            const int mine = query_row(u, c * G + lq, valid);
+            if (valid) {
                 const size_t obase = ((size_t)bh * N + mine) * D;
                 u16 *outp = reinterpret_cast<u16 *>(a.out) + obase;
 #pragma unroll

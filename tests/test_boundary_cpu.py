@@ -303,3 +303,41 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=60)
     assert r.returncode != 0
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def _kernel_metadata(path):
+    """The metadata of every kernel in a library built here: its code objects are the ELF images for gfx950 in the offload bundles
+    (magic, number of entries, then offset, size, length of the name and name of each), and hold a note with a msgpack map."""
+    import struct
+
+    import msgpack
+    blob = open(path, "rb").read()
+    magic, at, kernels = b"__CLANG_OFFLOAD_BUNDLE__", 0, []
+    while (at := blob.find(magic, at)) >= 0:
+        pos = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", blob, pos - 8)[0]):
+            off, size, length = struct.unpack_from("<3Q", blob, pos)
+            name = blob[pos + 24:pos + 24 + length]
+            pos += 24 + length
+            if not name.endswith(b"gfx950"):
+                continue
+            elf = blob[at + off:at + off + size]
+            phoff, (phentsize, phnum) = struct.unpack_from("<Q", elf, 32)[0], struct.unpack_from("<2H", elf, 54)
+            for i in range(phnum):
+                kind, _, start, _, _, filesz = struct.unpack_from("<2I4Q", elf, phoff + i * phentsize)
+                while kind == 4 and filesz > 0:              # PT_NOTE
+                    n, d, note = struct.unpack_from("<3I", elf, start)
+                    skip = 12 + (n + 3) // 4 * 4
+                    if note == 32:                           # NT_AMDGPU_METADATA
+                        kernels += msgpack.unpackb(elf[start + skip:start + skip + d])["amdhsa.kernels"]
+                    start, filesz = start + skip + (d + 3) // 4 * 4, filesz - skip - (d + 3) // 4 * 4
+        at = pos
+    return kernels
+
+
+def test_attention_kernels_keep_their_registers(lib):
+    """No instantiation of the large-tile kernel has registers in memory: a load of one behind a block's loads is waited for with all of them,
+    and its loop counts on some being still on their way."""
+    kernels = [k for k in _kernel_metadata(sb.LIB_PATH) if "sparse_attn_v5_kernel" in k[".name"]]
+    assert len(kernels) >= 30
+    assert {k[".name"]: k[".private_segment_fixed_size"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]} == {}
