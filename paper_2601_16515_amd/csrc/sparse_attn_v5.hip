@@ -392,6 +392,12 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     uint32_t eq[AK];                             // entries j .. j+3 of iteration j; the first one's past the end of the list
 #pragma unroll
     for (int b = 0; b < AK; ++b) eq[b] = GATHER ? (uint32_t)min(g_blk0 + b, nb - 1) | 0xff000000u : src[SPLIT ? min(list0 + b, list_cap - 1) : b];
+    // How many rows keep the list's first entries: for the choice of the products (G), and asked for here with the others.
+    constexpr int LOOKED_AT = 8;
+    int kept_bits = 0;
+    if (BOTH)
+#pragma unroll
+        for (int b = 0; b < LOOKED_AT; ++b) kept_bits += __popc(src[b] >> 24);
 
     // what chunk c of row r of a K or Q piece is swapped with (below)
     auto kswz = [](int row) INL -> int { return -(row >> 2) & 3; };
@@ -429,6 +435,12 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the power limit.  But each has its own start to line up with the vector instructions: a block takes 3140 cycles instead of 2960, and a
     // call of one round, or a tile that is half prologue and output, is held by those.  So G = 16 where the list is LONG_LIST entries or more and
     // the call more than one round (a.many); the whole list's length, so that the pieces of a cut tile are of one kind.
+    // And only where the rows keep five eighths of their tile's list.  A wave's entry that does not follow on another of its own is computed out of
+    // the woven part (start_cur, finish_prev), its products and its softmax one after the other, and the wave that does that is the one that the others
+    // wait for.  Eight entries in a row of a window that has more are kept by 20 of 32 rows or more.  Layer calls, N = 12480, 32x32x16 ->
+    // 16x16x32 products in all tiles (us), rows of random blocks, by the share that they keep of their tile's list: 15 heads of 128 0.39 509 -> 554,
+    // 0.53 673 -> 706, 0.62 746 -> 752, 0.71 884 -> 855, 0.80 968 -> 923; 30 heads of 64 0.39 615 -> 653, 0.53 819 -> 827, 0.62 913 -> 890, 0.80 1084 -> 1035;
+    // of random runs of four blocks: 15 heads 0.39 539 -> 610, 0.62 755 -> 784, 0.80 965 -> 937.
     auto rest = [&](auto g_) INL {
     constexpr int G = decltype(g_)::value;
     constexpr int KD = 512 / G, NS = D / KD;     // channels of a product of S, its steps
@@ -835,7 +847,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 
     bool lin = !GATHER && a.use_linear && !a.write_sparse_only && !(a.drop && a.drop[smp]);   // pruned sample (Sec. 4.3): out = O_s
     const u16 *hf = a.hfrag + (size_t)bh * D * D;
-    float coef = lin && !RIDE ? a.coef[bh] : 0.f;
+    float coef = lin && !RIDE && QS == 1 ? a.coef[bh] : 0.f;
     // RIDE: the sample's scale from the gate's partial sums, every wave for itself, in the order of finalize_kernel; tile 0 of a head writes it down
     auto reduce_gate = [&]() INL {
         CallRef c = call_args();
@@ -1093,6 +1105,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (RIDE || late) stage_state();
         if (ROPE && late) load_angles();
         if (RIDE) reduce_gate();
+        if (QS == 2) coef = a.coef[bh];          // there is no register for it before
 #pragma unroll
         for (int u = 0; u < QG; ++u)
 #pragma unroll
@@ -1102,7 +1115,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         WAIT_VM(0);
         __syncthreads();   // the staged fragments have landed in every wave's view
         float dpart[QG] = {};
-        const float *Zh = z_lds() + ls * 8;
+        const float *Zh = z_lds() + lane_again() / G * 8;
 #pragma unroll
         for (int st = 0; st < NS; ++st) {
             const float4 z0 = *reinterpret_cast<const float4 *>(Zh + st * KD), z1 = *reinterpret_cast<const float4 *>(Zh + st * KD + 4);
@@ -1277,7 +1290,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     }
     };
     if constexpr (BOTH) {
-        if (a.many && n_list >= LONG_LIST) rest(std::integral_constant<int, 16>{});
+        static_assert(LONG_LIST >= LOOKED_AT, "a list has the entries that are looked at");
+        if (a.many && n_list >= LONG_LIST && 8 * kept_bits >= 5 * LOOKED_AT * min(4, nb - tile * 4)) rest(std::integral_constant<int, 16>{});
         else rest(std::integral_constant<int, 32>{});
     } else {
         rest(std::integral_constant<int, 32>{});

@@ -889,6 +889,30 @@ def test_arbitrary_csr_with_two_query_sets_a_wave(oracle, H, grid, longest):
         assert r <= REL_L2
 
 
+def _heads_alone(w, dev, first, count, label):
+    """The workload and inputs of some of its heads."""
+    part, cols = wl.small(label, w.B, count, w.d, w.T, w.Hh, w.W, w.dtype, 0.5, seed=w.seed), slice(first * w.d, (first + count) * w.d)
+    some = {t: dev[t][:, first:first + count].contiguous() for t in ("q", "k", "v")}
+    return part, dict(some, x_t=dev["x_t"][..., cols].contiguous(), w_gate=dev["w_gate"][cols].contiguous(),
+                      head_scale=dev["head_scale"][first:first + count].contiguous())
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("step", [2, 3])
+def test_products_of_rows_with_gaps(d, step):
+    """Lists of 36 entries of which a row keeps every second or third one are computed with the same products in calls of any size: 504 tiles
+    against 252 of them, with the same bits."""
+    w = wl.small(f"gaps-{d}", 1, 56, d, 4, 23, 25, "bf16", 0.5, seed=141)
+    dev, kinds = upload(w, wl.make_inputs(w)), wl.head_kinds(w)
+    part, some = _heads_alone(w, dev, 0, 28, f"gaps-part-{d}")
+    rows = [np.arange(i % 4 % step, w.nb, step) for i in range(w.nb)]
+    got = []
+    for x, y, k in ((w, dev, kinds), (part, some, kinds[:28])):
+        csr = (np.cumsum([0] + [len(r) for r in rows] * x.H), np.concatenate(rows * x.H))
+        got.append(run_layer(x, None, y, None, k, csr=csr)["o_sparse"])
+    assert np.array_equal(got[0][:, :28], got[1])
+
+
 def test_unfused_epilogue_matches(oracle):
     w = SMALL[1]
     inp = wl.make_inputs(w)
