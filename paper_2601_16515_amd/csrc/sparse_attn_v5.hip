@@ -166,9 +166,6 @@ __device__ inline INL void unrolled(F &&f)
     unrolled_(f, std::make_integer_sequence<int, N>{});
 }
 
-// by value: a conditional expression of two array elements selects between their addresses, and the array goes to memory
-__device__ inline float either(bool second, float a, float b) { return second ? b : a; }
-
 union Frag5 {
     bf16x8 v;
     uint4 u;
@@ -365,7 +362,6 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const int g_blk0 = g_J * a.g_bpb;
     const uint32_t *src = GATHER ? nullptr : a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
-    const int n_list = n;
     if (SPLIT && pieces > 1) {
         int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
         if (QS == 2) {
@@ -434,7 +430,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // them alone reaches 12 % more at the power limit, with this softmax between them 8 %), and the loop of a call that fills the chip is held by
     // the power limit.  But each has its own start to line up with the vector instructions: a block takes 3140 cycles instead of 2960, and a
     // call of one round, or a tile that is half prologue and output, is held by those.  So G = 16 where the list is LONG_LIST entries or more and
-    // the call more than one round (a.many); the whole list's length, so that the pieces of a cut tile are of one kind.
+    // the call more than one round (a.many), and not in a last round that is cut, with a wave to a SIMD for 64-wide heads and dealt out by constants
+    // that are of the larger products: N = 12480, that round with 16x16x32 -> 32x32x16 products 12 heads of 128, 7 to 43 entries 91.9 -> 88.6,
+    // 142.3 -> 139.5, 216.3 -> 211.4 us; 12 heads of 64, 23 and 43 entries 92.9 -> 88.6, 138.8 -> 132.4.
     // And only where the rows keep five eighths of their tile's list.  A wave's entry that does not follow on another of its own is computed out of
     // the woven part (start_cur, finish_prev), its products and its softmax one after the other, and the wave that does that is the one that the others
     // wait for.  Eight entries in a row of a window that has more are kept by 20 of 32 rows or more.  Layer calls, N = 12480, 32x32x16 ->
@@ -448,6 +446,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     constexpr int QG = 32 / G * QS;              // groups of G queries that a wave owns: the columns of one product
     constexpr int NKG = 32 / G;                  // products of S for the 32 keys of a half
     constexpr int NP = G / 16;                   // P's operands for them
+    constexpr bool TURNS = QS == 1 || !SPLIT;    // whether waves raise and lower their priority (part)
     constexpr int EL = G / 2;                    // logits of a half that a lane owns, a group
     constexpr int AR = G * G / 64;               // accumulators of a lane
     typedef float acc_t __attribute__((ext_vector_type(AR)));
@@ -762,9 +761,12 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             constexpr int slot = slot_, i = slot / QG, uu = slot % QG, u = (i & 1) ? QG - 1 - uu : uu, pt = decltype(pt_)::value, hf = 1 - pt;
             constexpr int g = pt * NPS + i;
             // G = 16: the wave that is behind goes first, so that the two of a SIMD come to the barrier together.  480p, 90 % 3240 -> 3180 cycles a
-            // block (G = 32, where the oldest wave first has always been: 2957).
-            if constexpr (G == 16 && slot == 0) __builtin_amdgcn_s_setprio(pt ? 1 : 3);
-            if constexpr (G == 16 && slot == SLOTS / 2) __builtin_amdgcn_s_setprio(pt ? 0 : 2);
+            // block (G = 32, where the oldest wave first has always been: 2957).  Not where the two are of different workgroups and a last round is
+            // cut: both workgroups of a unit then end at the same time, and the tiles behind them, too few for two to each unit, start in pairs
+            // on half of the units.  64-wide heads, N = 12480, with -> without: 12 heads, 43 entries 133.0 -> 124.7 us; 26 heads, 101 entries 558 -> 511;
+            // the other way where those tiles are cut into pieces for two to a unit anyway: 24 heads, 43 entries 226 -> 238.
+            if constexpr (G == 16 && TURNS && slot == 0) __builtin_amdgcn_s_setprio(pt ? 1 : 3);
+            if constexpr (G == 16 && TURNS && slot == SLOTS / 2) __builtin_amdgcn_s_setprio(pt ? 0 : 2);
             if constexpr (i < SS) mfma_S(u, pt, i, ring[g % RING]); else mfma_PV(u, pt, i - SS, ring[g % RING]);
             if constexpr (uu == QG - 1) read_frag(g + RING, Vt, Kt, Kn);
             __builtin_amdgcn_sched_barrier(0);
@@ -1019,9 +1021,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if ((e_prev & mybit) != 0) finish_prev(e_prev, Vb + v_last * TILE);
     }
 
-    if (SPLIT && pieces > 1) {
+    if (SPLIT && G == 32 && pieces > 1) {
         const int first = (L - a.sp_full) * a.sp_pieces;      // the tile's pieces in the scratch
-        constexpr int PER = NKG * NDT * (AR / 2) * 512;       // register pairs of a piece: pair r of thread tid at r * 512 + tid
+        constexpr int PER = NDT * (AR / 2) * 512;             // register pairs of a piece: pair r of thread tid at r * 512 + tid
         // The pieces of a tile may run on different XCDs, whose L2 caches do not see each other.  Instead of fences, which
         // write back and invalidate a whole L2 (101 against 37 us for a layer call of N = 1950), the scratch is written and
         // read with device-scope accesses, which go past it: a piece's stores are at the common level when they are
@@ -1034,19 +1036,14 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
         };
         uint64_t *mine = a.sp_o + (size_t)(first + piece) * PER + tid;
-        auto pair_at = [&](int u, int dt, int r) INL -> int { return ((u % NKG * NDT + dt) * (AR / 2) + r) * 512 + u / NKG * NT; };
 #pragma unroll
-        for (int u = 0; u < QG; ++u)
+        for (int u = 0; u < QS; ++u) {
 #pragma unroll
             for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
-                for (int r = 0; r < AR / 2; ++r) put(mine + pair_at(u, dt, r), o[u][dt][2 * r], o[u][dt][2 * r + 1]);
-#pragma unroll
-        for (int u = 0; u < QS; ++u) {        // every lane its query of the set, twice
+                for (int r = 0; r < AR / 2; ++r) put(mine + (dt * (AR / 2) + r) * 512 + u * NT, o[u][dt][2 * r], o[u][dt][2 * r + 1]);
             // a wave that kept no entry of this piece has no reference, and nothing to add
-            const int u0 = NKG * u, u1 = NKG * u + NKG - 1;
-            const float m0 = have_ref[0] ? m_run[u0] : -INFINITY, m1 = have_ref[0] ? m_run[u1] : -INFINITY;
-            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, either(l32 >= G, m0, m1), either(l32 >= G, l_run[u0], l_run[u1]));
+            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, have_ref[0] ? m_run[u] : -INFINITY, l_run[u]);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         WAIT_VM(0);
@@ -1068,34 +1065,33 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         __syncthreads();
         if (!blist[0]) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        const uint64_t *ml_at = a.sp_ml + (size_t)first * 512 + wave * 64 + lq;
-        float mx[QG];
+        float mx[QS];
 #pragma unroll
-        for (int u = 0; u < QG; ++u) {
+        for (int u = 0; u < QS; ++u) {
             mx[u] = -INFINITY;
-            for (int p = 0; p < pieces; ++p) mx[u] = fmaxf(mx[u], get(ml_at + p * 512 + u / NKG * NT + u % NKG * G).x);
+            for (int p = 0; p < pieces; ++p) mx[u] = fmaxf(mx[u], get(a.sp_ml + (size_t)(first + p) * 512 + u * NT + tid).x);
 #pragma unroll
             for (int i = 0; i < NDT; ++i) o[u][i] = zero;
             l_run[u] = 0.f;
         }
         for (int p = 0; p < pieces; ++p)
 #pragma unroll
-            for (int u = 0; u < QG; ++u) {
-                const float2 ml = get(ml_at + p * 512 + u / NKG * NT + u % NKG * G);
+            for (int u = 0; u < QS; ++u) {
+                const float2 ml = get(a.sp_ml + (size_t)(first + p) * 512 + u * NT + tid);
                 const float wt = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - mx[u]);
-                const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + tid;
+                const uint64_t *src = a.sp_o + (size_t)(first + p) * PER + u * NT + tid;
                 l_run[u] = fmaf(wt, ml.y, l_run[u]);
 #pragma unroll
                 for (int dt = 0; dt < NDT; ++dt)
 #pragma unroll
                     for (int r = 0; r < AR / 2; ++r) {
-                        const float2 v = get(src + pair_at(u, dt, r));
+                        const float2 v = get(src + (dt * (AR / 2) + r) * 512);
                         o[u][dt][2 * r] = fmaf(wt, v.x, o[u][dt][2 * r]);
                         o[u][dt][2 * r + 1] = fmaf(wt, v.y, o[u][dt][2 * r + 1]);
                     }
             }
 #pragma unroll
-        for (int u = 0; u < QG; ++u) m_run[u] = mx[u];
+        for (int u = 0; u < QS; ++u) m_run[u] = mx[u];
     }
 
     // ---- epilogue ---------------------------------------------------------------------------------
@@ -1250,10 +1246,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 if (valid) *reinterpret_cast<uint4 *>(blk + i * 512) = v;
             }
         }
-        if (GATHER && valid && hh == 0) {       // lanes 0 .. 31, each for its query of the set
-            const float l_tot = either(l32 >= G, l_run[u0], l_run[u0 + NKG - 1]), m = either(l32 >= G, m_run[u0], m_run[u0 + NKG - 1]);
-            a.g_lse[(size_t)bh * N * a.g_kk + g_slot0 + qrow] = l_tot > 0.f ? m + log2f(l_tot) : -INFINITY;
-        }
+        if (GATHER && valid && hh == 0) a.g_lse[(size_t)bh * N * a.g_kk + g_slot0 + qrow] = l_run[u] > 0.f ? m_run[u] + log2f(l_run[u]) : -INFINITY;
     } else {
 #pragma unroll
         for (int c = 0; c < NKG; ++c) {
@@ -1291,7 +1284,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     };
     if constexpr (BOTH) {
         static_assert(LONG_LIST >= LOOKED_AT, "a list has the entries that are looked at");
-        if (a.many && n_list >= LONG_LIST && 8 * kept_bits >= 5 * LOOKED_AT * min(4, nb - tile * 4)) rest(std::integral_constant<int, 16>{});
+        if (a.many && n >= LONG_LIST && !(SPLIT && L >= a.sp_full) && 8 * kept_bits >= 5 * LOOKED_AT * min(4, nb - tile * 4)) rest(std::integral_constant<int, 16>{});
         else rest(std::integral_constant<int, 32>{});
     } else {
         rest(std::integral_constant<int, 32>{});

@@ -913,6 +913,18 @@ def test_products_of_rows_with_gaps(d, step):
     assert np.array_equal(got[0][:, :28], got[1])
 
 
+@pytest.mark.parametrize("d,H,first", [(128, 22, 16), (64, 47, 32)])
+def test_products_of_a_cut_last_round(d, H, first):
+    """Tiles of a last round that leaves half of the chip idle, here with lists too short to be cut: with the same products, and bits, as in a call of
+    their own.  16 tiles a head: 96 behind 256, or 240 behind 512 that go two to a compute unit."""
+    w = wl.small(f"round-{d}", 1, H, d, 4, 32, 32, "bf16", 0.5, seed=142)
+    dev, kinds = upload(w, wl.make_inputs(w)), wl.head_kinds(w)
+    part, some = _heads_alone(w, dev, first, H - first, f"round-part-{d}")
+    whole = run_layer(w, None, dev, [20] * H, kinds)["o_sparse"]
+    alone = run_layer(part, None, some, [20] * part.H, kinds[first:])["o_sparse"]
+    assert np.array_equal(whole[:, first:], alone)
+
+
 def test_unfused_epilogue_matches(oracle):
     w = SMALL[1]
     inp = wl.make_inputs(w)
