@@ -145,7 +145,7 @@ __device__ inline float max_of_query(float x)
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// The lane's number, computed where it is asked for: what follows from it is not kept in registers through the loop for a use behind it.
+// The lane's number, computed where it is asked for: what follows from it is not kept in registers through the loop for a use behind it (TIGHT).
 __device__ inline int lane_again()
 {
     unsigned all = ~0u;
@@ -447,6 +447,11 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     constexpr int NKG = 32 / G;                  // products of S for the 32 keys of a half
     constexpr int NP = G / 16;                   // P's operands for them
     constexpr bool TURNS = QS == 1 || !SPLIT;    // whether waves raise and lower their priority (part)
+    // Two query sets a wave take all registers for the loop.  What the epilogue and a call's last block need is then computed there, and flags are
+    // one for the wave: else 17 to 32 registers were in memory, some loaded again behind a block's loads, which the wait for them then waits for,
+    // too.  24 heads of 64, N = 12480: 23 entries 160.8 -> 155.4 us, rows that keep every second block 590 -> 567, a random 10 % 275 -> 263.  With one
+    // set there are registers for it all, and the same costs time: 12 heads, N = 1950 24.5 -> 24.8, 480p dense 5064 -> 5099.
+    constexpr bool TIGHT = QS == 2;
     constexpr int EL = G / 2;                    // logits of a half that a lane owns, a group
     constexpr int AR = G * G / 64;               // accumulators of a lane
     typedef float acc_t __attribute__((ext_vector_type(AR)));
@@ -456,12 +461,14 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     uint32_t qm_lo[QG] = {}, qm_hi[QG] = {};     // TOPK: this lane's queries' key-block bits
     auto rows_active = [&](int unit) INL -> bool { return !ROW_PAIRS || my_rows < 0 || my_rows == unit >> 2; };
     // Stored row of query i of the wave's set u (a valid one also where there is none), and whether there is one.  GATHER: the place in the run.
-    // For the epilogue, and computed there: kept from here on it is a register or two through the loop, of which d = 64 has none to spare.
     auto query_row = [&](int u, int i, bool &valid) INL -> int {
         const int unit = (int)wave_u * QS + u, p = GATHER ? unit * 32 + i : tile * 256 + unit * 32 + i;
         valid = GATHER ? p < g_cnt : p < N && rows_active(unit);
         return GATHER ? p : row_of_position5(kind, min(p, N - 1), T, HW, magic);
     };
+    bool valid0 = false;
+    int row0 = 0;                                // this lane's query, unless TIGHT
+    if (!TIGHT) row0 = query_row(0, l32, valid0);
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
         const int unit = wave * QS + u, qblk = tile * 4 + (unit >> 1);
@@ -574,11 +581,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     };
     acc_t o[QG][NDT];
     float m_run[QG], l_run[QG];
-    // Whether m_run has been set from a block's true maximum.  A wave's queries keep the same list entries but for TOPK, where each lane has its
-    // own: one flag then does for the wave.  With a flag a group 64-wide heads with two query sets a wave had 17 to 32 registers in memory, some
-    // loaded again behind a block's loads, which the wait for them then waits for, too; with one, and what the epilogue and a call's last block alone
-    // need computed there, none.  24 heads of 64, N = 12480: 23 entries 160.8 -> 155.4 us, rows that keep every second block 590 -> 567, a random 10 % 275 -> 263.
-    bool have_ref[TOPK ? QG : 1] = {};
+    // Whether m_run has been set from a block's true maximum: the same for all queries of a wave, which keep the same list entries, but for TOPK.
+    constexpr int NREF = TIGHT ? 1 : QG;
+    bool have_ref[NREF] = {};
 #pragma unroll
     for (int u = 0; u < QG; ++u) {
 #pragma unroll
@@ -620,12 +625,21 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (__builtin_expect((uint32_t)blk == tail_blk, 0)) {
             int first = blk * 64;
             asm volatile("" : "+s"(first));      // else the compares, the same in every such block, leave the loop and fill the scalar registers
-            const int kbase = first + hf * 32 + lane_again() / G * (G / 4);
+            const int kbase = first + hf * 32 + (TIGHT ? lane_again() / G : ls) * (G / 4);
+            auto mask = [&](int u, int e) INL {
+                if (kbase + 16 * (e / (G / 4)) + e % (G / 4) >= N) s[u][hf][e / AR][e % AR] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
+            };
+            if constexpr (TIGHT) {               // a key's compare is used at once, not kept for the other groups
 #pragma unroll
-            for (int e = 0; e < EL; ++e)
+                for (int e = 0; e < EL; ++e)
+#pragma unroll
+                    for (int u = 0; u < QG; ++u) mask(u, e);
+            } else {
 #pragma unroll
                 for (int u = 0; u < QG; ++u)
-                    if (kbase + 16 * (e / (G / 4)) + e % (G / 4) >= N) s[u][hf][e / AR][e % AR] = TOPK ? -1e30f : -INFINITY;   // TOPK: stays finite times a zero scale
+#pragma unroll
+                    for (int e = 0; e < EL; ++e) mask(u, e);
+            }
         }
     };
     // Sums of bf16 probabilities, every lane getting its query's, by 16x16x32 products.  With G = 16 the other operand is all ones.  With G = 32 a
@@ -693,7 +707,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         for (int u = 0; u < QG; ++u) {
             psum[u] = ps[u];
             all += psum[u];                      // none is negative: within the bound only if each is
-            first[u] = !started && !have_ref[TOPK ? u : 0];
+            first[u] = !started && !have_ref[TIGHT ? 0 : u];
             if (TOPK) first[u] = __any(selected(u, e) && first[u]);
             any = any || first[u];
         }
@@ -701,7 +715,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
             for (int u = 0; u < QG; ++u)
                 if (first[u] || __any(!(psum[u] <= 8192.f))) {
-                    const bool known = started || have_ref[TOPK ? u : 0];
+                    const bool known = started || have_ref[TIGHT ? 0 : u];
                     float own = psum[u];
                     if (G == 32 && (TOPK || known)) own = sums_apart(u, hf);
                     const bool rises = !known | !(own <= 8192.f), moves = TOPK ? rises & selected(u, e) : rises;
@@ -722,11 +736,11 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                             for (int r = 0; r < AR; ++r) o[u][i][r] *= alpha;
                     }
                     m_run[u] += shift;
-                    if constexpr (TOPK) have_ref[u] = moves || have_ref[u];
+                    if constexpr (!TIGHT) have_ref[u] = !TOPK || moves || have_ref[u];      // TOPK apart the same for all lanes, which the compiler is to see
                     psum[u] = exp_pack(u, hf, selected(u, e));
                     if (G == 32 && __builtin_expect(__any(!(psum[u] <= 8192.f)), 0)) psum[u] = sums_apart(u, hf);
                 }
-            if (!TOPK) have_ref[0] = true;
+            if (TIGHT) have_ref[0] = true;       // behind all groups: each is to find it as it was
         }
 #pragma unroll
         for (int u = 0; u < QG; ++u) l_run[u] += !TOPK || selected(u, e) ? psum[u] : 0.f;
@@ -917,8 +931,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         if (ROPE)
 #pragma unroll
             for (int u = 0; u < QG; ++u) {
-                bool valid;
-                const uint32_t *tr = a.rope_tab + (size_t)query_row(u / NKG, u % NKG * G + lq, valid) * (D / 2) + ls * 4;
+                const uint32_t *tr = a.rope_tab + (size_t)__shfl(row0, u * G + lq) * (D / 2) + ls * 4;
 #pragma unroll
                 for (int st = 0; st < NS; ++st) ang[u][st] = *reinterpret_cast<const uint4 *>(tr + st * (KD / 2));
             }
@@ -1043,7 +1056,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
                 for (int r = 0; r < AR / 2; ++r) put(mine + (dt * (AR / 2) + r) * 512 + u * NT, o[u][dt][2 * r], o[u][dt][2 * r + 1]);
             // a wave that kept no entry of this piece has no reference, and nothing to add
-            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, have_ref[0] ? m_run[u] : -INFINITY, l_run[u]);
+            put(a.sp_ml + (size_t)(first + piece) * 512 + u * NT + tid, have_ref[TIGHT ? 0 : u] ? m_run[u] : -INFINITY, l_run[u]);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         WAIT_VM(0);
@@ -1111,7 +1124,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         WAIT_VM(0);
         __syncthreads();   // the staged fragments have landed in every wave's view
         float dpart[QG] = {};
-        const float *Zh = z_lds() + lane_again() / G * 8;
+        const float *Zh = z_lds() + (TIGHT ? lane_again() / G : ls) * 8;
 #pragma unroll
         for (int st = 0; st < NS; ++st) {
             const float4 z0 = *reinterpret_cast<const float4 *>(Zh + st * KD), z1 = *reinterpret_cast<const float4 *>(Zh + st * KD + 4);
@@ -1154,7 +1167,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     if (ROW_PAIRS && my_rows >= 0 && mybit == 0u) return;      // a wave of the other rows, no barrier follows
 #pragma unroll
     for (int u = 0; u < QS; ++u) {
-    const int unit = (int)wave_u * QS + u, lane = lane_again(), lq = lane % G, ls = lane / G, l32 = lane & 31, hh = lane >> 5;
+    const int unit = wave * QS + u, lane = TIGHT ? lane_again() : tid & 63, lq = lane % G, ls = lane / G, l32 = lane & 31, hh = lane >> 5;
     const int u0 = NKG * u;                  // this set's groups: u0 .. u0 + NKG - 1
     float inv_l[NKG];
 #pragma unroll
@@ -1210,8 +1223,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
                 }
         asm volatile("" ::: "memory");       // the wave's LDS operations execute in order
         // destination of row r: the stored row (or the pair slot) of the lane that owns query r
-        bool valid;
-        const int qrow = query_row(u, l32, valid), dest_mine = !valid ? -1 : GATHER ? g_slot0 + qrow : qrow;
+        bool valid = valid0;
+        const int qrow = TIGHT ? query_row(u, l32, valid) : row0, dest_mine = !valid ? -1 : GATHER ? g_slot0 + qrow : qrow;
         constexpr int RPI = 64 / CH;          // rows per store instruction (4 rows x 16 chunks, or 8 x 8)
         const int r4 = lane / CH, c16 = lane % CH;
         u16 *dbase = GATHER ? a.g_po + (size_t)bh * N * a.g_kk * D : reinterpret_cast<u16 *>(a.out) + (size_t)bh * N * D;
@@ -1251,8 +1264,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
 #pragma unroll
         for (int c = 0; c < NKG; ++c) {
             bool valid;
-            const int mine = query_row(u, c * G + lq, valid);
-            if (valid) {
+            const int mine = TIGHT ? query_row(u, c * G + lq, valid) : __shfl(valid0 ? row0 : -1, c * G + lq);
+            if (TIGHT ? valid : mine >= 0) {
                 const size_t obase = ((size_t)bh * N + mine) * D;
                 u16 *outp = reinterpret_cast<u16 *>(a.out) + obase;
 #pragma unroll
