@@ -10,7 +10,7 @@
 //     (global_load_lds_dwordx4, bank swizzle applied on the global side).  The wait before the
 //     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
-//   * Products are 32x32x16 or, for long lists in calls that fill the chip, 16x16x32 ones (LONG_LIST): an instantiation holds both ways from the
+//   * Products are 32x32x16 or, for long lists in calls that fill the chip, 16x16x32 ones (long_list): an instantiation holds both ways from the
 //     queries' operands to the epilogue, and a tile takes one by its list's length.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
 //     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's
@@ -50,11 +50,15 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 // s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8)
 #define WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | ((n) >> 4) << 14)
 
-// Least entries of a list for 16x16x32 products (the kernel's G).  Layer calls of more than 256 tiles with 32x32x16 -> 16x16x32 products (us), by
-// entries: 4 to 9 40 heads, N = 1700 67.4 -> 68.6; 12 12 heads, N = 5500 64.4 -> 64.6; 16 8 heads, N = 16384 102.6 -> 100.8; 27 40 heads, N = 1700 113.0 ->
-// 112.4; 67 8 heads, N = 16384 267.5 -> 260.1; 52 12 heads, N = 12480 271.2 -> 263.0; 54 12 heads, N = 32760 671 -> 645, 512 5604 -> 5257; 64-wide heads: 13 24
-// heads, N = 12480 110.0 -> 124.5, 101 531 -> 488; 54 24 heads, N = 32760 737 -> 704.
-constexpr int LONG_LIST = 20;
+// Least entries of a list for 16x16x32 products (the kernel's G), by head width.  Layer calls with 32x32x16 -> 16x16x32 products (us), by entries:
+//   128-wide heads, 8, 10, 12, 16:  19 heads, N = 4096 (304 tiles) 53.7 -> 54.1, 59.0 -> 58.8, 64.2 -> 63.2, 74.8 -> 73.3;  50 heads, N = 4096 (800) 124.3 -> 124.2,
+//     134.5 -> 133.8, 147.0 -> 144.3, 168.0 -> 164.0;  15 heads, N = 12480 (735) 92.1 -> 93.3, 101.2 -> 101.5, 110.2 -> 109.5, 127.9 -> 126.7;  12 heads, N = 32760 (1536)
+//     198.6 -> 195.8, 215.0 -> 211.8, 234.1 -> 230.4, 271.0 -> 268.3
+//   64-wide heads, 16, 20, 24, 34:  30 heads, N = 4096 (480) 52.8 -> 52.8, 59.8 -> 58.9, 68.2 -> 65.9, 87.2 -> 83.0;  38 heads (608) 69.5 -> 71.0, 78.7 -> 79.3, 88.2 -> 87.7,
+//     112.1 -> 110.4;  24 heads, N = 12480 (1176) 110.4 -> 113.8, 128.9 -> 130.7, 148.1 -> 148.2, 202.3 -> 200.8;  30 heads (1470) 131.3 -> 131.2, 152.9 -> 151.0, 176.8 -> 172.5,
+//     234.6 -> 225.2
+// Long lists: 12 heads of 128, N = 32760, 54 entries 671 -> 645, 512 5604 -> 5257; 24 heads of 64, 54 entries 737 -> 704.
+constexpr int long_list(int d) { return d == 128 ? 12 : 20; }
 constexpr int SPLIT_MAX_PIECES = 8;
 constexpr int SPLIT_MIN_ENTRIES = 6;     // least entries of a piece: what a cut costs (two passes over 128 KB, a prologue) is about as long
 
@@ -289,7 +293,9 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     uint32_t *blist = reinterpret_cast<uint32_t *>(Vb + NV * TILE);      // [list_cap] union list: blk | mask << 24
 
     constexpr bool TOPK = MODE == 1, GATHER = MODE == 2;
-    // Which products the kernel has (G below): calls of one round of tiles and the gathered ones have the larger only.
+    // Which kernels have both kinds of products (G below).  Riders' calls are one round.  64-wide heads with one query set a wave are calls of up to
+    // 384 tiles, the most of which are cut, and those of more than 1792 blocks, whose lists leave no room for a second workgroup: for them, as for the
+    // modes of the dynamic mask, the smaller products have not been built.
     constexpr bool BOTH = MODE == 0 && !RIDE && (D == 128 || QS == 2);
     // chunk swizzle of the output staging
     auto oswz = [](int row) INL -> int { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
@@ -429,7 +435,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // ---- All else depends on the products.  16x16x32 ones read and write half the accumulators of 32x32x16 ones for the same work (a loop of
     // them alone reaches 12 % more at the power limit, with this softmax between them 8 %), and the loop of a call that fills the chip is held by
     // the power limit.  But each has its own start to line up with the vector instructions: a block takes 3140 cycles instead of 2960, and a
-    // call of one round, or a tile that is half prologue and output, is held by those.  So G = 16 where the list is LONG_LIST entries or more and
+    // call of one round, or a tile that is half prologue and output, is held by those.  So G = 16 where the list is long_list(D) entries or more and
     // the call more than one round (a.many), and not in a last round that is cut, with a wave to a SIMD for 64-wide heads and dealt out by constants
     // that are of the larger products: N = 12480, that round with 16x16x32 -> 32x32x16 products 12 heads of 128, 7 to 43 entries 91.9 -> 88.6,
     // 142.3 -> 139.5, 216.3 -> 211.4 us; 12 heads of 64, 23 and 43 entries 92.9 -> 88.6, 138.8 -> 132.4.
@@ -1296,8 +1302,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     }
     };
     if constexpr (BOTH) {
-        static_assert(LONG_LIST >= LOOKED_AT, "a list has the entries that are looked at");
-        if (a.many && n >= LONG_LIST && !(SPLIT && L >= a.sp_full) && 8 * kept_bits >= 5 * LOOKED_AT * min(4, nb - tile * 4)) rest(std::integral_constant<int, 16>{});
+        static_assert(long_list(D) >= LOOKED_AT, "a list has the entries that are looked at");
+        const bool smaller = a.many && n >= long_list(D) && !(SPLIT && L >= a.sp_full) && 8 * kept_bits >= 5 * LOOKED_AT * min(4, nb - tile * 4);
+        // the hint is for the registers and the order of the code: 480p dense without it 5262, with it 5215 us
+        if (__builtin_expect(smaller, 1)) rest(std::integral_constant<int, 16>{});
         else rest(std::integral_constant<int, 32>{});
     } else {
         rest(std::integral_constant<int, 32>{});

@@ -773,11 +773,14 @@ def test_references_of_two_query_sets_move_apart(oracle, profile, H, grid, keep)
 
 
 @pytest.mark.parametrize("H,d,grid,keep", [
-    (43, 128, (4, 17, 19), 16),       # 258 tiles of 21 blocks, lists of at most 19 entries: the larger products
-    (43, 128, (4, 17, 19), 17),       # lists of 17 to 20: both in one call
+    (43, 128, (4, 17, 19), 8),        # 258 tiles of 21 blocks, lists of at most 11 entries: the larger products
+    (43, 128, (4, 17, 19), 9),        # lists of 9 to 12: both in one call
+    (43, 128, (4, 17, 19), 16), (43, 128, (4, 17, 19), 17),
     (43, 128, (4, 17, 19), 21),       # 21, the last block of 12 keys
     (29, 128, (4, 23, 25), 36),       # 261 tiles: a round, and five in pieces
-    (43, 64, (4, 17, 19), 17), (58, 64, (4, 23, 25), 36),
+    (43, 64, (4, 17, 19), 16),        # lists of at most 19 entries: the larger products
+    (43, 64, (4, 17, 19), 17),        # lists of 17 to 20: both in one call
+    (58, 64, (4, 23, 25), 36),
 ], ids=lambda x: str(x).replace(" ", ""))
 def test_smaller_products_of_long_lists(oracle, topk_variant, H, d, grid, keep):
     """Calls of more than one round of tiles around the list length from which on a tile is computed with 16x16x32 products; key magnitudes
