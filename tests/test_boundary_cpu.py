@@ -341,3 +341,17 @@ def test_attention_kernels_keep_their_registers(lib):
     kernels = [k for k in _kernel_metadata(sb.LIB_PATH) if "sparse_attn_v5_kernel" in k[".name"]]
     assert len(kernels) >= 30
     assert {k[".name"]: k[".private_segment_fixed_size"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]} == {}
+
+
+@pytest.mark.parametrize("named", [True, False])
+def test_current_stream_with_and_without_its_handle(monkeypatch, named):
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=1000 + device))
+    if named:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 2000 + device, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert sb._stream() == (2003 if named else 1003)
