@@ -892,6 +892,48 @@ def test_arbitrary_csr_with_two_query_sets_a_wave(oracle, H, grid, longest):
         assert r <= REL_L2
 
 
+@pytest.mark.parametrize("H,d,grid", [(29, 128, (4, 23, 25)), (58, 64, (4, 23, 25))])
+def test_arbitrary_csr_in_calls_of_more_than_a_round(oracle, H, d, grid):
+    """Random rows of long lists with few gaps, which the smaller products take, between ones with many, which the larger take; rows that share a tile
+    and no block, an empty row, an empty tile; tiles of the last round in pieces."""
+    w = wl.small(f"csr-{H}-{d}", 1, H, d, *grid, "bf16", 0.5, seed=109)
+    inp = wl.make_inputs(w)
+    dev, kinds = upload(w, inp), wl.head_kinds(w)
+    u = wl.uniform(109, "pick", (w.H, w.nb, w.nb))
+    keep = u < np.array([0.95, 0.85, 0.75, 0.3])[np.arange(w.H) % 4][:, None, None]
+    keep[0, 3] = False
+    keep[1, 8:12] = np.arange(w.nb) % 4 == np.arange(4)[:, None]
+    keep[-2, 4:8] = False
+    csr = (np.cumsum(np.concatenate([[0], keep.sum(2).ravel()])).astype(np.int32), np.nonzero(keep.reshape(-1, w.nb))[1].astype(np.int32))
+    o_s, rows = oracle.sparse_attn(inp["q"], inp["k"], inp["v"], (w.T, w.Hh, w.W), 64, kinds, *csr)
+    for got in (run_layer(w, inp, dev, None, kinds, csr=csr)["o_sparse"], run_layer(w, inp, dev, None, kinds, csr=csr, lam=0.0, dbg=False)["out"]):
+        got, ok = gather_rows(got, rows)
+        a, r = errors(got[ok], o_s[ok])
+        say(f"  arbitrary CSR: o_sparse max_abs={a:.3e} rel_l2={r:.3e}")
+        assert r <= REL_L2
+
+
+def test_samples_with_the_smaller_products(oracle):
+    """Two samples, one without its linear branch, in a call of more than a round: 260 tiles, lists of 20 to 23, the last four in pieces."""
+    w = wl.small("pruned-columns", 2, 13, 128, 21, 10, 12, "bf16", 0.5, seed=143)
+    inp = wl.make_inputs(w)
+    wg = inp["w_gate"]
+    inp["x_t"] = inp["x_t"].copy()
+    inp["x_t"][1] = wl.round_to_bf16(inp["x_t"][1] + (2.0 * wg / float(np.dot(wg, wg))).astype(np.float32))   # pre-activations of sample 1 up by ~2
+    dev, kinds, kept = upload(w, inp), wl.head_kinds(w), [20] * w.H
+    sel = list(range(0, w.nb, 6)) + [w.nb - 1]
+    s = _oracle_layer(oracle, w, inp, kept, kinds, sel=[0])["s"]
+    tau = float(0.5 * (s[0] + s[1]))
+    ref = _oracle_layer(oracle, w, inp, kept, kinds, sel=sel, lam=20.0, drop_threshold=tau)
+    assert ref["dropped"].tolist() == [1, 0]
+    sparse_only = run_layer(w, inp, dev, kept, kinds, lam=0.0, dbg=False)["out_t"]
+    for dbg in (True, False):
+        res = run_layer(w, inp, dev, kept, kinds, lam=20.0, drop_threshold=tau, dbg=dbg)
+        assert res["dropped"].tolist() == [1, 0]
+        compare_layer(res, ref, check_linear=False, label="pruned")
+        assert torch.equal(res["out_t"][0], sparse_only[0]) and not torch.equal(res["out_t"][1], sparse_only[1])
+
+
 def _heads_alone(w, dev, first, count, label):
     """The workload and inputs of some of its heads."""
     part, cols = wl.small(label, w.B, count, w.d, w.T, w.Hh, w.W, w.dtype, 0.5, seed=w.seed), slice(first * w.d, (first + count) * w.d)
@@ -1226,6 +1268,7 @@ def test_full_projection(oracle, w):
     (2, 3, (3, 5, 13), 3),            # 195 rows, tiles dealt by rows, two samples
     (1, 4, (5, 15, 26), 31),          # 1950 rows, tiles cut along their lists
     (1, 13, (21, 12, 20), 8),    # 5040 rows, 260 tiles: whole ones and dealt ones
+    (1, 13, (21, 12, 20), 24),   # lists of 24 to 27: a round with the smaller products, and four tiles in pieces
 ])
 def test_full_projection_input_from_the_attention_epilogue(oracle, B, H, grid, keep):
     """Without debug outputs the attention kernel itself writes the projection's operand: both head orders, ragged last blocks,
@@ -1391,6 +1434,20 @@ def test_rotary_linear_branch(oracle, wi, flags):
     res0 = run_layer(w, inp, dev, kept, kinds, lam=20.0, rope=(one, zero), flags=flags)
     plain = run_layer(w, inp, dev, kept, kinds, lam=20.0, flags=flags)
     assert torch.equal(res0["out_t"], plain["out_t"])                            # identity rotation: the same bits
+
+
+@pytest.mark.parametrize("keep", [8, 24])
+def test_rotary_linear_branch_in_calls_of_more_than_a_round(oracle, keep):
+    """260 tiles of 5040 rows: with lists of 24 to 27 the smaller products rotate their queries, and the four tiles of the last round, in pieces, theirs."""
+    w = wl.small("rope-columns", 1, 13, 128, 21, 12, 20, "bf16", 0.5, seed=144)
+    inp = wl.make_inputs(w)
+    dev, kinds, kept = upload(w, inp), wl.head_kinds(w), [keep] * w.H
+    cs, sn = wl.rope_tables(w.T, w.Hh, w.W, w.d)
+    rope_dev = (torch.from_numpy(cs).cuda(), torch.from_numpy(sn).cuda())
+    ref = _oracle_layer(oracle, w, inp, kept, kinds, sel=list(range(0, w.nb, 9)) + [w.nb - 1], lam=20.0, rope=(cs, sn))
+    res = run_layer(w, inp, dev, kept, kinds, lam=20.0, rope=rope_dev)
+    compare_layer(res, ref, label="rope-columns")
+    assert torch.equal(run_layer(w, inp, dev, kept, kinds, lam=20.0, rope=rope_dev, dbg=False)["out_t"], res["out_t"])
 
 
 @pytest.mark.parametrize("w", PROJ_SHAPES, ids=lambda w: w.name)
@@ -1612,6 +1669,14 @@ def test_layer_call_under_graph_capture():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, eager), f"replay {rep} differs from the eager call"
+
+
+def test_stream_handle_is_the_current_streams():
+    side = torch.cuda.Stream()
+    assert sb._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert sb._stream() == side.cuda_stream
+    assert sb._stream() == torch.cuda.current_stream().cuda_stream
 
 
 def test_timing_modes_leave_results_alone():
