@@ -11,7 +11,7 @@
 //     per-block barrier is counted (s_waitcnt vmcnt(n)), so two blocks of loads stay in flight and
 //     L2 / fabric latency is covered without a second resident workgroup.
 //   * Products are 32x32x16 or, for long lists in calls that fill the chip, 16x16x32 ones (long_list): an instantiation holds both ways from the
-//     queries' operands to the epilogue, and a tile takes one by its list's length.
+//     queries' operands to the epilogue, and a tile takes one by its list's length, its gaps and its round.
 //   * The unit of work is half a block (32 keys).  While a wave multiplies (S of one half, then O += V^T P of another), the
 //     fma / exp / pack of a third half sit between its MFMAs, a few vector instructions after each.  A block's
 //     K and V loads are issued between its two halves.  One barrier per KV block (it also protects the rings).
@@ -437,8 +437,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // the power limit.  But each has its own start to line up with the vector instructions: a block takes 3140 cycles instead of 2960, and a
     // call of one round, or a tile that is half prologue and output, is held by those.  So G = 16 where the list is long_list(D) entries or more and
     // the call more than one round (a.many), and not in a last round that is cut, with a wave to a SIMD for 64-wide heads and dealt out by constants
-    // that are of the larger products: N = 12480, that round with 16x16x32 -> 32x32x16 products 12 heads of 128, 7 to 43 entries 91.9 -> 88.6,
-    // 142.3 -> 139.5, 216.3 -> 211.4 us; 12 heads of 64, 23 and 43 entries 92.9 -> 88.6, 138.8 -> 132.4.
+    // that are of the larger products: N = 12480, that round with 16x16x32 -> 32x32x16 products 11 heads of 128, 23 and 101 entries 142.8 -> 139.4,
+    // 428.6 -> 421.4 us; 12 heads of 64, 23 and 43 entries 85.6 -> 83.0, 127.8 -> 124.7.
     // And only where the rows keep five eighths of their tile's list.  A wave's entry that does not follow on another of its own is computed out of
     // the woven part (start_cur, finish_prev), its products and its softmax one after the other, and the wave that does that is the one that the others
     // wait for.  Eight entries in a row of a window that has more are kept by 20 of 32 rows or more.  Layer calls, N = 12480, 32x32x16 ->
@@ -812,7 +812,7 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // another query block of the tile keeps).  Lists of random or strided blocks live on it, so in the uncut d = 128 kernels start_cur has
     // the softmax of the first half between the S products of the second: every third block 1159 -> 1066 us at N = 12480, 24 heads.
     // The same in finish_prev lost (1182), and windows got slower by it where tiles are cut and at d = 64 (480p, 90 % 882 -> 895).
-    // Layer calls there, every second / third / a random 30 % of the blocks: 1138 / 1049 / 879 us; 24 heads of 64 593 / 553 / 514.
+    // Layer calls there, every second / third / a random 30 % of the blocks: 1104 / 998 / 830 us; 24 heads of 64 572 / 535 / 495.
     // Operands are read four steps ahead here, too; only vector and scalar instructions may pass from one step to another.
     auto in_turn = [&](auto count, auto read, auto use) INL {
         Frag5 f[4];
