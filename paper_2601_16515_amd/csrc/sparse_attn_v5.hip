@@ -368,8 +368,8 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     const int g_blk0 = g_J * a.g_bpb;
     const uint32_t *src = GATHER ? nullptr : a.tile_lists + ((size_t)(TOPK ? bh : h) * ntiles + tile) * list_cap;
     int n = GATHER ? min(min(nb, g_blk0 + a.g_bpb) - g_blk0, list_cap) : a.tile_counts[(TOPK ? bh : h) * ntiles + tile], list0 = 0;
-    if (SPLIT && pieces > 1) {
-        int by_length = min(pieces, n / SPLIT_MIN_ENTRIES);
+    auto pieces_of_list = [&]() INL -> int {
+        int by_length = min(a.sp_pieces, n / SPLIT_MIN_ENTRIES);
         if (QS == 2) {
             // A piece alone on its compute unit takes 0.9 us an entry, one that shares it 1.6, a cut costs 4.8 and 11 us (fitted to calls of 520
             // to 768 tiles): the best of no cut, as many pieces as have a unit each, and all that there is room for.  Cut wherever pieces had
@@ -378,6 +378,13 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             const int p = own > 1 && 18 * n * (own - 1) > 95 * own ? own : 1;
             if (by_length <= own || (18 * n + (p > 1 ? 95 * p : 0)) * by_length < (32 * n + 220 * by_length) * p) by_length = p;
         }
+        return by_length;
+    };
+    // Two query sets a wave, ahead of a last round that is cut: whether waves raise and lower their priority (part).  Not where each piece of that
+    // round, if its lists are as long as this one, may have a compute unit to itself.
+    const bool turns = SPLIT && QS == 2 && pieces_of_list() * (total - a.sp_full) > 256;
+    if (SPLIT && pieces > 1) {
+        const int by_length = pieces_of_list();
         if (by_length > 1 && (!ROW_PAIRS || n * (21 * by_length - 29) > (D == 64 ? 120 : 190) * by_length)) {
             pieces = by_length;
             if (piece >= pieces) return;
@@ -445,14 +452,14 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
     // 16x16x32 products in all tiles (us), rows of random blocks, by the share that they keep of their tile's list: 15 heads of 128 0.39 509 -> 554,
     // 0.53 673 -> 706, 0.62 746 -> 752, 0.71 884 -> 855, 0.80 968 -> 923; 30 heads of 64 0.39 615 -> 653, 0.53 819 -> 827, 0.62 913 -> 890, 0.80 1084 -> 1035;
     // of random runs of four blocks: 15 heads 0.39 539 -> 610, 0.62 755 -> 784, 0.80 965 -> 937.
-    auto rest = [&](auto g_) INL {
+    auto rest = [&](auto g_, auto turns_) INL {
     constexpr int G = decltype(g_)::value;
     constexpr int KD = 512 / G, NS = D / KD;     // channels of a product of S, its steps
     constexpr int NDT = D / G;                   // G-channel tiles of O^T
     constexpr int QG = 32 / G * QS;              // groups of G queries that a wave owns: the columns of one product
     constexpr int NKG = 32 / G;                  // products of S for the 32 keys of a half
     constexpr int NP = G / 16;                   // P's operands for them
-    constexpr bool TURNS = QS == 1 || !SPLIT;    // whether waves raise and lower their priority (part)
+    constexpr bool TURNS = decltype(turns_)::value;
     // Two query sets a wave take all registers for the loop.  What the epilogue and a call's last block need is then computed there, and flags are
     // one for the wave: else 17 to 32 registers were in memory, some loaded again behind a block's loads, which the wait for them then waits for,
     // too.  24 heads of 64, N = 12480: 23 entries 160.8 -> 155.4 us, rows that keep every second block 590 -> 567, a random 10 % 275 -> 263.  With one
@@ -781,10 +788,10 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
             constexpr int slot = slot_, i = slot / QG, uu = slot % QG, u = (i & 1) ? QG - 1 - uu : uu, pt = decltype(pt_)::value, hf = 1 - pt;
             constexpr int g = pt * NPS + i;
             // G = 16: the wave that is behind goes first, so that the two of a SIMD come to the barrier together.  480p, 90 % 3240 -> 3180 cycles a
-            // block (G = 32, where the oldest wave first has always been: 2957).  Not where the two are of different workgroups and a last round is
-            // cut: both workgroups of a unit then end at the same time, and the tiles behind them, too few for two to each unit, start in pairs
-            // on half of the units.  64-wide heads, N = 12480, with -> without: 12 heads, 43 entries 133.0 -> 124.7 us; 26 heads, 101 entries 558 -> 511;
-            // the other way where those tiles are cut into pieces for two to a unit anyway: 24 heads, 43 entries 226 -> 238.
+            // block (G = 32, where the oldest wave first has always been: 2957).  Where the two are of different workgroups (64-wide heads), both
+            // workgroups of a unit end at the same time by that, and tiles behind them that are too few for two to each unit start in pairs
+            // on half of the units.  N = 12480, with -> without: 12 heads, 43 entries 133.0 -> 124.7 us; 26 heads, 101 entries 558 -> 511; but 24 heads,
+            // 43 entries, whose last round is cut into pieces for two to a unit, 226 -> 238.  Hence turns, in two copies: branches in here spill.
             if constexpr (G == 16 && TURNS && slot == 0) __builtin_amdgcn_s_setprio(pt ? 1 : 3);
             if constexpr (G == 16 && TURNS && slot == SLOTS / 2) __builtin_amdgcn_s_setprio(pt ? 0 : 2);
             if constexpr (i < SS) mfma_S(u, pt, i, ring[g % RING]); else mfma_PV(u, pt, i - SS, ring[g % RING]);
@@ -1305,10 +1312,20 @@ __global__ __launch_bounds__(512 / QS, 2) void sparse_attn_v5_kernel(AttnArgs a,
         static_assert(long_list(D) >= LOOKED_AT, "a list has the entries that are looked at");
         const bool smaller = a.many && n >= long_list(D) && !(SPLIT && L >= a.sp_full) && 8 * kept_bits >= 5 * LOOKED_AT * min(4, nb - tile * 4);
         // the hint is for the registers and the order of the code: 480p dense without it 5262, with it 5215 us
-        if (__builtin_expect(smaller, 1)) rest(std::integral_constant<int, 16>{});
-        else rest(std::integral_constant<int, 32>{});
+        if (__builtin_expect(smaller, 1)) {
+            if constexpr (!SPLIT || QS == 1) {
+                rest(std::integral_constant<int, 16>{}, std::true_type{});
+            } else if constexpr (DBG) {          // the same results, and one copy
+                rest(std::integral_constant<int, 16>{}, std::false_type{});
+            } else {
+                if (turns) rest(std::integral_constant<int, 16>{}, std::true_type{});
+                else rest(std::integral_constant<int, 16>{}, std::false_type{});
+            }
+        } else {
+            rest(std::integral_constant<int, 32>{}, std::false_type{});
+        }
     } else {
-        rest(std::integral_constant<int, 32>{});
+        rest(std::integral_constant<int, 32>{}, std::false_type{});
     }
 }
 

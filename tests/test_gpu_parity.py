@@ -780,7 +780,8 @@ def test_references_of_two_query_sets_move_apart(oracle, profile, H, grid, keep)
     (29, 128, (4, 23, 25), 36),       # 261 tiles: a round, and five in pieces
     (43, 64, (4, 17, 19), 16),        # lists of at most 19 entries: the larger products
     (43, 64, (4, 17, 19), 17),        # lists of 17 to 20: both in one call
-    (58, 64, (4, 23, 25), 36),
+    (58, 64, (4, 23, 25), 36),        # 522 tiles: a round, and ten in pieces that have a compute unit each
+    (60, 64, (4, 25, 28), 44),        # 660: 148 in three pieces each, which share theirs
 ], ids=lambda x: str(x).replace(" ", ""))
 def test_smaller_products_of_long_lists(oracle, topk_variant, H, d, grid, keep):
     """Calls of more than one round of tiles around the list length from which on a tile is computed with 16x16x32 products; key magnitudes
